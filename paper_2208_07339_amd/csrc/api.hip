@@ -130,13 +130,8 @@ int llmint8_quantize_weight_granular(const void* W_f16, int h, int o, int granul
     if (h > LLMINT8_MAX_H) return LLMINT8_SHAPE;
     if (ws_bytes < weight_ws(h, o) + 256) return LLMINT8_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    unsigned short* part = (unsigned short*)ws_base(ws);
-    const int nslab = colmax_slabs(h, o);
-    hipError_t e = launch_colmax_partial(W_f16, h, o, part, nslab, st);
-    if (e == hipSuccess) e = launch_colmax_final(part, nslab, o, (unsigned short*)cw_f16, st);
-    if (e == hipSuccess && granularity != LLMINT8_VECTORWISE) e = launch_spread_max((unsigned short*)cw_f16, o, st);
-    if (e == hipSuccess) e = launch_quantize_weight(W_f16, h, o, (const unsigned short*)cw_f16, Wq, st);
-    return hip_status(e);
+    return hip_status(launch_quantize_weight(W_f16, h, o, (unsigned short*)ws_base(ws),
+                                             granularity != LLMINT8_VECTORWISE, (unsigned short*)cw_f16, Wq, st));
 }
 
 int llmint8_quantize_weight(const void* W_f16, int h, int o, int8_t* Wq, void* cw_f16, void* ws, size_t ws_bytes,

@@ -8,6 +8,8 @@
 
 namespace llmint8 {
 
+typedef unsigned short us8 __attribute__((ext_vector_type(8)));
+
 // ---- private int8 layout ---------------------------------------------------
 // A matrix M[rows][K] of int8 (rows = tokens of X, or output columns of W;
 // K = features) is cut into tiles of 32 rows x 32 features.  A tile is 1 KiB
@@ -31,6 +33,98 @@ __host__ __device__ inline int opad_of(int cap) { return (cap + 15) & ~15; }
 __device__ inline float f16_bits_to_float(unsigned short b)
 {
     return (float)__builtin_bit_cast(_Float16, b);  // exact widening
+}
+
+// ---- 16-byte accesses to rows of fp16 matrices ------------------------------------------------------------
+// Eight elements at any element-aligned address: the hardware takes 16-byte accesses at 2-byte alignment, so
+// matrices whose rows do not start on 16 bytes go the same way as those whose rows do.
+__device__ __forceinline__ us8 load8(const unsigned short* p)
+{
+    us8 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+
+// row[c0 .. c0+7] = v, without the columns that do not exist
+__device__ __forceinline__ void store8(unsigned short* row, int c0, int cols, us8 v)
+{
+    if (c0 + 8 <= cols) {
+        __builtin_memcpy(row + c0, &v, 16);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; e++)
+            if (c0 + e < cols) row[c0 + e] = v[e];
+    }
+}
+
+// One wave's share (rows r0 + w, r0 + w + 4, ...) of a scan over rows r0 .. r1-1 of M[rows][cols], a lane holding
+// columns c0 .. c0+7: f(v) for every row, eight rows in flight.  For reductions that do not mind seeing a row
+// twice (minima, maxima): a remainder repeats a row.  ragged: some of the wave's lanes have columns
+// c0 + e >= cols; what f sees there is some other element of M.  A 16-byte load that would reach past the last
+// element of M is taken apart (ragged: the last row, or the last few of a matrix narrower than 8 columns).
+template <class F>
+__device__ __forceinline__ void scan_rows(const unsigned short* __restrict__ M, int rows, int cols, int c0, bool ragged,
+                                          int r0, int r1, int w, F f)
+{
+    constexpr int RU = 8;
+    const int cl = c0 < cols ? c0 : 0;
+    int rv = r1;  // rows below rv are read in 16-byte pieces
+    if (ragged) {
+        const long long at = (long long)rows * cols - 8 - ((cols - 1) & ~7);
+        const long long safe = at < 0 ? 0 : at / cols + 1;
+        rv = safe < r1 ? (int)safe : r1;
+    }
+    const unsigned short* p = M + cl;
+    int r = r0 + w;
+    for (; r + 4 * (RU - 1) < rv; r += 4 * RU) {
+        us8 v[RU];
+#pragma unroll
+        for (int u = 0; u < RU; u++) v[u] = load8(p + (size_t)(r + 4 * u) * cols);
+#pragma unroll
+        for (int u = 0; u < RU; u++) f(v[u]);
+    }
+    if (r < rv) {
+        us8 v[RU];
+#pragma unroll
+        for (int u = 0; u < RU; u++) v[u] = load8(p + (size_t)(r + 4 * u < rv ? r + 4 * u : r) * cols);
+#pragma unroll
+        for (int u = 0; u < RU; u++) f(v[u]);
+    }
+    for (int q = (rv > r0 ? rv : r0) + w; q < r1; q += 4) {
+        us8 v;
+#pragma unroll
+        for (int e = 0; e < 8; e++) v[e] = M[(size_t)q * cols + (cl + e < cols ? cl + e : cols - 1)];
+        f(v);
+    }
+}
+
+// ---- absmax codes (Section 2.1) ------------------------------------------------------------------------------
+// code(x) = round-half-even of the exact quotient 127 x / c for fp16 x, c with |x| <= c, c > 0, in four
+// instructions.  With mx, mc the 11-bit significands, a quotient that is not a tie lies at least
+// 1 / (254 mx) > 2^-19 (relative) from the nearest half-integer n + 1/2 (254 mx 2^e and (2n + 1) mc are then
+// different integers).  code_factor() is 127 / c, correctly rounded, plus two ulps: x times it is above the exact quotient in
+// magnitude, by less than 2^-21 (relative).  Clearing the last three bits of that product, a step of at
+// most 2^-20, therefore brings a tie back to the tie itself and no other quotient across one, and adding
+// 1.5 * 2^23 rounds it to the nearest integer, ties to even, whose two's complement sits in the low bits of
+// the sum.  (Checked for every pair of fp16 values |x| <= c.)  c = 0: factor 0, code 0.
+__device__ __forceinline__ float code_factor(float c)
+{
+    return c > 0.0f ? __builtin_bit_cast(float, __builtin_bit_cast(unsigned, 127.0f / c) + 2u) : 0.0f;
+}
+
+// the code of x (fp16 bits) in the low byte
+__device__ __forceinline__ unsigned code_bits(unsigned short x, float factor)
+{
+    const float q = __builtin_fmaf(f16_bits_to_float(x), factor, 0.0f);  // conversion and product in one instruction
+    const float t = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, q) & ~7u);
+    return __builtin_bit_cast(unsigned, t + 12582912.0f);
+}
+
+// bytes 0 of four words
+__device__ __forceinline__ unsigned pack_low_bytes(unsigned a, unsigned b, unsigned c, unsigned d)
+{
+    const unsigned lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u), hi = __builtin_amdgcn_perm(d, c, 0x0c0c0400u);
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
 // hi - lo of a zeropoint record's first word (fp16 bits of lo in the low half, of hi in the high half): exact
@@ -70,6 +164,17 @@ __device__ __forceinline__ int zp_u_rcp(unsigned short xb, double D, double rD)
     const double q = a * rD;
     const double r = __builtin_fma(-q, D, a);
     return (int)__builtin_rint(__builtin_fma(r, rD, q));
+}
+
+// The same u(x) as the low word of an integer: adding 1.5 * 2^52 rounds the quotient to the nearest integer, ties
+// to even, and leaves its two's complement in the low bits of the sum.  D = 0 with rD = 0 gives 0.
+__device__ __forceinline__ unsigned zp_u_bits(unsigned short xb, double D, double rD)
+{
+    const double a = 254.0 * (double)f16_bits_to_float(xb);
+    const double q = a * rD;
+    const double r = __builtin_fma(-q, D, a);
+    const double t = __builtin_fma(r, rD, q) + 6755399441055744.0;
+    return (unsigned)__builtin_bit_cast(unsigned long long, t);
 }
 
 // The record of a vector from the keys of its smallest and largest element: fp16 bits of lo and hi,
@@ -252,10 +357,10 @@ struct ColumnJob {
 hipError_t launch_prepass_small(const void* X, int s, int h, unsigned thr, OutlierLists L, int32_t* idx, int cap,
                                 int32_t* count, int32_t* status, unsigned short* cx, unsigned short* Xo, int8_t* Xq,
                                 int shared_cx, hipStream_t st, int4* zc = nullptr, const ColumnJob* cj = nullptr);
-hipError_t launch_colmax_final(const unsigned short* part, int nslab, int cols, unsigned short* out,
-                               hipStream_t st);
-hipError_t launch_quantize_weight(const void* W, int h, int o, const unsigned short* cw, int8_t* Wq,
-                                  hipStream_t st);
+// constants and codes of W (weights.hip); part: scratch for colmax_slabs(h, o) * o magnitudes; shared: one constant
+// for all columns
+hipError_t launch_quantize_weight(const void* W, int h, int o, unsigned short* part, int shared, unsigned short* cw,
+                                  int8_t* Wq, hipStream_t st);
 hipError_t launch_quantize_rows(const void* X, int s, int h, const int32_t* idx, const int32_t* count, int cap,
                                 int8_t* Xq, unsigned short* cx, unsigned short* Xo, int shared_cx, hipStream_t st);
 hipError_t launch_export_tiled(const int8_t* T, int rows, int h, int8_t* out, int ld_rows_major,

@@ -5,7 +5,6 @@
 
 namespace llmint8 {
 
-typedef unsigned short us8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 
@@ -32,7 +31,7 @@ __device__ __forceinline__ int q8(float x, float c, float rc)
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) colmax_partial_kernel(const unsigned short* __restrict__ M, int rows,
                                                              int cols, unsigned short* __restrict__ part,
-                                                             int rows_per_slab, int vec_ok)
+                                                             int rows_per_slab)
 {
     __shared__ us8 red[4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -40,46 +39,14 @@ __global__ void __launch_bounds__(256) colmax_partial_kernel(const unsigned shor
     const int r0 = blockIdx.y * rows_per_slab;
     const int r1 = min(rows, r0 + rows_per_slab);
     us8 m = (us8)(0);
-    if (vec_ok) {
-        if (c0 < cols) {
-            const unsigned short* p = M + (size_t)c0;
-            int r = r0 + w;
-            for (; r + 12 < r1; r += 16) {
-                us8 a = *(const us8*)(p + (size_t)r * cols);
-                us8 b = *(const us8*)(p + (size_t)(r + 4) * cols);
-                us8 c = *(const us8*)(p + (size_t)(r + 8) * cols);
-                us8 d = *(const us8*)(p + (size_t)(r + 12) * cols);
-                a = __builtin_elementwise_max(a & (unsigned short)0x7fff, b & (unsigned short)0x7fff);
-                c = __builtin_elementwise_max(c & (unsigned short)0x7fff, d & (unsigned short)0x7fff);
-                m = __builtin_elementwise_max(m, __builtin_elementwise_max(a, c));
-            }
-            for (; r < r1; r += 4) {
-                us8 a = *(const us8*)(p + (size_t)r * cols);
-                m = __builtin_elementwise_max(m, a & (unsigned short)0x7fff);
-            }
-        }
-    } else {
-        for (int r = r0 + w; r < r1; r += 4)
-#pragma unroll
-            for (int e = 0; e < 8; e++)
-                if (c0 + e < cols) {
-                    unsigned short v = M[(size_t)r * cols + c0 + e] & 0x7fff;
-                    m[e] = v > m[e] ? v : m[e];
-                }
-    }
+    scan_rows(M, rows, cols, c0, blockIdx.x * 512 + 512 > cols, r0, r1, w,
+              [&](us8 v) { m = __builtin_elementwise_max(m, v & (unsigned short)0x7fff); });
     red[w][lane] = m;
     __syncthreads();
     if (w == 0) {
         m = __builtin_elementwise_max(__builtin_elementwise_max(red[0][lane], red[1][lane]),
                                       __builtin_elementwise_max(red[2][lane], red[3][lane]));
-        unsigned short* o = part + (size_t)blockIdx.y * cols + c0;
-        if (vec_ok) {
-            if (c0 < cols) *(us8*)o = m;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; e++)
-                if (c0 + e < cols) o[e] = m[e];
-        }
+        store8(part + (size_t)blockIdx.y * cols, c0, cols, m);
     }
 }
 
@@ -101,9 +68,8 @@ hipError_t launch_colmax_partial(const void* M, int rows, int cols, unsigned sho
                                  hipStream_t st)
 {
     int rps = (rows + nslab - 1) / nslab;
-    int vec_ok = (cols % 8 == 0) && aligned16(M) && aligned16(part);
     dim3 grid((cols + 511) / 512, nslab);
-    colmax_partial_kernel<<<grid, 256, 0, st>>>((const unsigned short*)M, rows, cols, part, rps, vec_ok);
+    colmax_partial_kernel<<<grid, 256, 0, st>>>((const unsigned short*)M, rows, cols, part, rps);
     return hipGetLastError();
 }
 
@@ -803,101 +769,6 @@ hipError_t launch_prepass_small(const void* X, int s, int h, unsigned thr, Outli
     quantize_small_kernel<false><<<nquant + job.pitch / 256, 256, shm, st>>>(
         (const unsigned short*)X, s, h, L, capc, vec_ok, idx, cap, opad_of(cap), count, status, cx, Xo, Xq, KT, shared_cx,
         nullptr, job);
-    return hipGetLastError();
-}
-
-// out[c] = max over slabs (weights: this is c_w as fp16 bits)
-__global__ void __launch_bounds__(256) colmax_final_kernel(const unsigned short* __restrict__ part, int nslab,
-                                                           int cols, unsigned short* __restrict__ out)
-{
-    int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= cols) return;
-    unsigned m = 0;
-    for (int sl = 0; sl < nslab; sl++) {
-        unsigned v = part[(size_t)sl * cols + j];
-        m = v > m ? v : m;
-    }
-    out[j] = (unsigned short)m;
-}
-
-hipError_t launch_colmax_final(const unsigned short* part, int nslab, int cols, unsigned short* out,
-                               hipStream_t st)
-{
-    colmax_final_kernel<<<(cols + 255) / 256, 256, 0, st>>>(part, nslab, cols, out);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// W_i8 in the tiled layout (tile rows = output columns, tile K = features).
-// One workgroup: 32 features (one kt) x 256 output columns (8 tiles), staged
-// through LDS so that the transposed tiles leave as whole 1 KiB pieces.
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) quantize_weight_kernel(const unsigned short* __restrict__ W, int h, int o,
-                                                              const unsigned short* __restrict__ cw,
-                                                              int8_t* __restrict__ Wq, int KT, int JT, int vec_ok)
-{
-    __shared__ __attribute__((aligned(16))) int8_t stage[8 * TILE_BYTES];
-    const int tid = threadIdx.x;
-    const int kt = blockIdx.y;
-    const int jt0 = blockIdx.x * 8;
-    const int cg = tid & 31, sub = tid >> 5;
-    const int j0 = jt0 * 32 + cg * 8;
-    // The vector path requests its column constants and the four rows of W without conditions (a row past h: the
-    // last one again, zeroed below), so that the loads are in flight together instead of one after the other.
-    const bool vec = vec_ok && j0 + 8 <= o;
-    us8 cv = (us8)(0), wv[4];
-    if (vec) {
-        cv = *(const us8*)(cw + j0);
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const int k = kt * 32 + q * 8 + sub;
-            wv[q] = *(const us8*)(W + (size_t)(k < h ? k : h - 1) * o + j0);
-        }
-    }
-    float c[8], rc[8];
-#pragma unroll
-    for (int e = 0; e < 8; e++) {
-        c[e] = vec ? f16_bits_to_float(cv[e]) : (j0 + e < o) ? f16_bits_to_float(cw[j0 + e]) : 0.0f;
-        rc[e] = c[e] > 0.0f ? 1.0f / c[e] : 0.0f;
-    }
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const int kk = q * 8 + sub;
-        const int k = kt * 32 + kk;
-        us8 v = (us8)(0);
-        if (k < h) {
-            if (vec) {
-                v = wv[q];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; e++)
-                    if (j0 + e < o) v[e] = W[(size_t)k * o + j0 + e];
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            int qv = (c[e] > 0.0f) ? q8(f16_bits_to_float(v[e]), c[e], rc[e]) : 0;
-            const int jj = cg * 8 + e;
-            stage[(jj >> 5) * TILE_BYTES + tile_byte(jj & 31, kk)] = (int8_t)qv;
-        }
-    }
-    __syncthreads();
-    const int tile = tid >> 5;
-    if (jt0 + tile < JT) {
-        const u4* src = (const u4*)(stage + tid * 32);
-        u4* dst = (u4*)(Wq + ((size_t)(jt0 + tile) * KT + kt) * TILE_BYTES + (tid & 31) * 32);
-        dst[0] = src[0];
-        dst[1] = src[1];
-    }
-}
-
-hipError_t launch_quantize_weight(const void* W, int h, int o, const unsigned short* cw, int8_t* Wq,
-                                  hipStream_t st)
-{
-    const int KT = k_tiles(h), JT = row_tiles(o);
-    int vec_ok = (o % 8 == 0) && aligned16(W) && aligned16(cw);
-    dim3 grid((JT + 7) / 8, KT);
-    quantize_weight_kernel<<<grid, 256, 0, st>>>((const unsigned short*)W, h, o, cw, Wq, KT, JT, vec_ok);
     return hipGetLastError();
 }
 

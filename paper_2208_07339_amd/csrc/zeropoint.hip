@@ -16,133 +16,10 @@
 
 namespace llmint8 {
 
-typedef unsigned short us8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 
 // f16_key / key_f16, zp_u / zp_u_rcp and make_const live in common.h (the short-X pre-pass uses them too).
-
-// ---------------------------------------------------------------------------
-// Weights: column ranges over slabs of rows, constants, codes + column sums.
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) zp_colrange_partial_kernel(const unsigned short* __restrict__ W, int h, int o,
-                                                                  unsigned short* __restrict__ pmin,
-                                                                  unsigned short* __restrict__ pmax, int rows_per_slab)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= o) return;
-    const int r0 = blockIdx.y * rows_per_slab, r1 = min(h, r0 + rows_per_slab);
-    unsigned kmin = 0xffffu, kmax = 0u;
-    for (int r = r0; r < r1; r++) {
-        const unsigned k = f16_key(W[(size_t)r * o + j]);
-        kmin = k < kmin ? k : kmin;
-        kmax = k > kmax ? k : kmax;
-    }
-    pmin[(size_t)blockIdx.y * o + j] = (unsigned short)kmin;
-    pmax[(size_t)blockIdx.y * o + j] = (unsigned short)kmax;
-}
-
-__global__ void __launch_bounds__(256) zp_colrange_final_kernel(const unsigned short* __restrict__ pmin,
-                                                                const unsigned short* __restrict__ pmax, int nslab,
-                                                                int o, int4* __restrict__ zc)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= o) return;
-    unsigned kmin = 0xffffu, kmax = 0u;
-    for (int sl = 0; sl < nslab; sl++) {
-        const unsigned a = pmin[(size_t)sl * o + j], b = pmax[(size_t)sl * o + j];
-        kmin = a < kmin ? a : kmin;
-        kmax = b > kmax ? b : kmax;
-    }
-    zc[j] = make_const(kmin, kmax);
-}
-
-// W_i8 in the tiled layout, as quantize_weight_kernel: one workgroup = 32 features x 256 output
-// columns, staged through LDS.  Also adds this slab's part of every column sum into the records.
-__global__ void __launch_bounds__(256) zp_quantize_weight_kernel(const unsigned short* __restrict__ W, int h, int o,
-                                                                 int4* __restrict__ zc, int8_t* __restrict__ Wq,
-                                                                 int KT, int JT)
-{
-    __shared__ __attribute__((aligned(16))) int8_t stage[8 * TILE_BYTES];
-    __shared__ int csum[256];
-    const int tid = threadIdx.x;
-    const int kt = blockIdx.y;
-    const int jt0 = blockIdx.x * 8;
-    const int cg = tid & 31, sub = tid >> 5;
-    const int j0 = jt0 * 32 + cg * 8;
-    csum[tid] = 0;
-    double D[8], rD[8];
-    int z[8], part[8];
-#pragma unroll
-    for (int e = 0; e < 8; e++) {
-        D[e] = 0.0;
-        rD[e] = 0.0;
-        z[e] = 0;
-        part[e] = 0;
-        if (j0 + e < o) {
-            const int4 r = zc[j0 + e];
-            D[e] = zp_range((unsigned)r.x);
-            rD[e] = D[e] > 0.0 ? 1.0 / D[e] : 0.0;
-            z[e] = r.y;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const int kk = q * 8 + sub;
-        const int k = kt * 32 + kk;
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            int qv = 0;  // padding rows and columns of the tiles stay zero
-            if (k < h && D[e] > 0.0) qv = zp_u_rcp(W[(size_t)k * o + j0 + e], D[e], rD[e]) - z[e];
-            part[e] += qv;
-            const int jj = cg * 8 + e;
-            stage[(jj >> 5) * TILE_BYTES + tile_byte(jj & 31, kk)] = (int8_t)qv;
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < 8; e++)
-        if (part[e]) atomicAdd(&csum[cg * 8 + e], part[e]);
-    __syncthreads();
-    const int tile = tid >> 5;
-    if (jt0 + tile < JT) {
-        const u4* src = (const u4*)(stage + tid * 32);
-        u4* dst = (u4*)(Wq + ((size_t)(jt0 + tile) * KT + kt) * TILE_BYTES + (tid & 31) * 32);
-        dst[0] = src[0];
-        dst[1] = src[1];
-    }
-    const int j = jt0 * 32 + tid;
-    if (j < o && csum[tid]) atomicAdd(&zc[j].z, csum[tid]);
-}
-
-int zp_colrange_slabs(int h, int o)
-{
-    const int colblocks = (o + 255) / 256;
-    int n = (2048 + colblocks - 1) / colblocks;
-    const int maxslab = (h + 31) / 32;
-    if (n > maxslab) n = maxslab;
-    if (n > 64) n = 64;
-    return n < 1 ? 1 : n;
-}
-
-hipError_t launch_zp_quantize_weight(const void* W, int h, int o, int8_t* Wq, int4* zc, unsigned short* part,
-                                     hipStream_t st)
-{
-    const int nslab = zp_colrange_slabs(h, o);
-    const int rps = (h + nslab - 1) / nslab;
-    unsigned short* pmin = part;
-    unsigned short* pmax = part + (size_t)nslab * o;
-    zp_colrange_partial_kernel<<<dim3((o + 255) / 256, nslab), 256, 0, st>>>((const unsigned short*)W, h, o, pmin, pmax,
-                                                                            rps);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    zp_colrange_final_kernel<<<(o + 255) / 256, 256, 0, st>>>(pmin, pmax, nslab, o, zc);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int KT = k_tiles(h), JT = row_tiles(o);
-    zp_quantize_weight_kernel<<<dim3((JT + 7) / 8, KT), 256, 0, st>>>((const unsigned short*)W, h, o, zc, Wq, KT, JT);
-    return hipGetLastError();
-}
 
 // ---------------------------------------------------------------------------
 // The per-column factors of Eq. 5 for column j, three planes of `pitch` doubles (see zp_kcol_kernel, which
