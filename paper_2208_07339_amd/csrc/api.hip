@@ -153,7 +153,7 @@ int llmint8_find_outliers(const void* X_f16, int s, int h, float alpha, int32_t*
     const OutlierLists L = carve_outlier_lists(base, h, cap);
     unsigned short* part = (unsigned short*)(base + scratch_ws(h, cap));
     const int nslab = colmax_slabs(s, h);
-    hipError_t e = launch_colmax_partial(X_f16, s, h, part, nslab, st);
+    hipError_t e = launch_colmax_partial(X_f16, s, h, part, nslab, false, st);
     if (e == hipSuccess) e = launch_outlier_lists(part, nslab, h, threshold_bits(alpha), L, cap, st);
     if (e == hipSuccess) e = launch_merge_lists(L, h, idx, cap, count, status, st);
     return hip_status(e);
@@ -292,7 +292,7 @@ static int linear_impl(const void* X_f16, int s, int h, float alpha, int granula
                     e = launch_quantize_rows_rowpart(X_f16, s, h, L, thr, rowpart, idx, count, status, cap, Xq,
                                                      (unsigned short*)cx_f16, (unsigned short*)Xo_f16, st);
             } else {
-                e = launch_colmax_partial(X_f16, s, h, part, nslab, st);
+                e = launch_colmax_partial(X_f16, s, h, part, nslab, false, st);
                 if (e == hipSuccess) e = launch_outlier_lists(part, nslab, h, thr, L, cap, st);
                 if (e == hipSuccess)
                     e = launch_quantize_rows_lists(X_f16, s, h, L, idx, count, status, cap, Xq,
@@ -461,7 +461,7 @@ int llmint8_zp_linear(const void* X_f16, int s, int h, float alpha, const int8_t
         unsigned short* part = (unsigned short*)(base + scratch_ws(h, cap));
         const int nslab = colmax_slabs(s, h);
         const ColumnJob job = {Wq, zc_w, base + scan_ws(s, h, o, cap) + rows_ws(o, cap), o, zp_col_pitch(o)};
-        hipError_t e = launch_colmax_partial(X_f16, s, h, part, nslab, st);
+        hipError_t e = launch_colmax_partial(X_f16, s, h, part, nslab, false, st);
         if (e == hipSuccess) e = launch_outlier_lists(part, nslab, h, threshold_bits(alpha), L, cap, st);
         if (e == hipSuccess)
             e = launch_zp_quantize_rows_lists(X_f16, s, h, L, idx, count, status, cap, Xq, (int4*)zc_x,

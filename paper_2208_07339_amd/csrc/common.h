@@ -38,12 +38,10 @@ __device__ inline float f16_bits_to_float(unsigned short b)
 // ---- 16-byte accesses to rows of fp16 matrices ------------------------------------------------------------
 // Eight elements at any element-aligned address: the hardware takes 16-byte accesses at 2-byte alignment, so
 // matrices whose rows do not start on 16 bytes go the same way as those whose rows do.
-__device__ __forceinline__ us8 load8(const unsigned short* p)
-{
-    us8 v;
-    __builtin_memcpy(&v, p, 16);
-    return v;
-}
+typedef unsigned short us8_at2 __attribute__((ext_vector_type(8), aligned(2)));
+__device__ __forceinline__ us8 load8(const unsigned short* p) { return *(const us8_at2*)p; }
+// the same for data that is not read again soon: it does not push anything else out of the caches
+__device__ __forceinline__ us8 load8_once(const unsigned short* p) { return __builtin_nontemporal_load((const us8_at2*)p); }
 
 // row[c0 .. c0+7] = v, without the columns that do not exist
 __device__ __forceinline__ void store8(unsigned short* row, int c0, int cols, us8 v)
@@ -62,7 +60,8 @@ __device__ __forceinline__ void store8(unsigned short* row, int c0, int cols, us
 // twice (minima, maxima): a remainder repeats a row.  ragged: some of the wave's lanes have columns
 // c0 + e >= cols; what f sees there is some other element of M.  A 16-byte load that would reach past the last
 // element of M is taken apart (ragged: the last row, or the last few of a matrix narrower than 8 columns).
-template <class F>
+// ONCE: M is larger than the caches, streamed past them (5 120 x 20 480: 35 against 39 us).
+template <bool ONCE, class F>
 __device__ __forceinline__ void scan_rows(const unsigned short* __restrict__ M, int rows, int cols, int c0, bool ragged,
                                           int r0, int r1, int w, F f)
 {
@@ -75,18 +74,19 @@ __device__ __forceinline__ void scan_rows(const unsigned short* __restrict__ M, 
         rv = safe < r1 ? (int)safe : r1;
     }
     const unsigned short* p = M + cl;
+    auto load = [](const unsigned short* q) { return ONCE ? load8_once(q) : load8(q); };
     int r = r0 + w;
     for (; r + 4 * (RU - 1) < rv; r += 4 * RU) {
         us8 v[RU];
 #pragma unroll
-        for (int u = 0; u < RU; u++) v[u] = load8(p + (size_t)(r + 4 * u) * cols);
+        for (int u = 0; u < RU; u++) v[u] = load(p + (size_t)(r + 4 * u) * cols);
 #pragma unroll
         for (int u = 0; u < RU; u++) f(v[u]);
     }
     if (r < rv) {
         us8 v[RU];
 #pragma unroll
-        for (int u = 0; u < RU; u++) v[u] = load8(p + (size_t)(r + 4 * u < rv ? r + 4 * u : r) * cols);
+        for (int u = 0; u < RU; u++) v[u] = load(p + (size_t)(r + 4 * u < rv ? r + 4 * u : r) * cols);
 #pragma unroll
         for (int u = 0; u < RU; u++) f(v[u]);
     }
@@ -166,15 +166,22 @@ __device__ __forceinline__ int zp_u_rcp(unsigned short xb, double D, double rD)
     return (int)__builtin_rint(__builtin_fma(r, rD, q));
 }
 
-// The same u(x) as the low word of an integer: adding 1.5 * 2^52 rounds the quotient to the nearest integer, ties
-// to even, and leaves its two's complement in the low bits of the sum.  D = 0 with rD = 0 gives 0.
-__device__ __forceinline__ unsigned zp_u_bits(unsigned short xb, double D, double rD)
+// The same u(x) in four instructions and a conversion, as code_bits() does it for absmax codes, in double.  A quotient that is
+// not a tie lies at least 2^(eD - ex) / (508 mx) > 2^-49 (relative) from the nearest half-integer, with mx and ex the
+// significand (an integer of 11 bits) and exponent of x and 2^eD the unit of D, because |x| <= max(|lo|, |hi|)
+// and fp16 units span 2^-24 .. 2^5.  zp_factor() is 254 / D, correctly rounded, plus one ulp: x times it is not
+// below the exact quotient in magnitude and less than 2^-50 (relative) above it; the three bits cleared are a
+// step of at most 2^-49, and adding 1.5 * 2^52 rounds to the nearest integer, ties to even, which sits in the low
+// word of the sum.  D = 0: factor 0, u = 0.
+__device__ __forceinline__ double zp_factor(double D)
 {
-    const double a = 254.0 * (double)f16_bits_to_float(xb);
-    const double q = a * rD;
-    const double r = __builtin_fma(-q, D, a);
-    const double t = __builtin_fma(r, rD, q) + 6755399441055744.0;
-    return (unsigned)__builtin_bit_cast(unsigned long long, t);
+    return D > 0.0 ? __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, 254.0 / D) + 1ull) : 0.0;
+}
+__device__ __forceinline__ unsigned zp_u_bits(unsigned short xb, double factor)
+{
+    const double q = (double)f16_bits_to_float(xb) * factor;
+    const double t = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, q) & ~7ull);
+    return (unsigned)__builtin_bit_cast(unsigned long long, t + 6755399441055744.0);
 }
 
 // The record of a vector from the keys of its smallest and largest element: fp16 bits of lo and hi,
@@ -319,7 +326,8 @@ __device__ inline int scan_lists(const int* __restrict__ count, int nl, int* s_c
 
 // partial column maxima of an fp16 matrix M[rows][cols]: part[slab][cols] (u16 magnitude bits)
 int colmax_slabs(int rows, int cols);
-hipError_t launch_colmax_partial(const void* M, int rows, int cols, unsigned short* part, int nslab,
+// (once: M is not read again soon)
+hipError_t launch_colmax_partial(const void* M, int rows, int cols, unsigned short* part, int nslab, bool once,
                                  hipStream_t st);
 // slab maxima -> column lists; lists -> idx, count, status
 hipError_t launch_outlier_lists(const unsigned short* part, int nslab, int h, unsigned thr, OutlierLists L, int cap,

@@ -29,6 +29,7 @@ __device__ __forceinline__ int q8(float x, float c, float rc)
 // columns (a wave reads 1 KiB of a row per load) and `rows_per_slab` rows, its
 // four waves taking every fourth row.
 // ---------------------------------------------------------------------------
+template <bool ONCE>
 __global__ void __launch_bounds__(256) colmax_partial_kernel(const unsigned short* __restrict__ M, int rows,
                                                              int cols, unsigned short* __restrict__ part,
                                                              int rows_per_slab)
@@ -39,7 +40,7 @@ __global__ void __launch_bounds__(256) colmax_partial_kernel(const unsigned shor
     const int r0 = blockIdx.y * rows_per_slab;
     const int r1 = min(rows, r0 + rows_per_slab);
     us8 m = (us8)(0);
-    scan_rows(M, rows, cols, c0, blockIdx.x * 512 + 512 > cols, r0, r1, w,
+    scan_rows<ONCE>(M, rows, cols, c0, blockIdx.x * 512 + 512 > cols, r0, r1, w,
               [&](us8 v) { m = __builtin_elementwise_max(m, v & (unsigned short)0x7fff); });
     red[w][lane] = m;
     __syncthreads();
@@ -64,12 +65,16 @@ int colmax_slabs(int rows, int cols)
 
 static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
-hipError_t launch_colmax_partial(const void* M, int rows, int cols, unsigned short* part, int nslab,
+hipError_t launch_colmax_partial(const void* M, int rows, int cols, unsigned short* part, int nslab, bool once,
                                  hipStream_t st)
 {
     int rps = (rows + nslab - 1) / nslab;
+    if (once) rps = (rps + 31) & ~31;  // whole passes of scan_rows (a slab may be left without rows: all zero)
     dim3 grid((cols + 511) / 512, nslab);
-    colmax_partial_kernel<<<grid, 256, 0, st>>>((const unsigned short*)M, rows, cols, part, rps);
+    if (once)
+        colmax_partial_kernel<true><<<grid, 256, 0, st>>>((const unsigned short*)M, rows, cols, part, rps);
+    else
+        colmax_partial_kernel<false><<<grid, 256, 0, st>>>((const unsigned short*)M, rows, cols, part, rps);
     return hipGetLastError();
 }
 

@@ -31,7 +31,7 @@ __global__ void __launch_bounds__(256) zp_colrange_partial_kernel(const unsigned
     const int c0 = blockIdx.x * 512 + lane * 8;
     const int r0 = blockIdx.y * rows_per_slab, r1 = min(h, r0 + rows_per_slab);
     us8 mn = (us8)((unsigned short)0xffff), mx = (us8)((unsigned short)0);
-    scan_rows(W, h, o, c0, blockIdx.x * 512 + 512 > o, r0, r1, w, [&](us8 v) {
+    scan_rows<true>(W, h, o, c0, blockIdx.x * 512 + 512 > o, r0, r1, w, [&](us8 v) {
         const us8 k = f16_key8(v);
         mn = __builtin_elementwise_min(mn, k);
         mx = __builtin_elementwise_max(mx, k);
@@ -91,20 +91,23 @@ __global__ void __launch_bounds__(1024) colconst_kernel(const unsigned short* __
 
 // ---------------------------------------------------------------------------
 // Codes in the tiled layout (tile rows = output columns, tile K = features), and for the zeropoint variant
-// the column sums of the codes into the records.
+// each workgroup's part of the column sums of the codes.
 //
 // One workgroup = 512 output columns x 64 * steps features, one wave = 512 columns x 16 features per step.  A lane
 // holds 8 columns x 16 features (16 loads of 16 bytes in flight), so the 16 codes that make up a 16-byte piece
 // of a tile meet in one lane and are packed in registers; LDS only swaps pieces between lanes, private to
 // the wave (no barrier), so that the stores leave as 512-byte runs.  The pieces are placed at
 // column ^ (lane & 7) within a lane's eight, which keeps both sides free of bank conflicts.
-// Measured on 5 120 x 20 480 (105 MB of codes from 210 MB of weights): codes per byte into LDS, from one
-// 2-byte (zeropoint) or 16-byte load per row at a time, took 178 us (absmax) and 219 us (zeropoint).
+// Measured on 5 120 x 20 480 (105 MB of codes from 210 MB of weights): 53 us (absmax) = 5.9 TB/s and 67 us
+// (zeropoint: the arithmetic in double); with the codes put into LDS byte by byte, from one 2-byte (zeropoint)
+// or 16-byte load per row at a time, 178 and 219 us.  W is streamed past the caches (102 us for both passes
+// together if not, 89 so); the codes are not (103 us).
 // ---------------------------------------------------------------------------
 template <bool ZP>
-__global__ void __launch_bounds__(256) weight_codes_kernel(const unsigned short* __restrict__ W, int h, int o,
-                                                           const unsigned short* __restrict__ cw, int4* __restrict__ zc,
-                                                           int8_t* __restrict__ Wq, int KT, int JT, int steps)
+__global__ void __launch_bounds__(256, ZP ? 2 : 4) weight_codes_kernel(const unsigned short* __restrict__ W, int h, int o,
+                                                           const unsigned short* __restrict__ cw, const int4* __restrict__ zc,
+                                                           int8_t* __restrict__ Wq, int KT, int JT, int steps,
+                                                           int* __restrict__ psum)
 {
     __shared__ u4 stage[4][512];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -114,17 +117,14 @@ __global__ void __launch_bounds__(256) weight_codes_kernel(const unsigned short*
 
     // column constants
     float kup[ZP ? 1 : 8];
-    double D[ZP ? 8 : 1], rD[ZP ? 8 : 1];
+    double zf[ZP ? 8 : 1];
     int z[ZP ? 8 : 1], sum[ZP ? 8 : 1];
     if constexpr (ZP) {
 #pragma unroll
         for (int e = 0; e < 8; e++) {
             const int4 r = zc[j0 + e < o ? j0 + e : 0];
-            const double d = zp_range((unsigned)r.x);
-            const bool dead = j0 + e >= o || !(d > 0.0);
-            D[e] = d;
-            rD[e] = dead ? 0.0 : 1.0 / d;
-            z[e] = dead ? 0 : r.y;
+            zf[e] = j0 + e < o ? zp_factor(zp_range((unsigned)r.x)) : 0.0;
+            z[e] = j0 + e < o ? r.y : 0;
             sum[e] = 0;
         }
     } else {
@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(256) weight_codes_kernel(const unsigned short*
         if (!ragged || (k + 15 < h - 1 && h >= 16 && o >= 8)) {
             const unsigned short* p = W + jl;
 #pragma unroll
-            for (int i = 0; i < 16; i++) v[i] = load8(p + (size_t)(k + i < h ? k + i : h - 1) * o);
+            for (int i = 0; i < 16; i++) v[i] = load8_once(p + (size_t)(k + i < h ? k + i : h - 1) * o);
         } else {
 #pragma unroll
             for (int i = 0; i < 16; i++)
@@ -165,7 +165,7 @@ __global__ void __launch_bounds__(256) weight_codes_kernel(const unsigned short*
                 unsigned t[4];
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    if constexpr (ZP) t[i] = zp_u_bits(v[4 * b + i][e], D[e], rD[e]) - (unsigned)z[e];
+                    if constexpr (ZP) t[i] = zp_u_bits(v[4 * b + i][e], zf[e]) - (unsigned)z[e];
                     else t[i] = code_bits(v[4 * b + i][e], kup[e]);
                 }
                 q[b] = pack_low_bytes(t[0], t[1], t[2], t[3]);
@@ -197,41 +197,61 @@ __global__ void __launch_bounds__(256) weight_codes_kernel(const unsigned short*
         asm volatile("" ::: "memory");  // the next step's pieces stay behind these reads
     }
     if constexpr (ZP) {
-        // the four waves' sums meet in LDS: one global addition per column and workgroup
+        // the four waves' sums meet in LDS; a workgroup stores its own, zp_colsum_kernel adds them up
         __syncthreads();
         int* s_sum = (int*)stage;
 #pragma unroll
         for (int e = 0; e < 8; e++) s_sum[w * 512 + e * 64 + lane] = sum[e];
         __syncthreads();
         for (int q = threadIdx.x; q < 512; q += 256) {
-            const int j = jb + (q & 63) * 8 + (q >> 6);
-            const int t = s_sum[q] + s_sum[512 + q] + s_sum[1024 + q] + s_sum[1536 + q];
-            if (j < o && t) atomicAdd(&zc[j].z, t);
+            const int at = (q & 7) * 64 + (q >> 3);
+            if (jb + q < o)
+                psum[(size_t)blockIdx.y * o + jb + q] = s_sum[at] + s_sum[512 + at] + s_sum[1024 + at] + s_sum[1536 + at];
         }
     }
 }
 
-// Steps per workgroup: the column constants and (zeropoint) the sums are paid once per workgroup, so several
-// steps while that leaves four workgroups per compute unit.
-static int code_steps(int KT, int JT)
+// Column sums of the codes into the records.  (Added there by weight_codes_kernel with one global addition per column
+// and workgroup, 40 to a record, that kernel took 110 us instead of 68 on a 5 120 x 20 480 W.)
+__global__ void __launch_bounds__(1024) zp_colsum_kernel(const int* __restrict__ psum, int n, int o, int4* __restrict__ zc)
 {
-    const long blocks = (long)((JT + 15) / 16) * ((KT + 1) / 2);
-    return blocks >= 4096 ? 4 : blocks >= 2048 ? 2 : 1;
+    __shared__ int red[4][256];
+    const int c = threadIdx.x & 255, g = threadIdx.x >> 8;
+    const int j = blockIdx.x * 256 + c, jj = j < o ? j : 0;
+    int t = 0;
+    for (int b = g; b < n; b += 32) {
+        int v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) v[u] = psum[(size_t)(b + 4 * u < n ? b + 4 * u : b) * o + jj];
+#pragma unroll
+        for (int u = 0; u < 8; u++) t += b + 4 * u < n ? v[u] : 0;
+    }
+    red[g][c] = t;
+    __syncthreads();
+    if (g == 0 && j < o) zc[j].z = red[0][c] + red[1][c] + red[2][c] + red[3][c];
+}
+
+// At most n slabs of rows, of 32 rows (one pass of a workgroup over eight rows per wave) or a multiple of that
+static int whole_pass_slabs(int h, int n)
+{
+    const int rps = ((h + n - 1) / n + 31) & ~31;
+    return (h + rps - 1) / rps;
 }
 
 hipError_t launch_quantize_weight(const void* W, int h, int o, unsigned short* part, int shared, unsigned short* cw,
                                   int8_t* Wq, hipStream_t st)
 {
-    const int nslab = colmax_slabs(h, o);
-    hipError_t e = launch_colmax_partial(W, h, o, part, nslab, st);
+    const int nslab = whole_pass_slabs(h, colmax_slabs(h, o));
+    hipError_t e = launch_colmax_partial(W, h, o, part, nslab, true, st);
     if (e != hipSuccess) return e;
     colconst_kernel<false><<<(o + 255) / 256, 1024, 0, st>>>(part, nullptr, nslab, o, cw, nullptr);
     e = hipGetLastError();
     if (e == hipSuccess && shared) e = launch_spread_max(cw, o, st);
     if (e != hipSuccess) return e;
-    const int KT = k_tiles(h), JT = row_tiles(o), steps = code_steps(KT, JT);
-    weight_codes_kernel<false><<<dim3((JT + 15) / 16, (KT / 2 + steps - 1) / steps), 256, 0, st>>>(
-        (const unsigned short*)W, h, o, cw, nullptr, Wq, KT, JT, steps);
+    // one step per workgroup: 88.7 us for the whole conversion of a 5 120 x 20 480 W, 91.8 with two, 96.1 with four
+    const int KT = k_tiles(h), JT = row_tiles(o);
+    weight_codes_kernel<false><<<dim3((JT + 15) / 16, KT / 2), 256, 0, st>>>((const unsigned short*)W, h, o, cw, nullptr, Wq,
+                                                                            KT, JT, 1, nullptr);
     return hipGetLastError();
 }
 
@@ -248,8 +268,8 @@ int zp_colrange_slabs(int h, int o)
 hipError_t launch_zp_quantize_weight(const void* W, int h, int o, int8_t* Wq, int4* zc, unsigned short* part,
                                      hipStream_t st)
 {
-    const int nslab = zp_colrange_slabs(h, o);
-    const int rps = (h + nslab - 1) / nslab;
+    const int nslab = whole_pass_slabs(h, zp_colrange_slabs(h, o));
+    const int rps = ((h + nslab - 1) / nslab + 31) & ~31;
     unsigned short* pmin = part;
     unsigned short* pmax = part + (size_t)nslab * o;
     zp_colrange_partial_kernel<<<dim3((o + 511) / 512, nslab), 256, 0, st>>>((const unsigned short*)W, h, o, pmin, pmax,
@@ -259,9 +279,14 @@ hipError_t launch_zp_quantize_weight(const void* W, int h, int o, int8_t* Wq, in
     colconst_kernel<true><<<(o + 255) / 256, 1024, 0, st>>>(pmax, pmin, nslab, o, nullptr, zc);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int KT = k_tiles(h), JT = row_tiles(o), steps = code_steps(KT, JT);
-    weight_codes_kernel<true><<<dim3((JT + 15) / 16, (KT / 2 + steps - 1) / steps), 256, 0, st>>>(
-        (const unsigned short*)W, h, o, nullptr, zc, Wq, KT, JT, steps);
+    // a workgroup's sums take the place of the ranges of a slab in the scratch (4 bytes per column): no more of them than slabs
+    const int KT = k_tiles(h), JT = row_tiles(o), most = zp_colrange_slabs(h, o);
+    const int steps = (KT / 2 + most - 1) / most, ny = (KT / 2 + steps - 1) / steps;
+    weight_codes_kernel<true><<<dim3((JT + 15) / 16, ny), 256, 0, st>>>((const unsigned short*)W, h, o, nullptr, zc, Wq, KT, JT,
+                                                                       steps, (int*)part);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    zp_colsum_kernel<<<(o + 255) / 256, 1024, 0, st>>>((const int*)part, ny, o, zc);
     return hipGetLastError();
 }
 

@@ -359,6 +359,29 @@ def test_weight_quantizer_sweep():
         assert np.array_equal(hip_weight_i8(qw), want)
 
 
+@pytest.mark.parametrize("h,o", [(1, 1), (3, 7), (15, 8), (16, 9), (17, 511), (64, 512), (65, 513), (127, 520), (129, 1031),
+                                 (300, 4104), (1000, 77), (2100, 1025), (4500, 5)])
+def test_weight_conversion_at_the_edges(h, o):
+    """Constants and codes of both quantizers on weights narrower and shorter than a workgroup's block, ragged in either
+    direction (rows that do not start on 16 bytes), and of several blocks with a remainder."""
+    import torch
+
+    import paper_2208_07339_amd as L
+    W = wl.make_custom(1, h, o, 0, seed=h + o)["W"]
+    W[0, 0] = 0.5  # no constant column, whatever the height
+    guard = torch.full((h * o + 64,), 777.0, dtype=torch.float16, device="cuda")  # what lies behind the matrix is not a weight
+    Wd = guard[:h * o].view(h, o)
+    Wd.copy_(torch.from_numpy(W.view(np.int16)).cuda().view(torch.float16))
+    want, cw = oracle.quantize_weight(W)
+    qw = L.quantize_weight(Wd)
+    assert np.array_equal(bits(qw.cw.cpu().numpy()), bits(cw)) and np.array_equal(hip_weight_i8(qw), want)
+    ref = oracle.zp_linear(np.zeros((1, h), np.float16), W, 6.0)
+    zw = L.zp_quantize_weight(Wd)
+    zc = zw.zc.cpu().numpy()
+    assert np.array_equal(zc[:, 1], ref["zp_w"]) and np.array_equal(zc[:, 2], ref["colsum"])
+    assert np.array_equal(hip_weight_i8(L.QuantizedWeight(zw.Wq, None, None, h, o)), ref["Wq"])
+
+
 def test_two_runs_are_bit_identical():
     d = wl.make_custom(300, 1000, 520, 4, seed=99)
     a = run_hip(d["X"], d["W"], 6.0, 32)
