@@ -265,6 +265,13 @@ static int linear_impl(const void* X_f16, int s, int h, float alpha, int granula
     // the constants of W were fixed when it was quantized; here only those of X depend on the granularity
     const int shared_cx = granularity == LLMINT8_TENSORWISE;
     hipError_t e;
+    // (one kernel reads X and writes Out: not where they overlap; and there is no matmul kernel to put events around)
+    const uintptr_t x0 = (uintptr_t)X_f16, x1 = x0 + (size_t)s * h * 2, o0 = (uintptr_t)Out_f16, o1 = o0 + (size_t)s * o * 2;
+    if (!shared_cx && !ev_before && !ev_after && (x1 <= o0 || o1 <= x0) && linear_small_takes(s, h, o, cap))
+        return hip_status(launch_linear_small(X_f16, s, h, threshold_bits(alpha), Wq, (const unsigned short*)cw_f16,
+                                              (const unsigned short*)W_f16, o, idx, cap, count, status, Xq,
+                                              (unsigned short*)cx_f16, (unsigned short*)Xo_f16, (unsigned short*)Out_f16,
+                                              st));
     if (s <= 32) {
         // without 16-bit weights the second kernel also rebuilds the outlier rows of W from the codes
         const ColumnJob job = {Wq, cw_f16, base + scan_ws(s, h, o, cap), o, (o + 255) & ~255};

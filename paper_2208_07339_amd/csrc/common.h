@@ -409,6 +409,11 @@ hipError_t launch_gemm_decode(const int8_t* Xq, const unsigned short* cx, const 
                               const int32_t* count, int cap, const int8_t* Wq, const unsigned short* cw,
                               const unsigned short* Wf, int rows_are_slots, const int32_t* idx, int s, int h, int o,
                               unsigned short* Out, int32_t* Cdbg, hipStream_t st, const ZpArgs* zp = nullptr);
+// the whole call in one kernel (small.hip), for the sizes linear_small_takes() says
+bool linear_small_takes(int s, int h, int o, int cap);
+hipError_t launch_linear_small(const void* X, int s, int h, unsigned thr, const int8_t* Wq, const unsigned short* cw,
+                               const unsigned short* Wf, int o, int32_t* idx, int cap, int32_t* count, int32_t* status,
+                               int8_t* Xq, unsigned short* cx, unsigned short* Xo, unsigned short* Out, hipStream_t st);
 hipError_t launch_dequant_rows(const int8_t* Wq, const unsigned short* cw, int h, int o, const int32_t* idx,
                                const int32_t* count, int cap, unsigned short* Wo, hipStream_t st);
 

@@ -1,0 +1,349 @@
+// A whole call in one kernel, for a few tokens of few features (s * h up to 32 768): outlier scan, row constants,
+// codes (Section 3.2, 2.1, 3.1) and the product (Eq. 7 + Eq. 8).
+#include "common.h"
+
+namespace llmint8 {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+
+#define FENCE() __builtin_amdgcn_sched_barrier(0)
+
+// ---------------------------------------------------------------------------
+// What bounds such a call is not the pre-pass's work but its launches: three kernels of 4.5 us each for 0.2 MB
+// (8 x 256 x 512), 10 us in front of a 15 us weight stream (1 x 5120 x 20480).  So there is one launch, and every
+// workgroup makes the codes of X for itself: X is at most 64 KiB, comes from L2, and the first two batches of the
+// workgroup's weights travel meanwhile.
+//
+// One workgroup = 4 waves, one tile of 32 output columns, K split over the waves, as in gemm_decode_kernel; the
+// codes of X are read from LDS instead of memory, which leaves registers for three workgroups per compute unit.
+// Row r of X belongs to 256 / sp threads (sp: s rounded up to a power of two), each holding XC chunks of 8
+// features in registers from the first load to the codes.  A column is an outlier when any of its entries says
+// so: those entries set bits of a bitmap in LDS, whose population counts place the columns in order.
+//
+// Every workgroup also writes its share of the codes; workgroup 0 writes idx, count, status, c_x and Xo.
+// ---------------------------------------------------------------------------
+struct SmallArgs {
+    const unsigned short* X;
+    int s, h, o, KT, lg_tpr;  // lg_tpr: log2 of the threads per row
+    unsigned thr;
+    const int8_t* Wq;
+    const unsigned short* cw;
+    const unsigned short* Wf;  // [h x o] fp16 weights, or NULL: outlier rows rebuilt from the codes
+    int32_t* idx;
+    int cap, opad;
+    int32_t* count;
+    int32_t* status;
+    int8_t* Xq;
+    unsigned short* cx;
+    unsigned short* Xo;
+    _Float16* Out;
+};
+
+constexpr int SSLOTS = 16;  // outlier slots whose operands are fetched before the weight stream goes on
+
+template <int XC>
+__global__ void __launch_bounds__(256, 3) linear_small_kernel(const SmallArgs a)
+{
+    constexpr int U = 8;                       // k-tiles per batch
+    extern __shared__ __attribute__((aligned(16))) int8_t xq[];  // codes [KT][2][sp][16], then 16 zero bytes
+    __shared__ int red[4][16][64];
+    __shared__ unsigned bitmap[XC * 64];       // outlier columns, 32 per word
+    __shared__ int s_idx[JOB_MAX_CAP];
+    __shared__ unsigned s_row[32];             // row constants, fp16 bits
+    __shared__ int s_wsum[4];
+    __shared__ unsigned short s_xo[SSLOTS][32], s_wo[SSLOTS][32];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int s = a.s, h = a.h, o = a.o, KT = a.KT;
+    const int lg = a.lg_tpr, tpr = 1 << lg, sp = 256 >> lg;
+    const int r = tid >> lg, g = tid & (tpr - 1);  // this thread's row, its first chunk
+    const unsigned short* row = a.X + (size_t)(r < s ? r : 0) * h;
+
+    // ---- X first, then the weights: loads are waited for in the order of issue
+    us8 v[XC];
+#pragma unroll
+    for (int m = 0; m < XC; m++) {
+        const int c = g + (m << lg);
+        v[m] = load8(row + (8 * c + 8 <= h ? 8 * c : 0));  // h >= 8; what does not exist is replaced below
+    }
+    const int jj = tid & 31, ig = tid >> 5;
+    const int jt = blockIdx.x, j = jt * 32 + jj;
+    const unsigned short cwb = a.cw[j < o ? j : 0];
+    const int kq = KT / 4;  // KT is a multiple of 4
+    const v4i* wp = (const v4i*)(a.Wq + ((size_t)jt * KT + (size_t)w * kq) * TILE_BYTES) + lane;
+    v4i wv[2][U];
+    auto load = [&](int B, int kt) {
+#pragma unroll
+        for (int u = 0; u < U; u++) wv[B][u] = __builtin_nontemporal_load(wp + (size_t)(kt + u < kq ? kt + u : kq - 1) * 64);
+    };
+    FENCE();
+    load(0, 0);
+    if (XC <= 8) load(1, U);  // 16 chunks of X take its registers
+    FENCE();
+
+    // ---- outlier columns
+    for (int q = tid; q < XC * 64; q += 256) bitmap[q] = 0;
+    if (tid < 32) s_row[tid] = 0;
+    if (tid < 4) ((int*)(xq + sp * KT * 32))[tid] = 0;
+    __syncthreads();
+    if (h & 7) {
+#pragma unroll
+        for (int m = 0; m < XC; m++) {
+            const int c = g + (m << lg);
+            if (8 * c < h && 8 * c + 8 > h)
+#pragma unroll
+                for (int e = 0; e < 8; e++) v[m][e] = 8 * c + e < h ? row[8 * c + e] : (unsigned short)0;
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < XC; m++) {
+        const int c = g + (m << lg);
+        if (r >= s || 8 * c >= h) v[m] = (us8)(0);
+        unsigned f = 0;
+        const us8 mag = v[m] & (unsigned short)0x7fff;
+        const us2 a2 = __builtin_elementwise_max(__builtin_elementwise_max(mag.s01, mag.s23),
+                                                 __builtin_elementwise_max(mag.s45, mag.s67));
+        if ((a2.x > a2.y ? a2.x : a2.y) >= a.thr && r < s) {
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+                if (8 * c + e < h && (unsigned)mag[e] >= a.thr) f |= 1u << e;
+        }
+        if (f) atomicOr(&bitmap[c >> 2], f << (8 * (c & 3)));
+    }
+    __syncthreads();
+    // positions of the columns: a thread has the words 4 tid .. 4 tid + 3
+    int cnt;
+    {
+        unsigned b[4];
+        int n = 0;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            b[q] = 4 * tid + q < XC * 64 ? bitmap[4 * tid + q] : 0u;
+            n += __popc(b[q]);
+        }
+        int incl = n;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int t = __shfl_up(incl, d);
+            if (lane >= d) incl += t;
+        }
+        if (lane == 63) s_wsum[w] = incl;
+        __syncthreads();
+        int pos = incl - n, total = 0;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            if (q < w) pos += s_wsum[q];
+            total += s_wsum[q];
+        }
+        cnt = total < a.cap ? total : a.cap;
+        if (n) {
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                unsigned left = b[q];
+                while (left) {
+                    const int bit = __ffs((int)left) - 1;
+                    left &= left - 1;
+                    if (pos < cnt) s_idx[pos] = 32 * (4 * tid + q) + bit;
+                    else b[q] &= ~(1u << bit);  // more columns than the buffer takes: ordinary ones from here on
+                    pos++;
+                }
+                if (total > cnt) bitmap[4 * tid + q] = b[q];
+            }
+        }
+        if (jt == 0 && tid == 0) {
+            *a.count = cnt;
+            if (a.status) *a.status = total > a.cap ? 1 : 0;
+        }
+    }
+    __syncthreads();
+
+    // ---- this workgroup's outlier operands: slots ig and ig + 8 of column jj, and of the tokens
+    unsigned short wo[2] = {0, 0}, xo[2] = {0, 0};
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        const int t = ig + 8 * q;
+        if (t < cnt) {
+            const int k = s_idx[t];
+            xo[q] = a.X[(size_t)(jj < s ? jj : 0) * h + k];
+            if (a.Wf)
+                wo[q] = a.Wf[(size_t)k * o + (j < o ? j : 0)];
+            else
+                wo[q] = (unsigned char)a.Wq[((size_t)jt * KT + (k >> 5)) * TILE_BYTES + tile_byte(jj, k & 31)];
+        }
+    }
+
+    // ---- row constants and codes
+    us8 mx = (us8)(0);
+    unsigned bits[XC];
+#pragma unroll
+    for (int m = 0; m < XC; m++) {
+        const int c = g + (m << lg);
+        bits[m] = c < 4 * KT ? (bitmap[c >> 2] >> (8 * (c & 3))) & 0xffu : 0u;
+        if (bits[m]) {
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+                if ((bits[m] >> e) & 1u) v[m][e] = 0;
+        }
+        mx = __builtin_elementwise_max(mx, v[m] & (unsigned short)0x7fff);
+    }
+    {
+        const us2 a2 = __builtin_elementwise_max(__builtin_elementwise_max(mx.s01, mx.s23),
+                                                 __builtin_elementwise_max(mx.s45, mx.s67));
+        unsigned m1 = a2.x > a2.y ? a2.x : a2.y;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1)
+            if (d < tpr) {
+                const unsigned t = (unsigned)__shfl_xor((int)m1, d);
+                m1 = t > m1 ? t : m1;
+            }
+        if ((g & 63) == 0) atomicMax(&s_row[r], m1);
+    }
+    __syncthreads();
+    {
+        const float f = code_factor(f16_bits_to_float((unsigned short)s_row[r]));
+#pragma unroll
+        for (int m = 0; m < XC; m++) {
+            const int c = g + (m << lg);
+            unsigned t[8];
+#pragma unroll
+            for (int e = 0; e < 8; e++) t[e] = code_bits(v[m][e], f);
+            const u2 pk = {pack_low_bytes(t[0], t[1], t[2], t[3]), pack_low_bytes(t[4], t[5], t[6], t[7])};
+            if (c < 4 * KT) *(u2*)(xq + (((c >> 1) * sp + r) * 16 + (c & 1) * 8)) = pk;
+        }
+    }
+    __syncthreads();
+    const int lr = lane & 31;
+    const int8_t* xb = lr < sp ? xq + ((lane >> 5) * sp + lr) * 16 : xq + sp * KT * 32;
+    const int xstep = lr < sp ? 32 * sp : 0;
+
+    // ---- the stream goes on
+    if (XC > 8) load(1, U);
+    v16i acc;
+#pragma unroll
+    for (int q = 0; q < 16; q++) acc[q] = 0;
+    const int8_t* xw = xb + w * kq * xstep;
+    auto mm = [&](int B, int kt) {
+        v4i x[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) x[u] = *(const v4i*)(xw + (kt + u) * xstep);
+#pragma unroll
+        for (int u = 0; u < U; u++) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wv[B][u], x[u], acc, 0, 0, 0);
+    };
+    auto mm_rest = [&](int B, int kt) {
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (kt + u < kq)
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wv[B][u], *(const v4i*)(xw + (kt + u) * xstep), acc, 0, 0, 0);
+    };
+    int kt = 0;
+    for (; kt + 2 * U <= kq; kt += 2 * U) {
+        mm(0, kt);
+        FENCE();
+        if (kt + 2 * U < kq) load(0, kt + 2 * U);
+        FENCE();
+        mm(1, kt + U);
+        FENCE();
+        if (kt + 3 * U < kq) load(1, kt + 3 * U);
+        FENCE();
+    }
+    mm_rest(0, kt);
+    mm_rest(1, kt + U);
+
+    // ---- this workgroup's share of the outputs of the pre-pass
+    for (int t = jt * 4 + w; t < KT; t += gridDim.x * 4) *((v4i*)(a.Xq + (size_t)t * TILE_BYTES) + lane) = *(const v4i*)(xb + t * xstep);
+    if (jt == 0) {
+        for (int q = tid; q < cnt; q += 256) a.idx[q] = s_idx[q];
+        for (int q = tid; q < s * a.opad; q += 256) {
+            const int i = q / a.opad, t = q - i * a.opad;
+            a.Xo[q] = t < cnt ? a.X[(size_t)i * h + s_idx[t]] : (unsigned short)0;
+        }
+        if (tid < s) a.cx[tid] = (unsigned short)s_row[tid];
+    }
+
+    // ---- the four partial sums meet in LDS; token i, column jj of the tile: register 4 (jj / 8) + jj % 4 of lane
+    // i + 32 ((jj / 4) % 2)
+#pragma unroll
+    for (int q = 0; q < 16; q++) red[w][q][lane] = acc[q];
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        s_xo[ig + 8 * q][jj] = xo[q];
+        s_wo[ig + 8 * q][jj] = a.Wf ? wo[q] : dequant_bits((int)(int8_t)wo[q], cwb);
+    }
+    __syncthreads();
+    if (j >= o) return;
+    const int rr = 4 * (jj >> 3) + (jj & 3), l0 = 32 * ((jj >> 2) & 1);
+    const float cwj = f16_bits_to_float(cwb);
+    for (int i = ig; i < s; i += 8) {
+        const int l = l0 + i;
+        const int c = red[0][rr][l] + red[1][rr][l] + red[2][rr][l] + red[3][rr][l];
+        // Eq. 7 dequantization, then the outlier product of Eq. 8 accumulated in fp32
+        float d = (float)c * (f16_bits_to_float((unsigned short)s_row[i]) * (1.0f / 16129.0f)) * cwj;
+        for (int t = 0; t < (cnt < SSLOTS ? cnt : SSLOTS); t++)
+            d = __builtin_fmaf(f16_bits_to_float(s_xo[t][i]), f16_bits_to_float(s_wo[t][jj]), d);
+        for (int t = SSLOTS; t < cnt; t++) {  // more outlier columns than were fetched: rare
+            const int k = s_idx[t];
+            const unsigned short wk =
+                a.Wf ? a.Wf[(size_t)k * o + j]
+                     : dequant_bits((int)a.Wq[((size_t)jt * KT + (k >> 5)) * TILE_BYTES + tile_byte(jj, k & 31)], cwb);
+            d = __builtin_fmaf(f16_bits_to_float(a.X[(size_t)i * h + k]), f16_bits_to_float(wk), d);
+        }
+        a.Out[(size_t)i * o + j] = (_Float16)d;
+    }
+}
+
+// log2 of the threads per row, and the chunks of 8 features per thread (0: X too large for this path)
+static int small_chunks(int s, int h, int cap, int* lg)
+{
+    if (s > 32 || h < 8 || cap > JOB_MAX_CAP) return 0;
+    int l = 8;
+    while ((256 >> l) < s) l--;
+    *lg = l;
+    const int n = (4 * k_tiles(h) + (1 << l) - 1) >> l;
+    return n <= 16 ? n : 0;
+}
+
+// Where one kernel is the better way, per call against the separate kernels.  Every workgroup repeats the
+// pre-pass, about 1 200 vector instructions per wave at 16 chunks, so its price grows with the chunks and with the
+// workgroups that share a compute unit; what it saves is two launches and two short kernels, 6 to 10 us.
+//   up to 8 chunks, any W: 8 x 256 x 512 10.2 against 15.3 us, 2 x 4096 x 4096 10.2 / 17.0, 1 x 5120 x 20480 18.4 /
+//     29.1, 8 x 2048 x 32768 21.6 / 23.9, 1 x 12288 x 49152 90.9 / 97.9
+//   9 to 16 chunks: 1 x 32768 x 4096 32.6 / 44.8, 16 x 2048 x 4096 14.3 / 16.6, 8 x 4096 x 12288 18.9 / 21.7 (384 column
+//     tiles), but 1 x 32768 x 16384 94.9 / 92.9 (512) and 32 x 1024 x 32768 35.5 / 27.5 (1 024): taken up to
+//     one and a half workgroups per compute unit
+bool linear_small_takes(int s, int h, int o, int cap)
+{
+    int lg, cus = 0;
+    if (g_decode_cfg.load(std::memory_order_relaxed) >= 0) return false;  // test hook: the separate kernels
+    const int n = small_chunks(s, h, cap, &lg);
+    if (n == 0 || n <= 8) return n != 0;
+    if (prefill_device_setup(&cus) != hipSuccess) cus = 256;
+    return 2 * row_tiles(o) <= 3 * cus;
+}
+
+hipError_t launch_linear_small(const void* X, int s, int h, unsigned thr, const int8_t* Wq, const unsigned short* cw,
+                               const unsigned short* Wf, int o, int32_t* idx, int cap, int32_t* count, int32_t* status,
+                               int8_t* Xq, unsigned short* cx, unsigned short* Xo, unsigned short* Out, hipStream_t st)
+{
+    int lg = 0;
+    const int n = small_chunks(s, h, cap, &lg);
+    if (n == 0) return hipErrorInvalidValue;
+    const int KT = k_tiles(h);
+    const SmallArgs a = {(const unsigned short*)X, s, h, o, KT, lg, thr, Wq, cw, Wf, idx, cap, opad_of(cap), count, status,
+                         Xq, cx, Xo, (_Float16*)Out};
+    const int grid = row_tiles(o);
+    const size_t shm = (size_t)(256 >> lg) * KT * 32 + 16;
+    if (n <= 1)
+        linear_small_kernel<1><<<grid, 256, shm, st>>>(a);
+    else if (n <= 4)
+        linear_small_kernel<4><<<grid, 256, shm, st>>>(a);
+    else if (n <= 8)
+        linear_small_kernel<8><<<grid, 256, shm, st>>>(a);
+    else
+        linear_small_kernel<16><<<grid, 256, shm, st>>>(a);
+    return hipGetLastError();
+}
+
+}  // namespace llmint8

@@ -447,6 +447,34 @@ def test_linear_short_x(s, h, o, ncol):
     linear_compare(wl.make_custom(s, h, o, ncol, seed=s * 11 + h))
 
 
+@pytest.mark.parametrize("s,h,o,ncol,cap", [(1, 8, 1, 0, 16), (5, 9, 33, 2, 16), (1, 2048, 32, 3, 32), (1, 2049, 40, 3, 32),
+                                            (1, 8192, 64, 5, 32), (2, 4224, 72, 4, 32), (1, 16383, 31, 6, 256),
+                                            (1, 32768, 96, 9, 32), (1, 32769, 32, 9, 32), (32, 511, 100, 20, 32),
+                                            (32, 1024, 64, 40, 48), (32, 1025, 64, 4, 32), (17, 1000, 200, 9, 4),
+                                            (3, 8190, 64, 6, 257)])
+def test_linear_in_one_kernel(s, h, o, ncol, cap):
+    """Around the bounds of the one-kernel call (chunks per thread, rows that do not fill their threads, features
+    that do not fill a chunk, more columns than slots or than the buffer takes): against the oracle, and on weights
+    kept as codes only against the staged calls, bit for bit."""
+    d = wl.make_custom(s, h, o, ncol, seed=s + h + o)
+    linear_compare(d, cap=cap)
+    linear_compare(d, alpha=0.0, cap=cap)
+    linear_compare(d, alpha=float("inf"), cap=cap)
+    if ncol <= cap:
+        int8_rows_compare(d, cap=cap, via_linear=True)
+
+
+def test_linear_with_the_result_in_the_place_of_x():
+    import torch
+
+    import paper_2208_07339_amd as L
+    d = wl.make_custom(8, 1024, 1024, 5, seed=77)
+    g = run_hip(d["X"], d["W"], 6.0, 32, want_c=False)
+    out = L.linear(g["Xd"], g["qw"], 6.0, g["outl"], g["rows"], g["ws"], out=g["Xd"])
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(out.cpu().numpy()), bits(g["Out"]))
+
+
 def test_linear_prefill_sizes():
     """llmint8_linear for s > 32: the row constants and the quantizer read the scan's column lists."""
     linear_compare(wl.make_custom(100, 512, 256, 3, seed=41))
