@@ -414,11 +414,18 @@ bool linear_small_takes(int s, int h, int o, int cap);
 hipError_t launch_linear_small(const void* X, int s, int h, unsigned thr, const int8_t* Wq, const unsigned short* cw,
                                const unsigned short* Wf, int o, int32_t* idx, int cap, int32_t* count, int32_t* status,
                                int8_t* Xq, unsigned short* cx, unsigned short* Xo, unsigned short* Out, hipStream_t st);
+// tiles of 32 to 64 columns, K split over the waves of a workgroup (ksplit.hip), for the sizes ksplit_takes() says
+bool ksplit_takes(int s, int h, int o);
+hipError_t launch_gemm_ksplit(const int8_t* Xq, const unsigned short* cx, const unsigned short* Xo,
+                              const int32_t* count, int cap, const int8_t* Wq, const unsigned short* cw,
+                              const unsigned short* Wf, int rows_are_slots, const int32_t* idx, int s, int h, int o,
+                              unsigned short* Out, int32_t* Cdbg, hipStream_t st, const ZpArgs* zp = nullptr);
 hipError_t launch_dequant_rows(const int8_t* Wq, const unsigned short* cw, int h, int o, const int32_t* idx,
                                const int32_t* count, int cap, unsigned short* Wo, hipStream_t st);
 
 // tile shape the prefill GEMM chooses for a product of s x h by h x o (host arithmetic only)
 int pick_cfg(int s, int h, int o);
+void prefill_tile_size(int s, int h, int o, int* cols, int* toks);
 // tile shape of the prefill GEMM forced by llmint8_debug_prefill_tile (-1: chosen from the shape)
 extern std::atomic<int> g_force_cfg;
 // work split of the decode kernel forced by llmint8_debug_decode_shape (-1: default)

@@ -819,9 +819,9 @@ static inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // five weight matrices at 33 to 1 024 tokens and to the three full-size workloads: the choice is then within
 // 0.8 % of the fastest shape on average and 9 % in the worst case (5 120 x 20 480 at 1 024 tokens).
 constexpr int NCFG = 6;
+static const int cols[NCFG] = {256, 192, 128, 128, 192, 192}, toks[NCFG] = {256, 256, 256, 128, 128, 64};
 int pick_cfg(int s, int h, int o)
 {
-    static const int cols[NCFG] = {256, 192, 128, 128, 192, 192}, toks[NCFG] = {256, 256, 256, 128, 128, 64};
     static const double eff[NCFG] = {1.0, 0.96, 0.95, 0.85, 0.8, 0.5};  // relative MFMA rate of the main loop
     const double mfma_per_cu = 8e12, l2_all = 14e12, hbm = 6.9e12, ncu = 256.0, per_pass = 1.5e-6;
     int best = 0;
@@ -837,6 +837,13 @@ int pick_cfg(int s, int h, int o)
         if (c == 0 || cost < bestc) { best = c; bestc = cost; }
     }
     return best;
+}
+
+void prefill_tile_size(int s, int h, int o, int* c, int* t)
+{
+    const int k = pick_cfg(s, h, o);
+    *c = cols[k];
+    *t = toks[k];
 }
 
 std::atomic<int> g_force_cfg{-1};  // test hook: tile shape override (-1 = automatic)

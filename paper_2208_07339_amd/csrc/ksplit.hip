@@ -1,0 +1,349 @@
+// Eq. 7 + Eq. 8 for products that are too small to fill the chip with the tiles of gemm.hip.
+#include "common.h"
+
+namespace llmint8 {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+
+#define FENCE() __builtin_amdgcn_sched_barrier(0)
+
+constexpr int KSLOTS = 32;  // outlier slots kept in LDS
+
+struct KsplitArgs {
+    const int8_t* Wq;
+    const int8_t* Xq;
+    int KT, JT, RT, nP, nQ;
+    const unsigned short* cw;
+    const unsigned short* cx;
+    const unsigned short* Wf;
+    int rows_are_slots, wrows;
+    const int32_t* idx;
+    const unsigned short* Xo;
+    const int32_t* count;
+    int cap, opad;
+    _Float16* Out;
+    int32_t* Cdbg;
+    int s, h, o;
+    ZpArgs zp;
+};
+
+// ---------------------------------------------------------------------------
+// A tile of 128 or more columns per workgroup leaves most compute units without work when the product is small, and
+// one compute unit pulls only so much: about 30 KB/us of W from memory (48 from the last-level cache), 60 to 85 in
+// all.  So the tiles here are 32 NJ columns x 32 NI tokens, and the eight waves of a workgroup split K among
+// them (wave w takes the k-tiles w, w + 8, ..), each with all NJ x NI accumulators.  Operands go straight into
+// registers, R k-tiles in flight per wave, with no barrier in the K loop.  The eight sums meet in LDS, token tile by
+// token tile (32-bit integers: the same in any order).  The kernel alone, against the tiles of gemm.hip, on a W from
+// memory / from the last-level cache: 53 x 9856 x 4480 39.6 -> 22.0 / 29.3 -> 16.0 us, 48 x 14336 x 4096 57.5 -> 20.3 /
+// 39.3 -> 13.7, 128 x 12288 x 8192 58.9 -> 35.4 / 36.3 -> 23.7, 64 x 4096 x 4096 15.7 -> 9.4, 96 x 12288 x 12288 57.6 ->
+// 46.8 / 35.9 -> 29.6.
+//
+// Measured and left out: batches of several k-tiles instead of a ring, contiguous parts of K per wave, and starting
+// points in K that differ from workgroup to workgroup (all the same time); W streamed past the caches (96 x 5120 x
+// 15360 26.5 -> 23.3 us from memory, but 19.4 -> 22.0 from the last-level cache).
+//
+// ZP: zeropoint constants, as in gemm.hip.
+// ---------------------------------------------------------------------------
+template <int NJ, int NI, int R, bool ZP>
+__global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
+{
+    constexpr int NW = 8, NC = 32 * NJ, NTK = 32 * NI;
+    __shared__ v4i red[4][NJ * 4][64];                  // [wave][4 columns of a tile][token + 32 half, swizzled]
+    __shared__ unsigned short s_wo[KSLOTS][NC];
+    __shared__ __attribute__((aligned(16))) unsigned short s_xo[NTK][KSLOTS];
+    __shared__ float s_sx[ZP ? 1 : NTK];
+    __shared__ double s_zc[ZP ? 3 : 1][ZP ? NC : 1];
+    __shared__ int4 s_zx[ZP ? NTK : 1];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int s = a.s, o = a.o, KT = a.KT;
+    // consecutive workgroups go round-robin to the 8 XCDs; each XCD gets a contiguous run of the tiles, column block by
+    // column block, so that the token blocks of one column block share its part of W in one L2
+    const int total = a.nP * a.nQ, xcd = blockIdx.x & 7, more = total & 7;
+    const int tile = xcd * (total >> 3) + (xcd < more ? xcd : more) + (blockIdx.x >> 3);
+    const int cb = tile / a.nQ, tb = tile - cb * a.nQ;
+    const int J0 = cb * NC, I0 = tb * NTK;
+
+    // ---- epilogue operands
+    int cnt = *a.count;
+    constexpr int TPC = 512 / NC;          // threads per column: a thread has slots q TPC + tid / NC of column tid % NC
+    constexpr int NS = KSLOTS / TPC;
+    const int jc = tid % NC, t0 = tid / NC;
+    unsigned short wo[NS], cx_raw = 0;
+    int kk[NS];
+#pragma unroll
+    for (int q = 0; q < NS; q++) {
+        const int t = t0 + q * TPC;
+        kk[q] = a.rows_are_slots ? t : a.idx[t < a.cap ? t : 0];
+    }
+    us8 xo = (us8)(0);
+    int4 zx = make_int4(0, 0, 0, 0);
+    double zc[3] = {0, 0, 0};
+    const int xs = (tid & 3) * 8;  // this thread's first slot of token tid / 4
+    if (tid < 4 * NTK && xs < a.opad) {
+        const int i = I0 + (tid >> 2);
+        xo = *(const us8*)(a.Xo + (size_t)(i < s ? i : s - 1) * a.opad + xs);
+    }
+    if (tid < NTK) {
+        const int i = I0 + tid;
+        if constexpr (ZP) zx = a.zp.zcx[i < s ? i : s - 1]; else cx_raw = a.cx[i < s ? i : s - 1];
+    }
+    if constexpr (ZP) {
+        if (tid < NC) {
+#pragma unroll
+            for (int q = 0; q < 3; q++) zc[q] = a.zp.colc[(size_t)q * a.zp.pitch + J0 + tid];
+        }
+    }
+    FENCE();
+
+    // ---- this wave's part of K
+    const int n = (KT - w + NW - 1) / NW;  // k-tiles w, w + 8, ..; none in a short K
+    const int k0 = n > 0 ? w : 0;
+    const v4i *wp[NJ], *xp[NI];
+#pragma unroll
+    for (int c = 0; c < NJ; c++) {
+        const int jt = cb * NJ + c < a.JT ? cb * NJ + c : a.JT - 1;
+        wp[c] = (const v4i*)(a.Wq + ((size_t)jt * KT + k0) * TILE_BYTES) + lane;
+    }
+#pragma unroll
+    for (int t = 0; t < NI; t++) {
+        const int rt = tb * NI + t < a.RT ? tb * NI + t : a.RT - 1;
+        xp[t] = (const v4i*)(a.Xq + ((size_t)rt * KT + k0) * TILE_BYTES) + lane;
+    }
+    v16i acc[NJ][NI];
+#pragma unroll
+    for (int c = 0; c < NJ; c++)
+#pragma unroll
+        for (int t = 0; t < NI; t++)
+#pragma unroll
+            for (int q = 0; q < 16; q++) acc[c][t][q] = 0;
+    v4i wv[R][NJ], xv[R][NI];
+    auto load = [&](int r, int kt) {
+        int k = kt < n ? kt : n - 1;
+        k = k > 0 ? k : 0;
+#pragma unroll
+        for (int c = 0; c < NJ; c++) wv[r][c] = wp[c][(size_t)k * (NW * 64)];
+#pragma unroll
+        for (int t = 0; t < NI; t++) xv[r][t] = xp[t][(size_t)k * (NW * 64)];
+    };
+    auto mm = [&](int r) {
+#pragma unroll
+        for (int c = 0; c < NJ; c++)
+#pragma unroll
+            for (int t = 0; t < NI; t++)
+                acc[c][t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wv[r][c], xv[r][t], acc[c][t], 0, 0, 0);
+    };
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        load(r, r);
+        FENCE();
+    }
+    cnt = cnt < 0 ? 0 : (cnt > a.cap ? a.cap : cnt);
+#pragma unroll
+    for (int q = 0; q < NS; q++) {
+        const unsigned k = (unsigned)kk[q];
+        const bool ok = k < (unsigned)a.wrows && t0 + q * TPC < cnt && J0 + jc < o;
+        wo[q] = a.Wf[(size_t)(ok ? k : 0u) * o + (J0 + jc < o ? J0 + jc : 0)];
+        if (!ok) wo[q] = 0;
+    }
+    FENCE();
+    int kt = 0;
+    for (; kt + R <= n; kt += R) {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            mm(r);
+            FENCE();
+            load(r, kt + R + r);
+            FENCE();
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++)
+        if (kt + r < n) mm(r);
+
+    // ---- epilogue operands into LDS
+#pragma unroll
+    for (int q = 0; q < NS; q++)
+        s_wo[t0 + q * TPC][jc] = wo[q];
+    if (tid < 4 * NTK) *(us8*)&s_xo[tid >> 2][xs] = xo;
+    if (tid < NTK) {
+        if constexpr (ZP) s_zx[tid] = zx; else s_sx[tid] = f16_bits_to_float(cx_raw) * (1.0f / 16129.0f);
+    }
+    if constexpr (ZP) {
+        if (tid < NC) {
+#pragma unroll
+            for (int q = 0; q < 3; q++) s_zc[q][tid] = zc[q];
+        }
+    }
+    // this thread's outputs: token il of a tile, columns jl .. jl + 3
+    const int il = tid / (8 * NJ), ch = tid % (8 * NJ), jl = 4 * ch, j = J0 + jl;
+    float cwj[4] = {0, 0, 0, 0};
+    if constexpr (!ZP) {
+#pragma unroll
+        for (int e = 0; e < 4; e++) cwj[e] = f16_bits_to_float(a.cw[j + e < o ? j + e : 0]);
+    }
+#pragma unroll
+    for (int t = 0; t < NI; t++) {
+        if (t > 0) __syncthreads();
+        // waves 4 .. 7 hand their sums to waves 0 .. 3
+        if (w >= 4) {
+#pragma unroll
+            for (int m = 0; m < 4 * NJ; m++) {
+                const v4i v = {acc[m >> 2][t][4 * (m & 3)], acc[m >> 2][t][4 * (m & 3) + 1], acc[m >> 2][t][4 * (m & 3) + 2],
+                               acc[m >> 2][t][4 * (m & 3) + 3]};
+                red[w - 4][m][lane ^ ((m & 7) << 2)] = v;
+            }
+        }
+        __syncthreads();
+        if (w < 4) {
+#pragma unroll
+            for (int m = 0; m < 4 * NJ; m++) {
+                v4i v = red[w][m][lane ^ ((m & 7) << 2)];
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] += acc[m >> 2][t][4 * (m & 3) + e];
+                red[w][m][lane ^ ((m & 7) << 2)] = v;
+            }
+        }
+        __syncthreads();
+        const int i = I0 + 32 * t + il;
+        if (il < 32 && i < s && j < o) {
+            const int m = ch >> 1, l = (il + 32 * (ch & 1)) ^ ((m & 7) << 2);
+            const v4i c = red[0][m][l] + red[1][m][l] + red[2][m][l] + red[3][m][l];
+            if (a.Cdbg) {
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    if (j + e < o) a.Cdbg[(size_t)i * o + j + e] = c[e];
+            }
+            // Eq. 7 (zeropoint: Eq. 5), to which Eq. 8 adds the outlier product: that sum first, as in gemm.hip, or, up
+            // to 32 tokens, last, as in the weight-streaming kernel (the one-call path there gives the same bits)
+            float p[4], d[4] = {0, 0, 0, 0};
+            if constexpr (ZP) {
+                const int4 rec = s_zx[32 * t + il];
+                const double sa = zp_range((unsigned)rec.x) * (1.0 / 254.0), za = (double)rec.y, rs = (double)rec.z;
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    p[e] = (float)(sa * __builtin_fma((double)c[e], s_zc[0][jl + e],
+                                                      __builtin_fma(rs, s_zc[1][jl + e], za * s_zc[2][jl + e])));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; e++) p[e] = (float)c[e] * s_sx[32 * t + il];
+            }
+            if (s <= 32) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) d[e] = ZP ? p[e] : p[e] * cwj[e];
+            }
+            const int ns = cnt < KSLOTS ? cnt : KSLOTS;
+            for (int q = 0; q < ns; q++) {
+                const float x = f16_bits_to_float(s_xo[32 * t + il][q]);
+#pragma unroll
+                for (int e = 0; e < 4; e++) d[e] = __builtin_fmaf(x, f16_bits_to_float(s_wo[q][jl + e]), d[e]);
+            }
+            for (int q = KSLOTS; q < cnt; q++) {  // more outlier columns than fit: rare
+                const unsigned k = a.rows_are_slots ? (unsigned)q : (unsigned)a.idx[q];
+                if (k >= (unsigned)a.wrows) continue;
+                const float x = f16_bits_to_float(a.Xo[(size_t)i * a.opad + q]);
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    d[e] = __builtin_fmaf(x, f16_bits_to_float(a.Wf[(size_t)k * o + (j + e < o ? j + e : 0)]), d[e]);
+            }
+            if (s > 32) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) d[e] = ZP ? d[e] + p[e] : __builtin_fmaf(p[e], cwj[e], d[e]);
+            }
+            const v4h hv = {(_Float16)d[0], (_Float16)d[1], (_Float16)d[2], (_Float16)d[3]};
+            _Float16* out = a.Out + (size_t)i * o + j;
+            if (j + 4 <= o) {
+                __builtin_memcpy(out, &hv, 8);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    if (j + e < o) out[e] = hv[e];
+            }
+        }
+    }
+}
+
+template <int NJ, int NI, int R>
+static hipError_t launch(KsplitArgs& a, bool zp, hipStream_t st)
+{
+    a.nP = (a.JT + NJ - 1) / NJ;
+    a.nQ = (a.RT + NI - 1) / NI;
+    const int grid = a.nP * a.nQ;
+    if (zp)
+        gemm_ksplit_kernel<NJ, NI, R, true><<<grid, 512, 0, st>>>(a);
+    else
+        gemm_ksplit_kernel<NJ, NI, R, false><<<grid, 512, 0, st>>>(a);
+    return hipGetLastError();
+}
+
+// Estimated time of a tile grid in us, without what every launch costs: the bytes a compute unit pulls, of W and
+// in all, and the bytes that all of them pull together (13 TB/s).  two: two workgroups fit a compute unit.
+static double pull_time(int s, int h, int o, int cols, int toks, int cus, bool two, double rate)
+{
+    const double tiles = (double)((o + cols - 1) / cols) * ((s + toks - 1) / toks);
+    double rounds = tiles / cus;
+    if (!two || rounds < 1) rounds = (double)(long)((tiles + cus - 1) / cus);
+    const double w = 1e-3 * h * cols, all = 1e-3 * h * (cols + toks);
+    const double t_w = rounds * w / ((double)h * o > 40e6 ? 38.0 : 48.0), t_all = rounds * all / rate;
+    const double t_l2 = tiles * all / 13000.0;
+    const double t = t_w > t_all ? t_w : t_all;
+    return t > t_l2 ? t : t_l2;
+}
+
+constexpr int KS_SHAPES = 4;
+static const int ks_nj[KS_SHAPES] = {1, 2, 2, 2}, ks_ni[KS_SHAPES] = {1, 1, 2, 3};
+
+// The shape for a product, or -1 where the other kernels are the better ones.  Products whose tiles in gemm.hip
+// fill the chip stay there (512 x 4096 x 4096 17.0 against 17.6 us at best, 630 x 13824 x 6528 68 against 103); the
+// others come here if the estimate says that they gain 8 % with the launch counted (it is within a third of
+// the measured times on 25 products of 33 to 1 094 tokens, and low for these kernels rather than for those).
+// Up to 32 tokens, the weight-streaming kernel keeps every W that gives a quarter of the compute units a column tile
+// (8 x 8192 x 8192 14.2 against 21.4 us); below that 8 waves per column tile pull more than 4: 10 x 9224 x 896 12.1 ->
+// 9.3, 4 x 12288 x 1024 13.0 -> 11.5.
+static int ksplit_shape(int s, int h, int o)
+{
+    if (g_decode_cfg.load(std::memory_order_relaxed) >= 0 || g_force_cfg.load(std::memory_order_relaxed) >= 0)
+        return -1;  // test hooks: the other kernels
+    int cus = 0;
+    if (prefill_device_setup(&cus) != hipSuccess) cus = 256;
+    if (s <= 32) return 4 * row_tiles(o) <= cus ? 0 : -1;
+    int cols, toks;
+    prefill_tile_size(s, h, o, &cols, &toks);
+    if ((long)((o + cols - 1) / cols) * ((s + toks - 1) / toks) >= cus) return -1;
+    // (a launch with next to nothing to do takes 5.5 us there, 4.5 us here and 0.6 us more per token tile of a
+    // workgroup: 384 x 700 x 4800 8.9 us there and 11.1 here)
+    double best = 0.92 * (pull_time(s, h, o, cols, toks, cus, false, 85.0) + 5.5);
+    int shape = -1;
+    for (int c = 0; c < KS_SHAPES; c++) {
+        const double t = pull_time(s, h, o, 32 * ks_nj[c], 32 * ks_ni[c], cus, ks_ni[c] == 1, 65.0) +
+                         4.5 + 0.6 * ks_ni[c];
+        if (t < best) {
+            best = t;
+            shape = c;
+        }
+    }
+    return shape;
+}
+
+bool ksplit_takes(int s, int h, int o) { return ksplit_shape(s, h, o) >= 0; }
+
+hipError_t launch_gemm_ksplit(const int8_t* Xq, const unsigned short* cx, const unsigned short* Xo,
+                              const int32_t* count, int cap, const int8_t* Wq, const unsigned short* cw,
+                              const unsigned short* Wf, int rows_are_slots, const int32_t* idx, int s, int h, int o,
+                              unsigned short* Out, int32_t* Cdbg, hipStream_t st, const ZpArgs* zp)
+{
+    KsplitArgs a = {Wq, Xq, k_tiles(h), row_tiles(o), row_tiles(s), 0, 0, cw, cx, Wf, rows_are_slots,
+                    rows_are_slots ? opad_of(cap) : h, idx, Xo, count, cap, opad_of(cap), (_Float16*)Out, Cdbg, s, h, o,
+                    zp ? *zp : ZpArgs{nullptr, nullptr, 0}};
+    switch (ksplit_shape(s, h, o)) {
+        case 0: return launch<1, 1, 8>(a, zp, st);
+        case 1: return zp ? launch<2, 1, 5>(a, zp, st) : launch<2, 1, 6>(a, zp, st);  // two workgroups per compute unit
+        case 2: return launch<2, 2, 6>(a, zp, st);
+        case 3: return launch<2, 3, 4>(a, zp, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace llmint8

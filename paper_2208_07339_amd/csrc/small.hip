@@ -42,10 +42,10 @@ struct SmallArgs {
     _Float16* Out;
 };
 
-constexpr int SSLOTS = 16;  // outlier slots whose operands are fetched before the weight stream goes on
+constexpr int SSLOTS = 32;  // outlier slots whose operands are fetched before the weight stream goes on
 
 template <int XC>
-__global__ void __launch_bounds__(256, 3) linear_small_kernel(const SmallArgs a)
+__global__ void __launch_bounds__(256, XC <= 4 ? 4 : 3) linear_small_kernel(const SmallArgs a)
 {
     constexpr int U = 8;                       // k-tiles per batch
     extern __shared__ __attribute__((aligned(16))) int8_t xq[];  // codes [KT][2][sp][16], then 16 zero bytes
@@ -160,11 +160,12 @@ __global__ void __launch_bounds__(256, 3) linear_small_kernel(const SmallArgs a)
     }
     __syncthreads();
 
-    // ---- this workgroup's outlier operands: slots ig and ig + 8 of column jj, and of the tokens
-    unsigned short wo[2] = {0, 0}, xo[2] = {0, 0};
+    // ---- this workgroup's outlier operands: slots ig, ig + 8, .. of column jj, and of the tokens
+    unsigned short wo[SSLOTS / 8], xo[SSLOTS / 8];
 #pragma unroll
-    for (int q = 0; q < 2; q++) {
+    for (int q = 0; q < SSLOTS / 8; q++) {
         const int t = ig + 8 * q;
+        wo[q] = xo[q] = 0;
         if (t < cnt) {
             const int k = s_idx[t];
             xo[q] = a.X[(size_t)(jj < s ? jj : 0) * h + k];
@@ -268,7 +269,7 @@ __global__ void __launch_bounds__(256, 3) linear_small_kernel(const SmallArgs a)
 #pragma unroll
     for (int q = 0; q < 16; q++) red[w][q][lane] = acc[q];
 #pragma unroll
-    for (int q = 0; q < 2; q++) {
+    for (int q = 0; q < SSLOTS / 8; q++) {
         s_xo[ig + 8 * q][jj] = xo[q];
         s_wo[ig + 8 * q][jj] = a.Wf ? wo[q] : dequant_bits((int)(int8_t)wo[q], cwb);
     }

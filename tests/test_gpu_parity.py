@@ -240,6 +240,23 @@ def test_short_x_goes_to_the_tiled_kernel_where_w_has_two_to_four_column_tiles_p
     assert_out_close(outs[1], ref["Out"])
 
 
+@pytest.mark.parametrize("s,h,o,ncol,cap", [(20, 3000, 1000, 5, 32), (33, 100, 40, 2, 16), (45, 1000, 700, 20, 32),
+                                            (300, 3000, 1000, 40, 48), (260, 1501, 1903, 33, 48), (43, 112, 4909, 4, 32),
+                                            (128, 3000, 5000, 6, 32), (100, 2900, 6001, 7, 32), (96, 5120, 9000, 7, 32),
+                                            (65, 4189, 8789, 9, 32)])
+def test_tiles_with_k_split_over_the_waves(s, h, o, ncol, cap):
+    """Every tile shape of the kernel for products that do not fill the chip, with ragged tokens, columns and K
+    (fewer k-tiles than waves among them), up to and above 32 outlier columns: staged with the accumulators, one-call,
+    zeropoint, and on weights kept as codes."""
+    import test_gpu_zeropoint as zp
+    d = wl.make_custom(s, h, o, ncol, seed=s + h + o)
+    full_compare(d, cap=cap)
+    linear_compare(d, cap=cap)
+    if s * h * o < 10 ** 9:
+        int8_rows_compare(d, cap=cap)
+        zp.zp_compare(d["X"], d["W"], d["alpha"], cap=cap)
+
+
 def test_alpha_zero_is_pure_fp16_matmul_on_both_paths():
     d = wl.make("tiny")
     g, r = full_compare(d, alpha=0.0, cap=256)
