@@ -293,7 +293,7 @@ static int linear_impl(const void* X_f16, int s, int h, float alpha, int granula
             unsigned short* part = (unsigned short*)(base + scratch_ws(h, cap));
             const int nslab = colmax_slabs(s, h);
             const unsigned thr = threshold_bits(alpha);
-            if (!shared_cx && h % 8 == 0 && !misaligned(X_f16, 16)) {
+            if (!shared_cx && h >= 8) {
                 // X is read twice instead of three times: the column scan leaves partial row maxima, from which
                 // a small kernel gets the row constants once the outlier columns are known
                 unsigned short* rowpart = (unsigned short*)(base + scratch_ws(h, cap) + slab_ws(s, h));

@@ -43,6 +43,18 @@ __device__ __forceinline__ us8 load8(const unsigned short* p) { return *(const u
 // the same for data that is not read again soon: it does not push anything else out of the caches
 __device__ __forceinline__ us8 load8_once(const unsigned short* p) { return __builtin_nontemporal_load((const us8_at2*)p); }
 
+// Columns c .. c+7 of a row of h >= 8 columns, zeros past its end, in two steps so that several loads can be in flight:
+// chunk_load() is one load inside the row whatever c is, chunk_fix() moves the elements of a row's last chunk into
+// place where h is not a multiple of 8 (a whole chunk needs no fixing; for c >= h it returns zeros).
+__device__ __forceinline__ us8 chunk_load(const unsigned short* row, int c, int h) { return load8(row + (c + 8 <= h ? c : h - 8)); }
+__device__ __forceinline__ us8 chunk_fix(us8 v, int c, int h)
+{
+    const int d = c + 8 - h;  // elements to drop at the low end
+    if (d <= 0) return v;
+    const unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v);
+    return __builtin_bit_cast(us8, d < 8 ? x >> (16 * d) : (unsigned __int128)0);
+}
+
 // row[c0 .. c0+7] = v, without the columns that do not exist
 __device__ __forceinline__ void store8(unsigned short* row, int c0, int cols, us8 v)
 {
@@ -343,7 +355,7 @@ hipError_t launch_quantize_rows_lists(const void* X, int s, int h, OutlierLists 
                                       int32_t* status, int cap, int8_t* Xq, unsigned short* cx, unsigned short* Xo,
                                       int shared_cx, hipStream_t st);
 // column scan of X that also leaves rowpart[ceil(h / 512)][s], the partial row maxima below the threshold
-// (needs h % 8 == 0 and 16-byte aligned X, part), and the row constants + codes + gathered columns from them
+// (needs h >= 8), and the row constants + codes + gathered columns from them
 hipError_t launch_colmax_rowmax(const void* X, int s, int h, unsigned short* part, int nslab, unsigned short* rowpart,
                                 unsigned thr, hipStream_t st);
 hipError_t launch_quantize_rows_rowpart(const void* X, int s, int h, OutlierLists L, unsigned thr,

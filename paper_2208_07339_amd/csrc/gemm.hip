@@ -129,7 +129,9 @@ constexpr int OSLOTS = 32;  // outlier slots staged through LDS; more are read f
 //
 // GUARDED: the epilogue reads its operands from memory with every access guarded and can export the raw
 // accumulators (o not a multiple of 8, unaligned operands, more than 32 outlier columns, or the export asked
-// for).  Otherwise the epilogue is fed from LDS by the two epilogue stages and nothing in it is guarded.
+// for).  Otherwise the epilogue is fed from LDS by the two epilogue stages and nothing in it is guarded.  Rows of
+// Out are stored in 16-byte pieces at any alignment, and the rows of W come from the lanes that have them: 75 -> 57.4 us
+// on 1013 x 4099 x 12301, where the unguarded kernel takes 55.6 for 12304 columns.
 template <int WA, int WB, int WQ, bool ZP, bool GUARDED>
 __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArgs g)
 {
@@ -483,7 +485,10 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
 #pragma unroll
             for (int e = 0; e < 8; e++) {
                 const int t = t0 + 8 * gl + e;
-                k[e] = g.rows_are_slots ? (unsigned)t : (unsigned)g.idx[t < cnt ? t : 0];
+                if (t0 < OSLOTS)  // every lane t < 32 has slot t's row
+                    k[e] = (unsigned)__shfl(myk, t);
+                else
+                    k[e] = g.rows_are_slots ? (unsigned)t : (unsigned)g.idx[t < cnt ? t : 0];
             }
             unsigned short v[8];
 #pragma unroll
@@ -610,10 +615,18 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                     } else {
                         if constexpr (!ZP) {
 #pragma unroll
-                            for (int r = 0; r < 16; r++) {
-                                const int j = cJ0w + jl + 8 * (r >> 2) + 4 * gl + (r & 3);
-                                const float cwj = f16_bits_to_float(g.cw[j < o ? j : 0]);
-                                cwv[aa][r] = (j < o) ? cwj : 0.0f;
+                            for (int rr = 0; rr < 4; rr++) {
+                                const int j = cJ0w + jl + 8 * rr + 4 * gl;  // c_w is 8-byte aligned
+                                unsigned short q[4] = {0, 0, 0, 0};
+                                if (j + 4 <= o) {
+                                    __builtin_memcpy(q, __builtin_assume_aligned(g.cw + j, 8), 8);
+                                } else {
+#pragma unroll
+                                    for (int e = 0; e < 4; e++)
+                                        if (j + e < o) q[e] = g.cw[j + e];
+                                }
+#pragma unroll
+                                for (int e = 0; e < 4; e++) cwv[aa][4 * rr + e] = f16_bits_to_float(q[e]);
                             }
                         }
                         wa[aa][0] = cnt > 0 ? load_w_mem(cJ0w + jl + ll, 0) : (v8h)(0);
@@ -698,8 +711,8 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                                 __builtin_amdgcn_raw_buffer_store_b128(v, obuf, j < o ? ((i - cI0w) * o + j) * 2 : 0x7fffffff,
                                                                        0, 2);
                         } else if ((tl < 32 || b0 + 1 < WB) && i < s && q < 4 * na) {
-                            if (g.fast_ok && j + 8 <= o) {
-                                *(u4*)(g.Out + (size_t)i * o + j) = v;
+                            if (j + 8 <= o) {  // at any alignment of the row
+                                __builtin_memcpy(g.Out + (size_t)i * o + j, &v, 16);
                             } else {
                                 const _Float16* hv = (const _Float16*)&v;
 #pragma unroll

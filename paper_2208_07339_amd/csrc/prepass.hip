@@ -8,22 +8,6 @@ namespace llmint8 {
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 
-// round-half-even of the exact quotient 127 x / c for fp16 x, c with |x| <= c, c > 0.
-// a = 127 x is exact in fp32; a non-tie quotient a / c lies further from a half-integer than half an
-// fp32 ulp, so rint() of the correctly rounded fp32 quotient is the exact answer.  The correctly
-// rounded quotient comes without a division per element: with rc = the correctly rounded reciprocal of
-// c (one IEEE division per row / column, by the caller), q = a rc is within an ulp of a / c, the fused
-// multiply-add gives the remainder r = a - q c exactly, and q + r rc rounds to the correctly rounded
-// quotient (Markstein's correction step).  Checked against integer arithmetic for every pair of fp16
-// values |x| <= c.  Do not drop the correction step, and do not let rc be an approximate reciprocal.
-__device__ __forceinline__ int q8(float x, float c, float rc)
-{
-    const float a = x * 127.0f;
-    const float q = a * rc;
-    const float r = __builtin_fmaf(-q, c, a);
-    return (int)__builtin_rintf(__builtin_fmaf(r, rc, q));
-}
-
 // ---------------------------------------------------------------------------
 // Column maxima of |M[r][c]| over a slab of rows.  One workgroup covers 512
 // columns (a wave reads 1 KiB of a row per load) and `rows_per_slab` rows, its
@@ -63,8 +47,6 @@ int colmax_slabs(int rows, int cols)
     return n;
 }
 
-static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
-
 hipError_t launch_colmax_partial(const void* M, int rows, int cols, unsigned short* part, int nslab, bool once,
                                  hipStream_t st)
 {
@@ -79,7 +61,7 @@ hipError_t launch_colmax_partial(const void* M, int rows, int cols, unsigned sho
 }
 
 // ---------------------------------------------------------------------------
-// The same column scan for X (vector path only) that also prepares the row
+// The same column scan for X that also prepares the row
 // constants: rowpart[colblock][row] = largest magnitude BELOW the threshold
 // among the row's entries in this workgroup's 512 columns.  Entries of
 // non-outlier columns are all below the threshold, so the maximum of a row's
@@ -94,6 +76,9 @@ __device__ __forceinline__ unsigned short hmax8(us8 v)
     return a.x > a.y ? a.x : a.y;
 }
 
+// RAGGED: cols is not a multiple of 8, or M not 16-byte aligned (66 registers instead of 57, 5.3 against 5.1 us on
+// 2 048 x 4 096)
+template <bool RAGGED>
 __global__ void __launch_bounds__(256) colmax_rowmax_kernel(const unsigned short* __restrict__ M, int rows, int cols,
                                                             unsigned short* __restrict__ part,
                                                             unsigned short* __restrict__ rowpart, int rows_per_slab,
@@ -105,7 +90,7 @@ __global__ void __launch_bounds__(256) colmax_rowmax_kernel(const unsigned short
     const int r0 = blockIdx.y * rows_per_slab;
     const int r1 = min(rows, r0 + rows_per_slab);
     const bool in = c0 < cols;
-    const unsigned short* p = M + (size_t)(in ? c0 : 0);
+    const unsigned short* p = M + (RAGGED ? (c0 + 8 <= cols ? c0 : cols - 8) : (in ? c0 : 0));
     const us8 thrv = (us8)((unsigned short)thr);
     us8 m = (us8)(0);
     // Unconditional loads, so that all four of a pass are in flight together (a row past the slab repeats its last
@@ -116,7 +101,7 @@ __global__ void __launch_bounds__(256) colmax_rowmax_kernel(const unsigned short
 #pragma unroll
         for (int u = 0; u < 4; u++) {
             const int rr = r + 4 * u < r1 ? r + 4 * u : r1 - 1;
-            nv[u] = *(const us8*)(p + (size_t)rr * cols);
+            nv[u] = RAGGED ? load8(p + (size_t)rr * cols) : *(const us8*)(p + (size_t)rr * cols);
         }
     };
     if (r0 + w < r1) request(r0 + w);
@@ -126,9 +111,13 @@ __global__ void __launch_bounds__(256) colmax_rowmax_kernel(const unsigned short
 #pragma unroll
         for (int u = 0; u < 4; u++) v[u] = nv[u];
         request(r + 16);
+        if (RAGGED && blockIdx.x * 512 + 512 > cols) {
+#pragma unroll
+            for (int u = 0; u < 4; u++) v[u] = chunk_fix(v[u], c0, cols);
+        }
 #pragma unroll
         for (int u = 0; u < 4; u++) {
-            v[u] = in ? v[u] & (unsigned short)0x7fff : (us8)(0);  // lanes past the last column read column 0
+            v[u] = in ? v[u] & (unsigned short)0x7fff : (us8)(0);  // lanes past the last column read some other one
             m = __builtin_elementwise_max(m, v[u]);
             const us8 below = v[u] & __builtin_convertvector(v[u] < thrv, us8);  // lanes that reach the threshold drop out
             x[u] = hmax8(below);
@@ -155,7 +144,10 @@ __global__ void __launch_bounds__(256) colmax_rowmax_kernel(const unsigned short
     if (w == 0 && in) {
         m = __builtin_elementwise_max(__builtin_elementwise_max(red[0][lane], red[1][lane]),
                                       __builtin_elementwise_max(red[2][lane], red[3][lane]));
-        *(us8*)(part + (size_t)blockIdx.y * cols + c0) = m;
+        if (RAGGED)
+            store8(part + (size_t)blockIdx.y * cols, c0, cols, m);
+        else
+            *(us8*)(part + (size_t)blockIdx.y * cols + c0) = m;
     }
 }
 
@@ -164,7 +156,10 @@ hipError_t launch_colmax_rowmax(const void* X, int s, int h, unsigned short* par
 {
     const int rps = (s + nslab - 1) / nslab;
     dim3 grid((h + 511) / 512, nslab);
-    colmax_rowmax_kernel<<<grid, 256, 0, st>>>((const unsigned short*)X, s, h, part, rowpart, rps, thr);
+    if (h % 8 != 0 || ((uintptr_t)X & 15) != 0)
+        colmax_rowmax_kernel<true><<<grid, 256, 0, st>>>((const unsigned short*)X, s, h, part, rowpart, rps, thr);
+    else
+        colmax_rowmax_kernel<false><<<grid, 256, 0, st>>>((const unsigned short*)X, s, h, part, rowpart, rps, thr);
     return hipGetLastError();
 }
 
@@ -342,11 +337,15 @@ __global__ void __launch_bounds__(256) scan_small_kernel(const unsigned short* _
 #pragma unroll
         for (int r = 0; r < 8; r++) {
             const int i = w + 4 * r;
-            v[r] = *(const us8*)(X + (size_t)(i < s ? i : 0) * h + (c0 < h ? c0 : 0));
+            v[r] = chunk_load(X + (size_t)(i < s ? i : 0) * h, c0, h);
+        }
+        if (blockIdx.x * 512 + 512 > h) {
+#pragma unroll
+            for (int r = 0; r < 8; r++) v[r] = chunk_fix(v[r], c0, h);
         }
 #pragma unroll
         for (int r = 0; r < 8; r++)
-            if (!(w + 4 * r < s && c0 < h)) v[r] = (us8)(0);
+            if (w + 4 * r >= s) v[r] = (us8)(0);
     } else {
 #pragma unroll
         for (int r = 0; r < 8; r++) {
@@ -540,13 +539,17 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
     const int kseg = (tid & 31) * 8;
     const int k = k0 + kseg;
     us8 xv[4];
-    if (vec_ok && k + 8 <= h) {
+    if (vec_ok) {
         // unconditional (a row that does not exist: row 0 again; its codes come out as 0 because its constant
         // is 0), or the compiler waits for each load before it issues the next
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             const int r = q * 8 + (tid >> 5);
-            xv[q] = *(const us8*)(X + (size_t)(r < s ? r : 0) * h + k);
+            xv[q] = chunk_load(X + (size_t)(r < s ? r : 0) * h, k, h);
+        }
+        if (k0 + 256 > h) {
+#pragma unroll
+            for (int q = 0; q < 4; q++) xv[q] = chunk_fix(xv[q], k, h);
         }
     } else {
 #pragma unroll
@@ -728,14 +731,18 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
             for (int d = 16; d >= 1; d >>= 1) part += __shfl_xor(part, d);
             if ((tid & 31) == 0 && r < s && part) atomicAdd(&zc[r].z, part);
         } else {
-            const float c = (r < s) ? f16_bits_to_float((unsigned short)s_cxb[r]) : 0.0f;
-            const float rc = c > 0.0f ? 1.0f / c : 0.0f;
+            us8 x = r < s ? v : (us8)(0);
+            if (bits) {
 #pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const int qv = (c > 0.0f && !((bits >> e) & 1u)) ? q8(f16_bits_to_float(v[e]), c, rc) : 0;
-                const unsigned byte = (unsigned)qv & 0xffu;
-                if (e < 4) lo |= byte << (8 * e); else hi |= byte << (8 * (e - 4));
+                for (int e = 0; e < 8; e++)
+                    if ((bits >> e) & 1u) x[e] = 0;
             }
+            const float f = code_factor(f16_bits_to_float((unsigned short)s_cxb[r]));
+            unsigned b8[8];
+#pragma unroll
+            for (int e = 0; e < 8; e++) b8[e] = code_bits(x[e], f);
+            lo = pack_low_bytes(b8[0], b8[1], b8[2], b8[3]);
+            hi = pack_low_bytes(b8[4], b8[5], b8[6], b8[7]);
         }
         u2 pk = {lo, hi};
         *(u2*)(stage + (kseg >> 5) * TILE_BYTES + tile_byte(r, kseg & 31)) = pk;
@@ -754,7 +761,7 @@ hipError_t launch_prepass_small(const void* X, int s, int h, unsigned thr, Outli
                                 int shared_cx, hipStream_t st, int4* zc, const ColumnJob* cj)
 {
     const int capc = list_capacity(cap);
-    const int vec_ok = (h % 8 == 0) && aligned16(X);
+    const int vec_ok = h >= 8;
     const int KT = k_tiles(h);
     const int nscan = (h + 511) / 512, nquant = (KT * 32 + 255) / 256;
     const size_t shm = ((size_t)(h + 31) / 32) * sizeof(unsigned);
@@ -838,17 +845,22 @@ __global__ void __launch_bounds__(256) row_absmax_kernel(const unsigned short* _
     __syncthreads();
     unsigned m = 0;
     if (vec_ok) {
-        // four unconditional loads in flight per pass (past the row: its start again, skipped below)
+        // four unconditional loads in flight per pass
         for (int c0 = tid * 8; c0 < h; c0 += 4 * 2048) {
             us8 v[4];
 #pragma unroll
             for (int u = 0; u < 4; u++) {
                 const int c = c0 + u * 2048;
-                v[u] = *(const us8*)(row + (c < h ? c : 0)) & (unsigned short)0x7fff;
+                v[u] = chunk_load(row, c, h);
+            }
+            if (c0 + 3 * 2048 + 8 > h) {
+#pragma unroll
+                for (int u = 0; u < 4; u++) v[u] = chunk_fix(v[u], c0 + u * 2048, h);
             }
 #pragma unroll
             for (int u = 0; u < 4; u++) {
                 const int c = c0 + u * 2048;
+                v[u] &= (unsigned short)0x7fff;
                 if (c < h) {
                     const unsigned bits = (bitmap[c >> 5] >> (c & 31)) & 0xffu;
 #pragma unroll
@@ -888,11 +900,11 @@ __global__ void __launch_bounds__(256) row_absmax_kernel(const unsigned short* _
 // Otherwise (rare), and whenever more columns qualify than cap allows (then
 // the columns beyond cap count as ordinary ones and their large entries
 // belong to c_x), the workgroup scans that row again without the outlier
-// columns.  Needs h % 8 == 0 and a 16-byte aligned X.
+// columns.  Needs h >= 8.
 // ---------------------------------------------------------------------------
 constexpr int RC_SLOTS = 256;  // outlier columns kept in LDS; more: every row takes the slow path
 
-__global__ void __launch_bounds__(256) row_const_kernel(const unsigned short* __restrict__ X, int s, int h,
+__global__ void __launch_bounds__(256, 5) row_const_kernel(const unsigned short* __restrict__ X, int s, int h,
                                                         OutlierLists L, int capc, int cap, int opad, unsigned thr,
                                                         const unsigned short* __restrict__ rowpart, int ncb,
                                                         int32_t* __restrict__ idx, int32_t* __restrict__ count,
@@ -982,7 +994,7 @@ __global__ void __launch_bounds__(256) row_const_kernel(const unsigned short* __
             const int i2 = blockIdx.x * 4 + r4;
             const unsigned short* row2 = X + (size_t)i2 * h;
             unsigned m = 0;
-            // h is a multiple of 8 here.  One slow row makes this workgroup the kernel's last, and every pass of
+            // One slow row makes this workgroup the kernel's last, and every pass of
             // this loop is a round trip to memory of its own: twelve 16-byte loads in flight per lane take a row
             // of 49 152 features in two passes (24 in one pass are no faster and cost 65 more registers).  (With each load under its own bounds check the compiler waited
             // for every one of them in turn: 16 us for the kernel instead of 5 whenever one row came here.)
@@ -990,9 +1002,11 @@ __global__ void __launch_bounds__(256) row_const_kernel(const unsigned short* __
             for (int c0 = tid * 8; c0 < h; c0 += RU * 2048) {
                 us8 v[RU];
 #pragma unroll
-                for (int u = 0; u < RU; u++) {  // unconditional loads (past the row: its start again, unused below),
-                    const int c = c0 + u * 2048;  // so that the compiler issues them together
-                    v[u] = *(const us8*)(row2 + (c < h ? c : 0)) & (unsigned short)0x7fff;
+                for (int u = 0; u < RU; u++) v[u] = chunk_load(row2, c0 + u * 2048, h);  // unconditional, so that the
+                // compiler issues them together
+                if (c0 + (RU - 1) * 2048 + 8 > h) {
+#pragma unroll
+                    for (int u = 0; u < RU; u++) v[u] = chunk_fix(v[u], c0 + u * 2048, h);
                 }
 #pragma unroll
                 for (int u = 0; u < RU; u++) {
@@ -1001,7 +1015,7 @@ __global__ void __launch_bounds__(256) row_const_kernel(const unsigned short* __
                         const unsigned bits = (fullmap[c >> 5] >> (c & 31)) & 0xffu;
 #pragma unroll
                         for (int e = 0; e < 8; e++) {
-                            const unsigned x = ((bits >> e) & 1u) ? 0u : (unsigned)v[u][e];
+                            const unsigned x = ((bits >> e) & 1u) ? 0u : (unsigned)(v[u][e] & 0x7fff);
                             m = x > m ? x : m;
                         }
                     }
@@ -1087,19 +1101,21 @@ __global__ void __launch_bounds__(256) quantize_rows_kernel(const unsigned short
     // (requested here and not at the top of the kernel, in front of the look-up of this block's outlier columns:
     // measured, that order is slower, 12.7 against 12.1 us on a 4096 x 5120 X)
     // The loads of the thread's four rows first, all of them unconditional (a row past the last one: the last
-    // one again, its constant taken as 0 below), so that they are in flight together: under a bounds check of
+    // one again, taken as 0 below), so that they are in flight together: under a bounds check of
     // its own each was waited for before the next was issued, four round trips to memory in a row.
     us8 vq[4];
     float cq[4];
-    const bool vec = vec_ok && k + 8 <= h;
 #pragma unroll
     for (int q = 0; q < 4; q++) {
         const int i = rt * 32 + q * 8 + (tid >> 5);
         const int ii = i < s ? i : s - 1;
         cq[q] = f16_bits_to_float(cx[ii]);
-        if (i >= s) cq[q] = 0.0f;
         vq[q] = (us8)(0);
-        if (vec) vq[q] = *(const us8*)(X + (size_t)ii * h + k);
+        if (vec_ok) vq[q] = chunk_load(X + (size_t)ii * h, k, h);
+    }
+    if (vec_ok && k0 + 256 > h) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) vq[q] = chunk_fix(vq[q], k, h);
     }
 #pragma unroll
     for (int q = 0; q < 4; q++) {
@@ -1107,21 +1123,23 @@ __global__ void __launch_bounds__(256) quantize_rows_kernel(const unsigned short
         const int i = rt * 32 + r;
         us8 v = vq[q];
         const float c = cq[q];
-        if (!vec && i < s) {
+        if (!vec_ok && i < s) {
             const unsigned short* row = X + (size_t)i * h;
 #pragma unroll
             for (int e = 0; e < 8; e++)
                 if (k + e < h) v[e] = row[k + e];
         }
-        const float rc = c > 0.0f ? 1.0f / c : 0.0f;
-        unsigned lo = 0, hi = 0;
+        if (bits) {
 #pragma unroll
-        for (int e = 0; e < 8; e++) {
-            int qv = (c > 0.0f && !((bits >> e) & 1u)) ? q8(f16_bits_to_float(v[e]), c, rc) : 0;
-            unsigned byte = (unsigned)qv & 0xffu;
-            if (e < 4) lo |= byte << (8 * e); else hi |= byte << (8 * (e - 4));
+            for (int e = 0; e < 8; e++)
+                if ((bits >> e) & 1u) v[e] = 0;
         }
-        u2 pk = {lo, hi};
+        if (i >= s) v = (us8)(0);
+        const float f = code_factor(c);
+        unsigned b8[8];
+#pragma unroll
+        for (int e = 0; e < 8; e++) b8[e] = code_bits(v[e], f);
+        u2 pk = {pack_low_bytes(b8[0], b8[1], b8[2], b8[3]), pack_low_bytes(b8[4], b8[5], b8[6], b8[7])};
         *(u2*)(stage + (kseg >> 5) * TILE_BYTES + tile_byte(r, kseg & 31)) = pk;
     }
     __syncthreads();
@@ -1139,7 +1157,7 @@ hipError_t launch_quantize_rows(const void* X, int s, int h, const int32_t* idx,
 {
     const int KT = k_tiles(h), RT = row_tiles(s);
     const int opad = opad_of(cap);
-    int vec_ok = (h % 8 == 0) && aligned16(X);
+    int vec_ok = h >= 8;
     size_t shm = ((size_t)(h + 31) / 32 + 4) * sizeof(unsigned);
     const OutlierLists none = {nullptr, nullptr, nullptr};
     row_absmax_kernel<false><<<s, 256, shm, st>>>((const unsigned short*)X, s, h, (int32_t*)idx, (int32_t*)count,
@@ -1160,7 +1178,7 @@ hipError_t launch_quantize_rows_lists(const void* X, int s, int h, OutlierLists 
 {
     const int KT = k_tiles(h), RT = row_tiles(s);
     const int opad = opad_of(cap), capc = list_capacity(cap);
-    int vec_ok = (h % 8 == 0) && aligned16(X);
+    int vec_ok = h >= 8;
     size_t shm = ((size_t)(h + 31) / 32 + 4) * sizeof(unsigned);
     row_absmax_kernel<true><<<s, 256, shm, st>>>((const unsigned short*)X, s, h, idx, count, status, L, capc, cap, opad,
                                                  cx, Xo, vec_ok);
@@ -1173,7 +1191,7 @@ hipError_t launch_quantize_rows_lists(const void* X, int s, int h, OutlierLists 
     return hipGetLastError();
 }
 
-// the per-call pre-pass for s > 32 when X allows 16-byte loads: row constants from the partial row maxima
+// the per-call pre-pass for s > 32: row constants from the partial row maxima
 // of the column scan instead of another full pass over X
 hipError_t launch_quantize_rows_rowpart(const void* X, int s, int h, OutlierLists L, unsigned thr,
                                         const unsigned short* rowpart, int32_t* idx, int32_t* count, int32_t* status,

@@ -142,13 +142,17 @@ __global__ void __launch_bounds__(256) zp_row_range_kernel(const unsigned short*
     __syncthreads();
     unsigned kmin = 0xffffu, kmax = 0u;
     if (vec_ok) {
-        // four unconditional loads in flight per pass (past the row: its start again, skipped below)
+        // four unconditional loads in flight per pass
         for (int c0 = tid * 8; c0 < h; c0 += 4 * 2048) {
             us8 v[4];
 #pragma unroll
             for (int u = 0; u < 4; u++) {
                 const int c = c0 + u * 2048;
-                v[u] = *(const us8*)(row + (c < h ? c : 0));
+                v[u] = chunk_load(row, c, h);
+            }
+            if (c0 + 3 * 2048 + 8 > h) {
+#pragma unroll
+                for (int u = 0; u < 4; u++) v[u] = chunk_fix(v[u], c0 + u * 2048, h);
             }
 #pragma unroll
             for (int u = 0; u < 4; u++) {
@@ -157,7 +161,7 @@ __global__ void __launch_bounds__(256) zp_row_range_kernel(const unsigned short*
                     const unsigned bits = (bitmap[c >> 5] >> (c & 31)) & 0xffu;
 #pragma unroll
                     for (int e = 0; e < 8; e++)
-                        if (!((bits >> e) & 1u)) {
+                        if (!((bits >> e) & 1u) && c + e < h) {
                             const unsigned k = f16_key(v[u][e]);
                             kmin = k < kmin ? k : kmin;
                             kmax = k > kmax ? k : kmax;
@@ -235,14 +239,17 @@ __global__ void __launch_bounds__(256 * ZQ_NB) zp_quantize_rows_kernel(const uns
     // its range taken as 0 below), so that they are in flight together, as in quantize_rows_kernel
     us8 vq[4];
     int4 recq[4];
-    const bool vec = vec_ok && k + 8 <= h;
 #pragma unroll
     for (int q = 0; q < 4; q++) {
         const int i = rt * 32 + q * 8 + (t >> 5);
         const int ii = i < s ? i : s - 1;
         recq[q] = zc[ii];
         vq[q] = (us8)(0);
-        if (vec) vq[q] = *(const us8*)(X + (size_t)ii * h + k);
+        if (vec_ok) vq[q] = chunk_load(X + (size_t)ii * h, k, h);
+    }
+    if (vec_ok && kw + 256 * NB > h) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) vq[q] = chunk_fix(vq[q], k, h);
     }
 #pragma unroll
     for (int q = 0; q < 4; q++) {
@@ -254,7 +261,7 @@ __global__ void __launch_bounds__(256 * ZQ_NB) zp_quantize_rows_kernel(const uns
         if (i < s) {
             D = zp_range((unsigned)recq[q].x);
             z = recq[q].y;
-            if (!vec) {
+            if (!vec_ok) {
                 const unsigned short* row = X + (size_t)i * h;
 #pragma unroll
                 for (int e = 0; e < 8; e++)
@@ -304,7 +311,7 @@ hipError_t launch_zp_quantize_rows(const void* X, int s, int h, const int32_t* i
                                    int8_t* Xq, int4* zc, unsigned short* Xo, hipStream_t st)
 {
     const size_t shm = ((size_t)(h + 31) / 32 + 8) * sizeof(unsigned);
-    const int vec_ok = (h % 8 == 0) && (((uintptr_t)X & 15) == 0);
+    const int vec_ok = h >= 8;
     const OutlierLists none = {nullptr, nullptr, nullptr};
     const ColumnJob nojob = {nullptr, nullptr, nullptr, 0, 0};
     zp_row_range_kernel<false><<<s, 256, shm, st>>>((const unsigned short*)X, s, h, (int32_t*)idx, (int32_t*)count,
@@ -321,7 +328,7 @@ hipError_t launch_zp_quantize_rows_lists(const void* X, int s, int h, OutlierLis
                                          const ColumnJob* cj, hipStream_t st)
 {
     const size_t shm = ((size_t)(h + 31) / 32 + 8) * sizeof(unsigned);
-    const int vec_ok = (h % 8 == 0) && (((uintptr_t)X & 15) == 0);
+    const int vec_ok = h >= 8;
     const ColumnJob job = (cj && cap <= JOB_MAX_CAP) ? *cj : ColumnJob{nullptr, nullptr, nullptr, 0, 0};
     zp_row_range_kernel<true><<<s + job.pitch / 256, 256, shm, st>>>((const unsigned short*)X, s, h, idx, count, status,
                                                                      L, list_capacity(cap), cap, opad_of(cap), zc, Xo,

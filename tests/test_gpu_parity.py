@@ -555,6 +555,33 @@ def test_linear_prefill_branches_of_the_prepass():
     linear_compare(d)
 
 
+@pytest.mark.parametrize("s,h,o", [(33, 8, 40), (40, 9, 33), (35, 15, 64), (64, 505, 31), (100, 511, 65), (129, 513, 520),
+                                   (70, 519, 263), (20, 1023, 77), (31, 2049, 90), (50, 8201, 43)])
+def test_rows_and_columns_that_do_not_start_on_16_bytes(s, h, o):
+    """Features and columns around the ends of 16-byte pieces, and X itself at an odd address: one-call, staged and
+    zeropoint against the oracle, the tiled kernel forced too."""
+    import torch
+
+    import paper_2208_07339_amd as L
+    import test_gpu_zeropoint as zp
+    d = wl.make_custom(s, h, o, min(3, h // 4), seed=s + h + o)
+    linear_compare(d)
+    g, _ = full_compare(d)
+    zp.zp_compare(d["X"], d["W"], 6.0)
+    buf = torch.zeros(s * h + 1, dtype=torch.float16, device="cuda")
+    Xd = buf[1:].view(s, h)
+    Xd.copy_(g["Xd"])
+    codes = g["rows"].Xq.clone()
+    try:
+        L.debug_decode_shape(0)  # every kernel of the pre-pass, and the tiles of the prefill kernel
+        want = L.linear(g["Xd"], g["qw"], 6.0, g["outl"], g["rows"], g["ws"]).clone()
+        got = L.linear(Xd, g["qw"], 6.0, g["outl"], g["rows"], g["ws"])
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16)) and torch.equal(g["rows"].Xq, codes)
+        assert_out_close(got.cpu().numpy(), g["Out"])
+    finally:
+        L.debug_decode_shape(-1)
+
+
 def test_linear_row_maximum_inside_an_outlier_column():
     """Rows whose largest magnitude below alpha sits in an outlier column (alone, or tied with a regular
     column): the row constant must come from the regular columns only."""
