@@ -269,6 +269,7 @@ static int linear_impl(const void* X_f16, int s, int h, float alpha, int granula
     // the constants of W were fixed when it was quantized; here only those of X depend on the granularity
     const int shared_cx = granularity == LLMINT8_TENSORWISE;
     hipError_t e;
+    bool have_rows = s <= 32 && cap <= JOB_MAX_CAP;  // the pre-pass rebuilds the outlier rows of W
     // (one kernel reads X and writes Out: not where they overlap; and there is no matmul kernel to put events around)
     const uintptr_t x0 = (uintptr_t)X_f16, x1 = x0 + (size_t)s * h * 2, o0 = (uintptr_t)Out_f16, o1 = o0 + (size_t)s * o * 2;
     if (!shared_cx && !ev_before && !ev_after && (x1 <= o0 || o1 <= x0) && linear_small_takes(s, h, o, cap))
@@ -282,6 +283,13 @@ static int linear_impl(const void* X_f16, int s, int h, float alpha, int granula
         e = launch_prepass_small(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status,
                                  (unsigned short*)cx_f16, (unsigned short*)Xo_f16, Xq, shared_cx, st, nullptr,
                                  W_f16 ? nullptr : &job);
+    } else if (!shared_cx && !(std::isinf(alpha) && alpha > 0.0f) && prepass_mid_takes(s, h, slab_ws(s, h) + rowpart_ws(s, h))) {
+        OutlierLists Lm = L;  // the partial row maxima in the place of the slab maxima
+        Lm.rowpart = (unsigned short*)(base + scratch_ws(h, cap));
+        const ColumnJob job = {Wq, cw_f16, base + scan_ws(s, h, o, cap), o, (o + 255) & ~255};
+        e = launch_prepass_mid(X_f16, s, h, threshold_bits(alpha), Lm, idx, cap, count, status, (unsigned short*)cx_f16,
+                               (unsigned short*)Xo_f16, Xq, st, nullptr, W_f16 ? nullptr : &job);
+        have_rows = cap <= JOB_MAX_CAP;
     } else {
         if (std::isinf(alpha) && alpha > 0.0f) {
             // no decomposition (the baselines of Table 1 without it): O is empty, X need not be scanned
@@ -314,7 +322,7 @@ static int linear_impl(const void* X_f16, int s, int h, float alpha, int granula
     if (e == hipSuccess && ev_before) e = hipEventRecord(ev_before, st);
     if (e != hipSuccess) return hip_status(e);
     const int r = matmul_impl(Xq, cx_f16, Xo_f16, idx, count, cap, Wq, cw_f16, W_f16, s, h, o, Out_f16, nullptr, ws,
-                              ws_bytes, stream, s <= 32 && cap <= JOB_MAX_CAP);
+                              ws_bytes, stream, have_rows);
     if (r == LLMINT8_OK && ev_after) return hip_status(hipEventRecord(ev_after, st));
     return r;
 }
@@ -466,6 +474,13 @@ int llmint8_zp_linear(const void* X_f16, int s, int h, float alpha, const int8_t
                                zp_col_pitch(o)};
         r = hip_status(launch_prepass_small(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status, nullptr,
                                             (unsigned short*)Xo_f16, Xq, 0, (hipStream_t)stream, (int4*)zc_x, &job));
+    } else if (prepass_mid_takes(s, h, slab_ws(s, h) + rowpart_ws(s, h))) {
+        char* base = (char*)ws_base(ws);
+        OutlierLists L = carve_outlier_lists(base, h, cap);
+        L.rowpart = (unsigned short*)(base + scratch_ws(h, cap));
+        const ColumnJob job = {Wq, zc_w, base + scan_ws(s, h, o, cap) + rows_ws(o, cap), o, zp_col_pitch(o)};
+        r = hip_status(launch_prepass_mid(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status, nullptr,
+                                          (unsigned short*)Xo_f16, Xq, (hipStream_t)stream, (int4*)zc_x, &job));
     } else {
         // the column scan as llmint8_find_outliers runs it, without its last kernel: the kernel that takes the
         // rows' ranges reads the column lists itself, writes idx / count / status, and carries the per-column

@@ -320,7 +320,7 @@ hipError_t launch_spread_max(unsigned short* c, int n, hipStream_t st)
 // them into the records (range, zeropoint), writes the codes u(x) - zp and adds
 // its part of every row's sum of codes into the record.
 // ---------------------------------------------------------------------------
-template <bool ZP>
+template <bool ZP, bool RAGGED>
 __global__ void __launch_bounds__(256) scan_small_kernel(const unsigned short* __restrict__ X, int s, int h,
                                                          unsigned thr, int vec_ok, OutlierLists L, int capc,
                                                          int4* __restrict__ zc)
@@ -337,15 +337,16 @@ __global__ void __launch_bounds__(256) scan_small_kernel(const unsigned short* _
 #pragma unroll
         for (int r = 0; r < 8; r++) {
             const int i = w + 4 * r;
-            v[r] = chunk_load(X + (size_t)(i < s ? i : 0) * h, c0, h);
+            const unsigned short* row = X + (size_t)(i < s ? i : 0) * h;
+            v[r] = RAGGED ? chunk_load(row, c0, h) : *(const us8*)(row + (c0 < h ? c0 : 0));
         }
-        if (blockIdx.x * 512 + 512 > h) {
+        if (RAGGED && blockIdx.x * 512 + 512 > h) {
 #pragma unroll
             for (int r = 0; r < 8; r++) v[r] = chunk_fix(v[r], c0, h);
         }
 #pragma unroll
         for (int r = 0; r < 8; r++)
-            if (w + 4 * r >= s) v[r] = (us8)(0);
+            if (!(w + 4 * r < s && c0 < h)) v[r] = (us8)(0);
     } else {
 #pragma unroll
         for (int r = 0; r < 8; r++) {
@@ -436,7 +437,22 @@ __global__ void __launch_bounds__(256) scan_small_kernel(const unsigned short* _
     }
 }
 
-template <bool ZP>
+// f(e, entry e) for the first n entries of a list, eight loads in flight (one thread takes a whole list)
+template <class F>
+__device__ __forceinline__ void list_entries(const int* list, int n, F f)
+{
+    for (int e0 = 0; e0 < n; e0 += 8) {
+        int j[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) j[u] = list[e0 + u < n ? e0 + u : e0];
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            if (e0 + u < n) f(e0 + u, j[u]);
+    }
+}
+
+// MID: more than one row tile, a row of workgroups (blockIdx.y) for each
+template <bool ZP, bool MID, bool RAGGED>
 __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned short* __restrict__ X, int s, int h,
                                                              OutlierLists L, int capc, int vec_ok,
                                                              int32_t* __restrict__ idx, int cap, int opad,
@@ -445,7 +461,7 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
                                                              unsigned short* __restrict__ cx,
                                                              unsigned short* __restrict__ Xo,
                                                              int8_t* __restrict__ Xq, int KT, int shared_cx,
-                                                             int4* __restrict__ zc, ColumnJob cj)
+                                                             int4* __restrict__ zc, int nwg, ColumnJob cj)
 {
     extern __shared__ unsigned fullmap[];  // ceil(h / 32) words, used only when |O| > cap
     __shared__ __attribute__((aligned(16))) int8_t stage[8 * TILE_BYTES];
@@ -459,20 +475,25 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
     __shared__ unsigned bitmap[8];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int k0 = blockIdx.x * 256;
-    const int nl = (h + 255) / 256, nwg = (h + 511) / 512;
+    const int nl = (h + 255) / 256;
+    const int i0 = MID ? blockIdx.y * 32 : 0;      // this row tile's first row
+    const int spad = MID ? gridDim.y * 32 : 32;    // rows of a block of partial maxima
+    s -= i0;                                 // rows from here on
 
     // One-call paths: the workgroups past those of the quantizer take a column job (see ColumnJob).  They read
     // the outlier set straight from the lists (slot t of the set is entry t of their concatenation) into LDS
     // first, so that a thread's loads of its column's codes in those rows do not wait for one another.
     const int nquant = (KT * 32 + 255) / 256;
     if ((int)blockIdx.x >= nquant) {
+        if (i0 > 0) return;
         __shared__ int s_idx[JOB_MAX_CAP];
         const int total = scan_lists(L.count, nl, s_cnt, s_base);
         const int cnt = total < cap ? total : cap;  // cap <= JOB_MAX_CAP (checked by the launcher)
         __syncthreads();
         for (int b = tid; b < nl; b += 256) {
             const int n = s_cnt[b] < capc ? s_cnt[b] : capc;
-            for (int e = 0; e < n && s_base[b] + e < cap; e++) s_idx[s_base[b] + e] = L.cand[(size_t)b * capc + e];
+            const int base = s_base[b], m = n < cap - base ? n : cap - base;
+            list_entries(L.cand + (size_t)b * capc, m, [&](int e, int j) { s_idx[base + e] = j; });
         }
         __syncthreads();
         const int j = ((int)blockIdx.x - nquant) * 256 + tid;
@@ -534,6 +555,7 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
         return;
     }
 
+    X += (size_t)i0 * h;
     // Everything whose address is known is requested first, so that the latencies overlap: this
     // thread's 8 features of 4 rows, and its share of the partial row maxima.
     const int kseg = (tid & 31) * 8;
@@ -545,11 +567,12 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             const int r = q * 8 + (tid >> 5);
-            xv[q] = chunk_load(X + (size_t)(r < s ? r : 0) * h, k, h);
+            const unsigned short* row = X + (size_t)(r < s ? r : 0) * h;
+            xv[q] = RAGGED ? chunk_load(row, k, h) : *(const us8*)(row + (k < h ? k : 0));
         }
         if (k0 + 256 > h) {
 #pragma unroll
-            for (int q = 0; q < 4; q++) xv[q] = chunk_fix(xv[q], k, h);
+            for (int q = 0; q < 4; q++) xv[q] = RAGGED ? chunk_fix(xv[q], k, h) : (k < h ? xv[q] : (us8)(0));
         }
     } else {
 #pragma unroll
@@ -568,20 +591,22 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
     unsigned rp_min = 0xffffu;
     {
         const int i = tid & 31, gq = tid >> 5;
-        for (int b = gq; b < nwg; b += 32) {  // 4 independent loads in flight
-            unsigned t4[4], t5[4];
+        constexpr int RU = MID ? 8 : 4;
+        for (int b = gq; b < nwg; b += 8 * RU) {  // RU independent loads in flight
+            unsigned t4[RU], t5[RU];
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const size_t at = (size_t)(b + 8 * u) * 32 + i;
+            for (int u = 0; u < RU; u++) {
+                const int bu = b + 8 * u < nwg ? b + 8 * u : b;  // (a block that does not exist: this one again)
+                const size_t at = (size_t)bu * spad + i0 + i;
                 if constexpr (ZP) {
-                    t5[u] = (b + 8 * u < nwg) ? (unsigned)L.rowpart[at] : 0xffffu;
-                    t4[u] = (b + 8 * u < nwg) ? (unsigned)L.rowpart[(size_t)nwg * 32 + at] : 0u;
+                    t5[u] = L.rowpart[at];
+                    t4[u] = L.rowpart[(size_t)nwg * spad + at];
                 } else {
-                    t4[u] = (b + 8 * u < nwg) ? (unsigned)L.rowpart[at] : 0u;
+                    t4[u] = L.rowpart[at];
                 }
             }
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
+            for (int u = 0; u < RU; u++) {
                 rp_max = t4[u] > rp_max ? t4[u] : rp_max;
                 if constexpr (ZP) rp_min = t5[u] < rp_min ? t5[u] : rp_min;
             }
@@ -672,7 +697,7 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
             s_rD[tid] = D > 0.0 ? 1.0 / D : 0.0;
             s_z[tid] = r.y;
             if (blockIdx.x == 0 && tid < s) {  // the sum of the codes (word 2) was cleared by the scan and is added to below
-                int* rec = (int*)(zc + tid);
+                int* rec = (int*)(zc + i0 + tid);
                 rec[0] = r.x;
                 rec[1] = r.y;
             }
@@ -688,23 +713,38 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
         __syncthreads();
     }
 
-    // ---- workgroup 0: the outputs of the outlier scan, c_x, Xo
+    // ---- the row tile's first workgroup: c_x, Xo (and, the very first, the outputs of the outlier scan)
     if (blockIdx.x == 0) {
+        __shared__ int s_list[JOB_MAX_CAP];  // the outlier columns in order, as many as fit
         for (int b = tid; b < nl; b += 256) {
             const int n = s_cnt[b] < capc ? s_cnt[b] : capc;
-            const int base = s_base[b];
-            for (int e = 0; e < n && base + e < cap; e++) idx[base + e] = L.cand[(size_t)b * capc + e];
+            const int base = s_base[b], m = n < cap - base ? n : cap - base;
+            if (cap <= JOB_MAX_CAP)
+                list_entries(L.cand + (size_t)b * capc, m, [&](int e, int j) {
+                    s_list[base + e] = j;
+                    if (i0 == 0) idx[base + e] = j;
+                });
+            else  // a larger buffer: straight from the lists
+                for (int e = 0; e < m; e++) {
+                    const int j = L.cand[(size_t)b * capc + e];
+                    if (i0 == 0) idx[base + e] = j;
+                    for (int i = 0; i < 32 && i < s; i++) Xo[(size_t)(i0 + i) * opad + base + e] = X[(size_t)i * h + j];
+                }
         }
-        __syncthreads();  // idx is read back by other threads of this workgroup
-        for (int q = tid; q < s * opad; q += 256) {
+        __syncthreads();
+        const int sr = s < 32 ? s : 32;
+        for (int q = tid; q < sr * opad; q += 256) {
             const int i = q / opad, t = q - i * opad;
-            Xo[q] = t < cnt ? X[(size_t)i * h + idx[t]] : (unsigned short)0;
+            if (t >= cnt)
+                Xo[(size_t)i0 * opad + q] = (unsigned short)0;
+            else if (cap <= JOB_MAX_CAP)
+                Xo[(size_t)i0 * opad + q] = X[(size_t)i * h + s_list[t]];
         }
-        if (tid == 0) {
+        if (tid == 0 && i0 == 0) {
             *count = cnt;
             if (status) *status = overflow ? 1 : 0;
         }
-        if (!ZP && tid < s) cx[tid] = (unsigned short)s_cxb[tid];
+        if (!ZP && tid < sr) cx[i0 + tid] = (unsigned short)s_cxb[tid];
     }
 
     // ---- codes of 32 rows x 256 features into the tiled layout
@@ -729,7 +769,7 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
             // the 32 lanes that share row r (one half of a wave) add up their parts
 #pragma unroll
             for (int d = 16; d >= 1; d >>= 1) part += __shfl_xor(part, d);
-            if ((tid & 31) == 0 && r < s && part) atomicAdd(&zc[r].z, part);
+            if ((tid & 31) == 0 && r < s && part) atomicAdd(&zc[i0 + r].z, part);
         } else {
             us8 x = r < s ? v : (us8)(0);
             if (bits) {
@@ -752,7 +792,7 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
 #pragma unroll
     for (int half = 0; half < 2; half++) {
         const int off = half * 4096 + tid * 16;
-        if (kt0 + (off >> 10) < KT) *(u4*)(Xq + (size_t)kt0 * TILE_BYTES + off) = *(const u4*)(stage + off);
+        if (kt0 + (off >> 10) < KT) *(u4*)(Xq + ((size_t)(MID ? blockIdx.y : 0) * KT + kt0) * TILE_BYTES + off) = *(const u4*)(stage + off);
     }
 }
 
@@ -766,21 +806,173 @@ hipError_t launch_prepass_small(const void* X, int s, int h, unsigned thr, Outli
     const int nscan = (h + 511) / 512, nquant = (KT * 32 + 255) / 256;
     const size_t shm = ((size_t)(h + 31) / 32) * sizeof(unsigned);
     const ColumnJob job = (cj && cap <= JOB_MAX_CAP) ? *cj : ColumnJob{nullptr, nullptr, nullptr, 0, 0};
-    if (zc) {
-        scan_small_kernel<true><<<nscan, 256, 0, st>>>((const unsigned short*)X, s, h, thr, vec_ok, L, capc, zc);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        quantize_small_kernel<true><<<nquant + job.pitch / 256, 256, shm, st>>>(
-            (const unsigned short*)X, s, h, L, capc, vec_ok, idx, cap, opad_of(cap), count, status, cx, Xo, Xq, KT, 0, zc,
-            job);
-        return hipGetLastError();
+    const bool ragged = h % 8 != 0 || ((uintptr_t)X & 15) != 0;
+    const unsigned short* x = (const unsigned short*)X;
+    const int grid = nquant + job.pitch / 256;
+#define SMALL(ZP, RAGGED)                                                                                               \
+    do {                                                                                                                \
+        scan_small_kernel<ZP, RAGGED><<<nscan, 256, 0, st>>>(x, s, h, thr, vec_ok, L, capc, zc);                        \
+        const hipError_t e = hipGetLastError();                                                                         \
+        if (e != hipSuccess) return e;                                                                                  \
+        quantize_small_kernel<ZP, false, RAGGED><<<grid, 256, shm, st>>>(x, s, h, L, capc, vec_ok, idx, cap, opad_of(cap), \
+                                                                         count, status, cx, Xo, Xq, KT, shared_cx, zc,  \
+                                                                         nscan, job);                                   \
+    } while (0)
+    if (zc && ragged)
+        SMALL(true, true);
+    else if (zc)
+        SMALL(true, false);
+    else if (ragged)
+        SMALL(false, true);
+    else
+        SMALL(false, false);
+#undef SMALL
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// 33 to 128 tokens: the same two kernels, the first one with all rows of 256 columns (one list) in the registers of
+// a workgroup of 512 threads, RM rows per thread, the second one with a row of workgroups per row tile.  The four
+// kernels that a longer X takes are 3 to 4 us each here, whatever they do.  Calls with those / with these two: 64 x 4096
+// x 4096 21.3 / 18.4 us, 128 x 12288 x 4096 29.8 / 28.3, 96 x 49152 x 2048 50.3 / 48.0, zeropoint 64 x 4096 x 4096 23.4 /
+// 21.3, 128 x 4096 x 4096 24.9 / 24.3; above 128 tokens it turns (256 x 4096 x 4096 24.8 / 25.2, zeropoint 160 x 4096 x
+// 4096 27.4 / 30.3): a workgroup then has 96 KiB of X and more to itself.
+// ---------------------------------------------------------------------------
+template <int RM, bool ZP>
+__global__ void __launch_bounds__(512) scan_mid_kernel(const unsigned short* __restrict__ X, int s, int h, unsigned thr,
+                                                       OutlierLists L, int capc, int spad, int4* __restrict__ zc)
+{
+    __shared__ us8 red[8][32];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = tid & 31, rg = tid >> 5;
+    const int c0 = blockIdx.x * 256 + c * 8;
+    us8 v[RM];
+#pragma unroll
+    for (int m = 0; m < RM; m++) {  // a row past the last one: the last one again
+        const int i = rg + 16 * m;
+        v[m] = chunk_load(X + (size_t)(i < s ? i : s - 1) * h, c0, h);
     }
-    scan_small_kernel<false><<<nscan, 256, 0, st>>>((const unsigned short*)X, s, h, thr, vec_ok, L, capc, nullptr);
+    if (ZP && blockIdx.x == 0 && tid < s) zc[tid] = make_int4(0, 0, 0, 0);
+    if (blockIdx.x * 256 + 256 > h) {
+#pragma unroll
+        for (int m = 0; m < RM; m++) v[m] = chunk_fix(v[m], c0, h);
+    }
+    typedef unsigned int ui4 __attribute__((ext_vector_type(4)));
+    us8 mx = (us8)(0);
+#pragma unroll
+    for (int m = 0; m < RM; m++) mx = __builtin_elementwise_max(mx, v[m] & (unsigned short)0x7fff);
+    {
+        const ui4 a = __builtin_bit_cast(ui4, mx);
+        ui4 b;
+#pragma unroll
+        for (int e = 0; e < 4; e++) b[e] = (unsigned)__shfl_xor((int)a[e], 32);
+        mx = __builtin_elementwise_max(mx, __builtin_bit_cast(us8, b));
+    }
+    if (lane < 32) red[w][c] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; q++) mx = __builtin_elementwise_max(mx, red[q][c]);
+    unsigned flags = 0;
+#pragma unroll
+    for (int e = 0; e < 8; e++)
+        if (c0 + e < h && (unsigned)mx[e] >= thr) flags |= 1u << e;
+    // partial row maxima over the non-outlier columns, two 16-bit values per register across the 32 lanes of a row
+    // (zeropoint: the key of the largest entry and, inverted, that of the smallest)
+    us2 x[ZP ? RM : RM / 2];
+#pragma unroll
+    for (int m = 0; m < RM; m++) {
+        if constexpr (ZP) {
+            unsigned kmin = 0xffffu, kmax = 0u;
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+                if (!((flags >> e) & 1u) && c0 + e < h) {
+                    const unsigned k = f16_key(v[m][e]);
+                    kmin = k < kmin ? k : kmin;
+                    kmax = k > kmax ? k : kmax;
+                }
+            x[m] = us2{(unsigned short)(0xffffu - kmin), (unsigned short)kmax};
+        } else {
+            us8 a = v[m] & (unsigned short)0x7fff;
+            if (flags) {
+#pragma unroll
+                for (int e = 0; e < 8; e++)
+                    if ((flags >> e) & 1u) a[e] = 0;
+            }
+            x[m >> 1][m & 1] = hmax8(a);
+        }
+    }
+#pragma unroll
+    for (int d = 16; d >= 1; d >>= 1)
+#pragma unroll
+        for (int m = 0; m < (ZP ? RM : RM / 2); m++)
+            x[m] = __builtin_elementwise_max(x[m], __builtin_bit_cast(us2, __shfl_xor(__builtin_bit_cast(int, x[m]), d)));
+    if (c == 0) {
+        unsigned short* o = L.rowpart + (size_t)blockIdx.x * spad;
+#pragma unroll
+        for (int m = 0; m < RM; m++) {
+            const int i = rg + 16 * m;
+            if (i >= spad) continue;
+            if constexpr (ZP) {
+                o[i] = (unsigned short)(0xffffu - x[m].x);
+                o[(size_t)gridDim.x * spad + i] = x[m].y;
+            } else {
+                o[i] = x[m >> 1][m & 1];
+            }
+        }
+    }
+    if (tid < 32) {  // the list of this workgroup, ascending: lane, then bit
+        const int mine = __popc(flags);
+        int incl = mine;
+#pragma unroll
+        for (int d = 1; d < 32; d <<= 1) {
+            const int t = __shfl_up(incl, d, 32);
+            if (lane >= d) incl += t;
+        }
+        int pos = incl - mine;
+#pragma unroll
+        for (int e = 0; e < 8; e++)
+            if ((flags >> e) & 1u) {
+                if (pos < capc) L.cand[(size_t)blockIdx.x * capc + pos] = c0 + e;
+                pos++;
+            }
+        if (lane == 31) L.count[blockIdx.x] = incl;
+    }
+}
+
+bool prepass_mid_takes(int s, int h, size_t room)
+{
+    return s > 32 && s <= 128 && h >= 8 && (size_t)4 * ((h + 255) / 256) * ((s + 31) & ~31) <= room;
+}
+
+hipError_t launch_prepass_mid(const void* X, int s, int h, unsigned thr, OutlierLists L, int32_t* idx, int cap,
+                              int32_t* count, int32_t* status, unsigned short* cx, unsigned short* Xo, int8_t* Xq,
+                              hipStream_t st, int4* zc, const ColumnJob* cj)
+{
+    const int capc = list_capacity(cap);
+    const int KT = k_tiles(h), RT = row_tiles(s), spad = RT * 32;
+    const int nscan = (h + 255) / 256, nquant = (KT * 32 + 255) / 256;
+    const size_t shm = ((size_t)(h + 31) / 32) * sizeof(unsigned);
+    const ColumnJob job = (cj && cap <= JOB_MAX_CAP) ? *cj : ColumnJob{nullptr, nullptr, nullptr, 0, 0};
+    const unsigned short* x = (const unsigned short*)X;
+    if (zc) {
+        if (s <= 64)
+            scan_mid_kernel<4, true><<<nscan, 512, 0, st>>>(x, s, h, thr, L, capc, spad, zc);
+        else
+            scan_mid_kernel<8, true><<<nscan, 512, 0, st>>>(x, s, h, thr, L, capc, spad, zc);
+    } else {
+        if (s <= 64)
+            scan_mid_kernel<4, false><<<nscan, 512, 0, st>>>(x, s, h, thr, L, capc, spad, zc);
+        else
+            scan_mid_kernel<8, false><<<nscan, 512, 0, st>>>(x, s, h, thr, L, capc, spad, zc);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    quantize_small_kernel<false><<<nquant + job.pitch / 256, 256, shm, st>>>(
-        (const unsigned short*)X, s, h, L, capc, vec_ok, idx, cap, opad_of(cap), count, status, cx, Xo, Xq, KT, shared_cx,
-        nullptr, job);
+    const dim3 grid(nquant + job.pitch / 256, RT);
+    if (zc)
+        quantize_small_kernel<true, true, true><<<grid, 256, shm, st>>>(x, s, h, L, capc, 1, idx, cap, opad_of(cap), count, status, cx,
+                                                            Xo, Xq, KT, 0, zc, nscan, job);
+    else
+        quantize_small_kernel<false, true, true><<<grid, 256, shm, st>>>(x, s, h, L, capc, 1, idx, cap, opad_of(cap), count, status, cx,
+                                                             Xo, Xq, KT, 0, zc, nscan, job);
     return hipGetLastError();
 }
 

@@ -582,6 +582,21 @@ def test_rows_and_columns_that_do_not_start_on_16_bytes(s, h, o):
         L.debug_decode_shape(-1)
 
 
+@pytest.mark.parametrize("s,h,o,ncol,cap", [(33, 8, 40, 1, 16), (64, 255, 33, 3, 32), (65, 256, 64, 4, 32), (96, 257, 72, 5, 32),
+                                            (97, 1000, 264, 20, 16), (127, 513, 100, 3, 32), (128, 4100, 136, 9, 4),
+                                            (128, 2048, 64, 300, 300), (129, 700, 96, 5, 32)])
+def test_two_kernel_pre_pass_of_33_to_128_tokens(s, h, o, ncol, cap):
+    """Around the ends of row tiles and of the scan's column blocks, more columns than the buffer takes, more than the
+    job's list holds: against the oracle; zeropoint and int8-rows calls against the staged calls."""
+    import test_gpu_zeropoint as zp
+    d = wl.make_custom(s, h, o, ncol, seed=s + h + o, frac=0.3)
+    linear_compare(d, cap=cap)
+    linear_compare(d, alpha=0.0, cap=cap)
+    if ncol <= cap:
+        int8_rows_compare(d, cap=cap, via_linear=True)
+        zp.zp_compare(d["X"], d["W"], d["alpha"], cap=cap)
+
+
 def test_linear_row_maximum_inside_an_outlier_column():
     """Rows whose largest magnitude below alpha sits in an outlier column (alone, or tied with a regular
     column): the row constant must come from the regular columns only."""
