@@ -128,9 +128,9 @@ int llmint8_dequantize_rows(const int8_t *Wq, const void *cw_f16, int h, int o, 
 /* Eq. 7 + Eq. 8: C_i32 = X_i8 W_i8 (int32 accumulation),
  * Out = fp16( C_i32 * c_x (x) c_w / 127^2 + Xo W_f16[O,:] ), the outlier product
  * accumulated in fp32.  Token counts s <= 32 (up to 48 against a wide W) take a weight-streaming
- * kernel unless the shape of W suits the tiled kernel better.  The two kernels add the outlier product
- * up in fp32 in different orders: an output may differ in its last fp16 bit between them (not
- * between the tile shapes or work splits of one kernel).
+ * kernel unless the shape of W suits the tiled kernel better; products too small to fill the chip take
+ * smaller tiles.  The kernels add the outlier product up in fp32 in different orders: an output may
+ * differ in its last fp16 bit between them (not between the tile shapes or work splits of one kernel).
  *   W_f16       in   the original weights; only rows O are read.  NULL: the rows rebuilt from
  *                    the codes (llmint8_dequantize_rows, done here into ws) take their place
  *   cx_f16      in   [s] fp16.  If the array starts on a 16-byte boundary it is read in aligned
@@ -146,7 +146,8 @@ int llmint8_matmul(const int8_t *Xq, const void *cx_f16, const void *Xo_f16, con
 
 /* The per-call sequence find_outliers -> quantize_rows -> matmul on one stream (W_f16 may be NULL
  * as for llmint8_matmul): the same outputs as the three calls, bit for bit, from fewer kernels
- * (two for the whole pre-pass when s <= 32, the rebuilt rows of W included).
+ * (two for the whole pre-pass when s <= 128, the rebuilt rows of W included; one for everything when X
+ * is small).
  * Xq, cx_f16, Xo_f16, idx, count, status are caller-provided scratch/outputs
  * of the sizes given above.                                                   */
 int llmint8_linear(const void *X_f16, int s, int h, float alpha, const int8_t *Wq, const void *cw_f16,
@@ -223,7 +224,7 @@ int llmint8_zp_matmul(const int8_t *Xq, const int32_t *zc_x, const void *Xo_f16,
                       int s, int h, int o, void *Out_f16, int32_t *C_i32_debug, void *ws, size_t ws_bytes,
                       llmint8_stream_t stream);
 /* find_outliers -> zp_quantize_rows -> zp_matmul on one stream; the same outputs as the three calls, bit
- * for bit (for s <= 32 from three kernels in all). */
+ * for bit (for s <= 128 from three kernels in all). */
 int llmint8_zp_linear(const void *X_f16, int s, int h, float alpha, const int8_t *Wq, const int32_t *zc_w,
                       const void *W_f16, int o, int32_t *idx, int cap, int32_t *count, int32_t *status,
                       int8_t *Xq, int32_t *zc_x, void *Xo_f16, void *Out_f16, void *ws, size_t ws_bytes,

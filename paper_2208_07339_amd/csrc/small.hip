@@ -6,6 +6,8 @@ namespace llmint8 {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 
@@ -22,6 +24,9 @@ typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 // Row r of X belongs to 256 / sp threads (sp: s rounded up to a power of two), each holding XC chunks of 8
 // features in registers from the first load to the codes.  A column is an outlier when any of its entries says
 // so: those entries set bits of a bitmap in LDS, whose population counts place the columns in order.
+//
+// Outputs are those of the separate calls bit for bit.  Where llmint8_matmul takes the tiled kernel for these sizes, the
+// outlier product therefore comes from the matrix unit, as there.
 //
 // Every workgroup also writes its share of the codes; workgroup 0 writes idx, count, status, c_x and Xo.
 // ---------------------------------------------------------------------------
@@ -40,6 +45,7 @@ struct SmallArgs {
     unsigned short* cx;
     unsigned short* Xo;
     _Float16* Out;
+    int tiled_order;  // llmint8_matmul takes the tiled kernel for these sizes: add up in its order
 };
 
 constexpr int SSLOTS = 32;  // outlier slots whose operands are fetched before the weight stream goes on
@@ -274,12 +280,38 @@ __global__ void __launch_bounds__(256, XC <= 4 ? 4 : 3) linear_small_kernel(cons
         s_wo[ig + 8 * q][jj] = a.Wf ? wo[q] : dequant_bits((int)(int8_t)wo[q], cwb);
     }
     __syncthreads();
+    __shared__ float s_t[16][64];  // the outlier product, laid out as the sums
+    if (a.tiled_order) {
+        if (w == 0) {
+            const int gl = lane >> 5, ll = lane & 31;
+            v16f t = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int ks = 0; ks < SSLOTS / 16; ks++) {
+                if (16 * ks >= cnt) continue;
+                v8h wa, xa;
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    wa[e] = __builtin_bit_cast(_Float16, s_wo[16 * ks + 8 * gl + e][ll]);
+                    xa[e] = __builtin_bit_cast(_Float16, s_xo[16 * ks + 8 * gl + e][ll]);
+                }
+                t = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa, xa, t, 0, 0, 0);
+            }
+#pragma unroll
+            for (int q = 0; q < 16; q++) s_t[q][lane] = t[q];
+        }
+        __syncthreads();
+    }
     if (j >= o) return;
     const int rr = 4 * (jj >> 3) + (jj & 3), l0 = 32 * ((jj >> 2) & 1);
     const float cwj = f16_bits_to_float(cwb);
     for (int i = ig; i < s; i += 8) {
         const int l = l0 + i;
         const int c = red[0][rr][l] + red[1][rr][l] + red[2][rr][l] + red[3][rr][l];
+        if (a.tiled_order) {
+            const float sx = f16_bits_to_float((unsigned short)s_row[i]) * (1.0f / 16129.0f);
+            a.Out[(size_t)i * o + j] = (_Float16)__builtin_fmaf((float)c * sx, cwj, s_t[rr][l]);
+            continue;
+        }
         // Eq. 7 dequantization, then the outlier product of Eq. 8 accumulated in fp32
         float d = (float)c * (f16_bits_to_float((unsigned short)s_row[i]) * (1.0f / 16129.0f)) * cwj;
         for (int t = 0; t < (cnt < SSLOTS ? cnt : SSLOTS); t++)
@@ -306,6 +338,8 @@ static int small_chunks(int s, int h, int cap, int* lg)
     return n <= 16 ? n : 0;
 }
 
+static bool tiled_order(int s, int h, int o) { return !ksplit_takes(s, h, o) && !decode_kernel_takes(s, h, o, false); }
+
 // Where one kernel is the better way, per call against the separate kernels.  Every workgroup repeats the
 // pre-pass, about 1 200 vector instructions per wave at 16 chunks, so its price grows with the chunks and with the
 // workgroups that share a compute unit; what it saves is two launches and two short kernels, 6 to 10 us.
@@ -319,7 +353,9 @@ bool linear_small_takes(int s, int h, int o, int cap)
     int lg, cus = 0;
     if (g_decode_cfg.load(std::memory_order_relaxed) >= 0) return false;  // test hook: the separate kernels
     const int n = small_chunks(s, h, cap, &lg);
-    if (n == 0 || n <= 8) return n != 0;
+    if (n == 0) return false;
+    if (cap > SSLOTS && tiled_order(s, h, o)) return false;
+    if (n <= 8) return true;
     if (prefill_device_setup(&cus) != hipSuccess) cus = 256;
     return 2 * row_tiles(o) <= 3 * cus;
 }
@@ -333,7 +369,7 @@ hipError_t launch_linear_small(const void* X, int s, int h, unsigned thr, const 
     if (n == 0) return hipErrorInvalidValue;
     const int KT = k_tiles(h);
     const SmallArgs a = {(const unsigned short*)X, s, h, o, KT, lg, thr, Wq, cw, Wf, idx, cap, opad_of(cap), count, status,
-                         Xq, cx, Xo, (_Float16*)Out};
+                         Xq, cx, Xo, (_Float16*)Out, tiled_order(s, h, o) ? 1 : 0};
     const int grid = row_tiles(o);
     const size_t shm = (size_t)(256 >> lg) * KT * 32 + 16;
     if (n <= 1)

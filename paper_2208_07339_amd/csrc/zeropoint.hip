@@ -158,10 +158,11 @@ __global__ void __launch_bounds__(256) zp_row_range_kernel(const unsigned short*
             for (int u = 0; u < 4; u++) {
                 const int c = c0 + u * 2048;
                 if (c < h) {
-                    const unsigned bits = (bitmap[c >> 5] >> (c & 31)) & 0xffu;
+                    unsigned bits = (bitmap[c >> 5] >> (c & 31)) & 0xffu;
+                    if (c + 8 > h) bits |= 0xffu << (h - c);  // nor what lies past the row
 #pragma unroll
                     for (int e = 0; e < 8; e++)
-                        if (!((bits >> e) & 1u) && c + e < h) {
+                        if (!((bits >> e) & 1u)) {
                             const unsigned k = f16_key(v[u][e]);
                             kmin = k < kmin ? k : kmin;
                             kmax = k > kmax ? k : kmax;

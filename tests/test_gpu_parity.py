@@ -481,6 +481,24 @@ def test_linear_in_one_kernel(s, h, o, ncol, cap):
         int8_rows_compare(d, cap=cap, via_linear=True)
 
 
+@pytest.mark.parametrize("s,h,o,ncol,cap", [(8, 512, 20480, 7, 32), (1, 1030, 17000, 20, 32), (32, 500, 16416, 17, 32),
+                                            (5, 1024, 28672, 0, 16), (3, 700, 18001, 9, 48), (16, 1024, 4096, 7, 32)])
+def test_small_calls_equal_the_staged_calls_whichever_kernel_those_take(s, h, o, ncol, cap):
+    """llmint8_linear in one kernel against find_outliers, quantize_rows and matmul, bit for bit, with W of two to four
+    column tiles per compute unit (matmul: the tiled kernel) and of fewer; with fp16 rows and with rebuilt ones."""
+    import dataclasses
+
+    import torch
+
+    import paper_2208_07339_amd as L
+    d = wl.make_custom(s, h, o, ncol, seed=s + h + o)
+    g = run_hip(d["X"], d["W"], 6.0, cap, want_c=False)
+    for qw in (g["qw"], dataclasses.replace(g["qw"], W=None)):
+        want = L.matmul(g["rows"], g["outl"], qw, g["ws"]).clone()
+        got = L.linear(g["Xd"], qw, 6.0, g["outl"], g["rows"], g["ws"])
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
 def test_linear_with_the_result_in_the_place_of_x():
     import torch
 
