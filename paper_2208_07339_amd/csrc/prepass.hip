@@ -1045,7 +1045,7 @@ __global__ void __launch_bounds__(256) row_absmax_kernel(const unsigned short* _
                 const int c = c0 + u * 2048;
                 v[u] = chunk_load(row, c, h);
             }
-            if (c0 + 3 * 2048 + 8 > h) {
+            if ((h & 7) && c0 + 3 * 2048 + 8 > h) {  // (whole chunks past the row are skipped below)
 #pragma unroll
                 for (int u = 0; u < 4; u++) v[u] = chunk_fix(v[u], c0 + u * 2048, h);
             }
@@ -1196,7 +1196,7 @@ __global__ void __launch_bounds__(256, 5) row_const_kernel(const unsigned short*
 #pragma unroll
                 for (int u = 0; u < RU; u++) v[u] = chunk_load(row2, c0 + u * 2048, h);  // unconditional, so that the
                 // compiler issues them together
-                if (c0 + (RU - 1) * 2048 + 8 > h) {
+                if ((h & 7) && c0 + (RU - 1) * 2048 + 8 > h) {
 #pragma unroll
                     for (int u = 0; u < RU; u++) v[u] = chunk_fix(v[u], c0 + u * 2048, h);
                 }

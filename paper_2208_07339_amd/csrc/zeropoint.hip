@@ -150,7 +150,7 @@ __global__ void __launch_bounds__(256) zp_row_range_kernel(const unsigned short*
                 const int c = c0 + u * 2048;
                 v[u] = chunk_load(row, c, h);
             }
-            if (c0 + 3 * 2048 + 8 > h) {
+            if ((h & 7) && c0 + 3 * 2048 + 8 > h) {  // (whole chunks past the row are skipped below)
 #pragma unroll
                 for (int u = 0; u < 4; u++) v[u] = chunk_fix(v[u], c0 + u * 2048, h);
             }
@@ -258,7 +258,7 @@ __global__ void __launch_bounds__(256 * ZQ_NB) zp_quantize_rows_kernel(const uns
         const int i = rt * 32 + r;
         double D = 0.0;
         int z = 0;
-        us8 v = vq[q];
+        us8 v = i < s ? vq[q] : (us8)(0);
         if (i < s) {
             D = zp_range((unsigned)recq[q].x);
             z = recq[q].y;
@@ -269,17 +269,17 @@ __global__ void __launch_bounds__(256 * ZQ_NB) zp_quantize_rows_kernel(const uns
                     if (k + e < h) v[e] = row[k + e];
             }
         }
-        const double rD = D > 0.0 ? 1.0 / D : 0.0;
-        unsigned lo = 0, hi = 0;
+        const double f = zp_factor(D);  // D = 0: codes 0 (then z = 0 too)
+        const unsigned off = k + 8 <= h ? bits : bits | (k < h ? 0xffu << (h - k) : 0xffu);  // no code: outlier columns, past the row
+        unsigned b8[8];
         int part = 0;
 #pragma unroll
         for (int e = 0; e < 8; e++) {
-            int qv = 0;
-            if (D > 0.0 && k + e < h && !((bits >> e) & 1u)) qv = zp_u_rcp(v[e], D, rD) - z;
+            const int qv = (off >> e) & 1u ? 0 : (int)zp_u_bits(v[e], f) - z;
             part += qv;
-            const unsigned byte = (unsigned)qv & 0xffu;
-            if (e < 4) lo |= byte << (8 * e); else hi |= byte << (8 * (e - 4));
+            b8[e] = (unsigned)qv;
         }
+        const unsigned lo = pack_low_bytes(b8[0], b8[1], b8[2], b8[3]), hi = pack_low_bytes(b8[4], b8[5], b8[6], b8[7]);
         u2 pk = {lo, hi};
         *(u2*)(stage + (g * 8 + (kseg >> 5)) * TILE_BYTES + tile_byte(r, kseg & 31)) = pk;
         // the 32 lanes that share row r (one half of a wave) add up their parts
