@@ -733,12 +733,20 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
         }
         __syncthreads();
         const int sr = s < 32 ? s : 32;
-        for (int q = tid; q < sr * opad; q += 256) {
-            const int i = q / opad, t = q - i * opad;
-            if (t >= cnt)
-                Xo[(size_t)i0 * opad + q] = (unsigned short)0;
-            else if (cap <= JOB_MAX_CAP)
-                Xo[(size_t)i0 * opad + q] = X[(size_t)i * h + s_list[t]];
+        for (int q0 = tid; q0 < sr * opad; q0 += 1024) {  // four values in flight
+            unsigned short x[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int q = q0 + 256 * u < sr * opad ? q0 + 256 * u : q0;
+                const int i = q / opad, t = q - i * opad;
+                x[u] = X[(size_t)i * h + (t < cnt && cap <= JOB_MAX_CAP ? s_list[t] : 0)];
+                if (t >= cnt) x[u] = 0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int q = q0 + 256 * u;
+                if (q < sr * opad && (cap <= JOB_MAX_CAP || q % opad >= cnt)) Xo[(size_t)i0 * opad + q] = x[u];
+            }
         }
         if (tid == 0 && i0 == 0) {
             *count = cnt;
