@@ -178,7 +178,8 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
     if (blockIdx.x == 9 && lane == 0) g_stamps[w][21] = clock64();  // kernel entry
 #endif
     // The number of outlier columns, and in lane t < 32 the weight row of outlier slot t (row 0 for unused
-    // slots: finite values that meet the zeros of Xo).  Both are loaded below, behind the requests of the
+    // slots: finite values that meet the zeros of Xo; GUARDED: also an index that names no row of W, which its
+    // epilogue leaves out).  Both are loaded below, behind the requests of the
     // first tile's first two stages: two dependent round trips that would otherwise sit in front of them.
     int cnt = 0;
     int myk = 0;
@@ -375,7 +376,7 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
         cnt = cnt < 0 ? 0 : (cnt > g.cap ? g.cap : cnt);
         if ((lane & 31) < cnt) {
             const unsigned k = g.rows_are_slots ? (unsigned)(lane & 31) : kraw;
-            myk = k < (unsigned)g.wrows ? (int)k : 0;
+            myk = GUARDED || k < (unsigned)g.wrows ? (int)k : 0;
         }
     }
     // once per kernel: with this load known to be complete, the compiler has no reason to drain the
@@ -485,7 +486,7 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
 #pragma unroll
             for (int e = 0; e < 8; e++) {
                 const int t = t0 + 8 * gl + e;
-                if (t0 < OSLOTS)  // every lane t < 32 has slot t's row
+                if (t0 < OSLOTS)  // lane t < 32 has slot t's index as the list gives it
                     k[e] = (unsigned)__shfl(myk, t);
                 else
                     k[e] = g.rows_are_slots ? (unsigned)t : (unsigned)g.idx[t < cnt ? t : 0];

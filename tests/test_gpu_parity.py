@@ -257,6 +257,40 @@ def test_tiles_with_k_split_over_the_waves(s, h, o, ncol, cap):
         zp.zp_compare(d["X"], d["W"], d["alpha"], cap=cap)
 
 
+@pytest.mark.parametrize("bad", [-1, 300, 2 ** 31 - 1])
+@pytest.mark.parametrize("s,o", [(300, 264), (300, 261), (20, 264)])
+def test_a_listed_index_that_names_no_row_of_w_adds_nothing(s, o, bad):
+    """An outlier list of the caller's with such an entry and values in its slot of Xo: the slot contributes zero, in
+    every kernel that checks its operands (tiled with the guarded epilogue, weight-streaming, K split over the waves),
+    among the slots that are staged and past them.  No kernel reads at such an index (all replace it by row 0)."""
+    import torch
+
+    import paper_2208_07339_amd as L
+    h, n, cap = 300, 40, 48
+    d = wl.make_custom(s, h, o, 3, seed=s + o)
+    g = run_hip(d["X"], d["W"], float("inf"), cap)
+    idx = np.arange(n, dtype=np.int32) * 7
+    idx[[0, 5, 31, 32, 39]] = bad
+    Xo = np.zeros((s, L.opad(cap)), np.float16)
+    Xo[:, :n] = np.random.default_rng(3).uniform(-4, 4, (s, n)).astype(np.float16)
+    good = (idx >= 0) & (idx < h)
+    want = g["C"].astype(np.float64) / 16129.0 * g["cx"].astype(np.float64)[:, None] * g["cw"].astype(np.float64)[None, :]
+    want += Xo[:, :n][:, good].astype(np.float64) @ d["W"][idx[good]].astype(np.float64)
+    g["outl"].idx[:n] = torch.from_numpy(idx).cuda()
+    g["outl"].count.fill_(n)
+    g["rows"].Xo.copy_(torch.from_numpy(Xo.view(np.int16)).cuda().view(torch.float16))
+    for tile, decode in ((-1, -1), (-1, 0), (3, 0), (-1, 1)):
+        try:
+            L.debug_prefill_tile(tile)
+            L.debug_decode_shape(decode)
+            out, _ = L.matmul(g["rows"], g["outl"], g["qw"], g["ws"], want_c_i32=True)
+            torch.cuda.synchronize()
+        finally:
+            L.debug_prefill_tile(-1)
+            L.debug_decode_shape(-1)
+        assert_out_close(out.cpu().numpy(), want.astype(np.float16))
+
+
 def test_alpha_zero_is_pure_fp16_matmul_on_both_paths():
     d = wl.make("tiny")
     g, r = full_compare(d, alpha=0.0, cap=256)
