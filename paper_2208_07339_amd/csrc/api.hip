@@ -283,13 +283,13 @@ static int linear_impl(const void* X_f16, int s, int h, float alpha, int granula
         e = launch_prepass_small(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status,
                                  (unsigned short*)cx_f16, (unsigned short*)Xo_f16, Xq, shared_cx, st, nullptr,
                                  W_f16 ? nullptr : &job);
-    } else if (!shared_cx && !(std::isinf(alpha) && alpha > 0.0f) && prepass_mid_takes(s, h, slab_ws(s, h) + rowpart_ws(s, h))) {
+    } else if (!shared_cx && !(std::isinf(alpha) && alpha > 0.0f) && prepass_mid_takes(s, h, cap, slab_ws(s, h) + rowpart_ws(s, h))) {
         OutlierLists Lm = L;  // the partial row maxima in the place of the slab maxima
         Lm.rowpart = (unsigned short*)(base + scratch_ws(h, cap));
         const ColumnJob job = {Wq, cw_f16, base + scan_ws(s, h, o, cap), o, (o + 255) & ~255};
         e = launch_prepass_mid(X_f16, s, h, threshold_bits(alpha), Lm, idx, cap, count, status, (unsigned short*)cx_f16,
                                (unsigned short*)Xo_f16, Xq, st, nullptr, W_f16 ? nullptr : &job);
-        have_rows = cap <= JOB_MAX_CAP;
+        have_rows = true;
     } else {
         if (std::isinf(alpha) && alpha > 0.0f) {
             // no decomposition (the baselines of Table 1 without it): O is empty, X need not be scanned
@@ -474,7 +474,7 @@ int llmint8_zp_linear(const void* X_f16, int s, int h, float alpha, const int8_t
                                zp_col_pitch(o)};
         r = hip_status(launch_prepass_small(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status, nullptr,
                                             (unsigned short*)Xo_f16, Xq, 0, (hipStream_t)stream, (int4*)zc_x, &job));
-    } else if (prepass_mid_takes(s, h, slab_ws(s, h) + rowpart_ws(s, h))) {
+    } else if (prepass_mid_takes(s, h, cap, slab_ws(s, h) + rowpart_ws(s, h))) {
         char* base = (char*)ws_base(ws);
         OutlierLists L = carve_outlier_lists(base, h, cap);
         L.rowpart = (unsigned short*)(base + scratch_ws(h, cap));

@@ -715,37 +715,38 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
 
     // ---- the row tile's first workgroup: c_x, Xo (and, the very first, the outputs of the outlier scan)
     if (blockIdx.x == 0) {
-        __shared__ int s_list[JOB_MAX_CAP];  // the outlier columns in order, as many as fit
+        __shared__ int s_list[JOB_MAX_CAP];  // the outlier columns in order
+        const bool fits = MID || cap <= JOB_MAX_CAP;
         for (int b = tid; b < nl; b += 256) {
             const int n = s_cnt[b] < capc ? s_cnt[b] : capc;
             const int base = s_base[b], m = n < cap - base ? n : cap - base;
-            if (cap <= JOB_MAX_CAP)
-                list_entries(L.cand + (size_t)b * capc, m, [&](int e, int j) {
-                    s_list[base + e] = j;
-                    if (i0 == 0) idx[base + e] = j;
-                });
-            else  // a larger buffer: straight from the lists
-                for (int e = 0; e < m; e++) {
-                    const int j = L.cand[(size_t)b * capc + e];
-                    if (i0 == 0) idx[base + e] = j;
-                    for (int i = 0; i < 32 && i < s; i++) Xo[(size_t)(i0 + i) * opad + base + e] = X[(size_t)i * h + j];
-                }
+            list_entries(L.cand + (size_t)b * capc, m, [&](int e, int j) {
+                if (fits) s_list[base + e] = j;
+                if (i0 == 0) idx[base + e] = j;
+            });
         }
         __syncthreads();
         const int sr = s < 32 ? s : 32;
-        for (int q0 = tid; q0 < sr * opad; q0 += 1024) {  // four values in flight
-            unsigned short x[4];
+        if (fits) {
+            for (int q0 = tid; q0 < sr * opad; q0 += 1024) {  // four values in flight
+                unsigned short x[4];
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const int q = q0 + 256 * u < sr * opad ? q0 + 256 * u : q0;
-                const int i = q / opad, t = q - i * opad;
-                x[u] = X[(size_t)i * h + (t < cnt && cap <= JOB_MAX_CAP ? s_list[t] : 0)];
-                if (t >= cnt) x[u] = 0;
+                for (int u = 0; u < 4; u++) {
+                    const int q = q0 + 256 * u < sr * opad ? q0 + 256 * u : q0;
+                    const int i = q / opad, t = q - i * opad;
+                    x[u] = X[(size_t)i * h + (t < cnt ? s_list[t] : 0)];
+                    if (t >= cnt) x[u] = 0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const int q = q0 + 256 * u;
+                    if (q < sr * opad) Xo[(size_t)i0 * opad + q] = x[u];
+                }
             }
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const int q = q0 + 256 * u;
-                if (q < sr * opad && (cap <= JOB_MAX_CAP || q % opad >= cnt)) Xo[(size_t)i0 * opad + q] = x[u];
+        } else {  // a larger buffer: idx is read back by other threads of this workgroup
+            for (int q = tid; q < sr * opad; q += 256) {
+                const int i = q / opad, t = q - i * opad;
+                Xo[q] = t < cnt ? X[(size_t)i * h + idx[t]] : (unsigned short)0;
             }
         }
         if (tid == 0 && i0 == 0) {
@@ -844,7 +845,9 @@ hipError_t launch_prepass_small(const void* X, int s, int h, unsigned thr, Outli
 // kernels that a longer X takes are 3 to 4 us each here, whatever they do.  Calls with those / with these two: 64 x 4096
 // x 4096 21.3 / 18.4 us, 128 x 12288 x 4096 29.8 / 28.3, 96 x 49152 x 2048 50.3 / 48.0, zeropoint 64 x 4096 x 4096 23.4 /
 // 21.3, 128 x 4096 x 4096 24.9 / 24.3; above 128 tokens it turns (256 x 4096 x 4096 24.8 / 25.2, zeropoint 160 x 4096 x
-// 4096 27.4 / 30.3): a workgroup then has 96 KiB of X and more to itself.
+// 4096 27.4 / 30.3): a workgroup then has 96 KiB of X and more to itself.  Outlier buffers of more than JOB_MAX_CAP columns
+// keep the kernels of a longer X, where every workgroup gathers its own rows' columns: here one workgroup per row tile
+// would (64 x 4096 x 4096, cap 300, 200 columns: 216 us with these two, 76 with those).
 // ---------------------------------------------------------------------------
 template <int RM, bool ZP>
 __global__ void __launch_bounds__(512) scan_mid_kernel(const unsigned short* __restrict__ X, int s, int h, unsigned thr,
@@ -946,9 +949,9 @@ __global__ void __launch_bounds__(512) scan_mid_kernel(const unsigned short* __r
     }
 }
 
-bool prepass_mid_takes(int s, int h, size_t room)
+bool prepass_mid_takes(int s, int h, int cap, size_t room)
 {
-    return s > 32 && s <= 128 && h >= 8 && (size_t)4 * ((h + 255) / 256) * ((s + 31) & ~31) <= room;
+    return s > 32 && s <= 128 && h >= 8 && cap <= JOB_MAX_CAP && (size_t)4 * ((h + 255) / 256) * ((s + 31) & ~31) <= room;
 }
 
 hipError_t launch_prepass_mid(const void* X, int s, int h, unsigned thr, OutlierLists L, int32_t* idx, int cap,
@@ -959,7 +962,7 @@ hipError_t launch_prepass_mid(const void* X, int s, int h, unsigned thr, Outlier
     const int KT = k_tiles(h), RT = row_tiles(s), spad = RT * 32;
     const int nscan = (h + 255) / 256, nquant = (KT * 32 + 255) / 256;
     const size_t shm = ((size_t)(h + 31) / 32) * sizeof(unsigned);
-    const ColumnJob job = (cj && cap <= JOB_MAX_CAP) ? *cj : ColumnJob{nullptr, nullptr, nullptr, 0, 0};
+    const ColumnJob job = cj ? *cj : ColumnJob{nullptr, nullptr, nullptr, 0, 0};
     const unsigned short* x = (const unsigned short*)X;
     if (zc) {
         if (s <= 64)
