@@ -283,7 +283,7 @@ static int linear_impl(const void* X_f16, int s, int h, float alpha, int granula
         e = launch_prepass_small(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status,
                                  (unsigned short*)cx_f16, (unsigned short*)Xo_f16, Xq, shared_cx, st, nullptr,
                                  W_f16 ? nullptr : &job);
-    } else if (!shared_cx && !(std::isinf(alpha) && alpha > 0.0f) && prepass_mid_takes(s, h, cap, slab_ws(s, h) + rowpart_ws(s, h))) {
+    } else if (!shared_cx && !(std::isinf(alpha) && alpha > 0.0f) && prepass_mid_takes(s, h, cap, false, slab_ws(s, h) + rowpart_ws(s, h))) {
         OutlierLists Lm = L;  // the partial row maxima in the place of the slab maxima
         Lm.rowpart = (unsigned short*)(base + scratch_ws(h, cap));
         const ColumnJob job = {Wq, cw_f16, base + scan_ws(s, h, o, cap), o, (o + 255) & ~255};
@@ -474,7 +474,7 @@ int llmint8_zp_linear(const void* X_f16, int s, int h, float alpha, const int8_t
                                zp_col_pitch(o)};
         r = hip_status(launch_prepass_small(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status, nullptr,
                                             (unsigned short*)Xo_f16, Xq, 0, (hipStream_t)stream, (int4*)zc_x, &job));
-    } else if (prepass_mid_takes(s, h, cap, slab_ws(s, h) + rowpart_ws(s, h))) {
+    } else if (prepass_mid_takes(s, h, cap, true, slab_ws(s, h) + rowpart_ws(s, h))) {
         char* base = (char*)ws_base(ws);
         OutlierLists L = carve_outlier_lists(base, h, cap);
         L.rowpart = (unsigned short*)(base + scratch_ws(h, cap));

@@ -377,8 +377,9 @@ struct ColumnJob {
 hipError_t launch_prepass_small(const void* X, int s, int h, unsigned thr, OutlierLists L, int32_t* idx, int cap,
                                 int32_t* count, int32_t* status, unsigned short* cx, unsigned short* Xo, int8_t* Xq,
                                 int shared_cx, hipStream_t st, int4* zc = nullptr, const ColumnJob* cj = nullptr);
-// the same for 33 to 128 tokens and cap <= JOB_MAX_CAP; L.rowpart: room for 2 ceil(h / 256) * 32 row_tiles(s) fp16 values
-bool prepass_mid_takes(int s, int h, int cap, size_t room);
+// the same for 33 to 128 tokens and cap <= JOB_MAX_CAP; L.rowpart: room for 2 (zeropoint: 4) ceil(h / 256) * 32 row_tiles(s)
+// fp16 values
+bool prepass_mid_takes(int s, int h, int cap, bool zeropoint, size_t room);
 hipError_t launch_prepass_mid(const void* X, int s, int h, unsigned thr, OutlierLists L, int32_t* idx, int cap,
                               int32_t* count, int32_t* status, unsigned short* cx, unsigned short* Xo, int8_t* Xq,
                               hipStream_t st, int4* zc, const ColumnJob* cj);

@@ -463,12 +463,13 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
                                                              int8_t* __restrict__ Xq, int KT, int shared_cx,
                                                              int4* __restrict__ zc, int nwg, ColumnJob cj)
 {
-    extern __shared__ unsigned fullmap[];  // ceil(h / 32) words, used only when |O| > cap
+    extern __shared__ unsigned fullmap[];  // ceil(h / 32) words, used only when |O| > cap (MID: not at all)
     __shared__ __attribute__((aligned(16))) int8_t stage[8 * TILE_BYTES];
     __shared__ int s_cnt[MAXLISTS], s_base[MAXLISTS];
-    __shared__ unsigned s_part[8][32];
+    constexpr int NPART = MID ? 9 : 8;  // the last one: the block that the end of the buffer cuts through
+    __shared__ unsigned s_part[NPART][32];
     __shared__ unsigned s_cxb[32];
-    __shared__ unsigned s_part_lo[ZP ? 8 : 1][32];  // zeropoint: s_part / s_cxb hold the keys of the maxima, these of the minima
+    __shared__ unsigned s_part_lo[ZP ? NPART : 1][32];  // zeropoint: s_part / s_cxb hold the keys of the maxima, these of the minima
     __shared__ unsigned s_lo[ZP ? 32 : 1];
     __shared__ double s_D[ZP ? 32 : 1], s_rD[ZP ? 32 : 1];  // zeropoint: range of each row and its reciprocal
     __shared__ int s_z[ZP ? 32 : 1];                        // and its zeropoint
@@ -618,15 +619,91 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
     const int cnt = total < cap ? total : cap;
     const bool overflow = total > cap;
 
+    if (MID && overflow) {
+        // Only the first cap columns count as outliers.  Blocks past them have all their columns back (the second set of
+        // partial maxima), and the block that the end of the buffer cuts through is scanned again without the columns
+        // that it keeps.
+        __shared__ int s_cut;
+        __shared__ unsigned keep[8];
+        if (tid == 0) s_cut = -1;
+        if (tid < 8) keep[tid] = 0;
+        if (tid < 32) {
+            s_part[NPART - 1][tid] = 0;
+            if constexpr (ZP) s_part_lo[NPART - 1][tid] = 0xffffu;
+        }
+        __syncthreads();
+        const int i = tid & 31, gq = tid >> 5;
+        rp_max = 0;
+        rp_min = 0xffffu;
+        for (int b0 = gq; b0 < nwg; b0 += 64) {
+            unsigned hi[8], lo[8];
+            bool cut[8];
+#pragma unroll
+            for (int u = 0; u < 8; u++) {
+                const int b = b0 + 8 * u < nwg ? b0 + 8 * u : b0;
+                const int n = s_cnt[b], base = s_base[b];
+                cut[u] = base < cap && base + n > cap;
+                if (cut[u]) s_cut = b;
+                const size_t at = (size_t)((n > 0 && base >= cap ? (ZP ? 2 : 1) * nwg : 0) + b) * spad + i0 + i;
+                hi[u] = L.rowpart[at + (ZP ? (size_t)nwg * spad : 0)];
+                if constexpr (ZP) lo[u] = L.rowpart[at];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; u++)
+                if (!cut[u]) {
+                    rp_max = hi[u] > rp_max ? hi[u] : rp_max;
+                    if constexpr (ZP) rp_min = lo[u] < rp_min ? lo[u] : rp_min;
+                }
+        }
+        __syncthreads();
+        const int b = s_cut;
+        if (b >= 0) {  // uniform
+            for (int e = tid; e < cap - s_base[b]; e += 256) {  // (entries that exist: fewer than the list's capacity)
+                const unsigned j = (unsigned)L.cand[(size_t)b * capc + e] & 255u;
+                atomicOr(&keep[j >> 5], 1u << (j & 31));
+            }
+            __syncthreads();
+            const int c = b * 256 + kseg;
+            const unsigned skip = (keep[kseg >> 5] >> (kseg & 31)) & 0xffu;
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const int r = q * 8 + (tid >> 5);
+                const us8 x = chunk_fix(chunk_load(X + (size_t)(r < s ? r : 0) * h, c, h), c, h);
+                unsigned mx = 0, mn = 0xffffu;
+#pragma unroll
+                for (int e = 0; e < 8; e++)
+                    if (!((skip >> e) & 1u) && c + e < h) {
+                        const unsigned k = ZP ? f16_key(x[e]) : (unsigned)(x[e] & 0x7fff);
+                        mx = k > mx ? k : mx;
+                        mn = k < mn ? k : mn;
+                    }
+#pragma unroll
+                for (int d = 16; d >= 1; d >>= 1) {
+                    const unsigned t1 = (unsigned)__shfl_xor((int)mx, d);
+                    mx = t1 > mx ? t1 : mx;
+                    if constexpr (ZP) {
+                        const unsigned t2 = (unsigned)__shfl_xor((int)mn, d);
+                        mn = t2 < mn ? t2 : mn;
+                    }
+                }
+                if ((tid & 31) == 0 && r < s) {
+                    s_part[NPART - 1][r] = mx;
+                    if constexpr (ZP) s_part_lo[NPART - 1][r] = mn;
+                }
+            }
+        }
+    }
+
     // ---- row constants
-    if (!overflow) {
+    if (MID || !overflow) {
         s_part[tid >> 5][tid & 31] = rp_max;
         if constexpr (ZP) s_part_lo[tid >> 5][tid & 31] = rp_min;
         __syncthreads();
         if (tid < 32) {
             unsigned m2 = 0, m1 = 0xffffu;
 #pragma unroll
-            for (int q = 0; q < 8; q++) {
+            for (int q = 0; q < NPART; q++) {
+                if (q == 8 && !overflow) break;
                 m2 = s_part[q][tid] > m2 ? s_part[q][tid] : m2;
                 if constexpr (ZP) m1 = s_part_lo[q][tid] < m1 ? s_part_lo[q][tid] : m1;
             }
@@ -849,6 +926,23 @@ hipError_t launch_prepass_small(const void* X, int s, int h, unsigned thr, Outli
 // keep the kernels of a longer X, where every workgroup gathers its own rows' columns: here one workgroup per row tile
 // would (64 x 4096 x 4096, cap 300, 200 columns: 216 us with these two, 76 with those).
 // ---------------------------------------------------------------------------
+
+// The larger of two 16-bit values each over the 32 lanes of half a wave, in all of them: four rotations within rows of
+// 16 lanes, then the other row's.  (With five exchanges through LDS one after the other, as __shfl_xor makes them, calls of
+// 33 to 128 tokens take 0.1 to 0.4 us more: 64 x 4096 x 4096 17.06 / 17.29, zeropoint 128 x 1024 x 4096 18.9 / 19.3.)
+__device__ __forceinline__ us2 max32(us2 x)
+{
+#define ROTATE(n)                                                                                                        \
+    x = __builtin_elementwise_max(                                                                                       \
+        x, __builtin_bit_cast(us2, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + (n), 0xf, 0xf, false)))
+    ROTATE(8);
+    ROTATE(4);
+    ROTATE(2);
+    ROTATE(1);
+#undef ROTATE
+    return __builtin_elementwise_max(x, __builtin_bit_cast(us2, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, x), 0x401f)));
+}
+
 template <int RM, bool ZP>
 __global__ void __launch_bounds__(512) scan_mid_kernel(const unsigned short* __restrict__ X, int s, int h, unsigned thr,
                                                        OutlierLists L, int capc, int spad, int4* __restrict__ zc)
@@ -886,50 +980,62 @@ __global__ void __launch_bounds__(512) scan_mid_kernel(const unsigned short* __r
 #pragma unroll
     for (int e = 0; e < 8; e++)
         if (c0 + e < h && (unsigned)mx[e] >= thr) flags |= 1u << e;
-    // partial row maxima over the non-outlier columns, two 16-bit values per register across the 32 lanes of a row
+    // partial row maxima without the columns in `skip`, two 16-bit values per register across the 32 lanes of a row
     // (zeropoint: the key of the largest entry and, inverted, that of the smallest)
-    us2 x[ZP ? RM : RM / 2];
+    auto row_extremes = [&](unsigned skip, unsigned short* o) {
+        typedef short ss2 __attribute__((ext_vector_type(2)));
+        if (ZP && c0 + 8 > h) skip |= c0 < h ? 0xffu << (h - c0) : 0xffu;
+        unsigned use[4];  // the pairs of columns that count
 #pragma unroll
-    for (int m = 0; m < RM; m++) {
-        if constexpr (ZP) {
-            unsigned kmin = 0xffffu, kmax = 0u;
-#pragma unroll
-            for (int e = 0; e < 8; e++)
-                if (!((flags >> e) & 1u) && c0 + e < h) {
-                    const unsigned k = f16_key(v[m][e]);
-                    kmin = k < kmin ? k : kmin;
-                    kmax = k > kmax ? k : kmax;
-                }
-            x[m] = us2{(unsigned short)(0xffffu - kmin), (unsigned short)kmax};
-        } else {
-            us8 a = v[m] & (unsigned short)0x7fff;
-            if (flags) {
-#pragma unroll
-                for (int e = 0; e < 8; e++)
-                    if ((flags >> e) & 1u) a[e] = 0;
-            }
-            x[m >> 1][m & 1] = hmax8(a);
-        }
-    }
-#pragma unroll
-    for (int d = 16; d >= 1; d >>= 1)
-#pragma unroll
-        for (int m = 0; m < (ZP ? RM : RM / 2); m++)
-            x[m] = __builtin_elementwise_max(x[m], __builtin_bit_cast(us2, __shfl_xor(__builtin_bit_cast(int, x[m]), d)));
-    if (c == 0) {
-        unsigned short* o = L.rowpart + (size_t)blockIdx.x * spad;
+        for (int q = 0; q < 4; q++)
+            use[q] = ((skip >> (2 * q)) & 1u ? 0u : 0xffffu) | ((skip >> (2 * q)) & 2u ? 0u : 0xffff0000u);
+        us2 x[ZP ? RM : RM / 2];
 #pragma unroll
         for (int m = 0; m < RM; m++) {
-            const int i = rg + 16 * m;
-            if (i >= spad) continue;
+            const ui4 p = __builtin_bit_cast(ui4, v[m]);
+            us2 hi[4], lo[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const unsigned pair = p[q];  // (a bit cast of p[q] itself takes element 0)
+                if constexpr (ZP) {
+                    const unsigned sign = __builtin_bit_cast(unsigned, __builtin_bit_cast(ss2, pair) >> 15);
+                    const unsigned k = pair ^ (sign | 0x80008000u);  // f16_key() of both
+                    hi[q] = __builtin_bit_cast(us2, k & use[q]);
+                    lo[q] = __builtin_bit_cast(us2, ~k & use[q]);
+                } else {
+                    hi[q] = __builtin_bit_cast(us2, pair & (use[q] & 0x7fff7fffu));
+                }
+            }
+            const us2 a = __builtin_elementwise_max(__builtin_elementwise_max(hi[0], hi[1]), __builtin_elementwise_max(hi[2], hi[3]));
+            const unsigned short mx = a.x > a.y ? a.x : a.y;
             if constexpr (ZP) {
-                o[i] = (unsigned short)(0xffffu - x[m].x);
-                o[(size_t)gridDim.x * spad + i] = x[m].y;
+                const us2 b = __builtin_elementwise_max(__builtin_elementwise_max(lo[0], lo[1]), __builtin_elementwise_max(lo[2], lo[3]));
+                x[m] = us2{b.x > b.y ? b.x : b.y, mx};  // no column: 0 and 0, the keys 0xffff above 0
             } else {
-                o[i] = x[m >> 1][m & 1];
+                x[m >> 1][m & 1] = mx;
             }
         }
-    }
+#pragma unroll
+        for (int m = 0; m < (ZP ? RM : RM / 2); m++) x[m] = max32(x[m]);
+        if (c == 0) {
+#pragma unroll
+            for (int m = 0; m < RM; m++) {
+                const int i = rg + 16 * m;
+                if (i >= spad) continue;
+                if constexpr (ZP) {
+                    o[i] = (unsigned short)(0xffffu - x[m].x);
+                    o[(size_t)gridDim.x * spad + i] = x[m].y;
+                } else {
+                    o[i] = x[m >> 1][m & 1];
+                }
+            }
+        }
+    };
+    row_extremes(flags, L.rowpart + (size_t)blockIdx.x * spad);
+    // Over all columns, for calls in which more columns qualify than the buffer takes and this block's are ordinary again:
+    // without these, every workgroup of the next kernel would scan its rows again whole (128 x 49152 x 2048 with 40 columns
+    // and cap 32: 1 984 us, with them 53).
+    if (__any(flags != 0)) row_extremes(0u, L.rowpart + (size_t)((ZP ? 2 : 1) * gridDim.x + blockIdx.x) * spad);
     if (tid < 32) {  // the list of this workgroup, ascending: lane, then bit
         const int mine = __popc(flags);
         int incl = mine;
@@ -949,9 +1055,9 @@ __global__ void __launch_bounds__(512) scan_mid_kernel(const unsigned short* __r
     }
 }
 
-bool prepass_mid_takes(int s, int h, int cap, size_t room)
+bool prepass_mid_takes(int s, int h, int cap, bool zeropoint, size_t room)
 {
-    return s > 32 && s <= 128 && h >= 8 && cap <= JOB_MAX_CAP && (size_t)4 * ((h + 255) / 256) * ((s + 31) & ~31) <= room;
+    return s > 32 && s <= 128 && h >= 8 && cap <= JOB_MAX_CAP && (size_t)(zeropoint ? 8 : 4) * ((h + 255) / 256) * ((s + 31) & ~31) <= room;
 }
 
 hipError_t launch_prepass_mid(const void* X, int s, int h, unsigned thr, OutlierLists L, int32_t* idx, int cap,
@@ -961,7 +1067,6 @@ hipError_t launch_prepass_mid(const void* X, int s, int h, unsigned thr, Outlier
     const int capc = list_capacity(cap);
     const int KT = k_tiles(h), RT = row_tiles(s), spad = RT * 32;
     const int nscan = (h + 255) / 256, nquant = (KT * 32 + 255) / 256;
-    const size_t shm = ((size_t)(h + 31) / 32) * sizeof(unsigned);
     const ColumnJob job = cj ? *cj : ColumnJob{nullptr, nullptr, nullptr, 0, 0};
     const unsigned short* x = (const unsigned short*)X;
     if (zc) {
@@ -979,10 +1084,10 @@ hipError_t launch_prepass_mid(const void* X, int s, int h, unsigned thr, Outlier
     if (e != hipSuccess) return e;
     const dim3 grid(nquant + job.pitch / 256, RT);
     if (zc)
-        quantize_small_kernel<true, true, true><<<grid, 256, shm, st>>>(x, s, h, L, capc, 1, idx, cap, opad_of(cap), count, status, cx,
+        quantize_small_kernel<true, true, true><<<grid, 256, 0, st>>>(x, s, h, L, capc, 1, idx, cap, opad_of(cap), count, status, cx,
                                                             Xo, Xq, KT, 0, zc, nscan, job);
     else
-        quantize_small_kernel<false, true, true><<<grid, 256, shm, st>>>(x, s, h, L, capc, 1, idx, cap, opad_of(cap), count, status, cx,
+        quantize_small_kernel<false, true, true><<<grid, 256, 0, st>>>(x, s, h, L, capc, 1, idx, cap, opad_of(cap), count, status, cx,
                                                              Xo, Xq, KT, 0, zc, nscan, job);
     return hipGetLastError();
 }

@@ -55,3 +55,13 @@ def test_an_outlier_buffer_above_256_columns_at_128_tokens(zeropoint):
     one workgroup per row tile gathers all columns, 2.1 (zeropoint 2.5)."""
     a, b = (prepare(s, 2048, 64, 2000, 2048, zeropoint) for s in (128, 129))
     assert ratio(a, b) < 1.5
+
+
+@pytest.mark.parametrize("zeropoint", [False, True])
+@pytest.mark.parametrize("s,alpha", [(128, 6.0), (33, 6.0), (128, 0.0)])
+def test_more_outlier_columns_than_the_buffer_takes_at_33_to_128_tokens(s, alpha, zeropoint):
+    """40 columns (alpha = 0: all 16 384) against none, in a buffer of 32: 1.1 to 1.35.  Where every workgroup of the
+    quantizer scans its rows again, 13 to 25."""
+    a = prepare(s, 16384, 64, 40, 32, zeropoint, alpha)
+    b = prepare(s, 16384, 64, 0, 32, zeropoint)
+    assert ratio(a, b) < 3.0

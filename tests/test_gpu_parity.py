@@ -649,6 +649,48 @@ def test_two_kernel_pre_pass_of_33_to_128_tokens(s, h, o, ncol, cap):
         zp.zp_compare(d["X"], d["W"], d["alpha"], cap=cap)
 
 
+@pytest.mark.parametrize("s", [33, 64, 65, 128])
+@pytest.mark.parametrize("h,cap,blocks", [(2048, 5, {1: 3, 3: 4, 6: 2}),  # the buffer ends inside a block of 256 columns
+                                          (2048, 7, {1: 3, 3: 4, 6: 2}),  # ... at the end of one
+                                          (1999, 4, {0: 9}),              # in the only one that has any
+                                          (1999, 2, {7: 5}),              # in the last, ragged one
+                                          (2048, 100, None),              # every column qualifies
+                                          (600, 256, None)])
+def test_33_to_128_tokens_with_more_columns_than_the_buffer_takes(s, h, cap, blocks):
+    """The columns past cap count as ordinary ones, and hold each row's largest values here: in blocks of 256 columns
+    of which the buffer takes all, some or none, against the oracle, absmax and zeropoint."""
+    import torch
+
+    import paper_2208_07339_amd as L
+    o = 40
+    rng = np.random.default_rng(s + h + cap)
+    d = wl.make_custom(s, h, o, 0, seed=s + h + cap)
+    X = d["X"].copy()
+    cols = [256 * b + int(c) for b, n in (blocks or {}).items()
+            for c in rng.choice(min(256, h - 256 * b), n, replace=False)]
+    for c in cols:
+        X[rng.integers(0, s), c] = 20.0 + rng.integers(0, 30)
+        X[:, c] = np.where(rng.random(s) < 0.5, X[:, c], np.float16(-7 - rng.integers(0, 9)))
+    d = dict(d, X=np.ascontiguousarray(X))
+    alpha = 6.0 if blocks else 0.0
+    assert len(oracle.find_outliers(d["X"], alpha)) > cap
+    linear_compare(d, alpha=alpha, cap=cap)
+    # zeropoint: the one call against the staged calls, whose records and codes the zeropoint tests hold against the oracle
+    Xd = torch.from_numpy(d["X"].view(np.int16)).cuda().view(torch.float16)
+    Wd = torch.from_numpy(d["W"].view(np.int16)).cuda().view(torch.float16)
+    ws = L.Workspace.allocate(s, h, o, cap)
+    qw = L.zp_quantize_weight(Wd, ws)
+    outl = L.find_outliers(Xd, alpha, cap, ws)
+    rows = L.zp_quantize_rows(Xd, outl)
+    want = [t.clone() for t in (rows.zc, rows.Xq, rows.Xo, outl.idx, outl.status, L.zp_matmul(rows, outl, qw, ws))]
+    for t in (rows.zc, rows.Xq, rows.Xo, outl.idx):
+        t.fill_(77)
+    out = L.zp_linear(Xd, qw, alpha, outl, rows, ws)
+    assert all(torch.equal(a, b) for a, b in zip(want, (rows.zc, rows.Xq, rows.Xo, outl.idx, outl.status, out)))
+    x = oracle.zp_quantize_rows(d["X"], oracle.find_outliers(d["X"], alpha)[:cap])
+    assert np.array_equal(rows.zc.cpu().numpy()[:, 1], x["zp"]) and np.array_equal(rows.zc.cpu().numpy()[:, 2], x["rowsum"])
+
+
 def test_linear_row_maximum_inside_an_outlier_column():
     """Rows whose largest magnitude below alpha sits in an outlier column (alone, or tied with a regular
     column): the row constant must come from the regular columns only."""
