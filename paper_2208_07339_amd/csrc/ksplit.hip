@@ -9,7 +9,7 @@ typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 
 #define FENCE() __builtin_amdgcn_sched_barrier(0)
 
-constexpr int KSLOTS = 32;  // outlier slots kept in LDS
+constexpr int KSLOTS = 32;  // outlier slots kept in LDS at a time
 
 struct KsplitArgs {
     const int8_t* Wq;
@@ -179,6 +179,62 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
     }
     // this thread's outputs: token il of a tile, columns jl .. jl + 3
     const int il = tid / (8 * NJ), ch = tid % (8 * NJ), jl = 4 * ch, j = J0 + jl;
+    // More outlier columns than fit: their product comes first, a chunk of slots in LDS after the other, the next one's
+    // operands on their way meanwhile.  (Up to 32 tokens, where it comes last, past the first chunk from memory below.)
+    // Calls with 200 columns, 128 x 12288 x 8192: 56 us; with every column's operands from memory for each output 180, with
+    // the tiles of gemm.hip 93.
+    const bool many = s > 32 && cnt > KSLOTS;
+    float od[NI][4];
+#pragma unroll
+    for (int t = 0; t < NI; t++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) od[t][e] = 0.0f;
+    if (many) {  // uniform
+        auto rows_of = [&](int q0) {  // the rows of this thread's slots of a chunk
+#pragma unroll
+            for (int q = 0; q < NS; q++) {
+                const int t = q0 + t0 + q * TPC;
+                kk[q] = a.rows_are_slots ? t : a.idx[t < cnt ? t : 0];
+            }
+        };
+        rows_of(KSLOTS);
+        for (int q0 = 0;; q0 += KSLOTS) {
+            const int q1 = q0 + KSLOTS;
+            if (q1 < cnt) {
+#pragma unroll
+                for (int q = 0; q < NS; q++) {
+                    const unsigned k = (unsigned)kk[q];
+                    const bool ok = k < (unsigned)a.wrows && q1 + t0 + q * TPC < cnt && J0 + jc < o;
+                    wo[q] = a.Wf[(size_t)(ok ? k : 0u) * o + (J0 + jc < o ? J0 + jc : 0)];
+                    if (!ok) wo[q] = 0;
+                }
+                if (tid < 4 * NTK && q1 + xs < a.opad) {
+                    const int i = I0 + (tid >> 2);
+                    xo = *(const us8*)(a.Xo + (size_t)(i < s ? i : s - 1) * a.opad + q1 + xs);
+                }
+                rows_of(q1 + KSLOTS);
+            }
+            __syncthreads();  // the chunk is in LDS
+            const int ns = cnt - q0 < KSLOTS ? cnt - q0 : KSLOTS;
+            if (il < 32)
+                for (int q = 0; q < ns; q++) {
+                    float wf[4];
+#pragma unroll
+                    for (int e = 0; e < 4; e++) wf[e] = f16_bits_to_float(s_wo[q][jl + e]);
+#pragma unroll
+                    for (int t = 0; t < NI; t++) {
+                        const float x = f16_bits_to_float(s_xo[32 * t + il][q]);
+#pragma unroll
+                        for (int e = 0; e < 4; e++) od[t][e] = __builtin_fmaf(x, wf[e], od[t][e]);
+                    }
+                }
+            if (q1 >= cnt) break;
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < NS; q++) s_wo[t0 + q * TPC][jc] = wo[q];
+            if (tid < 4 * NTK) *(us8*)&s_xo[tid >> 2][xs] = xo;
+        }
+    }
     float cwj[4] = {0, 0, 0, 0};
     if constexpr (!ZP) {
 #pragma unroll
@@ -234,13 +290,17 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
 #pragma unroll
                 for (int e = 0; e < 4; e++) d[e] = ZP ? p[e] : p[e] * cwj[e];
             }
-            const int ns = cnt < KSLOTS ? cnt : KSLOTS;
+            if (many) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) d[e] = od[t][e];
+            }
+            const int ns = many ? 0 : cnt < KSLOTS ? cnt : KSLOTS;
             for (int q = 0; q < ns; q++) {
                 const float x = f16_bits_to_float(s_xo[32 * t + il][q]);
 #pragma unroll
                 for (int e = 0; e < 4; e++) d[e] = __builtin_fmaf(x, f16_bits_to_float(s_wo[q][jl + e]), d[e]);
             }
-            for (int q = KSLOTS; q < cnt; q++) {  // more outlier columns than fit: rare
+            for (int q = many ? cnt : KSLOTS; q < cnt; q++) {  // up to 32 tokens, more outlier columns than fit: rare
                 const unsigned k = a.rows_are_slots ? (unsigned)q : (unsigned)a.idx[q];
                 if (k >= (unsigned)a.wrows) continue;
                 const float x = f16_bits_to_float(a.Xo[(size_t)i * a.opad + q]);

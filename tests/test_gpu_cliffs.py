@@ -65,3 +65,22 @@ def test_more_outlier_columns_than_the_buffer_takes_at_33_to_128_tokens(s, alpha
     a = prepare(s, 16384, 64, 40, 32, zeropoint, alpha)
     b = prepare(s, 16384, 64, 0, 32, zeropoint)
     assert ratio(a, b) < 3.0
+
+
+@pytest.mark.parametrize("s,h,o", [(96, 5120, 9000), (128, 12288, 8192)])
+def test_many_outlier_columns_where_k_is_split_over_the_waves(s, h, o):
+    """200 outlier columns, in the kernel that the library chooses against the tiled one: 0.55 to 0.65.  With each
+    column's operands read from memory for every output, 1.9 to 2.9."""
+    import paper_2208_07339_amd as L
+    call = prepare(s, h, o, 200, 256)
+
+    def tiled():
+        L.debug_prefill_tile(3)
+        call()
+        L.debug_prefill_tile(-1)
+
+    try:
+        r = ratio(call, tiled)
+    finally:
+        L.debug_prefill_tile(-1)
+    assert r < 1.3

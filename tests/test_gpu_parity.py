@@ -257,6 +257,19 @@ def test_tiles_with_k_split_over_the_waves(s, h, o, ncol, cap):
         zp.zp_compare(d["X"], d["W"], d["alpha"], cap=cap)
 
 
+@pytest.mark.parametrize("s,h,o,ncol,cap", [(33, 600, 70, 33, 64), (70, 517, 131, 64, 64), (45, 900, 333, 65, 80),
+                                            (64, 1100, 61, 250, 250), (300, 1000, 520, 97, 112)])
+def test_more_than_32_outlier_columns_with_k_split_over_the_waves(s, h, o, ncol, cap):
+    """One to seven chunks of slots past the first, full and part filled, ragged tokens and columns: staged with the
+    accumulators, one-call, zeropoint, and on weights kept as codes."""
+    import test_gpu_zeropoint as zp
+    d = wl.make_custom(s, h, o, ncol, seed=s + h + o, frac=0.3)
+    full_compare(d, cap=cap)
+    linear_compare(d, cap=cap)
+    int8_rows_compare(d, cap=cap, via_linear=True)
+    zp.zp_compare(d["X"], d["W"], d["alpha"], cap=cap)
+
+
 @pytest.mark.parametrize("bad", [-1, 300, 2 ** 31 - 1])
 @pytest.mark.parametrize("s,o", [(300, 264), (300, 261), (20, 264)])
 def test_a_listed_index_that_names_no_row_of_w_adds_nothing(s, o, bad):
