@@ -451,7 +451,10 @@ __device__ __forceinline__ void list_entries(const int* list, int n, F f)
     }
 }
 
-// MID: more than one row tile, a row of workgroups (blockIdx.y) for each
+// MID: more than one row tile, a row of workgroups (blockIdx.y) for each; and the rows of W that a column job rebuilds
+// are split over workgroups too, JOB_SLOTS to each, or a large outlier buffer's would take a column's thread longer than
+// a kernel of their own (64 x 4096 x 4096, cap 256, 200 columns found: 84 -> 32 us).
+constexpr int JOB_SLOTS = 32;
 template <bool ZP, bool MID, bool RAGGED>
 __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned short* __restrict__ X, int s, int h,
                                                              OutlierLists L, int capc, int vec_ok,
@@ -497,7 +500,10 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
             list_entries(L.cand + (size_t)b * capc, m, [&](int e, int j) { s_idx[base + e] = j; });
         }
         __syncthreads();
-        const int j = ((int)blockIdx.x - nquant) * 256 + tid;
+        int jb = (int)blockIdx.x - nquant, first = 0;  // this workgroup's first slot
+        if constexpr (MID && !ZP)
+            for (; jb >= cj.pitch >> 8; jb -= cj.pitch >> 8) first += JOB_SLOTS;
+        const int j = jb * 256 + tid;
         if (j >= cj.pitch) return;
         const int8_t* col = cj.Wq + (size_t)(j >> 5) * KT * TILE_BYTES;  // column j of W: row j & 31 of these tiles
         // codes of column j in outlier rows t0 .. t0+7 (0 and not valid where there is none)
@@ -542,16 +548,17 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
             if (j >= cj.o) return;
             const unsigned cwb = ((const unsigned short*)cj.wconst)[j];
             unsigned short* Wo = (unsigned short*)cj.out;
-            for (int t0 = 0; t0 < cnt; t0 += 8) {
+            const int end = MID && first + JOB_SLOTS < opad ? first + JOB_SLOTS : opad, stop = MID && cnt > end ? end : cnt;
+            for (int t0 = first; t0 < stop; t0 += 8) {
                 int c8[8];
                 bool ok[8];
                 codes8(t0, c8, ok);
 #pragma unroll
                 for (int u = 0; u < 8; u++)
-                    if (t0 + u < cnt)  // the same for every thread: no arithmetic for the empty slots
+                    if (t0 + u < stop)  // the same for every thread: no arithmetic for the empty slots
                         Wo[(size_t)(t0 + u) * cj.o + j] = ok[u] ? dequant_bits(c8[u], cwb) : (unsigned short)0;
             }
-            for (int t = cnt; t < opad; t++) Wo[(size_t)t * cj.o + j] = 0;
+            for (int t = MID && stop < first ? first : stop; t < end; t++) Wo[(size_t)t * cj.o + j] = 0;
         }
         return;
     }
@@ -1082,7 +1089,8 @@ hipError_t launch_prepass_mid(const void* X, int s, int h, unsigned thr, Outlier
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const dim3 grid(nquant + job.pitch / 256, RT);
+    const int parts = zc ? 1 : (opad_of(cap) + JOB_SLOTS - 1) / JOB_SLOTS;
+    const dim3 grid(nquant + job.pitch / 256 * parts, RT);
     if (zc)
         quantize_small_kernel<true, true, true><<<grid, 256, 0, st>>>(x, s, h, L, capc, 1, idx, cap, opad_of(cap), count, status, cx,
                                                             Xo, Xq, KT, 0, zc, nscan, job);

@@ -9,7 +9,7 @@ from paper_2208_07339_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-def prepare(s, h, o, ncol, cap, zeropoint=False, alpha=6.0):
+def prepare(s, h, o, ncol, cap, zeropoint=False, alpha=6.0, fp16_rows=True):
     """-> a call of linear / zp_linear on buffers of its own."""
     import torch
 
@@ -26,6 +26,8 @@ def prepare(s, h, o, ncol, cap, zeropoint=False, alpha=6.0):
         rows = L.ZpRows(Xq, torch.zeros((s, 4), dtype=torch.int32, device="cuda"), Xo, s, h)
         return lambda: L.zp_linear(X, qw, alpha, outl, rows, ws, out)
     qw = L.quantize_weight(W, ws)
+    if not fp16_rows:
+        qw.W = None
     rows = L.QuantizedRows(Xq, torch.zeros(s, dtype=torch.float16, device="cuda"), Xo, s, h)
     return lambda: L.linear(X, qw, alpha, outl, rows, ws, out)
 
@@ -84,3 +86,9 @@ def test_many_outlier_columns_where_k_is_split_over_the_waves(s, h, o):
     finally:
         L.debug_prefill_tile(-1)
     assert r < 1.3
+
+
+def test_many_rows_of_w_rebuilt_at_64_tokens():
+    """200 outlier columns on weights kept as codes only against fp16 rows: 1.05.  With all rows of a column rebuilt by
+    one thread, 2.7."""
+    assert ratio(prepare(64, 4096, 4096, 200, 256, fp16_rows=False), prepare(64, 4096, 4096, 200, 256)) < 1.8

@@ -258,7 +258,7 @@ def test_tiles_with_k_split_over_the_waves(s, h, o, ncol, cap):
 
 
 @pytest.mark.parametrize("s,h,o,ncol,cap", [(33, 600, 70, 33, 64), (70, 517, 131, 64, 64), (45, 900, 333, 65, 80),
-                                            (64, 1100, 61, 250, 250), (300, 1000, 520, 97, 112)])
+                                            (128, 700, 600, 30, 250), (64, 1100, 61, 250, 250), (300, 1000, 520, 97, 112)])
 def test_more_than_32_outlier_columns_with_k_split_over_the_waves(s, h, o, ncol, cap):
     """One to seven chunks of slots past the first, full and part filled, ragged tokens and columns: staged with the
     accumulators, one-call, zeropoint, and on weights kept as codes."""
