@@ -90,6 +90,8 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
         const int i = I0 + tid;
         if constexpr (ZP) zx = a.zp.zcx[i < s ? i : s - 1]; else cx_raw = a.cx[i < s ? i : s - 1];
     }
+    // this thread's outputs: token il of a tile, columns jl .. jl + 3
+    const int il = tid / (8 * NJ), ch = tid % (8 * NJ), jl = 4 * ch, j = J0 + jl;
     if constexpr (ZP) {
         if (tid < NC) {
 #pragma unroll
@@ -110,7 +112,9 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
 #pragma unroll
     for (int t = 0; t < NI; t++) {
         const int rt = tb * NI + t < a.RT ? tb * NI + t : a.RT - 1;
-        xp[t] = (const v4i*)(a.Xq + ((size_t)rt * KT + k0) * TILE_BYTES) + lane;
+        // lane -> token lane % 32 of the tile; for tokens that do not exist the first one again, so that their zeros are not
+        // fetched (unused: nothing is stored for them)
+        xp[t] = (const v4i*)(a.Xq + ((size_t)rt * KT + k0) * TILE_BYTES) + (NI > 1 || 32 * rt + (lane & 31) < s ? lane : lane & 32);
     }
     v16i acc[NJ][NI];
 #pragma unroll
@@ -177,8 +181,6 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
             for (int q = 0; q < 3; q++) s_zc[q][tid] = zc[q];
         }
     }
-    // this thread's outputs: token il of a tile, columns jl .. jl + 3
-    const int il = tid / (8 * NJ), ch = tid % (8 * NJ), jl = 4 * ch, j = J0 + jl;
     // More outlier columns than fit: their product comes first, a chunk of slots in LDS after the other, the next one's
     // operands on their way meanwhile.  (Up to 32 tokens, where it comes last, past the first chunk from memory below.)
     // Calls with 200 columns, 128 x 12288 x 8192: 56 us; with every column's operands from memory for each output 180, with
@@ -189,7 +191,7 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
     for (int t = 0; t < NI; t++)
 #pragma unroll
         for (int e = 0; e < 4; e++) od[t][e] = 0.0f;
-    if (many) {  // uniform
+    if (__builtin_expect(many, 0)) {  // uniform
         auto rows_of = [&](int q0) {  // the rows of this thread's slots of a chunk
 #pragma unroll
             for (int q = 0; q < NS; q++) {
@@ -360,15 +362,17 @@ static const int ks_nj[KS_SHAPES] = {1, 2, 2, 2}, ks_ni[KS_SHAPES] = {1, 1, 2, 3
 // others come here if the estimate says that they gain 8 % with the launch counted (it is within a third of
 // the measured times on 25 products of 33 to 1 094 tokens, and low for these kernels rather than for those).
 // Up to 32 tokens, the weight-streaming kernel keeps every W that gives a quarter of the compute units a column tile
-// (8 x 8192 x 8192 14.2 against 21.4 us); below that 8 waves per column tile pull more than 4: 10 x 9224 x 896 12.1 ->
-// 9.3, 4 x 12288 x 1024 13.0 -> 11.5.
+// (8 x 8192 x 8192 14.2 against 21.4 us).  Below that, 8 waves per column tile pull more than 4 where the tokens are
+// many or K is long; the matmul alone there / here on a W from memory: 32 x 2048 x 2048 7.3 / 7.0 us, 24 x 8192 x 512 12.0 /
+// 11.8, 8 x 8192 x 512 10.2 / 10.5 (from the caches 7.6 to 9.2 / 7.6), 16 x 12288 x 1024 15.2 / 14.7, 3 x 34608 x 512 34.9 /
+// 28.5, but 8 x 4096 x 1024 6.9 / 7.8, 1 x 2048 x 2048 4.8 / 6.2, 16 x 2048 x 512 5.8 / 6.3.
 static int ksplit_shape(int s, int h, int o)
 {
     if (g_decode_cfg.load(std::memory_order_relaxed) >= 0 || g_force_cfg.load(std::memory_order_relaxed) >= 0)
         return -1;  // test hooks: the other kernels
     int cus = 0;
     if (prefill_device_setup(&cus) != hipSuccess) cus = 256;
-    if (s <= 32) return 4 * row_tiles(o) <= cus ? 0 : -1;
+    if (s <= 32) return 4 * row_tiles(o) <= cus && (s > 16 || h >= 8192) ? 0 : -1;
     int cols, toks;
     prefill_tile_size(s, h, o, &cols, &toks);
     if ((long)((o + cols - 1) / cols) * ((s + toks - 1) / toks) >= cus) return -1;
