@@ -341,10 +341,14 @@ static int small_chunks(int s, int h, int cap, int* lg)
 static bool tiled_order(int s, int h, int o) { return !ksplit_takes(s, h, o) && !decode_kernel_takes(s, h, o, false); }
 
 // Where one kernel is the better way, per call against the separate kernels.  Every workgroup repeats the
-// pre-pass, about 1 200 vector instructions per wave at 16 chunks, so its price grows with the chunks and with the
-// workgroups that share a compute unit; what it saves is two launches and two short kernels, 6 to 10 us.
-//   up to 8 chunks, any W: 8 x 256 x 512 10.2 against 15.3 us, 2 x 4096 x 4096 10.2 / 17.0, 1 x 5120 x 20480 18.4 /
-//     29.1, 8 x 2048 x 32768 21.6 / 23.9, 1 x 12288 x 49152 90.9 / 97.9
+// pre-pass, about 1 200 vector instructions per wave at 16 chunks, so its price grows with the chunks, with the tokens and
+// with the workgroups that share a compute unit; what it saves is two launches and two short kernels, 6 to 10 us.
+//   up to 8 chunks, up to two workgroups per compute unit, or up to 8 tokens: 8 x 256 x 512 10.2 against 15.3 us, 2 x 4096 x
+//     4096 10.2 / 17.0, 1 x 5120 x 20480 18.4 / 29.1, 8 x 2048 x 49152 28.9 / 29.6, 32 x 512 x 16384 15.1 / 17.8
+//   more workgroups, 9 to 16 tokens: 16 x 1024 x 20480 16.6 / 19.9 (640 column tiles), 12 x 768 x 49152 26.2 / 31.1 (6
+//     chunks), but 16 x 1024 x 28672 22.2 / 20.7, x 49152 30.2 / 25.9 (8 chunks)
+//   more workgroups, 17 to 32 tokens: 32 x 256 x 49152 28.4 / 32.4 (4 chunks), but 32 x 384 x 32768 26.5 / 23.1, 24 x 400 x 49152
+//     30.5 / 26.3, and 32 x 256 x 28672 18.3 / 16.5, where llmint8_matmul takes the tiled kernel (x 20480 15.7 / 16.3)
 //   9 to 16 chunks: 1 x 32768 x 4096 32.6 / 44.8, 16 x 2048 x 4096 14.3 / 16.6, 8 x 4096 x 12288 18.9 / 21.7 (384 column
 //     tiles), but 1 x 32768 x 16384 94.9 / 92.9 (512) and 32 x 1024 x 32768 35.5 / 27.5 (1 024): taken up to
 //     one and a half workgroups per compute unit
@@ -355,9 +359,12 @@ bool linear_small_takes(int s, int h, int o, int cap)
     const int n = small_chunks(s, h, cap, &lg);
     if (n == 0) return false;
     if (cap > SSLOTS && tiled_order(s, h, o)) return false;
-    if (n <= 8) return true;
     if (prefill_device_setup(&cus) != hipSuccess) cus = 256;
-    return 2 * row_tiles(o) <= 3 * cus;
+    const int JT = row_tiles(o);
+    if (n > 8) return 2 * JT <= 3 * cus;
+    if (JT <= 2 * cus || s <= 8) return true;
+    if (s <= 16) return n <= 6 || 2 * JT <= 5 * cus;
+    return n <= 4 && (2 * JT <= 5 * cus || !tiled_order(s, h, o));
 }
 
 hipError_t launch_linear_small(const void* X, int s, int h, unsigned thr, const int8_t* Wq, const unsigned short* cw,
