@@ -505,47 +505,24 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
             for (; jb >= cj.pitch >> 8; jb -= cj.pitch >> 8) first += JOB_SLOTS;
         const int j = jb * 256 + tid;
         if (j >= cj.pitch) return;
-        const int8_t* col = cj.Wq + (size_t)(j >> 5) * KT * TILE_BYTES;  // column j of W: row j & 31 of these tiles
-        // codes of column j in outlier rows t0 .. t0+7 (0 and not valid where there is none)
-        auto codes8 = [&](int t0, int* q, bool* ok) {
-#pragma unroll
-            for (int u = 0; u < 8; u++) {
-                const unsigned k = (t0 + u < cnt) ? (unsigned)s_idx[t0 + u] : 0xffffffffu;
-                ok[u] = k < (unsigned)h;
-                q[u] = ok[u] ? col[(size_t)(k >> 5) * TILE_BYTES + tile_byte(j & 31, (int)(k & 31))] : 0;
-            }
-        };
         if constexpr (ZP) {
-            // the per-column factors of Eq. 5, as zp_kcol_kernel makes them from idx / count: p = D_w / 254,
-            // q = zp_w p, r = K p, K = (sum of the column's codes outside the outlier rows) + (h - |O|) zp_w;
-            // zero for the padding columns j >= o
-            double p = 0.0, q = 0.0, r = 0.0;
-            if (j < cj.o) {
-                const int4 rec = ((const int4*)cj.wconst)[j];
-                long long sum = rec.z;
-                int used = 0;
-                for (int t0 = 0; t0 < cnt; t0 += 8) {
-                    int c8[8];
-                    bool ok[8];
-                    codes8(t0, c8, ok);
-#pragma unroll
-                    for (int u = 0; u < 8; u++) {
-                        sum -= c8[u];
-                        used += ok[u] ? 1 : 0;
-                    }
-                }
-                p = zp_range((unsigned)rec.x) * (1.0 / 254.0);
-                q = (double)rec.y * p;
-                r = (double)(sum + (long long)(h - used) * rec.y) * p;
-            }
-            double* colc = (double*)cj.out;
-            colc[j] = p;
-            colc[(size_t)cj.pitch + j] = q;
-            colc[2 * (size_t)cj.pitch + j] = r;
+            zp_col_factors(cj.Wq, (const int4*)cj.wconst, h, cj.o, KT, s_idx, cnt, cj.pitch, (double*)cj.out, j);
         } else {
             // the outlier rows of W rebuilt from the codes, as dequant_rows_kernel writes them: slot t holds
             // row idx[t], zeros from |O| to opad
             if (j >= cj.o) return;
+            const int8_t* col = cj.Wq + (size_t)(j >> 5) * KT * TILE_BYTES;  // column j of W: row j & 31 of these tiles
+            // codes of column j in outlier rows t0 .. t0+7, requested without conditions so that they are in flight together
+            // (a slot past the count or with an index that does not exist reads some other row and is not valid)
+            auto codes8 = [&](int t0, int* q, bool* ok) {
+#pragma unroll
+                for (int u = 0; u < 8; u++) {
+                    const unsigned k = (unsigned)s_idx[t0 + u < cnt ? t0 + u : 0];
+                    ok[u] = t0 + u < cnt && k < (unsigned)h;
+                    const unsigned kk = k < (unsigned)h ? k : 0u;
+                    q[u] = col[(size_t)(kk >> 5) * TILE_BYTES + tile_byte(j & 31, (int)(kk & 31))];
+                }
+            };
             const unsigned cwb = ((const unsigned short*)cj.wconst)[j];
             unsigned short* Wo = (unsigned short*)cj.out;
             const int end = MID && first + JOB_SLOTS < opad ? first + JOB_SLOTS : opad, stop = MID && cnt > end ? end : cnt;

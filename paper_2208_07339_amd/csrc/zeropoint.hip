@@ -22,47 +22,6 @@ typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 // f16_key / key_f16, zp_u / zp_u_rcp and make_const live in common.h (the short-X pre-pass uses them too).
 
 // ---------------------------------------------------------------------------
-// The per-column factors of Eq. 5 for column j, three planes of `pitch` doubles (see zp_kcol_kernel, which
-// documents them).  idx[0 .. cnt): the outlier set, in global memory or in LDS.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void zp_col_factors(const int8_t* __restrict__ Wq, const int4* __restrict__ zcw, int h, int o,
-                                               int KT, const int32_t* idx, int cnt, int pitch,
-                                               double* __restrict__ colc, int j)
-{
-    double p = 0.0, q = 0.0, r = 0.0;
-    if (j < o) {
-        const int4 rec = zcw[j];
-        long long sum = rec.z;
-        int used = 0;
-        // eight codes per pass, requested without conditions so that they are in flight together (a slot past the
-        // count or with an index that does not exist reads row 0 and is skipped)
-        for (int t0 = 0; t0 < cnt; t0 += 8) {
-            int8_t q[8];
-            bool ok[8];
-#pragma unroll
-            for (int u = 0; u < 8; u++) {
-                const unsigned k = (unsigned)idx[t0 + u < cnt ? t0 + u : 0];
-                ok[u] = t0 + u < cnt && k < (unsigned)h;
-                const unsigned kk = ok[u] ? k : 0u;
-                q[u] = Wq[((size_t)(j >> 5) * KT + (kk >> 5)) * TILE_BYTES + tile_byte(j & 31, (int)(kk & 31))];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; u++)
-                if (ok[u]) {
-                    sum -= q[u];
-                    used++;
-                }
-        }
-        p = zp_range((unsigned)rec.x) * (1.0 / 254.0);
-        q = (double)rec.y * p;
-        r = (double)(sum + (long long)(h - used) * rec.y) * p;
-    }
-    colc[j] = p;
-    colc[(size_t)pitch + j] = q;
-    colc[2 * (size_t)pitch + j] = r;
-}
-
-// ---------------------------------------------------------------------------
 // Hidden states.  One workgroup per row: range over the non-outlier columns,
 // constants, and the gathered outlier columns Xo (as row_absmax_kernel).
 // LISTS: the outlier set comes straight from the column lists of the scan

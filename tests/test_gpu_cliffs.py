@@ -123,3 +123,10 @@ def test_few_features_of_many_tokens_against_a_wide_w(s, h, o):
     finally:
         L.debug_decode_shape(-1)
     assert r < 1.15
+
+
+def test_many_column_factors_at_128_tokens():
+    """Zeropoint, 200 outlier columns against a wide W, 128 against 129 tokens: 0.88.  With the factors in a loop whose
+    loads waited for one another, 1.28."""
+    a, b = (prepare(s, 8192, 28672, 200, 256, zeropoint=True) for s in (128, 129))
+    assert ratio(a, b) < 1.1
