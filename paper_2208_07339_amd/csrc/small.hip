@@ -345,10 +345,11 @@ static bool tiled_order(int s, int h, int o) { return !ksplit_takes(s, h, o) && 
 // with the workgroups that share a compute unit; what it saves is two launches and two short kernels, 6 to 10 us.
 //   up to 8 chunks, up to two workgroups per compute unit, or up to 8 tokens: 8 x 256 x 512 10.2 against 15.3 us, 2 x 4096 x
 //     4096 10.2 / 17.0, 1 x 5120 x 20480 18.4 / 29.1, 8 x 2048 x 49152 28.9 / 29.6, 32 x 512 x 16384 15.1 / 17.8
-//   more workgroups, 9 to 16 tokens: 16 x 1024 x 20480 16.6 / 19.9 (640 column tiles), 12 x 768 x 49152 26.2 / 31.1 (6
-//     chunks), but 16 x 1024 x 28672 22.2 / 20.7, x 49152 30.2 / 25.9 (8 chunks)
-//   more workgroups, 17 to 32 tokens: 32 x 256 x 49152 28.4 / 32.4 (4 chunks), but 32 x 384 x 32768 26.5 / 23.1, 24 x 400 x 49152
-//     30.5 / 26.3, and 32 x 256 x 28672 18.3 / 16.5, where llmint8_matmul takes the tiled kernel (x 20480 15.7 / 16.3)
+//   more workgroups, where llmint8_matmul takes the tiled kernel: 16 x 1024 x 20480 16.6 / 19.9 (640 column tiles), 16 x 512 x
+//     28672 16.3 / 17.3 (4 chunks), but 16 x 1024 x 28672 22.2 / 20.7, 32 x 384 x 28672 23.2 / 16.6, 32 x 512 x 20480 17.7 / 16.9
+//   more workgroups, where it takes the weight-streaming kernel: as long as K is too short for a full batch of loads there:
+//     12 x 768 x 49152 26.2 / 31.1, 16 x 896 x 36864 24.6 / 31.3, 32 x 384 x 36864 28.9 / 31.0, but 16 x 1024 x 49152 30.2 / 25.9,
+//     32 x 512 x 40960 30.5 / 28.4, and with its two full rounds of 2 x 4 tiles 32 x 384 x 32768 26.5 / 23.1
 //   9 to 16 chunks: 1 x 32768 x 4096 32.6 / 44.8, 16 x 2048 x 4096 14.3 / 16.6, 8 x 4096 x 12288 18.9 / 21.7 (384 column
 //     tiles), but 1 x 32768 x 16384 94.9 / 92.9 (512) and 32 x 1024 x 32768 35.5 / 27.5 (1 024): taken up to
 //     one and a half workgroups per compute unit
@@ -363,8 +364,10 @@ bool linear_small_takes(int s, int h, int o, int cap)
     const int JT = row_tiles(o);
     if (n > 8) return 2 * JT <= 3 * cus;
     if (JT <= 2 * cus || s <= 8) return true;
-    if (s <= 16) return n <= 6 || 2 * JT <= 5 * cus;
-    return n <= 4 && (2 * JT <= 5 * cus || !tiled_order(s, h, o));
+    if (tiled_order(s, h, o)) return 2 * JT <= 5 * cus ? s <= 16 || n <= 4 : s <= 16 && n <= 4;
+    const int kq = k_tiles(h) / 4;  // k-tiles per wave there
+    if (s <= 16) return kq < 8;
+    return JT > 4 * cus ? kq < 4 : n <= 4;
 }
 
 hipError_t launch_linear_small(const void* X, int s, int h, unsigned thr, const int8_t* Wq, const unsigned short* cw,
