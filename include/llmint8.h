@@ -243,24 +243,36 @@ int llmint8_probe_mfma(const int8_t *A_tiles, size_t a_bytes, const int8_t *B_ti
                        int32_t *sink, double *ops, llmint8_stream_t stream);
 int llmint8_probe_read(const void *buf, size_t bytes, int32_t *sink, llmint8_stream_t stream);
 
-/* Test/support: force the workgroup tile of the prefill GEMM (output columns x tokens):
+/* Test/support: force the workgroup tile of the tiled kernel (output columns x tokens):
  * 0 = 256 x 256, 1 = 192 x 256, 2 = 128 x 256, 3 = 128 x 128, 4 = 192 x 128, 5 = 192 x 64; -1 = choose
  * from the shape (default).
- * Process-wide; results do not depend on it.                                  */
+ * Process-wide.  Any tile gives the same bits.  While one is forced, products that the library gives to the
+ * kernel that splits K over the waves go to the tiled or the weight-streaming kernel instead: the last fp16 bit
+ * of their outputs may differ from the default's (see llmint8_matmul).                       */
 #define LLMINT8_PREFILL_TILES 6
 int llmint8_debug_prefill_tile(int cfg);
-/* Test/support: the tile (0 .. LLMINT8_PREFILL_TILES - 1) the library chooses by itself for a product of
- * [s x h] by [h x o]; -1 for a dimension < 1.  Host arithmetic only: needs no GPU.             */
+/* Test/support: the tile (0 .. LLMINT8_PREFILL_TILES - 1) the tiled kernel has for a product of
+ * [s x h] by [h x o], whether or not the library gives the product to that kernel (llmint8_debug_kernel_for);
+ * -1 for a dimension < 1.  Host arithmetic only: needs no GPU.                               */
 int llmint8_debug_prefill_tile_for(int s, int h, int o);
 
 /* Test/support: force the work split of the decode kernel (column tiles per workgroup, k-tiles per
  * load batch): 1 = 1 x 8, 2 = 2 x 4, 3 = 2 x 8, 4 = 3 x 4, 5 = 1 x 4; 0 = no weight-streaming kernel at all
  * (every token count through the tiled kernel); -1 = not forced (1 x 8; 2 x 4 above 16 tokens when W has
  * enough column tiles to fill the chip that way; the tiled kernel where the shape of W suits it better).
- * Anything else is LLMINT8_INVALID_ARG.  Process-wide; results do not depend on the work split (0 moves
- * short X to the other kernel: see llmint8_matmul).                                */
+ * Anything else is LLMINT8_INVALID_ARG.  Process-wide; results do not depend on the work split.  Any value but -1
+ * also switches off, for every token count, the kernel that splits K over the waves and the one-kernel calls of
+ * llmint8_linear*: their products go to the two other kernels, and the last fp16 bit of an output may differ
+ * from the default's (see llmint8_matmul).                                                   */
 #define LLMINT8_DECODE_SHAPES 5
 int llmint8_debug_decode_shape(int cfg);
+
+/* Test/support: the kernel that the matmul calls give a product of [s x h] by [h x o] to, with the hooks above as
+ * they are set: LLMINT8_KERNEL_TILED, LLMINT8_KERNEL_STREAMING, or LLMINT8_KERNEL_KSPLIT + q for the kernel that
+ * splits K over the waves, with tiles of 32 x 32, 64 x 32, 64 x 64, 64 x 96 (columns x tokens) for q = 0 .. 3;
+ * -1 for a dimension < 1.  Without a GPU, the answer for 256 compute units.                   */
+enum { LLMINT8_KERNEL_TILED = 0, LLMINT8_KERNEL_STREAMING = 1, LLMINT8_KERNEL_KSPLIT = 2 };
+int llmint8_debug_kernel_for(int s, int h, int o, int zeropoint);
 
 /* Test/support: private layouts -> plain row-major int8 ([h x o], [s x h]). */
 int llmint8_export_weight(const int8_t *Wq, int h, int o, int8_t *W_i8_rowmajor, llmint8_stream_t stream);

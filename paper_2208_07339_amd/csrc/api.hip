@@ -517,6 +517,14 @@ int llmint8_debug_prefill_tile_for(int s, int h, int o)
     return pick_cfg(s, h, o);
 }
 
+int llmint8_debug_kernel_for(int s, int h, int o, int zeropoint)
+{
+    if (s < 1 || h < 1 || o < 1) return -1;
+    const int shape = ksplit_shape(s, h, o);
+    if (shape >= 0) return LLMINT8_KERNEL_KSPLIT + shape;
+    return decode_kernel_takes(s, h, o, zeropoint != 0) ? LLMINT8_KERNEL_STREAMING : LLMINT8_KERNEL_TILED;
+}
+
 int llmint8_debug_decode_shape(int cfg)
 {
     if (cfg < -1 || cfg > LLMINT8_DECODE_SHAPES) return LLMINT8_INVALID_ARG;

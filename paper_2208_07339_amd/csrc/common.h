@@ -473,8 +473,10 @@ bool linear_small_takes(int s, int h, int o, int cap);
 hipError_t launch_linear_small(const void* X, int s, int h, unsigned thr, const int8_t* Wq, const unsigned short* cw,
                                const unsigned short* Wf, int o, int32_t* idx, int cap, int32_t* count, int32_t* status,
                                int8_t* Xq, unsigned short* cx, unsigned short* Xo, unsigned short* Out, hipStream_t st);
-// tiles of 32 to 64 columns, K split over the waves of a workgroup (ksplit.hip), for the sizes ksplit_takes() says
-bool ksplit_takes(int s, int h, int o);
+// tiles of 32 to 64 columns, K split over the waves of a workgroup (ksplit.hip): which of its tile shapes a product
+// takes, -1: none
+int ksplit_shape(int s, int h, int o);
+inline bool ksplit_takes(int s, int h, int o) { return ksplit_shape(s, h, o) >= 0; }
 hipError_t launch_gemm_ksplit(const int8_t* Xq, const unsigned short* cx, const unsigned short* Xo,
                               const int32_t* count, int cap, const int8_t* Wq, const unsigned short* cw,
                               const unsigned short* Wf, int rows_are_slots, const int32_t* idx, int s, int h, int o,

@@ -327,14 +327,15 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
     }
 }
 
-template <int NJ, int NI, int R>
+// R, RZ: k-tiles in flight per wave, absmax and zeropoint
+template <int NJ, int NI, int R, int RZ>
 static hipError_t launch(KsplitArgs& a, bool zp, hipStream_t st)
 {
     a.nP = (a.JT + NJ - 1) / NJ;
     a.nQ = (a.RT + NI - 1) / NI;
     const int grid = a.nP * a.nQ;
     if (zp)
-        gemm_ksplit_kernel<NJ, NI, R, true><<<grid, 512, 0, st>>>(a);
+        gemm_ksplit_kernel<NJ, NI, RZ, true><<<grid, 512, 0, st>>>(a);
     else
         gemm_ksplit_kernel<NJ, NI, R, false><<<grid, 512, 0, st>>>(a);
     return hipGetLastError();
@@ -366,7 +367,7 @@ static const int ks_nj[KS_SHAPES] = {1, 2, 2, 2}, ks_ni[KS_SHAPES] = {1, 1, 2, 3
 // many or K is long; the matmul alone there / here on a W from memory: 32 x 2048 x 2048 7.3 / 7.0 us, 24 x 8192 x 512 12.0 /
 // 11.8, 8 x 8192 x 512 10.2 / 10.5 (from the caches 7.6 to 9.2 / 7.6), 16 x 12288 x 1024 15.2 / 14.7, 3 x 34608 x 512 34.9 /
 // 28.5, but 8 x 4096 x 1024 6.9 / 7.8, 1 x 2048 x 2048 4.8 / 6.2, 16 x 2048 x 512 5.8 / 6.3.
-static int ksplit_shape(int s, int h, int o)
+int ksplit_shape(int s, int h, int o)
 {
     if (g_decode_cfg.load(std::memory_order_relaxed) >= 0 || g_force_cfg.load(std::memory_order_relaxed) >= 0)
         return -1;  // test hooks: the other kernels
@@ -391,8 +392,6 @@ static int ksplit_shape(int s, int h, int o)
     return shape;
 }
 
-bool ksplit_takes(int s, int h, int o) { return ksplit_shape(s, h, o) >= 0; }
-
 hipError_t launch_gemm_ksplit(const int8_t* Xq, const unsigned short* cx, const unsigned short* Xo,
                               const int32_t* count, int cap, const int8_t* Wq, const unsigned short* cw,
                               const unsigned short* Wf, int rows_are_slots, const int32_t* idx, int s, int h, int o,
@@ -402,10 +401,10 @@ hipError_t launch_gemm_ksplit(const int8_t* Xq, const unsigned short* cx, const 
                     rows_are_slots ? opad_of(cap) : h, idx, Xo, count, cap, opad_of(cap), (_Float16*)Out, Cdbg, s, h, o,
                     zp ? *zp : ZpArgs{nullptr, nullptr, 0}};
     switch (ksplit_shape(s, h, o)) {
-        case 0: return launch<1, 1, 8>(a, zp, st);
-        case 1: return zp ? launch<2, 1, 5>(a, zp, st) : launch<2, 1, 6>(a, zp, st);  // two workgroups per compute unit
-        case 2: return launch<2, 2, 6>(a, zp, st);
-        case 3: return launch<2, 3, 4>(a, zp, st);
+        case 0: return launch<1, 1, 8, 8>(a, zp, st);
+        case 1: return launch<2, 1, 6, 5>(a, zp, st);  // two workgroups per compute unit
+        case 2: return launch<2, 2, 6, 6>(a, zp, st);
+        case 3: return launch<2, 3, 4, 4>(a, zp, st);
     }
     return hipErrorInvalidValue;
 }

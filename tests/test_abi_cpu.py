@@ -103,6 +103,27 @@ def test_tile_choice_of_the_prefill_gemm(lib):
     assert f(0, 4, 4) == -1 and f(4, 4, -1) == -1
 
 
+def test_kernel_choice_of_the_matmul_calls(lib):
+    """Host logic, as on 256 compute units: 0 = tiled, 1 = weight-streaming, 2 + q = K split over the waves."""
+    import paper_2208_07339_amd as L
+    f = L.debug_kernel_for
+    assert f(4096, 5120, 20480) == f(2048, 49152, 12288) == f(2048, 4096, 4096) == 0
+    assert f(16, 12288, 49152) == f(16, 12288, 49152, True) == 1
+    assert f(33, 12288, 49152) == 1 and f(33, 12288, 49152, True) == 0
+    assert f(16, 5120, 20480) == 0  # two to four column tiles per compute unit
+    assert [f(64, 4096, 4096), f(300, 3000, 1000), f(128, 3000, 5000), f(96, 5120, 9000)] == [2, 3, 4, 5]
+    assert f(8, 4096, 1024) == 1 and f(16, 12288, 1024) == 2
+    assert f(0, 4, 4) == -1 and f(4, 4, -1) == -1
+    try:  # each hook switches K split off
+        assert lib.llmint8_debug_decode_shape(0) == 0 and f(64, 4096, 4096) == 0 and f(20, 3000, 1000) == 0
+        assert lib.llmint8_debug_decode_shape(1) == 0 and f(64, 4096, 4096) == 0 and f(20, 3000, 1000) == 1
+        assert lib.llmint8_debug_decode_shape(-1) == 0 and lib.llmint8_debug_prefill_tile(3) == 0
+        assert f(64, 4096, 4096) == 0 and f(20, 3000, 1000) == 1
+    finally:
+        lib.llmint8_debug_decode_shape(-1)
+        lib.llmint8_debug_prefill_tile(-1)
+
+
 def test_benchmark_shapes_fit_the_static_scratch(lib):
     import paper_2208_07339_amd as L
     from paper_2208_07339_amd import workloads as wl
