@@ -41,6 +41,22 @@ def run_hip(X, W, alpha, cap, want_c=True, qw=None):
     )
 
 
+class through:
+    """with through(kernel): the products go to that kernel, "tiled" or "streaming" (weight-streaming: up to 32 tokens, or
+    up to 48 against a wide W), or where the library sends them (None)."""
+
+    def __init__(self, kernel):
+        self.cfg = {None: -1, "tiled": 0, "streaming": 1}[kernel]
+
+    def __enter__(self):
+        import paper_2208_07339_amd as L
+        L.debug_decode_shape(self.cfg)
+
+    def __exit__(self, *exc):
+        import paper_2208_07339_amd as L
+        L.debug_decode_shape(-1)
+
+
 def hip_weight_i8(qw):
     import paper_2208_07339_amd as L
     return L.export_weight(qw).cpu().numpy()

@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 from paper_2208_07339_amd import workloads as wl
-from gpu_util import assert_out_close, bits, hip_weight_i8, run_hip
+from gpu_util import assert_out_close, bits, hip_weight_i8, run_hip, through
 
 pytestmark = pytest.mark.gpu
 
@@ -131,14 +131,22 @@ def test_workgroups_walk_full_and_ragged_tiles_in_turn(cfg, s, forced_tile):
     assert_out_close(g["Out"][ri, ci], Os, scale)
 
 
-@pytest.mark.parametrize("s,o", [(8, 64), (40, 96), (300, 264)])
-def test_accumulator_at_the_int32_bound(s, o):
+@pytest.mark.parametrize("s,o,kernel", [(8, 64, "streaming"), (8, 64, "tiled"), (8, 64, None), (40, 96, "tiled"), (40, 96, None),
+                                        (300, 264, "tiled"), (300, 264, None)])
+def test_accumulator_at_the_int32_bound(s, o, kernel):
     """Section 2.1: the int8 products are accumulated as 32-bit integers.  At the largest feature dimension
     the library accepts (h = 133 144) with every code at +-127 the accumulator reaches h * 127^2 =
-    2 147 479 576 = 2^31 - 4 072: weight-streaming path (s = 8) and tiled path (s = 40, 300), k-tile padding
-    included, and the dequantization of a value that large."""
+    2 147 479 576 = 2^31 - 4 072: weight-streaming kernel (s = 8), tiled kernel, and the kernel that splits K over the
+    waves, which the library takes for all three; k-tile padding included, and the dequantization of a value that
+    large."""
+    with through(kernel):
+        accumulator_at_the_int32_bound(s, o, {None: 2, "streaming": 1, "tiled": 0}[kernel])
+
+
+def accumulator_at_the_int32_bound(s, o, kernel):
     import paper_2208_07339_amd as L
     h = 133144
+    assert L.debug_kernel_for(s, h, o) == kernel
     X = np.full((s, h), 1.0, np.float16)
     X[1::2] = -0.5                                   # odd tokens: codes -127, constant 0.5
     W = np.full((h, o), 0.25, np.float16)
@@ -247,7 +255,7 @@ def test_short_x_goes_to_the_tiled_kernel_where_w_has_two_to_four_column_tiles_p
 def test_tiles_with_k_split_over_the_waves(s, h, o, ncol, cap):
     """Every tile shape of the kernel for products that do not fill the chip, with ragged tokens, columns and K
     (fewer k-tiles than waves among them), up to and above 32 outlier columns: staged with the accumulators, one-call,
-    zeropoint, and on weights kept as codes."""
+    and the smaller ones zeropoint and on weights kept as codes (those forms of the larger shapes: the next test)."""
     import test_gpu_zeropoint as zp
     d = wl.make_custom(s, h, o, ncol, seed=s + h + o)
     full_compare(d, cap=cap)
@@ -255,6 +263,20 @@ def test_tiles_with_k_split_over_the_waves(s, h, o, ncol, cap):
     if s * h * o < 10 ** 9:
         int8_rows_compare(d, cap=cap)
         zp.zp_compare(d["X"], d["W"], d["alpha"], cap=cap)
+
+
+@pytest.mark.parametrize("shape,s,h,o,ncol,cap", [(0, 20, 3000, 1000, 5, 32), (0, 45, 1000, 700, 20, 32), (1, 260, 1501, 1903, 33, 48),
+                                                  (1, 43, 112, 4909, 4, 32), (2, 100, 2900, 6001, 7, 32), (2, 128, 3000, 5000, 40, 48),
+                                                  (3, 65, 4189, 8789, 9, 32), (3, 95, 5001, 9003, 40, 48)])
+def test_every_tile_shape_with_k_split_in_its_zeropoint_and_codes_only_forms(shape, s, h, o, ncol, cap):
+    """Tiles of 32 x 32, 64 x 32, 64 x 64 and 64 x 96 (columns x tokens), ragged in every direction, up to and above 32
+    outlier columns: the zeropoint form stage by stage against the oracle, the rows of W rebuilt from the codes."""
+    import paper_2208_07339_amd as L
+    import test_gpu_zeropoint as zp
+    assert L.debug_kernel_for(s, h, o) == L.debug_kernel_for(s, h, o, True) == 2 + shape
+    d = wl.make_custom(s, h, o, ncol, seed=s + h + o)
+    zp.zp_compare(zp.one_sided(d), d["W"], d["alpha"], cap=cap)
+    int8_rows_compare(d, cap=cap, via_linear=True)
 
 
 @pytest.mark.parametrize("s,h,o,ncol,cap", [(33, 600, 70, 33, 64), (70, 517, 131, 64, 64), (45, 900, 333, 65, 80),
@@ -620,6 +642,19 @@ def test_linear_prefill_branches_of_the_prepass():
     linear_compare(d)
 
 
+def test_linear_prefill_branches_of_the_prepass_above_128_tokens():
+    """The same branches where 128 tokens and fewer have a pre-pass of their own: more columns than the row constants'
+    list in LDS holds (with and without overflow), overflow, a ragged h, a full list of 256 columns."""
+    linear_compare(wl.make_custom(140, 2048, 64, 3, seed=81), alpha=0.0, cap=2048)
+    linear_compare(wl.make_custom(140, 2048, 64, 3, seed=82), alpha=0.0, cap=1500)
+    linear_compare(wl.make_custom(150, 600, 64, 300, seed=46, frac=0.3), cap=300)
+    linear_compare(wl.make_custom(170, 384, 96, 9, seed=44), cap=4)
+    linear_compare(wl.make_custom(133, 333, 64, 9, seed=52), cap=4)
+    linear_compare(wl.make_custom(131, 96, 64, 2, seed=45), alpha=0.0, cap=96)
+    linear_compare(wl.make_custom(129, 8, 16, 1, seed=50))
+    linear_compare(wl.make_custom(140, 300, 64, 0, seed=47))
+
+
 @pytest.mark.parametrize("s,h,o", [(33, 8, 40), (40, 9, 33), (35, 15, 64), (64, 505, 31), (100, 511, 65), (129, 513, 520),
                                    (70, 519, 263), (20, 1023, 77), (31, 2049, 90), (50, 8201, 43)])
 def test_rows_and_columns_that_do_not_start_on_16_bytes(s, h, o):
@@ -704,13 +739,14 @@ def test_33_to_128_tokens_with_more_columns_than_the_buffer_takes(s, h, cap, blo
     assert np.array_equal(rows.zc.cpu().numpy()[:, 1], x["zp"]) and np.array_equal(rows.zc.cpu().numpy()[:, 2], x["rowsum"])
 
 
-def test_linear_row_maximum_inside_an_outlier_column():
+@pytest.mark.parametrize("s,h", [(200, 1024), (200, 1021), (100, 1021)])
+def test_linear_row_maximum_inside_an_outlier_column(s, h):
     """Rows whose largest magnitude below alpha sits in an outlier column (alone, or tied with a regular
     column): the row constant must come from the regular columns only."""
-    d = wl.make_custom(200, 1024, 128, 4, seed=51)
+    d = wl.make_custom(s, h, 128, 4, seed=51)
     X = d["X"]
     j0, j1 = int(d["planted"][0]), int(d["planted"][-1])
-    free = [j for j in range(1024) if j not in set(d["planted"].tolist())]
+    free = [j for j in range(h) if j not in set(d["planted"].tolist())]
     quiet = np.nonzero(np.abs(X[:, j0].astype(np.float32)) < 6.0)[0]
     assert len(quiet) >= 20
     X[quiet[:10], j0] = np.float16(5.5)            # alone at the top of the row
@@ -720,7 +756,7 @@ def test_linear_row_maximum_inside_an_outlier_column():
     X[quiet[15:20], j0] = np.float16(5.9)          # two outlier columns share it
     linear_compare(d)
     linear_compare(d, cap=2)                        # ... and with the columns beyond cap counted as regular
-    linear_compare(wl.make_custom(64, 333, 64, 3, seed=52))   # h not a multiple of 8: the three-pass pre-pass
+    linear_compare(wl.make_custom(64, 333, 64, 3, seed=52))
 
 
 def test_linear_short_x_degenerate_cases():
@@ -848,9 +884,12 @@ def test_argument_errors_are_reported_not_executed():
         L.binding._check(3)
 
 
-def test_random_shapes_through_the_one_call_path():
+@pytest.mark.parametrize("kernel", [None, "streaming", "tiled"])
+def test_random_shapes_through_the_one_call_path(kernel):
     """Seeded random shapes on both sides of the 32-token split, aligned and ragged, with random outlier
-    counts, capacities (some too small) and thresholds: llmint8_linear against the oracle, stage by stage."""
+    counts, capacities (some too small) and thresholds: llmint8_linear against the oracle, stage by stage, through the
+    kernels that the library chooses (K split over the waves and the one-kernel call, most of them) and the two others
+    (streaming: above 32 tokens the tiled one)."""
     rng = np.random.default_rng(20240607)
     for case in range(24):
         s = int(rng.choice([rng.integers(1, 33), rng.integers(33, 400)]))
@@ -861,7 +900,8 @@ def test_random_shapes_through_the_one_call_path():
         alpha = float(rng.choice([6.0, 6.0, 4.5, 9.0]))
         d = wl.make_custom(s, h, o, ncol, seed=1000 + case)
         try:
-            linear_compare(d, alpha=alpha, cap=cap)
+            with through(kernel):
+                linear_compare(d, alpha=alpha, cap=cap)
         except AssertionError as e:
             raise AssertionError(f"case {case}: s={s} h={h} o={o} ncol={ncol} cap={cap} alpha={alpha}: {e}") from e
 

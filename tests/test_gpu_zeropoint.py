@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_2208_07339_amd import workloads as wl
-from gpu_util import assert_out_close, bits
+from gpu_util import assert_out_close, bits, through
 
 pytestmark = pytest.mark.gpu
 
@@ -85,18 +85,33 @@ def one_sided(d, shift=0.0):
     return np.ascontiguousarray(X.astype(np.float16))
 
 
-SHAPES = [(8, 256, 512, 2), (16, 1024, 2048, 5), (13, 200, 61, 2), (32, 4160, 96, 6),   # weight-streaming path
-          (33, 64, 32, 1), (100, 300, 200, 3), (256, 1024, 512, 4), (333, 520, 260, 5),  # tiled path
-          (48, 1000, 264, 4), (64, 384, 96, 7)]                       # ... with two row tiles of X
+SHORT = [(8, 256, 512, 2), (16, 1024, 2048, 5), (13, 200, 61, 2), (32, 4160, 96, 6)]
+LONG = [(33, 64, 32, 1), (100, 300, 200, 3), (256, 1024, 512, 4), (333, 520, 260, 5),
+        (48, 1000, 264, 4), (64, 384, 96, 7)]  # the last two: two row tiles of X
+SHAPES = [c + (k,) for c in SHORT for k in (None, "streaming", "tiled")] + [c + (k,) for c in LONG for k in (None, "tiled")]
 
 
 @pytest.mark.parametrize("alpha", [6.0, INF])
-@pytest.mark.parametrize("s,h,o,ncol", SHAPES)
-def test_zeropoint_on_one_sided_inputs(s, h, o, ncol, alpha):
+@pytest.mark.parametrize("s,h,o,ncol,kernel", SHAPES)
+def test_zeropoint_on_one_sided_inputs(s, h, o, ncol, kernel, alpha):
+    """Through the kernel that the library chooses (weight-streaming, or K split over the waves), and through the two that
+    can be forced."""
     d = wl.make_custom(s, h, o, ncol, seed=5 * s + h)
-    ref = zp_compare(one_sided(d), d["W"], alpha)
+    with through(kernel):
+        ref = zp_compare(one_sided(d), d["W"], alpha)
     if alpha == 6.0:
         assert (ref["zp_x"] != 0).all()  # these rows are far from symmetric
+
+
+@pytest.mark.parametrize("s,h,o,ncol,cap", [(20, 520, 4100, 20, 32), (7, 300, 2333, 40, 48), (32, 1111, 9000, 5, 32),
+                                            (1, 97, 2113, 0, 16), (24, 384, 33001, 17, 32)])
+def test_the_weight_streaming_kernel_by_the_librarys_own_choice(s, h, o, ncol, cap):
+    """Ragged column tiles and K, no outlier column, more than the kernel fetches before the stream (16), and the two
+    column tiles per workgroup of a wide W."""
+    import paper_2208_07339_amd as L
+    assert L.debug_kernel_for(s, h, o, True) == 1
+    d = wl.make_custom(s, h, o, ncol, seed=s + o)
+    zp_compare(one_sided(d), d["W"], 6.0, cap=cap)
 
 
 @pytest.mark.parametrize("cfg", [0, 1, 2, 3, 4, 5])
@@ -257,19 +272,19 @@ def test_more_outlier_columns_than_cap():
     assert_out_close(out.cpu().numpy().reshape(-1), Os)
 
 
-@pytest.mark.parametrize("s", [12, 70])
+@pytest.mark.parametrize("s", [12, 70, 150])
 def test_one_call_with_an_outlier_buffer_too_large_for_the_column_job(s):
     """cap > 256: the per-column factors come from zp_kcol_kernel as in the staged calls, not from extra
-    workgroups of a pre-pass kernel (the short-X one for 12 tokens, the one that takes the rows' ranges for 70).
+    workgroups of a pre-pass kernel (the short-X one for 12 tokens, the one that takes the rows' ranges above 32).
     Same outputs as the staged calls, Out against the oracle."""
     d = wl.make_custom(s, 264, 72, 5, seed=91)
     zp_compare(one_sided(d), d["W"], 6.0, cap=300)
 
 
-@pytest.mark.parametrize("s", [7, 32, 33, 57, 64])
+@pytest.mark.parametrize("s", [7, 32, 33, 57, 64, 150])
 def test_short_x_in_one_call_with_more_outlier_columns_than_cap(s):
-    """The two-kernel pre-pass of a short X (s <= 32) inside llmint8_zp_linear, when more columns qualify
-    than the buffer takes: the row ranges are taken again over everything but the first cap columns.  Every
+    """The two-kernel pre-passes (up to 32 and up to 128 tokens) inside llmint8_zp_linear, and the longer one (150), when
+    more columns qualify than the buffer takes: the row ranges are taken again over everything but the first cap columns.  Every
     output of the call against the staged calls (which the test above pins to the oracle), Out against the
     oracle."""
     import torch
@@ -342,8 +357,10 @@ def test_argument_errors_are_reported_not_executed():
                                  p(Xo), p(out), p(ws.buf), 64, None) == WORKSPACE
 
 
-def test_random_shapes():
-    """Seeded random shapes on both GEMM paths, aligned and ragged, random numbers of outlier columns,
+@pytest.mark.parametrize("kernel", [None, "streaming", "tiled"])
+def test_random_shapes(kernel):
+    """Seeded random shapes through the kernels that the library chooses (K split over the waves, most of them) and through
+    the two others (streaming: above 32 tokens the tiled one), aligned and ragged, random numbers of outlier columns,
     one-sided and shifted inputs, with and without the decomposition: every stage against the oracle."""
     rng = np.random.default_rng(20240611)
     for case in range(16):
@@ -358,6 +375,7 @@ def test_random_shapes():
         if len(oracle.find_outliers(X, alpha)) > 32:
             continue
         try:
-            zp_compare(X, d["W"], alpha)
+            with through(kernel):
+                zp_compare(X, d["W"], alpha)
         except AssertionError as e:
             raise AssertionError(f"case {case}: s={s} h={h} o={o} ncol={ncol} alpha={alpha} shift={shift}: {e}") from e
