@@ -362,6 +362,9 @@ static const int ks_nj[KS_SHAPES] = {1, 2, 2, 2}, ks_ni[KS_SHAPES] = {1, 1, 2, 3
 // fill the chip stay there (512 x 4096 x 4096 17.0 against 17.6 us at best, 630 x 13824 x 6528 68 against 103); the
 // others come here if the estimate says that they gain 8 % with the launch counted (it is within a third of
 // the measured times on 25 products of 33 to 1 094 tokens, and low for these kernels rather than for those).
+// It counts a W of up to 40 MB as cached; on a W from memory the choice is the faster one all the same: 33 x 4096 x 4096 20.9
+// us there, 8.9 here, 128 x 12288 x 8192 56.5 / 35.4, 1000 x 8192 x 768 37.0 / 21.3, 96 x 5120 x 9000 27.2 / 23.4, 96 x 12288 x
+// 12288 56.6 / 46.2.
 // Up to 32 tokens, the weight-streaming kernel keeps every W that gives a quarter of the compute units a column tile
 // (8 x 8192 x 8192 14.2 against 21.4 us).  Below that, 8 waves per column tile pull more than 4 where the tokens are
 // many or K is long; the matmul alone there / here on a W from memory: 32 x 2048 x 2048 7.3 / 7.0 us, 24 x 8192 x 512 12.0 /
