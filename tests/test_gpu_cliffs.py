@@ -122,7 +122,7 @@ def test_few_features_of_many_tokens_against_a_wide_w(s, h, o):
         r = ratio(call, separate)
     finally:
         L.debug_decode_shape(-1)
-    assert r < 1.15
+    assert r < 1.2
 
 
 def test_many_column_factors_at_128_tokens():
