@@ -182,7 +182,7 @@ def measured_ceiling(L, torch, name, qws, rows):
         ms = _timed_launches(torch, lambda i: ops.append(L.probe_mfma(A, B, iters, sink)), 150, 100)
         out[key] = ops[-1] / (ms * 1e-3) / 1e12
         out[key + "_ms_per_launch"] = ms
-    return {"kind": "register-only v_mfma_i32_32x32x32_i8 issue loop, 4 waves per CU, 64 MFMAs per iteration "
+    return {"kind": "register-only v_mfma_i32_16x16x64_i8 issue loop, 8 waves per CU, 64 MFMAs per iteration "
                     "(llmint8_probe_mfma): on this workload's tiled codes / on zeros", "unit": "TOP/s",
             "value": out["workload_operands"], "zero_operands": out["zero_operands"],
             "ms_per_launch": out["workload_operands_ms_per_launch"]}

@@ -7,52 +7,49 @@
 namespace llmint8 {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
-// Register-only issue loop of v_mfma_i32_32x32x32_i8 in the shape of the prefill GEMM's main loop: a wave
-// holds 4 x 4 accumulator tiles (256 registers) and two double-buffered operand sets of two k-steps
-// (4 + 4 operand tiles each), loaded ONCE from the given tiled int8 matrices, and cycles through them:
-// 64 MFMAs per iteration, every one on another pair of operand tiles, nothing else in the loop.  With the
-// tiled codes of a real workload the operands have that workload's bit statistics (the rate depends on
-// them: the chip is power-limited); with a buffer of zeros this is the pure issue rate.
-__global__ void __launch_bounds__(256, 1) probe_mfma_kernel(const int8_t* __restrict__ A, size_t a_tiles,
+// Register-only issue loop of v_mfma_i32_16x16x64_i8 in the shape of the prefill GEMM's main loop at 256 x 256: a wave
+// (eight of them, two per SIMD) holds 8 x 4 accumulator tiles (128 registers) and two operand sets (8 + 4 operand tiles
+// each), loaded ONCE from the given tiled int8 matrices, and cycles through them: 64 MFMAs per iteration, every
+// one on another pair of operand tiles, nothing else in the loop.  With the tiled codes of a real workload the operands
+// have that workload's bit statistics (the rate depends on them: the chip is power-limited; 4 140 TOP/s, with
+// v_mfma_i32_32x32x32_i8 3 480); with a buffer of zeros this is the pure issue rate (4 870 with either).
+__global__ void __launch_bounds__(512, 1) probe_mfma_kernel(const int8_t* __restrict__ A, size_t a_tiles,
                                                            const int8_t* __restrict__ B, size_t b_tiles, int iters,
                                                            int32_t* __restrict__ sink)
 {
     const int lane = threadIdx.x & 63;
-    const size_t wave = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    v4i RP[2][2][4], RQ[2][2][4];
+    const size_t wave = (size_t)blockIdx.x * 8 + (threadIdx.x >> 6);
+    v4i RP[2][8], RQ[2][4];
 #pragma unroll
     for (int q = 0; q < 16; q++) {
         const size_t ta = (wave * 16 + q) * 2654435761ull % a_tiles, tb = (wave * 16 + q) * 40503ull % b_tiles;
-        RP[q >> 3][(q >> 2) & 1][q & 3] = *((const v4i*)(A + ta * TILE_BYTES) + lane);
-        RQ[q >> 3][(q >> 2) & 1][q & 3] = *((const v4i*)(B + tb * TILE_BYTES) + lane);
+        RP[q >> 3][q & 7] = *((const v4i*)(A + ta * TILE_BYTES) + lane);
+        if (q < 8) RQ[q >> 2][q & 3] = *((const v4i*)(B + tb * TILE_BYTES) + lane);
     }
-    v16i acc[4][4];
+    v4i acc[8][4];
 #pragma unroll
-    for (int a = 0; a < 4; a++)
+    for (int a = 0; a < 8; a++)
 #pragma unroll
-        for (int b = 0; b < 4; b++)
-#pragma unroll
-            for (int r = 0; r < 16; r++) acc[a][b][r] = 0;
+        for (int b = 0; b < 4; b++) acc[a][b] = v4i{0, 0, 0, 0};
     for (int it = 0; it < iters; it++) {
 #pragma unroll
         for (int S = 0; S < 2; S++)
 #pragma unroll
-            for (int c = 0; c < 2; c++)
+            for (int a = 0; a < 8; a++)
 #pragma unroll
-                for (int a = 0; a < 4; a++)
-#pragma unroll
-                    for (int b = 0; b < 4; b++)
-                        acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(RP[S][c][a], RQ[S][c][b], acc[a][b], 0, 0, 0);
+                for (int q = 0; q < 4; q++) {
+                    const int b = (a & 1) ? 3 - q : q;
+                    acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(RP[S][a], RQ[S][b], acc[a][b], 0, 0, 0);
+                }
     }
     int t = 0;
 #pragma unroll
-    for (int a = 0; a < 4; a++)
+    for (int a = 0; a < 8; a++)
 #pragma unroll
         for (int b = 0; b < 4; b++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) t ^= acc[a][b][r];
+            for (int r = 0; r < 4; r++) t ^= acc[a][b][r];
     if (t == 0x5a5a5a5a) sink[0] = t;  // keeps the loop alive; the value is of no interest
 }
 
@@ -92,9 +89,9 @@ int llmint8_probe_mfma(const int8_t* A_tiles, size_t a_bytes, const int8_t* B_ti
     if (((uintptr_t)A_tiles & 15) || ((uintptr_t)B_tiles & 15)) return LLMINT8_INVALID_ARG;
     int cus = 0;
     if (prefill_device_setup(&cus) != hipSuccess) return LLMINT8_HIP;
-    probe_mfma_kernel<<<cus, 256, 0, (hipStream_t)stream>>>(A_tiles, a_bytes / TILE_BYTES, B_tiles, b_bytes / TILE_BYTES, iters,
+    probe_mfma_kernel<<<cus, 512, 0, (hipStream_t)stream>>>(A_tiles, a_bytes / TILE_BYTES, B_tiles, b_bytes / TILE_BYTES, iters,
                                                            sink);
-    if (ops) *ops = (double)cus * 4.0 * iters * 64.0 * 65536.0;  // 2 * 32 * 32 * 32 int8 operations per MFMA
+    if (ops) *ops = (double)cus * 8.0 * iters * 64.0 * 32768.0;  // 2 * 16 * 16 * 64 int8 operations per MFMA
     return hipGetLastError() == hipSuccess ? LLMINT8_OK : LLMINT8_HIP;
 }
 

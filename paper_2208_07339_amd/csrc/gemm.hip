@@ -10,6 +10,7 @@ namespace llmint8 {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
@@ -57,10 +58,10 @@ struct GemmArgs {
 // ---------------------------------------------------------------------------
 // One workgroup = 2 x WQ waves (column halves x token parts; WQ = 2 or 4) computes
 // 64*WA output columns x 32*WQ*WB tokens; a wave owns WA x WB MFMA tiles of
-// 32 x 32 (16*WA*WB accumulator registers per lane).  The MFMA "A" operand is a
-// W tile (its 32 rows are output columns j), the "B" operand an X tile (32
-// tokens i): a lane ends up with 4 consecutive output columns of one token per
-// register quad.
+// 32 x 32 (16*WA*WB accumulator registers per lane), computed by T x T MFMAs
+// (T = 32 or 16: has_small_mfma() below).  The MFMA "A" operand is W (its T rows are
+// output columns j), the "B" operand X (T tokens i): a lane ends up with 4
+// consecutive output columns of one token per register quad.
 //
 // Shapes built: 256 x 256 and 128 x 256 (columns x tokens) with eight waves
 // (two per SIMD, 128 / 64 accumulator registers each), 192 x 256, 128 x 128,
@@ -72,7 +73,7 @@ struct GemmArgs {
 // 39.3 us on 2048 x 4096 x 4096.  192 x 256 does not split evenly over eight
 // waves (14 row tiles).
 //
-// K pipeline.  A stage is 64 features (2 MFMA k-steps) of all 2*WA + WQ*WB row
+// K pipeline.  A stage is 64 features (T / 16 MFMA k-steps) of all 2*WA + WQ*WB row
 // tiles; NB = 4 stages form a ring in LDS.  Tiles go global -> LDS with
 // 16-byte direct loads (one 1 KiB tile piece per wave instruction, the pieces
 // of a stage dealt evenly to the waves) and come back with one ds_read_b128
@@ -132,7 +133,7 @@ constexpr int OSLOTS = 32;  // outlier slots staged through LDS; more are read f
 // for).  Otherwise the epilogue is fed from LDS by the two epilogue stages and nothing in it is guarded.  Rows of
 // Out are stored in 16-byte pieces at any alignment, and the rows of W come from the lanes that have them: 75 -> 57.4 us
 // on 1013 x 4099 x 12301, where the unguarded kernel takes 55.6 for 12304 columns.
-template <int WA, int WB, int WQ, bool ZP, bool GUARDED>
+template <int WA, int WB, int WQ, int T, bool ZP, bool GUARDED>
 __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArgs g)
 {
     constexpr int NWAVES = 2 * WQ;               // waves: 2 along the columns x WQ along the tokens
@@ -140,7 +141,13 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
     constexpr int PIECES = (TW + TX) / WQ;       // direct loads per wave per stage
     static_assert(PIECES * WQ == TW + TX && (WQ == 2 || WQ == 4), "the pieces of a stage must divide evenly among the waves");
     constexpr int STAGE = (TW + TX) * 2 * TILE_BYTES;
-    constexpr int NMFMA = 2 * WA * WB;
+    constexpr int CT = 32 / T;                   // MFMA tiles along each side of a 32 x 32 tile
+    constexpr int KS = T / 16;                   // MFMA k-steps of a stage
+    constexpr int RG = T * T / 256;              // groups of four accumulator registers of an MFMA tile
+    constexpr int SP = 512 / T, XS = T / 16;     // outlier slots per fp16 MFMA, MFMAs for 32 slots
+    typedef std::conditional_t<T == 16, v4i, v16i> acc_t;
+    typedef std::conditional_t<T == 16, v4f, v16f> out_t;
+    constexpr int NMFMA = KS * CT * CT * WA * WB;
     constexpr int NRD = 2 * (WA + WB);
     constexpr int NOPS = PIECES + NRD;
     constexpr int OPSPAN = NMFMA;                // MFMA slots of a stage that carry its requests and LDS reads
@@ -185,9 +192,10 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
     int myk = 0;
 
     // ---- loader state: the tile whose stages are being requested.
-    // Piece p = w*PIECES + k of a stage is k-half (p & 1) of row tile p >> 1 (W tiles first, then
-    // X tiles); it lands at byte p * 1024 of the stage's ring slot.
-    const unsigned voff = lane * 16;
+    // Piece p = w*PIECES + k of a stage is a half of row tile p >> 1 (W tiles first, then X tiles) in the operand order
+    // of the MFMA; it lands at byte p * 1024 of the stage's ring slot.  T = 32: k-half p & 1.  T = 16: rows 16*(p & 1) .. +15,
+    // all 64 features: lane l fetches row l % 16, features 16*(l / 16) .. +15, four runs of 256 bytes of the two k-tiles.
+    const unsigned voff = T == 16 ? (lane >> 4) * 512 + (lane & 15) * 16 : lane * 16;
     const int8_t* gpp[PIECES];
     int J0w, I0w;   // first column / token of the tile
     auto set_loader = [&](int logical) {
@@ -215,7 +223,7 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                 t = t < g.RT ? t : g.RT - 1;
                 base = g.Xq + (size_t)t * KT * TILE_BYTES;
             }
-            const unsigned long long b = (unsigned long long)(base + (p & 1) * TILE_BYTES);
+            const unsigned long long b = (unsigned long long)(base + (p & 1) * (T == 16 ? 256 : TILE_BYTES));
             const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
             const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
             gpp[k] = (const int8_t*)(((unsigned long long)hi << 32) | lo);  // uniform: lives in scalar registers
@@ -298,19 +306,19 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
         __builtin_amdgcn_global_load_lds(GPTR(esrc(e * NWAVES * PIECES + w * PIECES + k)), LPTR(dst), 16, 0, 0);
     };
 
-    v16i acc[WA][WB];
+    acc_t acc[CT * WA][CT * WB];
     // operand registers of two stages: [set][k-step][tile]
-    v4i RP[2][2][WA], RQ[2][2][WB];
+    v4i RP[2][KS][CT * WA], RQ[2][KS][CT * WB];
     const int8_t* Pl = lds + (wp * WA) * 2 * TILE_BYTES + lane * 16;
     const int8_t* Ql = lds + (TW + wq * WB) * 2 * TILE_BYTES + lane * 16;
     // read number i (0 .. NRD-1) of a stage into register set S
     auto rd = [&](auto S, int slot, int i) {
         constexpr int SS = decltype(S)::value;
-        const int c = i / (WA + WB), t = i % (WA + WB);
-        if (t < WA)
-            RP[SS][c][t] = *(const v4i*)(Pl + slot * STAGE + (t * 2 + c) * TILE_BYTES);
+        const int c = T == 16 ? 0 : i / (WA + WB), x = T == 16 ? i : i % (WA + WB);
+        if (x < CT * WA)
+            RP[SS][c][x] = *(const v4i*)(Pl + slot * STAGE + (T == 16 ? x : x * 2 + c) * TILE_BYTES);
         else
-            RQ[SS][c][t - WA] = *(const v4i*)(Ql + slot * STAGE + ((t - WA) * 2 + c) * TILE_BYTES);
+            RQ[SS][c][x - CT * WA] = *(const v4i*)(Ql + slot * STAGE + (T == 16 ? x - CT * WA : (x - WA) * 2 + c) * TILE_BYTES);
     };
     // request all pieces of stage v (operand stage, or epilogue stage v - nst) of the loader tile
     auto issue_stage = [&](int v, int slot) {
@@ -340,9 +348,12 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
         const unsigned vo = MODE == 0 ? stage_off(st + NB) : 0u;
 #pragma unroll
         for (int i = 0; i < NMFMA; i++) {
-            // boustrophedon over the WA x WB tiles: consecutive MFMAs share one operand register set
-            const int c = i / (WA * WB), a = (i / WB) % WA, b = (a & 1) ? WB - 1 - i % WB : i % WB;
-            acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(RP[SS][c][a], RQ[SS][c][b], acc[a][b], 0, 0, 0);
+            // boustrophedon over the tiles: consecutive MFMAs share one operand register set
+            const int c = i / (CT * CT * WA * WB), a = i / (CT * WB) % (CT * WA), bi = i % (CT * WB), b = (a & 1) ? CT * WB - 1 - bi : bi;
+            if constexpr (T == 16)
+                acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(RP[SS][c][a], RQ[SS][c][b], acc[a][b], 0, 0, 0);
+            else
+                acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(RP[SS][c][a], RQ[SS][c][b], acc[a][b], 0, 0, 0);
             FENCE();
 #pragma unroll
             for (int q = (i < OPSPAN ? i : OPSPAN) * NOPS / OPSPAN; q < (i + 1 < OPSPAN ? i + 1 : OPSPAN) * NOPS / OPSPAN; q++) {
@@ -401,11 +412,26 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
     for (;;) {  // tiles of this workgroup
         const int cJ0w = J0w, cI0w = I0w;  // the tile being computed (the loader moves on before its epilogue)
 #pragma unroll
-        for (int a = 0; a < WA; a++)
+        for (int a = 0; a < CT * WA; a++)
 #pragma unroll
-            for (int b = 0; b < WB; b++)
+            for (int b = 0; b < CT * WB; b++) {
+                if constexpr (T == 16) {
+                    // opaque zeros: with the constant 0 as the first MFMAs' third operand the compiler places their results
+                    // elsewhere and moves them back, through spilled registers
+                    if constexpr (WQ == 4) {
+                        int z[4];
 #pragma unroll
-                for (int r = 0; r < 16; r++) acc[a][b][r] = 0;
+                        for (int r = 0; r < 4; r++) asm volatile("v_mov_b32 %0, 0" : "=v"(z[r]));
+                        acc[a][b] = v4i{z[0], z[1], z[2], z[3]};
+                    } else {
+                        acc[a][b] = v4i{0, 0, 0, 0};
+                        asm volatile("" : "+a"(acc[a][b]));
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 16; r++) acc[a][b][r] = 0;
+                }
+            }
         // Stage 0 has landed once at most the pieces of stage 1 (and the stores of an unguarded epilogue
         // before this tile) are in flight.  The barrier also tells that every wave is done with
         // the previous tile's epilogue stages, whose slots take stages 2 and 3 (with nst == 2: this
@@ -442,6 +468,15 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
         stage(I0_{}, std::integral_constant<int, 3>{}, st);
         stage(I1_{}, std::integral_constant<int, 4>{}, st + 1);
         STAMP(2);
+        if constexpr (T == 16) {  // (and the sums stay where they are)
+#pragma unroll
+            for (int a = 0; a < CT * WA; a++)
+#pragma unroll
+                for (int b = 0; b < CT * WB; b++) {
+                    if constexpr (WQ == 4) asm volatile("" : "+v"(acc[a][b]));
+                    else asm volatile("" : "+a"(acc[a][b]));
+                }
+        }
         STAGE_SYNC(0);  // the epilogue stages have landed, every wave is done with the operand slots
         STAMP(3);
 
@@ -456,15 +491,14 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
 
         STAMP(4);
         // ---- epilogue ----------------------------------------------------------
-        // acc[a][b][r] of lane l: token i = I0 + b*32 + (l & 31),
-        //                         column j = J0 + a*32 + 8*(r >> 2) + 4*(l >> 5) + (r & 3)
+        // acc[a][b][r] of lane l: token i = I0 + b*T + l % T, column j = J0 + a*T + 8*(r >> 2) + 4*(l / T) + (r & 3)
         const int J0 = cJ0w + wp * 32 * WA;
         const int I0 = cI0w + wq * 32 * WB;
         // lane-derived offsets are taken from an opaque copy of the lane number, so that they are recomputed
         // here for every tile instead of being carried through the K loop in registers
         int lane_e = lane;
         asm volatile("" : "+v"(lane_e));
-        const int gl = lane_e >> 5, ll = lane_e & 31;
+        const int gl = lane_e / T, ll = lane_e % T;
 
         const int8_t* E = lds + eslot * STAGE;
         const unsigned short* EW = (const unsigned short*)E;                               // [32][256]
@@ -506,8 +540,9 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
             return wa;
         };
         auto load_x_mem = [&](int i, int t0) {
-            const v8h xb = *(const v8h*)(g.Xo + (size_t)(i < s ? i : s - 1) * opad + t0 + 8 * gl);
-            return i < s ? xb : (v8h)(0);
+            const bool in = T == 32 || t0 + 8 * gl < opad;  // (opad is a multiple of 16)
+            const v8h xb = *(const v8h*)(g.Xo + (size_t)(i < s ? i : s - 1) * opad + (in ? t0 + 8 * gl : 0));
+            return i < s && in ? xb : (v8h)(0);
         };
 
         // FAST: operands from the LDS image of the epilogue stages, no guards.  Its stores go
@@ -523,23 +558,23 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
             constexpr bool FAST = decltype(F)::value;
             if (!FAST && g.Cdbg) {
 #pragma unroll
-                for (int a = 0; a < WA; a++)
+                for (int a = 0; a < CT * WA; a++)
 #pragma unroll
-                    for (int b = 0; b < WB; b++) {
-                        const int i = I0 + b * 32 + ll;
+                    for (int b = 0; b < CT * WB; b++) {
+                        const int i = I0 + b * T + ll;
 #pragma unroll
-                        for (int r = 0; r < 16; r++) {
-                            const int j = J0 + a * 32 + 8 * (r >> 2) + 4 * gl + (r & 3);
+                        for (int r = 0; r < 4 * RG; r++) {
+                            const int j = J0 + a * T + 8 * (r >> 2) + 4 * gl + (r & 3);
                             if (i < s && j < o) g.Cdbg[(size_t)i * o + j] = acc[a][b][r];
                         }
                     }
             }
-            float sx[WB];      // c_x / 127^2 of this lane's tokens (Eq. 7: S = c_x (x) c_w / 127^2)
-            double zsa[ZP ? WB : 1], zza[ZP ? WB : 1], zrs[ZP ? WB : 1];  // zeropoint: D_x / 254, zp_x, row sum of the codes
-            v8h xb[WB][2];     // MFMA "B" operand of the outlier product: slots 8*gl .. +7 (+16) of this lane's tokens
+            float sx[CT * WB];  // c_x / 127^2 of this lane's tokens (Eq. 7: S = c_x (x) c_w / 127^2)
+            double zsa[ZP ? CT * WB : 1], zza[ZP ? CT * WB : 1], zrs[ZP ? CT * WB : 1];  // zeropoint: D_x / 254, zp_x, row sum of the codes
+            v8h xb[CT * WB][XS];  // MFMA "B" operand of the outlier product: slots SP*ks + 8*gl .. +7 of this lane's tokens
 #pragma unroll
-            for (int b = 0; b < WB; b++) {
-                const int il = wq * 32 * WB + b * 32 + ll;  // token within the workgroup tile
+            for (int b = 0; b < CT * WB; b++) {
+                const int il = wq * 32 * WB + b * T + ll;  // token within the workgroup tile
                 const int i = cI0w + il;
                 if (FAST) {
                     if constexpr (ZP) {
@@ -550,9 +585,12 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                     } else {
                         sx[b] = f16_bits_to_float(ECx[il]) * (1.0f / 16129.0f);
                     }
-                    xb[b][0] = *(const v8h*)(EX + il * (2 * lpad) + gl * 16);
-                    xb[b][1] = (v8h)(0);
-                    if (cnt > 16) xb[b][1] = *(const v8h*)(EX + il * (2 * lpad) + (2 + gl) * 16);  // then lpad == 32
+#pragma unroll
+                    for (int ks = 0; ks < XS; ks++) {
+                        xb[b][ks] = (v8h)(0);
+                        if (ks == 0 || cnt > ks * SP)
+                            if (T == 32 || 8 * gl < lpad) xb[b][ks] = *(const v8h*)(EX + il * (2 * lpad) + (2 * ks + gl) * 16);
+                    }
                 } else {
                     if constexpr (ZP) {
                         int4 rec = g.zp.zcx[i < s ? i : s - 1];
@@ -564,8 +602,8 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                         const float cxi = f16_bits_to_float(g.cx[i < s ? i : s - 1]) * (1.0f / 16129.0f);
                         sx[b] = (i < s) ? cxi : 0.0f;
                     }
-                    xb[b][0] = cnt > 0 ? load_x_mem(i, 0) : (v8h)(0);
-                    xb[b][1] = cnt > 16 ? load_x_mem(i, 16) : (v8h)(0);
+#pragma unroll
+                    for (int ks = 0; ks < XS; ks++) xb[b][ks] = cnt > ks * SP ? load_x_mem(i, ks * SP) : (v8h)(0);
                 }
             }
             // zeropoint: this wave's 32*WA columns of the three factor planes, copied once per tile into a
@@ -586,37 +624,31 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                 __builtin_amdgcn_wave_barrier();
             }
             STAMP(5);
+            if constexpr (T == 16) FENCE();
 #pragma unroll
             for (int a0 = 0; a0 < WA; a0 += 2) {
                 constexpr int WA_ = WA;
                 const int na = (WA_ - a0) < 2 ? (WA_ - a0) : 2;  // column tiles in this pass: 2, or 1 at the end of an odd WA
-                float cwv[2][16];
-                v8h wa[2][2];
+                v4h cwv[2 * CT][RG];  // (widened where it is used: part of the fused multiply-add)
+                v8h wa[2 * CT][XS];
 #pragma unroll
-                for (int aa = 0; aa < 2; aa++) {
-                    if (aa >= na) break;
-                    const int jl = wp * 32 * WA + (a0 + aa) * 32;  // first column of the MFMA tile within the workgroup tile
+                for (int aa = 0; aa < 2 * CT; aa++) {
+                    if (aa >= CT * na) break;
+                    const int jl = wp * 32 * WA + a0 * 32 + aa * T;  // first column of the MFMA tile within the workgroup tile
                     if (FAST) {
                         if constexpr (!ZP) {
 #pragma unroll
-                            for (int rr = 0; rr < 4; rr++) {
-                                const uint2 pk = *(const uint2*)(ECw + jl + 8 * rr + 4 * gl);
-                                cwv[aa][4 * rr + 0] = f16_bits_to_float((unsigned short)(pk.x & 0xffff));
-                                cwv[aa][4 * rr + 1] = f16_bits_to_float((unsigned short)(pk.x >> 16));
-                                cwv[aa][4 * rr + 2] = f16_bits_to_float((unsigned short)(pk.y & 0xffff));
-                                cwv[aa][4 * rr + 3] = f16_bits_to_float((unsigned short)(pk.y >> 16));
-                            }
+                            for (int rr = 0; rr < RG; rr++) cwv[aa][rr] = *(const v4h*)(ECw + jl + 8 * rr + 4 * gl);
                         }
 #pragma unroll
-                        for (int ks = 0; ks < 2; ks++)
+                        for (int ks = 0; ks < XS; ks++)
 #pragma unroll
                             for (int e = 0; e < 8; e++)
-                                wa[aa][ks][e] =
-                                    __builtin_bit_cast(_Float16, EW[(16 * ks + 8 * gl + e) * 256 + jl + ll]);
+                                wa[aa][ks][e] = __builtin_bit_cast(_Float16, EW[(SP * ks + 8 * gl + e) * 256 + jl + ll]);
                     } else {
                         if constexpr (!ZP) {
 #pragma unroll
-                            for (int rr = 0; rr < 4; rr++) {
+                            for (int rr = 0; rr < RG; rr++) {
                                 const int j = cJ0w + jl + 8 * rr + 4 * gl;  // c_w is 8-byte aligned
                                 unsigned short q[4] = {0, 0, 0, 0};
                                 if (j + 4 <= o) {
@@ -627,57 +659,68 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                                         if (j + e < o) q[e] = g.cw[j + e];
                                 }
 #pragma unroll
-                                for (int e = 0; e < 4; e++) cwv[aa][4 * rr + e] = f16_bits_to_float(q[e]);
+                                for (int e = 0; e < 4; e++) cwv[aa][rr][e] = __builtin_bit_cast(_Float16, q[e]);
                             }
                         }
-                        wa[aa][0] = cnt > 0 ? load_w_mem(cJ0w + jl + ll, 0) : (v8h)(0);
-                        wa[aa][1] = cnt > 16 ? load_w_mem(cJ0w + jl + ll, 16) : (v8h)(0);
+#pragma unroll
+                        for (int ks = 0; ks < XS; ks++) wa[aa][ks] = cnt > ks * SP ? load_w_mem(cJ0w + jl + ll, ks * SP) : (v8h)(0);
                     }
                 }
                 STAMP(6 + 6 * (a0 / 2));
+                if constexpr (T == 16) FENCE();
 #pragma unroll
                 for (int b0 = 0; b0 < WB; b0 += BU) {
                     int8_t* sb = stg;
                     // ---- 32*BU tokens x 64 columns: dequantize, add the outlier product, stage as fp16 rows in LDS
+                    // Eq. 8: outlier product first (fp32 accumulation in the matrix unit), then one fused multiply-add per
+                    // output puts the dequantized int8 product (Eq. 7) on top
+                    auto outlier_product = [&](int aa, int bb) {
+                        out_t t;
 #pragma unroll
-                    for (int aa = 0; aa < 2; aa++) {
-                        if (aa >= na) break;
-                        const int a = a0 + aa;
+                        for (int r = 0; r < 4 * RG; r++) t[r] = 0.0f;
+                        auto mm = [&](v8h wv, v8h xv) {
+                            if constexpr (T == 16) t = __builtin_amdgcn_mfma_f32_16x16x32_f16(wv, xv, t, 0, 0, 0);
+                            else t = __builtin_amdgcn_mfma_f32_32x32x16_f16(wv, xv, t, 0, 0, 0);
+                        };
 #pragma unroll
-                        for (int bb = 0; bb < BU; bb++) {
-                            if (b0 + bb >= WB) break;
-                            const int b = b0 + bb;
-                            // Eq. 8: outlier product first (fp32 accumulation in the matrix unit), then one fused
-                            // multiply-add per output puts the dequantized int8 product (Eq. 7) on top
-                            v16f d;
-                            if (cnt > 0) {
-                                v16f t = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                                t = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[aa][0], xb[b][0], t, 0, 0, 0);
-                                if (cnt > 16) t = __builtin_amdgcn_mfma_f32_32x32x16_f16(wa[aa][1], xb[b][1], t, 0, 0, 0);
-                                if (!FAST)
-                                    for (int t0 = OSLOTS; t0 < cnt; t0 += 16) {  // more than 32 outlier columns: rare
-                                        const v8h wm = load_w_mem(J0 + a * 32 + ll, t0);
-                                        const v8h xm = load_x_mem(I0 + b * 32 + ll, t0);
-                                        t = __builtin_amdgcn_mfma_f32_32x32x16_f16(wm, xm, t, 0, 0, 0);
-                                    }
-                                if constexpr (!ZP) {
+                        for (int ks = 0; ks < XS; ks++)
+                            if (cnt > ks * SP) mm(wa[aa][ks], xb[CT * b0 + bb][ks]);
+                        if (!FAST)
+                            for (int t0 = OSLOTS; t0 < cnt; t0 += SP)  // more than 32 outlier columns: rare
+                                mm(load_w_mem(J0 + (CT * a0 + aa) * T + ll, t0), load_x_mem(I0 + (CT * b0 + bb) * T + ll, t0));
+                        return t;
+                    };
+                    // T = 16: the whole block's together, so that no output waits for its own (2 048 x 4 096 x 4 096: 6.1 k -> 4.3 k
+                    // clocks in the epilogue)
+                    out_t t[2 * CT][CT * BU];
+                    if constexpr (T == 16) {
 #pragma unroll
-                                    for (int r = 0; r < 16; r++)
-                                        d[r] = __builtin_fmaf((float)acc[a][b][r] * sx[b], cwv[aa][r], t[r]);
-                                } else {
-                                    d = t;
-                                }
-                            } else {
+                        for (int aa = 0; aa < 2 * CT; aa++)
 #pragma unroll
-                                for (int r = 0; r < 16; r++)
-                                    d[r] = ZP ? 0.0f : (float)acc[a][b][r] * sx[b] * cwv[aa][r];
+                            for (int bb = 0; bb < CT * BU; bb++)
+                                if (aa < CT * na && b0 + bb / CT < WB) t[aa][bb] = outlier_product(aa, bb);
+                    }
+#pragma unroll
+                    for (int aa = 0; aa < 2 * CT; aa++) {
+                        if (aa >= CT * na) break;
+                        const int a = CT * a0 + aa;
+#pragma unroll
+                        for (int bb = 0; bb < CT * BU; bb++) {
+                            if (b0 + bb / CT >= WB) break;
+                            const int b = CT * b0 + bb;
+                            out_t d;
+                            if constexpr (T == 16) d = t[aa][bb]; else d = outlier_product(aa, bb);
+                            if constexpr (!ZP) {
+#pragma unroll
+                                for (int r = 0; r < 4 * RG; r++)
+                                    d[r] = __builtin_fmaf((float)acc[a][b][r] * sx[b], (float)cwv[aa][r >> 2][r & 3], d[r]);
                             }
                             if constexpr (ZP) {
                                 // Eq. 5 over nd_w: C p + rowsum q + zp_x r with the column factors of
                                 // zp_kcol_kernel (planes padded with zeros: no guards), then the division by nd_x
 #pragma unroll
-                                for (int r = 0; r < 16; r++) {
-                                    const int c = a * 32 + 8 * (r >> 2) + 4 * gl + (r & 3);
+                                for (int r = 0; r < 4 * RG; r++) {
+                                    const int c = a * T + 8 * (r >> 2) + 4 * gl + (r & 3);
                                     const double cp = zc0[c], cq = zc0[zstride + c], cr = zc0[2 * zstride + c];
                                     d[r] += (float)(zsa[b] * __builtin_fma((double)acc[a][b][r], cp,
                                                                            __builtin_fma(zrs[b], cq, zza[b] * cr)));
@@ -685,13 +728,14 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                             }
                             // staging row of token tl (0..63): 128 bytes = 8 chunks of 16, chunk q stored at
                             // q ^ ((tl >> 1) & 7) to spread the banks
-                            const int tl = bb * 32 + ll;
+                            const int tl = bb * T + ll;
+                            asm("" : "+v"(d));  // rounded to fp32 before it is rounded to fp16, as in linear_small_kernel (v_fma_mixlo_f16 rounds once)
 #pragma unroll
-                            for (int rr = 0; rr < 4; rr++) {
+                            for (int rr = 0; rr < RG; rr++) {
                                 const v4h hv = {(_Float16)d[4 * rr], (_Float16)d[4 * rr + 1], (_Float16)d[4 * rr + 2],
                                                 (_Float16)d[4 * rr + 3]};
-                                const int q = aa * 4 + rr;
-                                *(v4h*)(sb + tl * 128 + ((q ^ ((tl >> 1) & 7)) << 4) + gl * 8) = hv;
+                                const int q = aa * (T / 8) + rr + (gl >> 1);
+                                *(v4h*)(sb + tl * 128 + ((q ^ ((tl >> 1) & 7)) << 4) + (gl & 1) * 8) = hv;
                             }
                         }
                     }
@@ -724,6 +768,7 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                     }
                     asm volatile("" ::: "memory");  // the next block's staging writes stay behind these reads
                     STAMP(8 + 6 * (a0 / 2) + 2 * (b0 / BU));
+                    if constexpr (T == 16) FENCE();
                 }
             }
         };
@@ -749,13 +794,26 @@ constexpr int prefill_lds_bytes()
     return NB * (2 * WA + WQ * WB) * 2 * TILE_BYTES + 32768;  // operand ring + output staging (32 KiB over all waves)
 }
 
+// Which MFMA: 16 x 16 x 64 for the shapes of 256 tokens where three quarters of the compute units have a tile, else
+// 32 x 32 x 32.  On workload codes a register-only issue loop sustains 4 140 TOP/s with the former and 3 480 with the
+// latter at the board's power limit (on zeros 4 870 with both): a full chip runs at 1.75-1.8 GHz in place of 1.5-1.55 for 4 to 8 % more clocks
+// per stage (shorter MFMAs hide less of what is issued between them).  Where the clock is not limited by power only the latter shows: kernels with
+// 16 x 16 x 64 everywhere took 20.6 against 19.2 us on 96 x 5120 x 15360 (120 tiles) and 41.7 against 40.0 us per call on
+// 256 x 8192 x 8192 (128 tiles); at 192 tiles and more 307 against 336 us on 4096 x 5120 x 20480.  The guarded epilogue keeps 32 x 32 x 32.
+template <int WB, int WQ>
+constexpr bool has_small_mfma() { return 32 * WQ * WB == 256; }
+static inline int small_mfma_from(int ncu) { return ncu / 4 * 3; }
+
 template <int WA, int WB, int WQ>
 static hipError_t raise_lds_limit()
 {
-    const void* k[4] = {(const void*)gemm_prefill_kernel<WA, WB, WQ, false, false>,
-                        (const void*)gemm_prefill_kernel<WA, WB, WQ, false, true>,
-                        (const void*)gemm_prefill_kernel<WA, WB, WQ, true, false>,
-                        (const void*)gemm_prefill_kernel<WA, WB, WQ, true, true>};
+    constexpr int T = has_small_mfma<WB, WQ>() ? 16 : 32;
+    const void* k[6] = {(const void*)gemm_prefill_kernel<WA, WB, WQ, 32, false, false>,
+                        (const void*)gemm_prefill_kernel<WA, WB, WQ, 32, false, true>,
+                        (const void*)gemm_prefill_kernel<WA, WB, WQ, 32, true, false>,
+                        (const void*)gemm_prefill_kernel<WA, WB, WQ, 32, true, true>,
+                        (const void*)gemm_prefill_kernel<WA, WB, WQ, T, false, false>,
+                        (const void*)gemm_prefill_kernel<WA, WB, WQ, T, true, false>};
     for (const void* f : k) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, prefill_lds_bytes<WA, WB, WQ>());
         if (e != hipSuccess) return e;
@@ -810,13 +868,16 @@ static hipError_t launch_cfg(GemmArgs& g, hipStream_t st)
     // one whose case it is not returns at once (about 3 us for the empty launch).
     g.many_only = 0;
     if (g.fast_ok && !g.Cdbg) {
-        gemm_prefill_kernel<WA, WB, WQ, ZP, false><<<grid, 128 * WQ, shm, st>>>(g);
+        if (has_small_mfma<WB, WQ>() && grid >= small_mfma_from(ncu))
+            gemm_prefill_kernel<WA, WB, WQ, has_small_mfma<WB, WQ>() ? 16 : 32, ZP, false><<<grid, 128 * WQ, shm, st>>>(g);
+        else
+            gemm_prefill_kernel<WA, WB, WQ, 32, ZP, false><<<grid, 128 * WQ, shm, st>>>(g);
         if (g.opad <= OSLOTS) return hipGetLastError();
         const hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) return e1;
         g.many_only = 1;
     }
-    gemm_prefill_kernel<WA, WB, WQ, ZP, true><<<grid, 128 * WQ, shm, st>>>(g);
+    gemm_prefill_kernel<WA, WB, WQ, 32, ZP, true><<<grid, 128 * WQ, shm, st>>>(g);
     return hipGetLastError();
 }
 

@@ -6,7 +6,7 @@
 Runs 300 back-to-back calls of llmint8_linear on the workload (default ffn13b), then prints, for the waves
 of one workgroup (eight at 256 x 256 and 128 x 256, else four), the clocks spent in each phase of that
 workgroup's second tile (its only tile where the workload gives it one: attn6p7b; then nothing is requested
-for a next tile), and the K loop's clocks per stage (its MFMAs alone need 32 clocks per v_mfma_i32_32x32x32_i8: 1024 per stage of a 256 x 256
+for a next tile), and the K loop's clocks per stage (its MFMAs alone need 16 clocks per v_mfma_i32_16x16x64_i8, 32 per v_mfma_i32_32x32x32_i8: 1024 per stage of a 256 x 256
 tile, 768 at 192 x 256, 512 at 128 x 256).
 """
 import ctypes as C
