@@ -1,8 +1,8 @@
 // Conversion of the weights, done once when they are loaded (Section 3.1: one set of constants per column
 // of W): fp16 W [h x o] -> tiled codes and column constants, absmax (Section 2.1) and zeropoint (Eq. 1-3).
 //
-// W is read twice (the constants need every row of a column before its first code), the codes are written
-// once: 5 bytes per weight over HBM, which is what bounds both kernels.
+// The constants need every row of a column before its first code.  Where the columns of a tile fit a workgroup's
+// registers W is read once (weight_strip_kernel, 3 bytes per weight over HBM), else twice (5 bytes), which bounds these kernels.
 #include "common.h"
 
 namespace llmint8 {
@@ -231,6 +231,224 @@ __global__ void __launch_bounds__(1024) zp_colsum_kernel(const int* __restrict__
     if (g == 0 && j < o) zc[j].z = red[0][c] + red[1][c] + red[2][c] + red[3][c];
 }
 
+// ---------------------------------------------------------------------------
+// The whole conversion of 32 output columns (one row tile of the codes) in one workgroup, W read once: the columns stay
+// in registers between their constants and their codes, so 3 bytes per weight move instead of 5.
+//
+// A lane holds 8 columns x 16 features per unit (16 loads of 16 bytes; four lanes side by side cover the 64 bytes that
+// the tile has in a row), a wave 256 features, so that the 16 codes of a 16-byte piece meet in one lane as in
+// weight_codes_kernel; wave w of the nw takes the units w, w + nw, ... (U of them).  What fits is h up to
+// 16 * 256 features with one unit to a wave and 12 * 2 * 256 with two (LDS swaps pieces between lanes, 8 KiB to a wave).
+// Two tiles side by side share the 128-byte lines of W, and rows of 4 096 bytes or a multiple send all of a tile to one
+// L2 channel: each XCD takes a run of tiles side by side (neighbours alternating between the XCDs: 100.7 us instead of 85.1 on
+// 5 120 x 20 480).  What bounds it: the memory while all workgroups load; loading, coding and storing follow one
+// another in a workgroup.  Against the two passes over W, us: 4 096 x 4 096 16.7 / 20.2, 4 096 x 16 384 63.1 / 67.0, 2 048 x 49 152
+// 73.7 / 85.9, 3 333 x 5 001 16.1 / 29.1; zeropoint 4 096 x 8 192 25.9 / 44.2, 2 048 x 49 152 77.5 / 98.4.
+// ---------------------------------------------------------------------------
+constexpr int STRIP_WAVES = 16, STRIP_STAGE = 512 * 16;
+constexpr int strip_max_waves(int units) { return units == 1 ? 16 : units == 2 ? 12 : 8; }
+
+template <int U, bool ZP>
+__global__ void __launch_bounds__(64 * strip_max_waves(U))
+    weight_strip_kernel(const unsigned short* __restrict__ W, int h, int o, unsigned short* __restrict__ cw,
+                        int4* __restrict__ zc, int8_t* __restrict__ Wq, int KT, int JT)
+{
+    extern __shared__ u4 stage[];  // 512 pieces for each wave
+    __shared__ us8 rmax[STRIP_WAVES][4], rmin[ZP ? STRIP_WAVES : 1][4];
+    __shared__ float s_kup[32];
+    __shared__ double s_zf[ZP ? 32 : 1];
+    __shared__ int s_z[ZP ? 32 : 1], s_sum[ZP ? STRIP_WAVES : 1][32];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+    const int b = blockIdx.x;
+    const int jt = (b & 7) * (JT >> 3) + min(b & 7, JT & 7) + (b >> 3);
+    const int oct = (lane & 3) * 8, j0 = jt * 32 + oct, g16 = (lane >> 2) * 16;
+    const unsigned short* p = W + (j0 + 8 <= o ? j0 : o - 8);  // (chunk_fix() below moves the row's last columns into place)
+    us8 v[U][16];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int k0 = (u * nw + w) * 256;
+        if (k0 + 256 <= h) {
+            const unsigned short* q = p + (size_t)(k0 + g16) * o;
+#pragma unroll
+            for (int i = 0; i < 16; i++) v[u][i] = load8(q + (size_t)i * o);
+        } else {  // rows past h: the last row again, which changes no extreme; zeroed below
+#pragma unroll
+            for (int i = 0; i < 16; i++) v[u][i] = load8(p + (size_t)(k0 + g16 + i < h ? k0 + g16 + i : h - 1) * o);
+        }
+    }
+    if (jt * 32 + 32 > o) {  // uniform
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) v[u][i] = chunk_fix(v[u][i], j0, o);  // columns that do not exist: all zero
+    }
+    // ---- the columns' extremes
+    us8 mx = (us8)((unsigned short)0), mn = (us8)((unsigned short)0xffff);
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            if constexpr (ZP) {
+                const us8 k = f16_key8(v[u][i]);
+                mn = __builtin_elementwise_min(mn, k);
+                mx = __builtin_elementwise_max(mx, k);
+            } else {
+                mx = __builtin_elementwise_max(mx, v[u][i] & (unsigned short)0x7fff);
+            }
+        }
+#pragma unroll
+    for (int d = 4; d <= 32; d <<= 1) {
+        u4 a = __builtin_bit_cast(u4, mx), c = __builtin_bit_cast(u4, mn);
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            a[q] = (unsigned)__shfl_xor((int)a[q], d);
+            if constexpr (ZP) c[q] = (unsigned)__shfl_xor((int)c[q], d);
+        }
+        mx = __builtin_elementwise_max(mx, __builtin_bit_cast(us8, a));
+        if constexpr (ZP) mn = __builtin_elementwise_min(mn, __builtin_bit_cast(us8, c));
+    }
+    if (lane < 4) {
+        rmax[w][lane] = mx;
+        if constexpr (ZP) rmin[w][lane] = mn;
+    }
+    __syncthreads();
+    if (tid < 32) {
+        unsigned kx = 0, kn = 0xffffu;
+        for (int q = 0; q < nw; q++) {
+            const unsigned x = rmax[q][tid >> 3][tid & 7];
+            kx = x > kx ? x : kx;
+            if constexpr (ZP) {
+                const unsigned n = rmin[q][tid >> 3][tid & 7];
+                kn = n < kn ? n : kn;
+            }
+        }
+        const int j = jt * 32 + tid;
+        if constexpr (ZP) {
+            const int4 r = make_const(kn, kx);
+            if (j < o) {
+                zc[j].x = r.x;
+                zc[j].y = r.y;
+                zc[j].w = 0;
+            }
+            s_zf[tid] = zp_factor(zp_range((unsigned)r.x));
+            s_z[tid] = r.y;
+        } else {
+            if (j < o) cw[j] = (unsigned short)kx;
+            s_kup[tid] = code_factor(f16_bits_to_float((unsigned short)kx));
+        }
+    }
+    __syncthreads();
+    // ---- codes
+    u4* mine = stage + w * 512;
+    int sum[ZP ? 8 : 1];
+    if constexpr (ZP) {
+#pragma unroll
+        for (int e = 0; e < 8; e++) sum[e] = 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int unit = u * nw + w, k = unit * 256 + g16;
+        if (unit * 8 >= KT) break;  // uniform in a wave
+        if (k + 16 > h) {
+#pragma unroll
+            for (int i = 0; i < 16; i++)
+                if (k + i >= h) v[u][i] = (us8)((unsigned short)0);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            const float f = ZP ? 0.0f : s_kup[oct + e];
+            const double zf = ZP ? s_zf[oct + e] : 0.0;
+            const unsigned z = ZP ? (unsigned)s_z[oct + e] : 0u;
+            unsigned q[4];
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                unsigned t[4];
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    if constexpr (ZP) t[i] = zp_u_bits(v[u][4 * c + i][e], zf) - z;
+                    else t[i] = code_bits(v[u][4 * c + i][e], f);
+                }
+                q[c] = pack_low_bytes(t[0], t[1], t[2], t[3]);
+            }
+            if constexpr (ZP) {
+                if (k + 16 > h) {  // a padding row's u(0) - zp is not its code: padding is 0 whatever the zeropoint
+#pragma unroll
+                    for (int c = 0; c < 4; c++)
+#pragma unroll
+                        for (int i = 0; i < 4; i++)
+                            if (k + 4 * c + i >= h) q[c] &= ~(0xffu << (8 * i));
+                }
+#pragma unroll
+                for (int c = 0; c < 4; c++) sum[e] = __builtin_amdgcn_sdot4((int)q[c], 0x01010101, sum[e], false);
+            }
+            mine[lane * 8 + (e ^ (lane & 7))] = u4{q[0], q[1], q[2], q[3]};
+        }
+        // (wave-private, as in weight_codes_kernel)
+        asm volatile("" ::: "memory");
+        int8_t* out = Wq + ((size_t)jt * KT + unit * 8) * TILE_BYTES;
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const int c = i * 64 + lane;  // piece of the unit, in the order of the tiles
+            const u4 piece = mine[(c & ~7) + ((c & 7) ^ ((c >> 3) & 7))];
+            if (unit * 8 + i < KT) *(u4*)(out + (size_t)c * 16) = piece;
+        }
+        asm volatile("" ::: "memory");
+    }
+    if constexpr (ZP) {
+#pragma unroll
+        for (int d = 4; d <= 32; d <<= 1)
+#pragma unroll
+            for (int e = 0; e < 8; e++) sum[e] += __shfl_xor(sum[e], d);
+        if (lane < 4) {
+#pragma unroll
+            for (int e = 0; e < 8; e++) s_sum[w][oct + e] = sum[e];
+        }
+        __syncthreads();
+        if (tid < 32 && jt * 32 + tid < o) {
+            int t = 0;
+            for (int q = 0; q < nw; q++) t += s_sum[q][tid];
+            zc[jt * 32 + tid].z = t;
+        }
+    }
+}
+
+// Waves of a workgroup of weight_strip_kernel and units per wave; 0: the kernels that read W twice take the call.
+// Up to 2 048 features a compute unit holds two workgroups, one of which loads while the other stores.  Above, it holds one, and the
+// time is that of whole rounds of the compute units: a round of 5 120 features takes 28.3 us, the two passes over W 0.139 us per
+// column tile, so that rounds have to be four fifths full (zeropoint, where the codes take longer: only where all
+// tiles are one round; 5 120 x 20 480 in two and a half 110.8 us here, 105.2 there).
+static int strip_waves(int h, int o, bool zeropoint, int cus, int* units)
+{
+    const int n = (h + 255) / 256, JT = row_tiles(o);
+    *units = n <= 8 || (zeropoint && n <= strip_max_waves(1)) ? 1 : zeropoint ? 3 : 2;
+    const int nw = (n + *units - 1) / *units;
+    if (o < 8 || nw > strip_max_waves(*units)) return 0;
+    const long rounds = (JT + cus - 1) / cus;
+    const bool take = n <= 8 || rounds == 1 || (!zeropoint && 5l * JT >= 4l * rounds * cus);
+    return take ? nw : 0;
+}
+
+template <int U, bool ZP>
+static hipError_t launch_weight_strip(const void* W, int h, int o, unsigned short* cw, int4* zc, int8_t* Wq, int nw, hipStream_t st)
+{
+    const int JT = row_tiles(o);
+    weight_strip_kernel<U, ZP><<<JT, nw * 64, nw * STRIP_STAGE, st>>>((const unsigned short*)W, h, o, cw, zc, Wq, k_tiles(h), JT);
+    return hipGetLastError();
+}
+
+// the dynamic LDS of every instantiation, once per device
+hipError_t weights_raise_lds()
+{
+    const void* k[4] = {(const void*)weight_strip_kernel<1, false>, (const void*)weight_strip_kernel<1, true>,
+                        (const void*)weight_strip_kernel<2, false>, (const void*)weight_strip_kernel<3, true>};
+    const int waves[4] = {strip_max_waves(1), strip_max_waves(1), strip_max_waves(2), strip_max_waves(3)};
+    for (int i = 0; i < 4; i++) {
+        const hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, waves[i] * STRIP_STAGE);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // At most n slabs of rows, of 32 rows (one pass of a workgroup over eight rows per wave) or a multiple of that
 static int whole_pass_slabs(int h, int n)
 {
@@ -241,8 +459,14 @@ static int whole_pass_slabs(int h, int n)
 hipError_t launch_quantize_weight(const void* W, int h, int o, unsigned short* part, int shared, unsigned short* cw,
                                   int8_t* Wq, hipStream_t st)
 {
+    int units, cus;
+    hipError_t e = prefill_device_setup(&cus);
+    if (e != hipSuccess) return e;
+    if (const int nw = shared ? 0 : strip_waves(h, o, false, cus, &units))
+        return units == 1 ? launch_weight_strip<1, false>(W, h, o, cw, nullptr, Wq, nw, st)
+                          : launch_weight_strip<2, false>(W, h, o, cw, nullptr, Wq, nw, st);
     const int nslab = whole_pass_slabs(h, colmax_slabs(h, o));
-    hipError_t e = launch_colmax_partial(W, h, o, part, nslab, true, st);
+    e = launch_colmax_partial(W, h, o, part, nslab, true, st);
     if (e != hipSuccess) return e;
     colconst_kernel<false><<<(o + 255) / 256, 1024, 0, st>>>(part, nullptr, nslab, o, cw, nullptr);
     e = hipGetLastError();
@@ -268,13 +492,19 @@ int zp_colrange_slabs(int h, int o)
 hipError_t launch_zp_quantize_weight(const void* W, int h, int o, int8_t* Wq, int4* zc, unsigned short* part,
                                      hipStream_t st)
 {
+    int units, cus;
+    hipError_t e = prefill_device_setup(&cus);
+    if (e != hipSuccess) return e;
+    if (const int nw = strip_waves(h, o, true, cus, &units))
+        return units == 1 ? launch_weight_strip<1, true>(W, h, o, nullptr, zc, Wq, nw, st)
+                          : launch_weight_strip<3, true>(W, h, o, nullptr, zc, Wq, nw, st);
     const int nslab = whole_pass_slabs(h, zp_colrange_slabs(h, o));
     const int rps = ((h + nslab - 1) / nslab + 31) & ~31;
     unsigned short* pmin = part;
     unsigned short* pmax = part + (size_t)nslab * o;
     zp_colrange_partial_kernel<<<dim3((o + 511) / 512, nslab), 256, 0, st>>>((const unsigned short*)W, h, o, pmin, pmax,
                                                                             rps);
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     colconst_kernel<true><<<(o + 255) / 256, 1024, 0, st>>>(pmax, pmin, nslab, o, nullptr, zc);
     e = hipGetLastError();

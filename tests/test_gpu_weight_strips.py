@@ -1,0 +1,45 @@
+"""The weight conversion that reads W once (32 columns to a workgroup, held in registers) at the edges of its units and of
+its rule, against the oracle: codes, constants and padding, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import have_gpu
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs a GPU")]
+
+# features: one lane group, one unit and one more, the last with one unit per wave and the first with two, with an odd number
+# of units, the largest and one past it; columns: the fewest, one past a tile, a ragged last tile, nothing aligned
+SIZES = [(16, 8), (1, 33), (255, 40), (257, 100), (2048, 72), (2049, 65), (4096, 33), (4097, 31), (5000, 77), (6144, 64),
+         (6145, 64), (300, 7)]
+
+
+@pytest.mark.parametrize("h,o", SIZES)
+@pytest.mark.parametrize("zeropoint", [False, True])
+def test_codes_and_constants(h, o, zeropoint):
+    import torch
+
+    import paper_2208_07339_amd as L
+    rng = np.random.default_rng([h, o])
+    W = rng.normal(0.0, 0.02, (h, o)).astype(np.float16)
+    W[:, 0] = 0                                # constant 0
+    W[h // 2, o - 1] = np.float16(3.0)         # the extremes in the last column and the last row
+    W[h - 1, o // 2] = np.float16(-5.0)
+    if zeropoint:
+        W[:, 1] = np.abs(W[:, 1]) + np.float16(1.0)   # a zeropoint far from 0
+    Wd = torch.from_numpy(W.view(np.int16)).cuda().view(torch.float16)
+    ws = L.Workspace.allocate(1, h, o, 1)
+    qw = L.zp_quantize_weight(Wd, ws) if zeropoint else L.quantize_weight(Wd, ws)
+    codes = L.export_weight(L.QuantizedWeight(qw.Wq, None, None, h, o)).cpu().numpy()
+    if zeropoint:
+        want = oracle.zp_quantize_weight(W)
+        zc = qw.zc.cpu().numpy()
+        assert np.array_equal(codes, want["Wq"])
+        assert np.array_equal(zc[:, 0] & 0xffff, want["lo"].view(np.uint16) & 0xffff)
+        assert np.array_equal((zc[:, 0] >> 16) & 0xffff, want["hi"].view(np.uint16) & 0xffff)
+        assert np.array_equal(zc[:, 1], want["zp"]) and np.array_equal(zc[:, 2], want["colsum"])
+    else:
+        Wq, cw = oracle.quantize_weight(W)
+        assert np.array_equal(codes, Wq) and np.array_equal(qw.cw.cpu().numpy(), cw)
+    # the padding (columns up to a multiple of 32, features up to a multiple of 128) is zero: the buffer sums to the codes
+    assert int(qw.Wq.cpu().to(torch.int64).abs().sum()) == int(np.abs(codes.astype(np.int64)).sum())
