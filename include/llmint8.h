@@ -274,6 +274,11 @@ int llmint8_debug_decode_shape(int cfg);
 enum { LLMINT8_KERNEL_TILED = 0, LLMINT8_KERNEL_STREAMING = 1, LLMINT8_KERNEL_KSPLIT = 2 };
 int llmint8_debug_kernel_for(int s, int h, int o, int zeropoint);
 
+/* Test/support: the MFMA of the tiled kernel for a product of [s x h] by [h x o] without the accumulator export, the
+ * tile forced by llmint8_debug_prefill_tile or chosen: 16 = v_mfma_i32_16x16x64_i8, 32 = v_mfma_i32_32x32x32_i8; -1 for a
+ * dimension < 1.  (The guarded variant keeps 32.)  Without a GPU, the answer for 256 compute units.  */
+int llmint8_debug_mfma_for(int s, int h, int o, int zeropoint);
+
 /* Test/support: private layouts -> plain row-major int8 ([h x o], [s x h]). */
 int llmint8_export_weight(const int8_t *Wq, int h, int o, int8_t *W_i8_rowmajor, llmint8_stream_t stream);
 int llmint8_export_rows(const int8_t *Xq, int s, int h, int8_t *X_i8_rowmajor, llmint8_stream_t stream);

@@ -16,7 +16,7 @@ SYMBOLS = [
     "llmint8_zp_quantize_weight", "llmint8_zp_quantize_rows", "llmint8_zp_matmul", "llmint8_zp_linear",
     "llmint8_export_weight",
     "llmint8_export_rows", "llmint8_debug_prefill_tile", "llmint8_debug_prefill_tile_for",
-    "llmint8_debug_decode_shape", "llmint8_debug_kernel_for",
+    "llmint8_debug_decode_shape", "llmint8_debug_kernel_for", "llmint8_debug_mfma_for",
 ]
 
 _lib = None
@@ -98,6 +98,8 @@ def lib():
     L.llmint8_debug_prefill_tile_for.argtypes = [i32, i32, i32]
     L.llmint8_debug_kernel_for.restype = i32
     L.llmint8_debug_kernel_for.argtypes = [i32, i32, i32, i32]
+    L.llmint8_debug_mfma_for.restype = i32
+    L.llmint8_debug_mfma_for.argtypes = [i32, i32, i32, i32]
     L.llmint8_debug_decode_shape.restype = i32
     L.llmint8_debug_decode_shape.argtypes = [i32]
     _lib = L
@@ -314,6 +316,11 @@ def debug_prefill_tile_for(s, h, o):
 def debug_kernel_for(s, h, o, zeropoint=False):
     """llmint8_debug_kernel_for: the kernel a product takes: 0 tiled, 1 weight-streaming, 2 .. 5 K split over the waves."""
     return int(lib().llmint8_debug_kernel_for(int(s), int(h), int(o), int(zeropoint)))
+
+
+def debug_mfma_for(s, h, o, zeropoint=False):
+    """llmint8_debug_mfma_for: 16 or 32, the MFMA the tiled kernel uses for a product."""
+    return int(lib().llmint8_debug_mfma_for(int(s), int(h), int(o), int(zeropoint)))
 
 
 def debug_decode_shape(cfg):

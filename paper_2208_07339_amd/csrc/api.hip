@@ -525,6 +525,12 @@ int llmint8_debug_kernel_for(int s, int h, int o, int zeropoint)
     return decode_kernel_takes(s, h, o, zeropoint != 0) ? LLMINT8_KERNEL_STREAMING : LLMINT8_KERNEL_TILED;
 }
 
+int llmint8_debug_mfma_for(int s, int h, int o, int zeropoint)
+{
+    if (s < 1 || h < 1 || o < 1) return -1;
+    return prefill_mfma_size(s, h, o, zeropoint != 0);
+}
+
 int llmint8_debug_decode_shape(int cfg)
 {
     if (cfg < -1 || cfg > LLMINT8_DECODE_SHAPES) return LLMINT8_INVALID_ARG;

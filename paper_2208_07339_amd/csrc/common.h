@@ -487,6 +487,7 @@ hipError_t launch_dequant_rows(const int8_t* Wq, const unsigned short* cw, int h
 // tile shape the prefill GEMM chooses for a product of s x h by h x o (host arithmetic only)
 int pick_cfg(int s, int h, int o);
 void prefill_tile_size(int s, int h, int o, int* cols, int* toks);
+int prefill_mfma_size(int s, int h, int o, bool zeropoint);
 // tile shape of the prefill GEMM forced by llmint8_debug_prefill_tile (-1: chosen from the shape)
 extern std::atomic<int> g_force_cfg;
 // work split of the decode kernel forced by llmint8_debug_decode_shape (-1: default)

@@ -794,15 +794,34 @@ constexpr int prefill_lds_bytes()
     return NB * (2 * WA + WQ * WB) * 2 * TILE_BYTES + 32768;  // operand ring + output staging (32 KiB over all waves)
 }
 
-// Which MFMA: 16 x 16 x 64 for the shapes of 256 tokens where three quarters of the compute units have a tile, else
-// 32 x 32 x 32.  On workload codes a register-only issue loop sustains 4 140 TOP/s with the former and 3 480 with the
+// Which MFMA: 16 x 16 x 64 in the shapes of 256 tokens where the chip is full for long enough, else 32 x 32 x 32.
+// On workload codes a register-only issue loop sustains 4 140 TOP/s with the former and 3 480 with the
 // latter at the board's power limit (on zeros 4 870 with both): a full chip runs at 1.75-1.8 GHz in place of 1.5-1.55 for 4 to 8 % more clocks
-// per stage (shorter MFMAs hide less of what is issued between them).  Where the clock is not limited by power only the latter shows: kernels with
-// 16 x 16 x 64 everywhere took 20.6 against 19.2 us on 96 x 5120 x 15360 (120 tiles) and 41.7 against 40.0 us per call on
-// 256 x 8192 x 8192 (128 tiles); at 192 tiles and more 307 against 336 us on 4096 x 5120 x 20480.  The guarded epilogue keeps 32 x 32 x 32.
+// per stage (shorter MFMAs hide less of what is issued between them).  Where power does not limit the clock only the latter shows, and
+// the epilogue takes longer with them: by 0.1 to 0.8 us per tile for absmax, for zeropoint by 0.6 us at 128 x 256, 1.8 at 256 x 256
+// and 2.8 at 192 x 256 (four token records to a lane instead of two, and 0, 32 and 84 spilled registers).
+// What K has to be for the one to outweigh the other depends on how full the rounds of tiles are, about as the cube.  Time with
+// 16 x 16 x 64 over time with 32 x 32 x 32, products in a graph, at a fill of 3/4 and of 1 (one box; another, whose power
+// limit bites earlier, is up to 0.05 lower for absmax and the same for zeropoint):
+//   absmax     256 x 256: K = 256 1.02 / 1.00,   768 1.01 / 0.97, 2 048 0.97 / 0.94, 12 288 0.95 / 0.90
+//              192 x 256: K = 256 1.05 / 1.02, 1 024 1.04 / 0.99, 2 048 1.01 / 0.98, 12 288 0.96 / 0.92
+//              128 x 256: K = 256 1.05 / 1.03,   768 1.03 / 1.01, 2 048 0.99 / 0.97, 12 288 0.94 / 0.92
+//   zeropoint  256 x 256: K = 256 1.11 / 1.04, 1 024 1.06 / 1.01, 2 048 1.03 / 1.00, 4 096 1.01 / 0.98, 12 288 0.99 / 0.97
+//              192 x 256: K = 256 1.12 / 1.10, 1 024 1.09 / 1.06, 4 096 1.04 / 1.02, 8 192 1.00 / 0.97, 12 288 1.01 / 0.98
+//              128 x 256: K = 256 1.06 / 1.05, 1 024 1.04 / 1.01, 2 048 1.02 / 1.00, 4 096 1.00 / 0.97, 12 288 0.99 / 0.96
+// (96 x 5120 x 15360, 120 tiles: 20.6 against 19.2 us; 256 x 8192 x 8192, 128 tiles: 41.7 against 40.0 us per call.)
+// The guarded epilogue keeps 32 x 32 x 32: 3 % slower with the other on 1013 x 4099 x 12301.
 template <int WB, int WQ>
 constexpr bool has_small_mfma() { return 32 * WQ * WB == 256; }
-static inline int small_mfma_from(int ncu) { return ncu / 4 * 3; }
+template <int WA, int WB, int WQ>
+static bool small_mfma_takes(int h, int o, int s, bool zeropoint, int ncu)
+{
+    if (!has_small_mfma<WB, WQ>()) return false;
+    constexpr double from[3][2] = {{640, 2048}, {1024, 8192}, {320, 2048}};  // [WA - 2][zeropoint]: K at a fill of 1
+    const long total = (long)((row_tiles(o) + 2 * WA - 1) / (2 * WA)) * ((row_tiles(s) + WQ * WB - 1) / (WQ * WB));
+    const double fill = (double)total / (double)((total + ncu - 1) / ncu * ncu);
+    return 4 * total >= 3l * ncu && h * fill * fill * fill >= from[WA - 2][zeropoint];
+}
 
 template <int WA, int WB, int WQ>
 static hipError_t raise_lds_limit()
@@ -869,7 +888,7 @@ static hipError_t launch_cfg(GemmArgs& g, hipStream_t st)
     // one whose case it is not returns at once (about 3 us for the empty launch).
     g.many_only = 0;
     if (g.fast_ok && !g.Cdbg) {
-        if (has_small_mfma<WB, WQ>() && grid >= small_mfma_from(ncu))
+        if (small_mfma_takes<WA, WB, WQ>(g.h, g.o, g.s, ZP, ncu))
             gemm_prefill_kernel<WA, WB, WQ, has_small_mfma<WB, WQ>() ? 16 : 32, ZP, false><<<grid, 128 * WQ, shm, st>>>(g);
         else
             gemm_prefill_kernel<WA, WB, WQ, 32, ZP, false><<<grid, 128 * WQ, shm, st>>>(g);
@@ -923,6 +942,20 @@ void prefill_tile_size(int s, int h, int o, int* c, int* t)
 }
 
 std::atomic<int> g_force_cfg{-1};  // test hook: tile shape override (-1 = automatic)
+
+// side of the MFMAs of the unguarded kernel that a product goes to (tile shape forced or chosen)
+int prefill_mfma_size(int s, int h, int o, bool zeropoint)
+{
+    int ncu = 256;
+    if (prefill_device_setup(&ncu) != hipSuccess) ncu = 256;
+    const int forced = g_force_cfg.load(std::memory_order_relaxed);
+    switch (forced >= 0 ? forced : pick_cfg(s, h, o)) {
+        case 0: return small_mfma_takes<4, 2, 4>(h, o, s, zeropoint, ncu) ? 16 : 32;
+        case 1: return small_mfma_takes<3, 4, 2>(h, o, s, zeropoint, ncu) ? 16 : 32;
+        case 2: return small_mfma_takes<2, 2, 4>(h, o, s, zeropoint, ncu) ? 16 : 32;
+        default: return 32;
+    }
+}
 
 hipError_t launch_gemm_prefill(const int8_t* Xq, const unsigned short* cx, const unsigned short* Xo,
                                const int32_t* count, int cap, const int8_t* Wq, const unsigned short* cw,

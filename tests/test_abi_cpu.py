@@ -124,6 +124,30 @@ def test_kernel_choice_of_the_matmul_calls(lib):
         lib.llmint8_debug_prefill_tile(-1)
 
 
+def test_mfma_choice_of_the_tiled_kernel(lib):
+    """Host logic, as on 256 compute units: 16 x 16 x 64 MFMAs only where rounds of 256-token tiles fill the chip and K is
+    long enough for how full they are, by tile shape and quantizer."""
+    import paper_2208_07339_amd as L
+    f = L.debug_mfma_for
+    # the benchmark's prefill workloads, both quantizers
+    for shape in [(4096, 5120, 20480), (2048, 49152, 12288), (2048, 4096, 4096)]:
+        assert f(*shape) == f(*shape, True) == 16
+    assert f(96, 5120, 15360) == f(256, 8192, 8192) == 32                 # too few tiles
+    assert f(512, 1023, 24576) == 32 and f(512, 1024, 24576) == 16         # 256 tiles of 192 x 256: a fill of 1
+    assert f(512, 8191, 24576, True) == 32 and f(512, 8192, 24576, True) == 16
+    assert f(512, 2427, 18432) == 32 and f(512, 2428, 18432) == 16         # 192 of them: 3/4, 1 024 / 0.75^3
+    assert f(512, 16384, 18240) == 32                                      # 190
+    try:
+        assert lib.llmint8_debug_prefill_tile(0) == 0                      # 256 x 256
+        assert f(1024, 319, 16384) == 32 and f(1024, 320, 16384) == 16 and f(1024, 2047, 16384, True) == 32
+        assert lib.llmint8_debug_prefill_tile(2) == 0                      # 128 x 256
+        assert f(1024, 639, 8192) == 32 and f(1024, 640, 8192) == 16 and f(1024, 2048, 8192, True) == 16
+        assert lib.llmint8_debug_prefill_tile(3) == 0 and f(4096, 8192, 8192) == 32
+    finally:
+        lib.llmint8_debug_prefill_tile(-1)
+    assert f(0, 4, 4) == -1 and f(4, 4, -1) == -1
+
+
 def test_benchmark_shapes_fit_the_static_scratch(lib):
     import paper_2208_07339_amd as L
     from paper_2208_07339_amd import workloads as wl

@@ -130,3 +130,30 @@ def test_many_column_factors_at_128_tokens():
     loads waited for one another, 1.28."""
     a, b = (prepare(s, 8192, 28672, 200, 256, zeropoint=True) for s in (128, 129))
     assert ratio(a, b) < 1.1
+
+
+@pytest.mark.parametrize("tile,cols", [(1, 192), (0, 256)])
+def test_short_sums_where_tiles_cover_three_quarters_of_the_chip(tile, cols):
+    """Zeropoint products of 256 features on 3/4 of the compute units against two tiles of 192 x 256 (256 x 256) less: 1.00, the
+    same MFMA.  With 16 x 16 x 64 from 3/4 on whatever K is, 1.09 (1.07)."""
+    import torch
+
+    import paper_2208_07339_amd as L
+    blocks = torch.cuda.get_device_properties(0).multi_processor_count * 3 // 8
+
+    def product(o, h=256):
+        g = torch.Generator(device="cuda").manual_seed(o)
+        X = torch.empty((512, h), dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+        W = torch.empty((h, o), dtype=torch.float16, device="cuda").normal_(0.0, 0.02, generator=g)
+        ws = L.Workspace.allocate(512, h, o, 32)
+        outl = L.find_outliers(X, 6.0, 32, ws)
+        out = torch.zeros((512, o), dtype=torch.float16, device="cuda")
+        qw, rows = L.zp_quantize_weight(W, ws), L.zp_quantize_rows(X, outl)
+        return lambda: L.zp_matmul(rows, outl, qw, ws, out)
+
+    L.debug_prefill_tile(tile)
+    try:
+        r = ratio(product(cols * blocks), product(cols * (blocks - 1)))
+    finally:
+        L.debug_prefill_tile(-1)
+    assert r < 1.045
