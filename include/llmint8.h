@@ -279,6 +279,11 @@ int llmint8_debug_kernel_for(int s, int h, int o, int zeropoint);
  * dimension < 1.  (The guarded variant keeps 32.)  Without a GPU, the answer for 256 compute units.  */
 int llmint8_debug_mfma_for(int s, int h, int o, int zeropoint);
 
+/* Test/support: how often llmint8_quantize_weight (zeropoint: llmint8_zp_quantize_weight) reads a W of [h x o]: 1 = in one
+ * kernel that keeps 32 columns in registers, 2 = in the kernels that take W of any size; -1 for a dimension < 1.  The
+ * coarser constants of llmint8_quantize_weight_granular always read it twice.  Without a GPU, the answer for 256 compute units. */
+int llmint8_debug_weight_reads_for(int h, int o, int zeropoint);
+
 /* Test/support: private layouts -> plain row-major int8 ([h x o], [s x h]). */
 int llmint8_export_weight(const int8_t *Wq, int h, int o, int8_t *W_i8_rowmajor, llmint8_stream_t stream);
 int llmint8_export_rows(const int8_t *Xq, int s, int h, int8_t *X_i8_rowmajor, llmint8_stream_t stream);

@@ -17,6 +17,7 @@ SYMBOLS = [
     "llmint8_export_weight",
     "llmint8_export_rows", "llmint8_debug_prefill_tile", "llmint8_debug_prefill_tile_for",
     "llmint8_debug_decode_shape", "llmint8_debug_kernel_for", "llmint8_debug_mfma_for",
+    "llmint8_debug_weight_reads_for",
 ]
 
 _lib = None
@@ -100,6 +101,8 @@ def lib():
     L.llmint8_debug_kernel_for.argtypes = [i32, i32, i32, i32]
     L.llmint8_debug_mfma_for.restype = i32
     L.llmint8_debug_mfma_for.argtypes = [i32, i32, i32, i32]
+    L.llmint8_debug_weight_reads_for.restype = i32
+    L.llmint8_debug_weight_reads_for.argtypes = [i32, i32, i32]
     L.llmint8_debug_decode_shape.restype = i32
     L.llmint8_debug_decode_shape.argtypes = [i32]
     _lib = L
@@ -321,6 +324,11 @@ def debug_kernel_for(s, h, o, zeropoint=False):
 def debug_mfma_for(s, h, o, zeropoint=False):
     """llmint8_debug_mfma_for: 16 or 32, the MFMA the tiled kernel uses for a product."""
     return int(lib().llmint8_debug_mfma_for(int(s), int(h), int(o), int(zeropoint)))
+
+
+def debug_weight_reads_for(h, o, zeropoint=False):
+    """llmint8_debug_weight_reads_for: 1 or 2, how often the conversion reads a W of [h x o]."""
+    return int(lib().llmint8_debug_weight_reads_for(int(h), int(o), int(zeropoint)))
 
 
 def debug_decode_shape(cfg):

@@ -531,6 +531,12 @@ int llmint8_debug_mfma_for(int s, int h, int o, int zeropoint)
     return prefill_mfma_size(s, h, o, zeropoint != 0);
 }
 
+int llmint8_debug_weight_reads_for(int h, int o, int zeropoint)
+{
+    if (h < 1 || o < 1) return -1;
+    return weight_reads(h, o, zeropoint != 0);
+}
+
 int llmint8_debug_decode_shape(int cfg)
 {
     if (cfg < -1 || cfg > LLMINT8_DECODE_SHAPES) return LLMINT8_INVALID_ARG;

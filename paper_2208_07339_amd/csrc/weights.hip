@@ -237,13 +237,14 @@ __global__ void __launch_bounds__(1024) zp_colsum_kernel(const int* __restrict__
 //
 // A lane holds 8 columns x 16 features per unit (16 loads of 16 bytes; four lanes side by side cover the 64 bytes that
 // the tile has in a row), a wave 256 features, so that the 16 codes of a 16-byte piece meet in one lane as in
-// weight_codes_kernel; wave w of the nw takes the units w, w + nw, ... (U of them).  What fits is h up to
-// 16 * 256 features with one unit to a wave and 12 * 2 * 256 with two (LDS swaps pieces between lanes, 8 KiB to a wave).
+// weight_codes_kernel; wave w of the nw takes the units w, w + nw, ... (U of them).  What fits in registers is 16 waves
+// of one unit, 12 of two (absmax, above 2 048 features: 150 registers) or 8 of three (zeropoint, above 4 096: 253), up to 6 144
+// features in all; LDS swaps pieces between lanes, 8 KiB to a wave.
 // Two tiles side by side share the 128-byte lines of W, and rows of 4 096 bytes or a multiple send all of a tile to one
 // L2 channel: each XCD takes a run of tiles side by side (neighbours alternating between the XCDs: 100.7 us instead of 85.1 on
 // 5 120 x 20 480).  What bounds it: the memory while all workgroups load; loading, coding and storing follow one
-// another in a workgroup.  Against the two passes over W, us: 4 096 x 4 096 16.7 / 20.2, 4 096 x 16 384 63.1 / 67.0, 2 048 x 49 152
-// 73.7 / 85.9, 3 333 x 5 001 16.1 / 29.1; zeropoint 4 096 x 8 192 25.9 / 44.2, 2 048 x 49 152 77.5 / 98.4.
+// another in a workgroup.  Against the two passes, W from memory, us:
+// 5 120 x 20 480 82.5 / 88.5, 4 096 x 8 192 28.1 / 33.0, 2 048 x 49 152 67.2 / 85.4; zeropoint 30.5 / 44.0 and 74.3 / 98.3 on the latter two.
 // ---------------------------------------------------------------------------
 constexpr int STRIP_WAVES = 16, STRIP_STAGE = 512 * 16;
 constexpr int strip_max_waves(int units) { return units == 1 ? 16 : units == 2 ? 12 : 8; }
@@ -413,19 +414,51 @@ __global__ void __launch_bounds__(64 * strip_max_waves(U))
 }
 
 // Waves of a workgroup of weight_strip_kernel and units per wave; 0: the kernels that read W twice take the call.
-// Up to 2 048 features a compute unit holds two workgroups, one of which loads while the other stores.  Above, it holds one, and the
-// time is that of whole rounds of the compute units: a round of 5 120 features takes 28.3 us, the two passes over W 0.139 us per
-// column tile, so that rounds have to be four fifths full (zeropoint, where the codes take longer: only where all
-// tiles are one round; 5 120 x 20 480 in two and a half 110.8 us here, 105.2 there).
+// Where the line lies was measured with W from memory (copies of W in turn; strips / two passes, us).
+// At most one strip to a compute unit: a unit takes its strip in at 20 to 30 GB/s and then codes it, however few strips
+// there are, while two passes spread over all units.  So tall strips need many of them: 5 120 x 2 048 26.4 / 18.2, x 4 096
+// 28.2 / 22.5, x 6 144 32.3 / 31.7, x 7 168 33.8 / 36.7 (zeropoint 35.9 / 25.7, 38.1 / 32.9, 39.7 / 39.7, 40.7 / 51.6); 3 072 x 2 048
+// 13.2 / 14.3, x 3 072 1.15 times the two passes.  That holds for rows of whole KiB (o a multiple of 512), which the two passes read in whole
+// blocks of 512 columns and which crowd a strip's loads on few memory channels.  With others strips are ahead (5 120 x 5 000 0.65
+// times the two passes, zeropoint 0.77) down to few of them, where it depends on how much of the last block of 512 columns
+// the two passes do for nothing (5 467 x 1 608 1.17, x 1 928 0.95, x 560 1.17, x 1 000 0.86; zeropoint 1.22, 1.03, 1.19, 0.94):
+// there the line is within 10 % of the faster one, elsewhere within 5 %.
+// More strips than units, up to 2 048 features, where a unit holds two workgroups: strips, but where the share of 1 or 2
+// to a unit is most uneven and the rows are whole KiB (2 048 x 9 216 24.0 / 23.3, x 10 240 25.1 / 23.5, x 12 288 24.8 / 24.9; zeropoint 24.8 / 30.9).
+// Above, the time is that of whole rounds of the units (absmax, 5 120 features: 28.3 us a round, the two passes 0.139 us per strip), which have to be
+// four fifths full; that up to 3 072 features two workgroups fit (absmax: 150 registers, 6 waves) changes little (2 560 x 10 240
+// 31.8 / 28.0, x 12 288 31.2 / 31.1, x 14 336 32.7 / 35.5).  Zeropoint there: only where all strips are one round (5 120 x 20 480,
+// where the codes take longer, 108.9 / 106.1).
 static int strip_waves(int h, int o, bool zeropoint, int cus, int* units)
 {
     const int n = (h + 255) / 256, JT = row_tiles(o);
     *units = n <= 8 || (zeropoint && n <= strip_max_waves(1)) ? 1 : zeropoint ? 3 : 2;
     const int nw = (n + *units - 1) / *units;
     if (o < 8 || nw > strip_max_waves(*units)) return 0;
-    const long rounds = (JT + cus - 1) / cus;
-    const bool take = n <= 8 || rounds == 1 || (!zeropoint && 5l * JT >= 4l * rounds * cus);
+    const bool kib_rows = o % 512 == 0;
+    bool take = true;
+    if (JT <= cus) {  // (lines in sixteenths of the compute units)
+        if (kib_rows) {
+            const int least = zeropoint ? (n > 20 ? 11 : n > 16 ? 13 : n > 12 ? 9 : 0) : n > 12 || n == 10 ? 13 : n > 10 ? 11 : 0;
+            take = 16 * JT >= least * cus || (!zeropoint && n <= 12 && 4 * JT <= cus);
+        } else if (n > (zeropoint ? 16 : 14)) {
+            const int many = zeropoint ? 6 : n > 20 ? 5 : 2, few = zeropoint ? 1 : 0;
+            take = 16 * JT >= many * cus || (16 * JT > few * cus && o % 512 >= 288);
+        }
+    } else if (n <= 8) {
+        take = zeropoint || !kib_rows || n < 7 || 16l * JT >= 21l * cus;
+    } else {
+        take = !zeropoint && 5l * JT >= 4l * ((JT + cus - 1) / cus) * cus;
+    }
     return take ? nw : 0;
+}
+
+// how often a conversion reads W
+int weight_reads(int h, int o, bool zeropoint)
+{
+    int units, cus = 256;
+    if (prefill_device_setup(&cus) != hipSuccess) cus = 256;
+    return strip_waves(h, o, zeropoint, cus, &units) ? 1 : 2;
 }
 
 template <int U, bool ZP>

@@ -148,6 +148,24 @@ def test_mfma_choice_of_the_tiled_kernel(lib):
     assert f(0, 4, 4) == -1 and f(4, 4, -1) == -1
 
 
+def test_kernel_choice_of_the_weight_conversion(lib):
+    """Host logic, as on 256 compute units: 1 = W read once, 32 columns to a workgroup; 2 = read twice."""
+    import paper_2208_07339_amd as L
+    f = L.debug_weight_reads_for
+    # the weights of the benchmark's workloads
+    assert f(5120, 20480) == 1 and f(5120, 20480, True) == 2 and f(4096, 4096) == 2 and f(4096, 8192, True) == 1
+    assert f(12288, 49152) == f(49152, 12288) == f(6145, 8192) == f(6145, 8192, True) == 2
+    assert f(256, 512) == f(256, 512, True) == 1 and f(300, 7) == f(300, 7, True) == 2
+    # few tall strips
+    assert f(6144, 2048) == f(6144, 2048, True) == f(5120, 4096) == f(5120, 4096, True) == 2
+    assert f(5120, 6144) == 2 and f(5120, 7168) == f(5120, 7168, True) == 1
+    assert f(3333, 5001) == f(3333, 5001, True) == f(5120, 5000) == f(5120, 5000, True) == 1
+    # rounds of the compute units that are badly filled
+    assert f(2048, 10240) == 2 and f(2048, 12288) == f(2048, 49152) == f(2048, 10240, True) == 1
+    assert f(5120, 257 * 32) == 2 and f(5120, 410 * 32) == 1 and f(5120, 410 * 32, True) == 2
+    assert f(0, 4) == -1 and f(4, -1) == -1
+
+
 def test_benchmark_shapes_fit_the_static_scratch(lib):
     import paper_2208_07339_amd as L
     from paper_2208_07339_amd import workloads as wl

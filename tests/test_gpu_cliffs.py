@@ -157,3 +157,29 @@ def test_short_sums_where_tiles_cover_three_quarters_of_the_chip(tile, cols):
     finally:
         L.debug_prefill_tile(-1)
     assert r < 1.045
+
+
+@pytest.mark.parametrize("zeropoint", [False, True])
+def test_conversion_of_a_tall_w_of_few_columns(zeropoint):
+    """6 144 against 6 145 features of 2 048 columns, from memory (another W each call): 1.0, both read W twice.  With the
+    one-read kernel on 64 compute units, 1.6 (zeropoint 1.4)."""
+    import torch
+
+    import paper_2208_07339_amd as L
+
+    def convert(h, o):
+        Ws = [torch.randn((h, o), dtype=torch.float16, device="cuda") for _ in range(20)]
+        ws = L.Workspace.allocate(1, h, o, 1)
+        Wq = torch.empty(L.wq_bytes(h, o), dtype=torch.int8, device="cuda")
+        c = torch.empty((o, 4), dtype=torch.int32, device="cuda")
+        f = L.lib().llmint8_zp_quantize_weight if zeropoint else L.lib().llmint8_quantize_weight
+        n = [0]
+
+        def call():
+            n[0] += 1
+            W = Ws[n[0] % len(Ws)]
+            assert f(W.data_ptr(), h, o, Wq.data_ptr(), c.data_ptr(), ws.buf.data_ptr(), ws.nbytes,
+                     torch.cuda.current_stream().cuda_stream) == 0
+        return call
+
+    assert ratio(convert(6144, 2048), convert(6145, 2048)) < 1.15
