@@ -496,6 +496,6 @@ extern std::atomic<int> g_decode_cfg;
 // returns the device's number of compute units.  Thread-safe; cheap after the first call on a device.
 hipError_t prefill_device_setup(int* compute_units);
 int weight_reads(int h, int o, bool zeropoint);  // 1 or 2: the kernels that a conversion (vector-wise, zeropoint) takes
-hipError_t weights_raise_lds();  // its part for the kernels of weights.hip
+hipError_t weights_device_setup(int* compute_units);  // its part for the kernels of weights.hip, all that these need
 
 }  // namespace llmint8

@@ -864,9 +864,8 @@ hipError_t prefill_device_setup(int* cus)
     if ((e = raise_lds_limit<2, 2, 2>()) != hipSuccess) return e;
     if ((e = raise_lds_limit<3, 2, 2>()) != hipSuccess) return e;
     if ((e = raise_lds_limit<3, 1, 2>()) != hipSuccess) return e;
-    if ((e = weights_raise_lds()) != hipSuccess) return e;
     int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) n = 256;
+    if ((e = weights_device_setup(&n)) != hipSuccess) return e;
     *cus = n;
     if (cached) g_dev_cus[dev].store(n, std::memory_order_release);
     return hipSuccess;

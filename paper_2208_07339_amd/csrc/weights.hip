@@ -3,6 +3,8 @@
 //
 // The constants need every row of a column before its first code.  Where the columns of a tile fit a workgroup's
 // registers W is read once (weight_strip_kernel, 3 bytes per weight over HBM), else twice (5 bytes), which bounds these kernels.
+#include <mutex>
+
 #include "common.h"
 
 namespace llmint8 {
@@ -453,14 +455,6 @@ static int strip_waves(int h, int o, bool zeropoint, int cus, int* units)
     return take ? nw : 0;
 }
 
-// how often a conversion reads W
-int weight_reads(int h, int o, bool zeropoint)
-{
-    int units, cus = 256;
-    if (prefill_device_setup(&cus) != hipSuccess) cus = 256;
-    return strip_waves(h, o, zeropoint, cus, &units) ? 1 : 2;
-}
-
 template <int U, bool ZP>
 static hipError_t launch_weight_strip(const void* W, int h, int o, unsigned short* cw, int4* zc, int8_t* Wq, int nw, hipStream_t st)
 {
@@ -469,17 +463,36 @@ static hipError_t launch_weight_strip(const void* W, int h, int o, unsigned shor
     return hipGetLastError();
 }
 
-// the dynamic LDS of every instantiation, once per device
-hipError_t weights_raise_lds()
+// Once per device, for the conversions: the dynamic LDS of weight_strip_kernel's instantiations and the compute units (as
+// prefill_device_setup(), which calls this, does it for the tiled kernel: a program that only converts need not wait for
+// its 36 instantiations, 2 ms in all).
+hipError_t weights_device_setup(int* cus)
 {
+    constexpr int MAX_DEVICES = 64;
+    static std::atomic<int> done[MAX_DEVICES];  // 0: not set up yet; else the device's compute units
+    static std::mutex lock;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const bool cached = dev >= 0 && dev < MAX_DEVICES;
+    if (cached && (*cus = done[dev].load(std::memory_order_acquire)) > 0) return hipSuccess;
+    std::lock_guard<std::mutex> hold(lock);
     const void* k[4] = {(const void*)weight_strip_kernel<1, false>, (const void*)weight_strip_kernel<1, true>,
                         (const void*)weight_strip_kernel<2, false>, (const void*)weight_strip_kernel<3, true>};
     const int waves[4] = {strip_max_waves(1), strip_max_waves(1), strip_max_waves(2), strip_max_waves(3)};
-    for (int i = 0; i < 4; i++) {
-        const hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, waves[i] * STRIP_STAGE);
-        if (e != hipSuccess) return e;
-    }
+    for (int i = 0; i < 4; i++)
+        if ((e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, waves[i] * STRIP_STAGE)) != hipSuccess) return e;
+    if (hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || *cus < 1) *cus = 256;
+    if (cached) done[dev].store(*cus, std::memory_order_release);
     return hipSuccess;
+}
+
+// how often a conversion reads W
+int weight_reads(int h, int o, bool zeropoint)
+{
+    int units, cus = 256;
+    if (weights_device_setup(&cus) != hipSuccess) cus = 256;
+    return strip_waves(h, o, zeropoint, cus, &units) ? 1 : 2;
 }
 
 // At most n slabs of rows, of 32 rows (one pass of a workgroup over eight rows per wave) or a multiple of that
@@ -493,7 +506,7 @@ hipError_t launch_quantize_weight(const void* W, int h, int o, unsigned short* p
                                   int8_t* Wq, hipStream_t st)
 {
     int units, cus;
-    hipError_t e = prefill_device_setup(&cus);
+    hipError_t e = weights_device_setup(&cus);
     if (e != hipSuccess) return e;
     if (const int nw = shared ? 0 : strip_waves(h, o, false, cus, &units))
         return units == 1 ? launch_weight_strip<1, false>(W, h, o, cw, nullptr, Wq, nw, st)
@@ -526,7 +539,7 @@ hipError_t launch_zp_quantize_weight(const void* W, int h, int o, int8_t* Wq, in
                                      hipStream_t st)
 {
     int units, cus;
-    hipError_t e = prefill_device_setup(&cus);
+    hipError_t e = weights_device_setup(&cus);
     if (e != hipSuccess) return e;
     if (const int nw = strip_waves(h, o, true, cus, &units))
         return units == 1 ? launch_weight_strip<1, true>(W, h, o, nullptr, zc, Wq, nw, st)

@@ -43,3 +43,29 @@ def test_codes_and_constants(h, o, zeropoint):
         assert np.array_equal(codes, Wq) and np.array_equal(qw.cw.cpu().numpy(), cw)
     # the padding (columns up to a multiple of 32, features up to a multiple of 128) is zero: the buffer sums to the codes
     assert int(qw.Wq.cpu().to(torch.int64).abs().sum()) == int(np.abs(codes.astype(np.int64)).sum())
+
+
+def test_the_first_conversion_of_a_process_sets_up_the_conversions_only():
+    """In a fresh process the first conversion takes a small part of what llmint8_init still has to do after it: 0.09.  With
+    the set-up of every kernel in the first conversion, 0.37."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = r'''
+import sys, time
+sys.path.insert(0, %r)
+import torch
+import paper_2208_07339_amd as L
+W = torch.zeros((512, 1024), dtype=torch.float16, device="cuda")
+ws = L.Workspace.allocate(1, 512, 1024, 1)
+torch.cuda.synchronize()
+t = [time.perf_counter()]
+for f in (lambda: L.zp_quantize_weight(W, ws), L.init):
+    f()
+    t.append(time.perf_counter())
+print("ratio", (t[1] - t[0]) / (t[2] - t[1]))
+''' % root
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    assert float(r.stdout.split()[1]) < 0.22
