@@ -140,6 +140,7 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
     constexpr int TW = 2 * WA, TX = WQ * WB;     // row tiles of W and of X in the workgroup tile
     constexpr int PIECES = (TW + TX) / WQ;       // direct loads per wave per stage
     static_assert(PIECES * WQ == TW + TX && (WQ == 2 || WQ == 4), "the pieces of a stage must divide evenly among the waves");
+    static_assert(T == 32 || !GUARDED, "the guarded epilogue is written for T = 32");
     constexpr int STAGE = (TW + TX) * 2 * TILE_BYTES;
     constexpr int CT = 32 / T;                   // MFMA tiles along each side of a 32 x 32 tile
     constexpr int KS = T / 16;                   // MFMA k-steps of a stage
@@ -540,9 +541,8 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
             return wa;
         };
         auto load_x_mem = [&](int i, int t0) {
-            const bool in = T == 32 || t0 + 8 * gl < opad;  // (opad is a multiple of 16)
-            const v8h xb = *(const v8h*)(g.Xo + (size_t)(i < s ? i : s - 1) * opad + (in ? t0 + 8 * gl : 0));
-            return i < s && in ? xb : (v8h)(0);
+            const v8h xb = *(const v8h*)(g.Xo + (size_t)(i < s ? i : s - 1) * opad + t0 + 8 * gl);
+            return i < s ? xb : (v8h)(0);
         };
 
         // FAST: operands from the LDS image of the epilogue stages, no guards.  Its stores go
@@ -556,18 +556,20 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
             __builtin_amdgcn_make_buffer_rsrc(g.Out + (size_t)cI0w * o, 0, trows * o * 2, 0x00020000);
         auto epilogue = [&](auto F) {
             constexpr bool FAST = decltype(F)::value;
-            if (!FAST && g.Cdbg) {
+            if constexpr (!FAST) {
+                if (g.Cdbg) {
 #pragma unroll
-                for (int a = 0; a < CT * WA; a++)
+                    for (int a = 0; a < WA; a++)
 #pragma unroll
-                    for (int b = 0; b < CT * WB; b++) {
-                        const int i = I0 + b * T + ll;
+                        for (int b = 0; b < WB; b++) {
+                            const int i = I0 + b * 32 + ll;
 #pragma unroll
-                        for (int r = 0; r < 4 * RG; r++) {
-                            const int j = J0 + a * T + 8 * (r >> 2) + 4 * gl + (r & 3);
-                            if (i < s && j < o) g.Cdbg[(size_t)i * o + j] = acc[a][b][r];
+                            for (int r = 0; r < 16; r++) {
+                                const int j = J0 + a * 32 + 8 * (r >> 2) + 4 * gl + (r & 3);
+                                if (i < s && j < o) g.Cdbg[(size_t)i * o + j] = acc[a][b][r];
+                            }
                         }
-                    }
+                }
             }
             float sx[CT * WB];  // c_x / 127^2 of this lane's tokens (Eq. 7: S = c_x (x) c_w / 127^2)
             double zsa[ZP ? CT * WB : 1], zza[ZP ? CT * WB : 1], zrs[ZP ? CT * WB : 1];  // zeropoint: D_x / 254, zp_x, row sum of the codes
@@ -576,7 +578,7 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
             for (int b = 0; b < CT * WB; b++) {
                 const int il = wq * 32 * WB + b * T + ll;  // token within the workgroup tile
                 const int i = cI0w + il;
-                if (FAST) {
+                if constexpr (FAST) {
                     if constexpr (ZP) {
                         const int4 rec = EZx[il];
                         zsa[b] = zp_range((unsigned)rec.x) * (1.0 / 254.0);
@@ -603,7 +605,7 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                         sx[b] = (i < s) ? cxi : 0.0f;
                     }
 #pragma unroll
-                    for (int ks = 0; ks < XS; ks++) xb[b][ks] = cnt > ks * SP ? load_x_mem(i, ks * SP) : (v8h)(0);
+                    for (int ks = 0; ks < 2; ks++) xb[b][ks] = cnt > ks * 16 ? load_x_mem(i, ks * 16) : (v8h)(0);
                 }
             }
             // zeropoint: this wave's 32*WA columns of the three factor planes, copied once per tile into a
@@ -635,7 +637,7 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                 for (int aa = 0; aa < 2 * CT; aa++) {
                     if (aa >= CT * na) break;
                     const int jl = wp * 32 * WA + a0 * 32 + aa * T;  // first column of the MFMA tile within the workgroup tile
-                    if (FAST) {
+                    if constexpr (FAST) {
                         if constexpr (!ZP) {
 #pragma unroll
                             for (int rr = 0; rr < RG; rr++) cwv[aa][rr] = *(const v4h*)(ECw + jl + 8 * rr + 4 * gl);
@@ -648,7 +650,7 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                     } else {
                         if constexpr (!ZP) {
 #pragma unroll
-                            for (int rr = 0; rr < RG; rr++) {
+                            for (int rr = 0; rr < 4; rr++) {
                                 const int j = cJ0w + jl + 8 * rr + 4 * gl;  // c_w is 8-byte aligned
                                 unsigned short q[4] = {0, 0, 0, 0};
                                 if (j + 4 <= o) {
@@ -663,7 +665,7 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
                             }
                         }
 #pragma unroll
-                        for (int ks = 0; ks < XS; ks++) wa[aa][ks] = cnt > ks * SP ? load_w_mem(cJ0w + jl + ll, ks * SP) : (v8h)(0);
+                        for (int ks = 0; ks < 2; ks++) wa[aa][ks] = cnt > ks * 16 ? load_w_mem(cJ0w + jl + ll, ks * 16) : (v8h)(0);
                     }
                 }
                 STAMP(6 + 6 * (a0 / 2));
@@ -685,9 +687,9 @@ __global__ void __launch_bounds__(128 * WQ, 1) gemm_prefill_kernel(const GemmArg
 #pragma unroll
                         for (int ks = 0; ks < XS; ks++)
                             if (cnt > ks * SP) mm(wa[aa][ks], xb[CT * b0 + bb][ks]);
-                        if (!FAST)
-                            for (int t0 = OSLOTS; t0 < cnt; t0 += SP)  // more than 32 outlier columns: rare
-                                mm(load_w_mem(J0 + (CT * a0 + aa) * T + ll, t0), load_x_mem(I0 + (CT * b0 + bb) * T + ll, t0));
+                        if constexpr (!FAST)
+                            for (int t0 = OSLOTS; t0 < cnt; t0 += 16)  // more than 32 outlier columns: rare
+                                mm(load_w_mem(J0 + (a0 + aa) * 32 + ll, t0), load_x_mem(I0 + (b0 + bb) * 32 + ll, t0));
                         return t;
                     };
                     // T = 16: the whole block's together, so that no output waits for its own (2 048 x 4 096 x 4 096: 6.1 k -> 4.3 k
