@@ -232,8 +232,8 @@ int llmint8_zp_linear(const void *X_f16, int s, int h, float alpha, const int8_t
 
 /* Measurement support: the ceilings the roofline fractions are held against, measured on the box itself.
  * llmint8_probe_mfma: one workgroup per compute unit runs a register-only issue loop of the int8 MFMA
- *   in the shape of the prefill GEMM's main loop (Eq. 7: 4 x 4 accumulator tiles per wave, 64 MFMAs per
- *   iteration), its operands read once from the tiled int8 buffers A_tiles / B_tiles (llmint8_xq_bytes /
+ *   (16 x 16 x 64) in the shape of the prefill GEMM's main loop (Eq. 7: eight waves, 8 x 4 accumulator tiles each,
+ *   64 MFMAs per iteration), its operands read once from the tiled int8 buffers A_tiles / B_tiles (llmint8_xq_bytes /
  *   llmint8_wq_bytes layouts, or a buffer of zeros; at least one 1 KiB tile each): no memory traffic in
  *   the loop, so its rate is what the matrix cores sustain on operands with those statistics.  *ops (host,
  *   may be NULL) receives the int8 operations the launch performs; time it with events on the stream.

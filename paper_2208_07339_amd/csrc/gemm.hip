@@ -68,7 +68,7 @@ struct GemmArgs {
 // 192 x 128 and 192 x 64 with four.  Eight waves read each X tile from LDS twice as often, but two
 // waves per SIMD cover each other's waits in the epilogue, which takes 7.5 k
 // to 9 k clocks instead of 13 k at 256 x 256 (the K loop is fed by the same
-// loads: 1 100-1 170 clocks per stage either way); measured A/B on one box:
+// loads: 1 100-1 170 clocks per stage either way); measured A/B on one box, with T = 32:
 // 338.5 against 344.7 us on a 4096 x 5120 x 20480 product, 38.1 against
 // 39.3 us on 2048 x 4096 x 4096.  192 x 256 does not split evenly over eight
 // waves (14 row tiles).
@@ -912,8 +912,9 @@ static inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 // unit pulls operands at once, the third short X, where the call is bound by streaming W once and compute
 // units without a tile waste their share of that stream (with 192-column tiles a 49 152-column weight matrix
 // is exactly one tile per compute unit).  The constants are fitted to the kernel times of all six shapes on
-// five weight matrices at 33 to 1 024 tokens and to the three full-size workloads: the choice is then within
-// 0.8 % of the fastest shape on average and 9 % in the worst case (5 120 x 20 480 at 1 024 tokens).
+// five weight matrices at 33 to 1 024 tokens and to the three full-size workloads, all of them with 32 x 32 x 32 MFMAs (the
+// choice was within 0.8 % of the fastest shape on average).  Not refitted to the other MFMA in the 256-token shapes: over 77
+// products of 33 to 4 096 tokens it is 1.8 % behind the fastest shape on average, worst 1 536 x 8 192 x 8 192 (102.8 us, 256 x 256: 81.7).
 constexpr int NCFG = 6;
 static const int cols[NCFG] = {256, 192, 128, 128, 192, 192}, toks[NCFG] = {256, 256, 256, 128, 128, 64};
 int pick_cfg(int s, int h, int o)
