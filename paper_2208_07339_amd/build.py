@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libllmint8.so")
 LIB_STAMPS = os.path.join(HERE, "libllmint8_stamps.so")  # measurement build: see build(stamps=True)
-SOURCES = ["api.hip", "weights.hip", "prepass.hip", "gemm.hip", "decode.hip", "small.hip", "ksplit.hip", "zeropoint.hip", "ceiling.hip"]
+SOURCES = ["api.hip", "weights.hip", "prepass.hip", "rows.hip", "gemm.hip", "decode.hip", "small.hip", "ksplit.hip", "zeropoint.hip", "ceiling.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

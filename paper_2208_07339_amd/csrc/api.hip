@@ -152,6 +152,8 @@ int llmint8_find_outliers(const void* X_f16, int s, int h, float alpha, int32_t*
     char* base = (char*)ws_base(ws);
     const OutlierLists L = carve_outlier_lists(base, h, cap);
     unsigned short* part = (unsigned short*)(base + scratch_ws(h, cap));
+    const int nrec = scan_records(s, h, cap, slab_ws(s, h) + rowpart_ws(s, h));
+    if (nrec) return hip_status(launch_outlier_scan(X_f16, s, h, threshold_bits(alpha), part, nrec, idx, cap, count, status, st));
     const int nslab = colmax_slabs(s, h);
     hipError_t e = launch_colmax_partial(X_f16, s, h, part, nslab, false, st);
     if (e == hipSuccess) e = launch_outlier_lists(part, nslab, h, threshold_bits(alpha), L, cap, st);
@@ -169,6 +171,9 @@ int llmint8_quantize_rows_granular(const void* X_f16, int s, int h, const int32_
         misaligned(cx_f16, 2) || misaligned(Xo_f16, 16))
         return LLMINT8_INVALID_ARG;
     if (h > LLMINT8_MAX_H) return LLMINT8_SHAPE;
+    if (granularity != LLMINT8_TENSORWISE && row_codes_takes(s, h, cap, RowCall::known, 0))
+        return hip_status(launch_quantize_rows_known(X_f16, s, h, idx, count, cap, Xq, (unsigned short*)cx_f16, nullptr,
+                                                     (unsigned short*)Xo_f16, (hipStream_t)stream));
     return hip_status(launch_quantize_rows(X_f16, s, h, idx, count, cap, Xq, (unsigned short*)cx_f16,
                                            (unsigned short*)Xo_f16, granularity == LLMINT8_TENSORWISE,
                                            (hipStream_t)stream));
@@ -283,6 +288,13 @@ static int linear_impl(const void* X_f16, int s, int h, float alpha, int granula
         e = launch_prepass_small(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status,
                                  (unsigned short*)cx_f16, (unsigned short*)Xo_f16, Xq, shared_cx, st, nullptr,
                                  W_f16 ? nullptr : &job);
+    } else if (!shared_cx && !(std::isinf(alpha) && alpha > 0.0f) &&
+               row_codes_takes(s, h, cap, W_f16 ? RowCall::absmax : RowCall::rebuilt, scan_ws(s, h, o, cap) - scratch_ws(h, cap))) {
+        // X read once: codes by rows held in registers, then the outlier set settled
+        const ColumnJob job = {Wq, cw_f16, base + scan_ws(s, h, o, cap), o, (o + 255) & ~255};
+        e = launch_prepass_rows(X_f16, s, h, threshold_bits(alpha), base + scratch_ws(h, cap), idx, cap, count, status, Xq,
+                                (unsigned short*)cx_f16, nullptr, (unsigned short*)Xo_f16, W_f16 ? nullptr : &job, st);
+        have_rows = true;
     } else if (!shared_cx && !(std::isinf(alpha) && alpha > 0.0f) && prepass_mid_takes(s, h, cap, false, slab_ws(s, h) + rowpart_ws(s, h))) {
         OutlierLists Lm = L;  // the partial row maxima in the place of the slab maxima
         Lm.rowpart = (unsigned short*)(base + scratch_ws(h, cap));
@@ -402,6 +414,9 @@ int llmint8_zp_quantize_rows(const void* X_f16, int s, int h, const int32_t* idx
         misaligned(zc_x, 16) || misaligned(Xo_f16, 16))
         return LLMINT8_INVALID_ARG;
     if (h > LLMINT8_MAX_H) return LLMINT8_SHAPE;
+    if (row_codes_takes(s, h, cap, RowCall::known, 0))
+        return hip_status(launch_quantize_rows_known(X_f16, s, h, idx, count, cap, Xq, nullptr, (int4*)zc_x,
+                                                     (unsigned short*)Xo_f16, (hipStream_t)stream));
     return hip_status(launch_zp_quantize_rows(X_f16, s, h, idx, count, cap, Xq, (int4*)zc_x, (unsigned short*)Xo_f16,
                                               (hipStream_t)stream));
 }
@@ -474,6 +489,11 @@ int llmint8_zp_linear(const void* X_f16, int s, int h, float alpha, const int8_t
                                zp_col_pitch(o)};
         r = hip_status(launch_prepass_small(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status, nullptr,
                                             (unsigned short*)Xo_f16, Xq, 0, (hipStream_t)stream, (int4*)zc_x, &job));
+    } else if (row_codes_takes(s, h, cap, RowCall::zeropoint, scan_ws(s, h, o, cap) - scratch_ws(h, cap))) {
+        char* base = (char*)ws_base(ws);
+        const ColumnJob job = {Wq, zc_w, base + scan_ws(s, h, o, cap) + rows_ws(o, cap), o, zp_col_pitch(o)};
+        r = hip_status(launch_prepass_rows(X_f16, s, h, threshold_bits(alpha), base + scratch_ws(h, cap), idx, cap, count, status, Xq,
+                                           nullptr, (int4*)zc_x, (unsigned short*)Xo_f16, &job, (hipStream_t)stream));
     } else if (prepass_mid_takes(s, h, cap, true, slab_ws(s, h) + rowpart_ws(s, h))) {
         char* base = (char*)ws_base(ws);
         OutlierLists L = carve_outlier_lists(base, h, cap);

@@ -291,6 +291,37 @@ __device__ inline unsigned short dequant_bits(int q, unsigned cwb)
     return (unsigned short)(sign | bits);
 }
 
+// Column j of the outlier rows of W rebuilt from the codes, as dequant_rows_kernel writes them: slot t holds row idx[t],
+// zeros from |O| to opad; slots first .. end - 1.  idx[0 .. cnt) is in LDS, so that a thread's loads of its column's codes
+// do not wait for one another.
+constexpr int JOB_SLOTS = 32;  // slots that a workgroup of a column job takes where they are dealt out
+__device__ __forceinline__ void rebuild_rows(const int8_t* __restrict__ Wq, const unsigned short* __restrict__ cw, int h, int o,
+                                             int KT, const int* idx, int cnt, int first, int end,
+                                             unsigned short* __restrict__ Wo, int j)
+{
+    const int8_t* col = Wq + (size_t)(j >> 5) * KT * TILE_BYTES;  // column j of W: row j & 31 of these tiles
+    const unsigned cwb = cw[j];
+    const int stop = cnt > end ? end : cnt;
+    for (int t0 = first; t0 < stop; t0 += 8) {
+        // requested without conditions so that they are in flight together (a slot past the count or with an index that
+        // does not exist reads some other row and is not valid)
+        int q[8];
+        bool ok[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const unsigned k = (unsigned)idx[t0 + u < cnt ? t0 + u : 0];
+            ok[u] = t0 + u < cnt && k < (unsigned)h;
+            const unsigned kk = k < (unsigned)h ? k : 0u;
+            q[u] = col[(size_t)(kk >> 5) * TILE_BYTES + tile_byte(j & 31, (int)(kk & 31))];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            if (t0 + u < stop)  // the same for every thread: no arithmetic for the empty slots
+                Wo[(size_t)(t0 + u) * o + j] = ok[u] ? dequant_bits(q[u], cwb) : (unsigned short)0;
+    }
+    for (int t = stop < first ? first : stop; t < end; t++) Wo[(size_t)t * o + j] = 0;
+}
+
 // Smallest magnitude bit pattern whose value is >= alpha (0 if alpha <= 0,
 // 0x7c00 if no finite fp16 reaches alpha).
 __host__ inline unsigned threshold_bits(float alpha)
@@ -424,6 +455,19 @@ bool prepass_mid_takes(int s, int h, int cap, bool zeropoint, size_t room);
 hipError_t launch_prepass_mid(const void* X, int s, int h, unsigned thr, OutlierLists L, int32_t* idx, int cap,
                               int32_t* count, int32_t* status, unsigned short* cx, unsigned short* Xo, int8_t* Xq,
                               hipStream_t st, int4* zc, const ColumnJob* cj);
+// The pre-pass with X read once (rows.hip), for the calls row_codes_takes() says (room: bytes at `records`): cx or, zc != NULL,
+// zeropoint records; a column job as above.  launch_quantize_rows_known: the outlier columns are in idx / count already.
+enum class RowCall { absmax, rebuilt /* absmax without 16-bit weights */, zeropoint, known };
+bool row_codes_takes(int s, int h, int cap, RowCall call, size_t room);
+hipError_t launch_prepass_rows(const void* X, int s, int h, unsigned thr, void* records, int32_t* idx, int cap,
+                               int32_t* count, int32_t* status, int8_t* Xq, unsigned short* cx, int4* zc,
+                               unsigned short* Xo, const ColumnJob* cj, hipStream_t st);
+hipError_t launch_quantize_rows_known(const void* X, int s, int h, const int32_t* idx, const int32_t* count, int cap,
+                                      int8_t* Xq, unsigned short* cx, int4* zc, unsigned short* Xo, hipStream_t st);
+// the stand-alone scan through records (how many fit in room; 0: it does not take these sizes)
+int scan_records(int s, int h, int cap, size_t room);
+hipError_t launch_outlier_scan(const void* X, int s, int h, unsigned thr, void* records, int nrec, int32_t* idx, int cap,
+                               int32_t* count, int32_t* status, hipStream_t st);
 // constants and codes of W (weights.hip); part: scratch for colmax_slabs(h, o) * o magnitudes; shared: one constant
 // for all columns
 hipError_t launch_quantize_weight(const void* W, int h, int o, unsigned short* part, int shared, unsigned short* cw,

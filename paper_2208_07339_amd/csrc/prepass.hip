@@ -454,7 +454,6 @@ __device__ __forceinline__ void list_entries(const int* list, int n, F f)
 // MID: more than one row tile, a row of workgroups (blockIdx.y) for each; and the rows of W that a column job rebuilds
 // are split over workgroups too, JOB_SLOTS to each, or a large outlier buffer's would take a column's thread longer than
 // a kernel of their own (64 x 4096 x 4096, cap 256, 200 columns found: 84 -> 32 us).
-constexpr int JOB_SLOTS = 32;
 template <bool ZP, bool MID, bool RAGGED>
 __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned short* __restrict__ X, int s, int h,
                                                              OutlierLists L, int capc, int vec_ok,
@@ -508,34 +507,9 @@ __global__ void __launch_bounds__(256) quantize_small_kernel(const unsigned shor
         if constexpr (ZP) {
             zp_col_factors(cj.Wq, (const int4*)cj.wconst, h, cj.o, KT, s_idx, cnt, cj.pitch, (double*)cj.out, j);
         } else {
-            // the outlier rows of W rebuilt from the codes, as dequant_rows_kernel writes them: slot t holds
-            // row idx[t], zeros from |O| to opad
-            if (j >= cj.o) return;
-            const int8_t* col = cj.Wq + (size_t)(j >> 5) * KT * TILE_BYTES;  // column j of W: row j & 31 of these tiles
-            // codes of column j in outlier rows t0 .. t0+7, requested without conditions so that they are in flight together
-            // (a slot past the count or with an index that does not exist reads some other row and is not valid)
-            auto codes8 = [&](int t0, int* q, bool* ok) {
-#pragma unroll
-                for (int u = 0; u < 8; u++) {
-                    const unsigned k = (unsigned)s_idx[t0 + u < cnt ? t0 + u : 0];
-                    ok[u] = t0 + u < cnt && k < (unsigned)h;
-                    const unsigned kk = k < (unsigned)h ? k : 0u;
-                    q[u] = col[(size_t)(kk >> 5) * TILE_BYTES + tile_byte(j & 31, (int)(kk & 31))];
-                }
-            };
-            const unsigned cwb = ((const unsigned short*)cj.wconst)[j];
-            unsigned short* Wo = (unsigned short*)cj.out;
-            const int end = MID && first + JOB_SLOTS < opad ? first + JOB_SLOTS : opad, stop = MID && cnt > end ? end : cnt;
-            for (int t0 = first; t0 < stop; t0 += 8) {
-                int c8[8];
-                bool ok[8];
-                codes8(t0, c8, ok);
-#pragma unroll
-                for (int u = 0; u < 8; u++)
-                    if (t0 + u < stop)  // the same for every thread: no arithmetic for the empty slots
-                        Wo[(size_t)(t0 + u) * cj.o + j] = ok[u] ? dequant_bits(c8[u], cwb) : (unsigned short)0;
-            }
-            for (int t = MID && stop < first ? first : stop; t < end; t++) Wo[(size_t)t * cj.o + j] = 0;
+            if (j < cj.o)
+                rebuild_rows(cj.Wq, (const unsigned short*)cj.wconst, h, cj.o, KT, s_idx, cnt, first,
+                             MID && first + JOB_SLOTS < opad ? first + JOB_SLOTS : opad, (unsigned short*)cj.out, j);
         }
         return;
     }

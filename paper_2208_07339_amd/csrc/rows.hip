@@ -1,0 +1,875 @@
+// Hidden states of 33 tokens and more: constants and codes with X read once.
+//
+// row_codes_kernel     a workgroup holds a few whole rows in registers.  Inside the one-call entry points the outlier
+//                      columns are not known yet: the kernel takes its rows' constants over the entries below the
+//                      threshold, which is right unless the entry that decides sits in a column that another row
+//                      makes an outlier, writes the codes, and leaves the list of the columns in which its own rows
+//                      reach the threshold.  With the columns known (KNOWN: the stand-alone calls) the constants are
+//                      final and the gathered columns Xo are written too.
+// settle_rows_kernel   joins the lists to the outlier set, writes idx, count, status and Xo, clears the codes of
+//                      entries below the threshold in outlier columns, and makes the rows anew whose constant came
+//                      from one of those (or all rows, where more columns qualify than the buffer takes: the columns
+//                      past its end are ordinary ones).
+// outlier_scan_kernel  the lists alone, merge_records_kernel the set from them: the stand-alone scan.
+#include "common.h"
+
+namespace llmint8 {
+
+typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+
+// A record: the outlier columns that one workgroup found.  Word 0 counts them, words 1 .. hold the first cap + 1 of them in
+// ascending order: the set is cut after cap columns, none of its first cap columns is missing from the first cap of the
+// lists that have it, and one more says that there are more.  A multiple of 32 bytes each.
+__host__ __device__ inline int record_words(int cap) { return (2 + cap + 15) & ~15; }
+
+namespace {
+
+// Sixteen features of a row as eight words of two: whole-word operations and the packed 16-bit instructions.  (From vectors
+// of sixteen-bit elements the compiler takes words apart and puts them together again: 24 instructions for the
+// eight of mags().)
+struct w8 { unsigned w[8]; };
+
+__device__ __forceinline__ w8 words(us8 a, us8 b)
+{
+    const u4 x = __builtin_bit_cast(u4, a), y = __builtin_bit_cast(u4, b);
+    return {{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]}};
+}
+__device__ __forceinline__ unsigned pk_max_u16(unsigned a, unsigned b)
+{
+    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(us2, a), __builtin_bit_cast(us2, b)));
+}
+// two fp16 values each, finite: larger and smaller as numbers (the operators of the language insert an instruction per
+// operand that only signalling NaNs need)
+__device__ __forceinline__ unsigned pk_max_f16(unsigned a, unsigned b)
+{
+    unsigned r;
+    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ unsigned pk_min_f16(unsigned a, unsigned b)
+{
+    unsigned r;
+    asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ w8 mags(const w8& v)
+{
+    w8 a;
+#pragma unroll
+    for (int q = 0; q < 8; q++) a.w[q] = v.w[q] & 0x7fff7fffu;
+    return a;
+}
+// the largest of 16 magnitudes
+__device__ __forceinline__ unsigned top16(const w8& a)
+{
+    const unsigned m = pk_max_u16(pk_max_u16(pk_max_u16(a.w[0], a.w[1]), pk_max_u16(a.w[2], a.w[3])),
+                                  pk_max_u16(pk_max_u16(a.w[4], a.w[5]), pk_max_u16(a.w[6], a.w[7])));
+    const unsigned lo = m & 0xffffu, hi = m >> 16;
+    return lo > hi ? lo : hi;
+}
+
+// The columns whose bits are set in bitmap[0 .. nw), as a record: by one wave.
+__device__ __forceinline__ void write_record(const unsigned* bitmap, int nw, int lane, int cap, unsigned short* rec)
+{
+    const int q = (nw + 63) >> 6, b0 = lane * q, b1 = min(nw, b0 + q);
+    int mine = 0;
+    for (int b = b0; b < b1; b++) mine += __popc(bitmap[b]);
+    int incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(incl, d);
+        if (lane >= d) incl += t;
+    }
+    if (lane == 63) rec[0] = (unsigned short)min(incl, 0xffff);
+    int pos = incl - mine;
+    if (mine)
+        for (int b = b0; b < b1 && pos <= cap; b++)
+            for (unsigned x = bitmap[b]; x && pos <= cap; x &= x - 1) rec[1 + pos++] = (unsigned short)(b * 32 + __ffs(x) - 1);
+}
+
+// The bits of those of 16 magnitudes that reach thr = t1 + 1, t2 = t1 | t1 << 16: per pair a saturating subtraction that leaves
+// 0 below the threshold, a minimum with 1, and the two bits into place.
+__device__ __forceinline__ unsigned reach16(const w8& a, unsigned t2)
+{
+    unsigned f = 0;
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+        unsigned x;
+        asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(x) : "v"(a.w[q]), "v"(t2));
+        asm("v_pk_min_u16 %0, %1, %2" : "=v"(x) : "v"(x), "v"(0x10001u));
+        f |= ((x | x >> 15) & 3u) << (2 * q);
+    }
+    return f;
+}
+
+// a word of two features with ones where their bits (2q, 2q + 1) are set
+__device__ __forceinline__ unsigned spread(unsigned bits, int q)
+{
+    return __builtin_amdgcn_perm((unsigned)__builtin_amdgcn_sbfe((int)bits, 2 * q + 1, 1), (unsigned)__builtin_amdgcn_sbfe((int)bits, 2 * q, 1), 0x05040100u);
+}
+__device__ __forceinline__ void clear16(w8& v, unsigned off)
+{
+#pragma unroll
+    for (int q = 0; q < 8; q++) v.w[q] &= ~spread(off, q);
+}
+
+// 16 codes of a row, from its 16 features: absmax.  code_bits() (common.h) with the half of a word picked by the instruction
+// that converts and multiplies.
+__device__ __forceinline__ unsigned code_of(unsigned w, float f, bool high)
+{
+    float q;
+    if (high)
+        asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(q) : "v"(w), "v"(f));
+    else
+        asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(q) : "v"(w), "v"(f));
+    const float t = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, q) & ~7u);
+    return __builtin_bit_cast(unsigned, t + 12582912.0f);
+}
+__device__ __forceinline__ u4 codes16(const w8& v, float f)
+{
+    u4 r;
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+        r[e] = pack_low_bytes(code_of(v.w[2 * e], f, false), code_of(v.w[2 * e], f, true), code_of(v.w[2 * e + 1], f, false),
+                              code_of(v.w[2 * e + 1], f, true));
+    return r;
+}
+
+// zeropoint; features whose bit in `off` is set have no code (0).  sum: of the codes
+__device__ __forceinline__ u4 zp_codes16(const w8& v, double f, int z, unsigned off, int& sum)
+{
+    u4 r;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        unsigned c[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) c[e] = zp_u_bits((unsigned short)(v.w[2 * q + (e >> 1)] >> (16 * (e & 1))), f) - (unsigned)z;
+        r[q] = pack_low_bytes(c[0], c[1], c[2], c[3]);
+    }
+    if (off) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const unsigned o4 = (off >> (4 * q)) & 0xfu;
+            r[q] &= ~(((o4 & 1u) | (o4 & 2u) << 7 | (o4 & 4u) << 14 | (o4 & 8u) << 21) * 0xffu);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) sum = __builtin_amdgcn_sdot4((int)r[q], 0x01010101, sum, false);
+    return r;
+}
+
+// Which of the features c .. c+15 do not exist in a row of h
+__device__ __forceinline__ unsigned past_row(int c, int h)
+{
+    return c + 16 <= h ? 0u : (c < h ? (0xffffu << (h - c)) & 0xffffu : 0xffffu);
+}
+
+// The extremes of 16 values into hi and lo, two of each in a word
+__device__ __forceinline__ void range16(const w8& v, unsigned& hi, unsigned& lo)
+{
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+        hi = pk_max_f16(hi, v.w[q]);
+        lo = pk_min_f16(lo, v.w[q]);
+    }
+}
+// the same without the features whose bit in `off` is set: they take part as the lowest and the highest finite value
+__device__ __forceinline__ void range16_without(const w8& v, unsigned off, unsigned& hi, unsigned& lo)
+{
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+        const unsigned m = spread(off, q);
+        hi = pk_max_f16(hi, (v.w[q] & ~m) | (0xfbfffbffu & m));
+        lo = pk_min_f16(lo, (v.w[q] & ~m) | (0x7bff7bffu & m));
+    }
+}
+__device__ __forceinline__ void keys_of(unsigned hi, unsigned lo, unsigned& kmin, unsigned& kmax)
+{
+    const unsigned k0 = f16_key(lo & 0xffffu), k1 = f16_key(lo >> 16), k2 = f16_key(hi & 0xffffu), k3 = f16_key(hi >> 16);
+    kmin = k1 < k0 ? k1 : k0;
+    kmax = k3 > k2 ? k3 : k2;
+}
+
+__device__ __forceinline__ void add_bit(unsigned* bitmap, unsigned j)
+{
+    if (!((*(volatile unsigned*)&bitmap[j >> 5] >> (j & 31)) & 1u)) atomicOr(&bitmap[j >> 5], 1u << (j & 31));  // (mostly there already)
+}
+
+}  // namespace
+
+// ---------------------------------------------------------------------------
+// R = 2^LR rows per workgroup of NT threads, N groups of 16 features per thread.  Lane l of a wave holds row l % R: a
+// wave's 16-byte stores are R * 16 bytes side by side in the tiled layout, its loads 64 / R * 32 bytes of each row.
+//
+// Bound by memory where X is large and by its own arithmetic close behind (about 100 instructions for 16 features, a third of
+// a large call's time), by one workgroup's chain of loads, two barriers and stores where it is not.  Us, against the floor of
+// 2.8 us of launch and drain and 6.9 TB/s, and against what took its place before (colmax_rowmax, outlier_lists, row_const and
+// quantize_rows, the kernel below included in both): 4096 x 5120 13.5 (floor 11.9), with settle_rows 19.8 / 33; 2048 x 4096 7.8
+// (6.4), 12.2 / 20; 1013 x 4099 7.7 (4.6), 12.8 / 19; 2048 x 49152 71 (46), 82 / 103; zeropoint 2048 x 5120 11.4 (7.4), 16.5 / 27.
+// The columns that a workgroup's own rows make outliers are left out at once, between the two barriers: where outlier columns
+// are outliers in most tokens, eight rows know nearly all of them and settle_rows_kernel has next to nothing to take back.
+// ---------------------------------------------------------------------------
+struct RowArgs {
+    const unsigned short* X;
+    int s, h, KT, cap, opad;
+    unsigned thr;          // !KNOWN
+    const int32_t *idx, *count;  // KNOWN
+    unsigned short* rec;   // !KNOWN: a record per workgroup
+    int8_t* Xq;
+    unsigned short* cx;    // absmax
+    int4* zc;              // zeropoint
+    unsigned short* Xo;    // KNOWN
+};
+
+// RAGGED: h is not a multiple of 128 or X not 16-byte aligned.
+template <int N, int LR, int NT, bool ZP, bool KNOWN, bool RAGGED>
+__global__ void __launch_bounds__(NT, N <= 3 ? 8 : N <= 4 ? 7 : N <= 5 ? 6 : N <= 7 ? 5 : N <= 8 ? 4 : 3) row_codes_kernel(const RowArgs g)
+{
+    constexpr int R = 1 << LR, STEP = NT >> LR, NW = NT / 64;
+    extern __shared__ unsigned bitmap[];  // ceil(h / 32) words
+    __shared__ unsigned red[ZP ? 2 : 1][NW][R];
+    __shared__ int s_sum[ZP ? NW : 1][R], s_like[ZP && !KNOWN ? NW : 1][R];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & (R - 1);
+    const int s = g.s, h = g.h, G = g.KT * 2;
+    // Row groups that share 128-byte lines of the codes go to one XCD, one after the other.
+    const int nb = gridDim.x, xcd = blockIdx.x & 7;
+    const int rg = xcd * (nb >> 3) + min(xcd, nb & 7) + (blockIdx.x >> 3);
+    const int i = rg * R + r;
+    const bool valid = i < s;  // (a row past the last one: the last one again, its constant and codes zero in the end)
+    const unsigned short* row = g.X + (size_t)(valid ? i : s - 1) * h;
+    const int g0 = w * (64 >> LR) + (lane >> LR);  // this lane's first group
+    // first feature of this lane's group n; past the last group: the last one again
+    auto first = [&](int n) { return (n < N - 1 ? g0 + n * STEP : min(g0 + n * STEP, G - 1)) * 16; };
+    w8 v[N];
+    us8 x[N][2];
+#pragma unroll
+    for (int n = 0; n < N; n++) {
+        const int c = first(n);
+        x[n][0] = RAGGED ? chunk_load(row, c, h) : *(const us8*)(row + c);
+        x[n][1] = RAGGED ? chunk_load(row, c + 8, h) : *(const us8*)(row + c + 8);
+    }
+    const int nw = (h + 31) >> 5;
+    for (int q = tid; q < nw; q += NT) bitmap[q] = 0;
+    int cnt = 0;
+    if constexpr (KNOWN) {
+        cnt = *g.count;
+        cnt = cnt < 0 ? 0 : (cnt > g.cap ? g.cap : cnt);
+    }
+    __syncthreads();
+    if constexpr (KNOWN) {
+        for (int t = tid; t < cnt; t += NT) {
+            const unsigned j = (unsigned)g.idx[t];
+            if (j < (unsigned)h) atomicOr(&bitmap[j >> 5], 1u << (j & 31));
+        }
+        for (int q = tid; q < R * g.opad; q += NT) {
+            const int rr = q / g.opad, t = q - rr * g.opad, ii = rg * R + rr;
+            unsigned short x = 0;
+            if (t < cnt && ii < s) {
+                const unsigned j = (unsigned)g.idx[t];
+                if (j < (unsigned)h) x = g.X[(size_t)ii * h + j];
+            }
+            if (ii < s) g.Xo[(size_t)ii * g.opad + t] = x;
+        }
+    }
+    // ---- the columns that reach the threshold
+    unsigned top[N];  // largest magnitude of each group
+    const unsigned thr2 = (g.thr ? g.thr - 1 : 0) * 0x10001u, all = g.thr ? 0u : 0xffffu;
+#pragma unroll
+    for (int n = 0; n < N; n++) {
+        const int c = first(n);
+        if (RAGGED && c + 16 > h) {
+            x[n][0] = chunk_fix(x[n][0], c, h);
+            x[n][1] = chunk_fix(x[n][1], c + 8, h);
+        }
+        v[n] = words(x[n][0], x[n][1]);
+        if (KNOWN) continue;
+        const w8 a = mags(v[n]);
+        top[n] = top16(a);
+        if (top[n] >= g.thr) {
+            unsigned f = reach16(a, thr2) | all;
+            if (RAGGED) f &= ~past_row(c, h);
+            if (!RAGGED || f) atomicOr(&bitmap[c >> 5], f << (c & 31));
+        }
+        // (opaque: what was worked out from them is not kept for later)
+#pragma unroll
+        for (int q = 0; q < 8; q++) asm volatile("" : "+v"(v[n].w[q]));
+    }
+    __syncthreads();
+    // ---- constants of the rows, without those columns
+    unsigned skip[ZP ? (N + 1) / 2 : 1];  // zeropoint: features without a code, 16 bits per group
+    unsigned mx = 0, kmin = 0xffffu, kmax = 0;
+    unsigned hi = 0xfbfffbffu, lo = 0x7bff7bffu;
+    if constexpr (ZP) {
+#pragma unroll
+        for (int n = 0; n < (N + 1) / 2; n++) skip[n] = 0;
+    }
+#pragma unroll
+    for (int n = 0; n < N; n++) {
+        const int c = first(n);
+        unsigned off = !RAGGED || c < h ? (bitmap[c >> 5] >> (c & 31)) & 0xffffu : 0u;
+        if constexpr (ZP) {
+            if (RAGGED) off |= past_row(c, h);
+            if (__any(off != 0)) {
+                range16_without(v[n], off, hi, lo);
+                skip[n / 2] |= off << (16 * (n & 1));
+            } else {
+                range16(v[n], hi, lo);
+            }
+        } else {
+            unsigned m = KNOWN ? 0u : top[n];
+            const bool some = __any(off != 0);
+            if (some) clear16(v[n], off);
+            if (KNOWN || some) m = top16(mags(v[n]));
+            mx = m > mx ? m : mx;
+        }
+    }
+    if constexpr (ZP) keys_of(hi, lo, kmin, kmax);
+    const unsigned mykeys = kmin | kmax << 16;
+#pragma unroll
+    for (int d = 32; d >= R; d >>= 1) {
+        if constexpr (ZP) {
+            const unsigned a = (unsigned)__shfl_xor((int)kmin, d), b = (unsigned)__shfl_xor((int)kmax, d);
+            kmin = a < kmin ? a : kmin;
+            kmax = b > kmax ? b : kmax;
+        } else {
+            const unsigned t = (unsigned)__shfl_xor((int)mx, d);
+            mx = t > mx ? t : mx;
+        }
+    }
+    if (lane < R) {
+        if constexpr (ZP) {
+            red[0][w][r] = kmin;
+            red[1][w][r] = kmax;
+        } else {
+            red[0][w][r] = mx;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NW; q++) {
+        if constexpr (ZP) {
+            kmin = red[0][q][r] < kmin ? red[0][q][r] : kmin;
+            kmax = red[1][q][r] > kmax ? red[1][q][r] : kmax;
+        } else {
+            mx = red[0][q][r] > mx ? red[0][q][r] : mx;
+        }
+    }
+    // ---- codes
+    int8_t* dst = g.Xq + ((size_t)((rg * R) >> 5) * g.KT) * TILE_BYTES + (((rg * R) & 31) + r) * 16;
+    int sum = 0;
+    int4 rec = make_int4(0, 0, 0, 0);
+    double D = 0.0;
+    if constexpr (ZP) {
+        if (valid && kmin <= kmax) rec = make_const(kmin, kmax);
+        D = zp_factor(zp_range((unsigned)rec.x));
+    }
+    const float f = !ZP && valid ? code_factor(f16_bits_to_float((unsigned short)mx)) : 0.0f;
+#pragma unroll
+    for (int n = 0; n < N; n++) {
+        const int grp = g0 + n * STEP;
+        if (n < N - 1 || grp < G) {
+            if constexpr (ZP)
+                *(u4*)(dst + (size_t)grp * 512) = zp_codes16(v[n], D, rec.y, (skip[n / 2] >> (16 * (n & 1))) & 0xffffu, sum);
+            else
+                *(u4*)(dst + (size_t)grp * 512) = codes16(v[n], f);
+        }
+    }
+    if constexpr (ZP) {
+#pragma unroll
+        for (int d = 32; d >= R; d >>= 1) sum += __shfl_xor(sum, d);
+        if (lane < R) s_sum[w][r] = sum;
+        if constexpr (!KNOWN) {  // how many threads have the smallest and the largest, for settle_rows_kernel
+            const unsigned long long mine = (R == 8 ? 0x0101010101010101ull : R == 4 ? 0x1111111111111111ull : R == 2 ? 0x5555555555555555ull : ~0ull) << r;
+            const int n0 = __popcll(__ballot((mykeys & 0xffffu) == kmin) & mine), n1 = __popcll(__ballot(mykeys >> 16 == kmax) & mine);
+            if (lane < R) s_like[w][r] = n0 | n1 << 16;
+        }
+        __syncthreads();
+        if (tid < R && valid) {
+            sum = 0;
+#pragma unroll
+            for (int q = 0; q < NW; q++) sum += s_sum[q][r];
+            rec.z = sum;
+            if constexpr (!KNOWN) {
+#pragma unroll
+                for (int q = 0; q < NW; q++) rec.w += s_like[q][r];
+            }
+            g.zc[i] = rec;
+        }
+    } else {
+        if (tid < R && valid) g.cx[i] = (unsigned short)mx;
+    }
+    if (!KNOWN && w == NW - 1) write_record(bitmap, nw, lane, g.cap, g.rec + (size_t)rg * record_words(g.cap));
+}
+
+// The records' columns into the bitmap (cleared here), U records in flight per thread
+template <int U>
+__device__ __forceinline__ void gather_records(const unsigned short* __restrict__ rec, int nrec, int cap, int nw, unsigned* bitmap)
+{
+    const int tid = threadIdx.x, pitch = record_words(cap);
+    // Most records name the same columns.  Sixteen of them go into the bitmap first, two columns to a thread; of the others only
+    // those that know more add anything.  (Every record's columns added to the bitmap by its thread, 64 at a time to one
+    // word of LDS: 34 us for 2 048 records of 20 columns.)
+    us8 a[U], b[U];
+    auto request = [&](int r0) {
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int r = r0 + 256 * u < nrec ? r0 + 256 * u : nrec - 1;
+            a[u] = *(const us8*)(rec + (size_t)r * pitch);
+            b[u] = *(const us8*)(rec + (size_t)r * pitch + 8);
+        }
+    };
+    const int e0 = tid & 15;
+    const unsigned short* seed = rec + (size_t)((long long)(tid >> 4) * nrec >> 4) * pitch;
+    const int sn = min((int)seed[0], cap + 1);
+    const unsigned sj = seed[e0], sk = seed[min(16 + e0, pitch - 1)];
+    request(tid);
+    for (int q = tid; q < nw; q += 256) bitmap[q] = 0;
+    __syncthreads();
+    if (e0 > 0 && e0 <= sn) add_bit(bitmap, sj);
+    if (16 + e0 <= sn) add_bit(bitmap, sk);
+    __syncthreads();
+    for (int r0 = tid; r0 < nrec; r0 += 256 * U) {
+        if (r0 != tid) request(r0);
+        int n[U], most = 0;
+        unsigned known[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            n[u] = r0 + 256 * u < nrec ? min((int)a[u][0], cap + 1) : 0;
+            known[u] = ~0u;
+            most = n[u] > most ? n[u] : most;
+        }
+        // eight columns (e, ... of each record, from word k of a piece) looked up together
+        auto look = [&](const us8* piece, int e, int k0) {
+#pragma unroll
+            for (int u = 0; u < U; u++)
+#pragma unroll
+                for (int k = k0; k < 8; k++) {
+                    const bool in = e + k - k0 < n[u];
+                    const unsigned j = in ? piece[u][k] : 0u;
+                    const unsigned word = bitmap[j >> 5] >> (j & 31);
+                    known[u] &= in ? word : ~0u;
+                }
+        };
+        look(a, 0, 1);
+        if (__any(most > 7)) look(b, 7, 0);
+        if (__any(most > 15)) {
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int r = r0 + 256 * u < nrec ? r0 + 256 * u : nrec - 1;
+                a[u] = *(const us8*)(rec + (size_t)r * pitch + min(16, pitch - 8));
+                b[u] = *(const us8*)(rec + (size_t)r * pitch + min(24, pitch - 8));
+            }
+            look(a, 15, 0);
+            if (__any(most > 23)) look(b, 23, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (n[u] > 31 || !(known[u] & 1u)) {
+                const unsigned short* p = rec + (size_t)(r0 + 256 * u) * pitch;
+                for (int e = 0; e < n[u]; e += 8) {
+                    unsigned short c[8];
+#pragma unroll
+                    for (int k = 0; k < 8; k++) c[k] = p[1 + (e + k < n[u] ? e + k : e)];
+#pragma unroll
+                    for (int k = 0; k < 8; k++) add_bit(bitmap, c[k]);
+                }
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The outlier set from the records, by all 256 threads of a workgroup: s_idx[0 .. min(total, cap)) ascending.  bitmap:
+// ceil(h / 32) words of LDS, left with the bits of all qualifying columns.  Returns their number.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ int join_records(const unsigned short* __restrict__ rec, int nrec, int cap, int nw, unsigned* bitmap,
+                                            int* s_idx)
+{
+    __shared__ int s_wsum[4];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (nrec <= 256)
+        gather_records<1>(rec, nrec, cap, nw, bitmap);
+    else
+        gather_records<4>(rec, nrec, cap, nw, bitmap);
+    __syncthreads();
+    const int q = (nw + 255) >> 8, b0 = tid * q, b1 = min(nw, b0 + q);
+    int mine = 0;
+    for (int x = b0; x < b1; x++) mine += __popc(bitmap[x]);
+    int incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(incl, d);
+        if (lane >= d) incl += t;
+    }
+    if (lane == 63) s_wsum[w] = incl;
+    __syncthreads();
+    int woff = 0, total = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        if (k < w) woff += s_wsum[k];
+        total += s_wsum[k];
+    }
+    int pos = woff + incl - mine;
+    if (mine)
+        for (int x = b0; x < b1 && pos < cap; x++)
+            for (unsigned m = bitmap[x]; m && pos < cap; m &= m - 1) s_idx[pos++] = x * 32 + __ffs(m) - 1;
+    __syncthreads();
+    return total;
+}
+
+// ---------------------------------------------------------------------------
+// A workgroup settles SR = 8 rows (32 lanes each); the workgroups past the rows take a column job.  A chain of round trips:
+// records, columns of X and codes, stores; 4 us for 256 records, 6.3 for 512, 10.5 for 1 024 of 20 columns (2.8 of them launch
+// and drain).
+// ---------------------------------------------------------------------------
+constexpr int SR = 8;
+
+template <bool ZP>
+__global__ void __launch_bounds__(256) settle_rows_kernel(const unsigned short* __restrict__ X, int s, int h, unsigned thr,
+                                                          const unsigned short* __restrict__ rec, int nrec,
+                                                          int32_t* __restrict__ idx, int cap, int opad,
+                                                          int32_t* __restrict__ count, int32_t* __restrict__ status,
+                                                          int8_t* __restrict__ Xq, int KT, unsigned short* __restrict__ cx,
+                                                          int4* __restrict__ zc, unsigned short* __restrict__ Xo,
+                                                          ColumnJob cj)
+{
+    extern __shared__ unsigned bitmap[];
+    __shared__ int s_idx[JOB_MAX_CAP];
+    __shared__ unsigned s_need;
+    __shared__ unsigned s_red[2][4];
+    __shared__ int s_sum[4];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int nw = (h + 31) >> 5, nrows = (s + SR - 1) / SR;
+    const int i = (int)blockIdx.x * SR + (tid >> 5);
+    const bool mine = i < s;
+    unsigned m1 = 0;
+    int4 z = make_int4(0, 0, 0, 0);
+    if constexpr (ZP)
+        z = zc[mine ? i : 0];
+    else
+        m1 = cx[mine ? i : 0];
+    if (tid == 0) s_need = 0;
+    const int total = join_records(rec, nrec, cap, nw, bitmap, s_idx);
+    const int cnt = total < cap ? total : cap;
+    if ((int)blockIdx.x >= nrows) {
+        const int jb = (int)blockIdx.x - nrows, parts = cj.pitch >> 8;
+        const int j = (jb % parts) * 256 + tid;
+        if constexpr (ZP)
+            zp_col_factors(cj.Wq, (const int4*)cj.wconst, h, cj.o, KT, s_idx, cnt, cj.pitch, (double*)cj.out, j);
+        else if (j < cj.o)
+            rebuild_rows(cj.Wq, (const unsigned short*)cj.wconst, h, cj.o, KT, s_idx, cnt, jb / parts * JOB_SLOTS,
+                         min(jb / parts * JOB_SLOTS + JOB_SLOTS, opad), (unsigned short*)cj.out, j);
+        return;
+    }
+    if (blockIdx.x == 0) {
+        for (int t = tid; t < cnt; t += 256) idx[t] = s_idx[t];
+        if (tid == 0) {
+            *count = cnt;
+            if (status) *status = total > cap ? 1 : 0;
+        }
+    }
+    const unsigned short* row = X + (size_t)(mine ? i : 0) * h;
+    // An entry below the threshold in an outlier column went into its row's constants and has a code if no row of its
+    // workgroup reached the threshold there.  Where it is an extreme of the row (its code is then 127 in magnitude) and
+    // the row may have no other like it, the row is made anew; else its code goes.
+    int8_t* q = Xq + (size_t)(mine ? i >> 5 : 0) * KT * TILE_BYTES;
+    bool need = total > cap;
+    int gone = 0, nlo = 0, nhi = 0;  // zeropoint: sum of the codes that go, entries that are the smallest, the largest
+    for (int t = tid & 31; t < opad; t += 32) {
+        const int j = t < cnt ? s_idx[t] : 0;
+        int8_t* at = q + (size_t)(j >> 5) * TILE_BYTES + tile_byte(i & 31, j & 31);
+        const unsigned short x = t < cnt ? row[j] : (unsigned short)0;
+        const int code = *at;
+        if (mine) Xo[(size_t)i * opad + t] = x;
+        if (mine && t < cnt && code != 0) {
+            if constexpr (ZP) {
+                nlo += code == -127;
+                nhi += code == 127;
+                gone += code;
+            } else {
+                need |= (unsigned)(x & 0x7fff) == m1;
+            }
+            *at = 0;
+        }
+    }
+    if constexpr (ZP) {
+#pragma unroll
+        for (int d = 16; d >= 1; d >>= 1) {
+            gone += __shfl_xor(gone, d);
+            nlo += __shfl_xor(nlo, d);
+            nhi += __shfl_xor(nhi, d);
+        }
+        need |= nlo > 0 && nlo >= (z.w & 0xffff);
+        need |= nhi > 0 && nhi >= (int)((unsigned)z.w >> 16);
+    }
+    need = ((__ballot(need) >> (lane & 32)) & 0xffffffffull) != 0 && mine;  // (the half of the wave that shares the row)
+    if ((tid & 31) == 0 && mine) {
+        if (need) {
+            atomicOr(&s_need, 1u << (tid >> 5));
+        } else if (ZP) {
+            z.z -= gone;
+            z.w = 0;
+            zc[i] = z;
+        }
+    }
+    __syncthreads();
+    unsigned again = s_need;
+    if (!again) return;
+    // ---- rows to be made anew: the bitmap of the outlier columns that the buffer takes, then each row by the whole workgroup
+    for (int q = tid; q < nw; q += 256) bitmap[q] = 0;
+    __syncthreads();
+    for (int t = tid; t < cnt; t += 256) atomicOr(&bitmap[s_idx[t] >> 5], 1u << (s_idx[t] & 31));
+    __syncthreads();
+    for (; again; again &= again - 1) {
+        const int i2 = (int)blockIdx.x * SR + __ffs(again) - 1, G = KT * 2;
+        const unsigned short* row2 = X + (size_t)i2 * h;
+        unsigned kmin = 0xffffu, kmax = 0, hi = 0xfbfffbffu, lo = 0x7bff7bffu;
+        // two groups of 16 features in flight per thread, in both passes
+        auto pass = [&](auto f) {
+            for (int g0 = tid; g0 < G; g0 += 512) {
+                us8 a[2][2];
+#pragma unroll
+                for (int u = 0; u < 2; u++) {
+                    a[u][0] = chunk_load(row2, (g0 + 256 * u) * 16, h);
+                    a[u][1] = chunk_load(row2, (g0 + 256 * u) * 16 + 8, h);
+                }
+#pragma unroll
+                for (int u = 0; u < 2; u++) {
+                    const int grp = g0 + 256 * u, c = grp * 16;
+                    if (grp >= G) continue;
+                    unsigned off = past_row(c, h);
+                    if (off) {
+                        a[u][0] = chunk_fix(a[u][0], c, h);
+                        a[u][1] = chunk_fix(a[u][1], c + 8, h);
+                    }
+                    if (c < h) off |= (bitmap[c >> 5] >> (c & 31)) & 0xffffu;
+                    w8 v = words(a[u][0], a[u][1]);
+                    if (!ZP) clear16(v, off);
+                    f(grp, v, off);
+                }
+            }
+        };
+        pass([&](int, const w8& v, unsigned off) {
+            if constexpr (ZP) {
+                range16_without(v, off, hi, lo);
+            } else {
+                const unsigned x = top16(mags(v));
+                kmax = x > kmax ? x : kmax;
+            }
+        });
+        if constexpr (ZP) keys_of(hi, lo, kmin, kmax);
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            const unsigned a = (unsigned)__shfl_xor((int)kmin, d), b = (unsigned)__shfl_xor((int)kmax, d);
+            kmin = a < kmin ? a : kmin;
+            kmax = b > kmax ? b : kmax;
+        }
+        __syncthreads();  // s_red and s_sum of the row before have been read
+        if (lane == 0) {
+            s_red[0][w] = kmin;
+            s_red[1][w] = kmax;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            kmin = s_red[0][q] < kmin ? s_red[0][q] : kmin;
+            kmax = s_red[1][q] > kmax ? s_red[1][q] : kmax;
+        }
+        int8_t* q2 = Xq + (size_t)(i2 >> 5) * KT * TILE_BYTES + (i2 & 31) * 16;
+        if constexpr (ZP) {
+            int4 r = make_int4(0, 0, 0, 0);
+            if (kmin <= kmax) r = make_const(kmin, kmax);
+            const double fd = zp_factor(zp_range((unsigned)r.x));
+            int sum = 0;
+            pass([&](int grp, const w8& v, unsigned off) { *(u4*)(q2 + (size_t)grp * 512) = zp_codes16(v, fd, r.y, off, sum); });
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
+            if (lane == 0) s_sum[w] = sum;
+            __syncthreads();
+            r.z = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+            if (tid == 0) zc[i2] = r;
+        } else {
+            const float ff = code_factor(f16_bits_to_float((unsigned short)kmax));
+            pass([&](int grp, const w8& v, unsigned) { *(u4*)(q2 + (size_t)grp * 512) = codes16(v, ff); });
+            if (tid == 0) cx[i2] = (unsigned short)kmax;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The stand-alone scan.  X as one run of fp16 values: a workgroup takes 2 048 * U of them per round, 8 per thread and load.
+// ---------------------------------------------------------------------------
+constexpr int SCAN_U = 8;
+__global__ void __launch_bounds__(256) outlier_scan_kernel(const unsigned short* __restrict__ X, long long n, int h, int nw,
+                                                           unsigned thr, int cap, unsigned short* __restrict__ rec)
+{
+    extern __shared__ unsigned bitmap[];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    constexpr int U = SCAN_U;
+    for (int q = tid; q < nw; q += 256) bitmap[q] = 0;
+    __syncthreads();
+    const int step = 2048 % h;  // columns from one load of a thread to its next one
+    for (long long b0 = (long long)blockIdx.x * 2048 * U; b0 < n; b0 += (long long)gridDim.x * 2048 * U) {
+        us8 v[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {  // (past the end: the last eight values again; what they reach counts for their own columns)
+            const long long e = b0 + tid * 8 + 2048 * u;
+            v[u] = load8(X + (e + 8 <= n ? e : n - 8));
+        }
+        int c = (int)((b0 + tid * 8) % h);
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const u4 x = __builtin_bit_cast(u4, v[u]) & 0x7fff7fffu;
+            const unsigned m2 = pk_max_u16(pk_max_u16(x[0], x[1]), pk_max_u16(x[2], x[3]));
+            if ((m2 >> 16) >= thr || (m2 & 0xffffu) >= thr) {
+                const long long e = b0 + tid * 8 + 2048 * u;
+                int c1 = e + 8 <= n ? c : h - 8;
+                unsigned f = 0;
+#pragma unroll
+                for (int k = 0; k < 8; k++)
+                    if ((unsigned)(v[u][k] & 0x7fff) >= thr) f |= 1u << k;
+                for (; f; f &= f - 1) {
+                    int j = c1 + __ffs(f) - 1;
+                    j = j < h ? j : j - h;
+                    add_bit(bitmap, (unsigned)j);
+                }
+            }
+            c += step;
+            c = c < h ? c : c - h;
+        }
+    }
+    __syncthreads();
+    if (w == 0) write_record(bitmap, nw, lane, cap, rec + (size_t)blockIdx.x * record_words(cap));
+}
+
+__global__ void __launch_bounds__(256) merge_records_kernel(const unsigned short* __restrict__ rec, int nrec, int nw,
+                                                            int32_t* __restrict__ idx, int cap, int32_t* __restrict__ count,
+                                                            int32_t* __restrict__ status)
+{
+    extern __shared__ unsigned bitmap[];
+    __shared__ int s_idx[JOB_MAX_CAP];
+    const int total = join_records(rec, nrec, cap, nw, bitmap, s_idx);
+    const int cnt = total < cap ? total : cap;
+    for (int t = threadIdx.x; t < cnt; t += 256) idx[t] = s_idx[t];
+    if (threadIdx.x == 0) {
+        *count = cnt;
+        if (status) *status = total > cap ? 1 : 0;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Launchers
+// ---------------------------------------------------------------------------
+struct RowShape { int lr, n, nt; };
+// Rows per workgroup (log2), groups per thread and threads.  Eight rows where that gives the chip at least one workgroup per
+// compute unit, two or one below, so that more of them are in flight; as many more as fill 256 threads where rows are short; and
+// fewer where the registers do not hold them (n <= 8).
+static RowShape row_shape(int s, int h)
+{
+    const int G = k_tiles(h) * 2;
+    int lr = s >= 2048 ? 3 : s >= 512 ? 1 : 0;
+    while (lr < 3 && (G << lr) < 256) lr++;
+    while (lr > 1 && (G << lr) > 512 * 5) lr--;
+    const int items = G << lr;
+    const int nt = items <= (lr == 1 ? 1536 : 1024) ? 256 : items <= 512 * (lr ? 5 : 8) ? 512 : 1024;
+    return {lr, (items + nt - 1) / nt, nt};
+}
+
+// Which calls come here, us per call, here / with the kernels of prepass.hip and zeropoint.hip (which keep the rest):
+//   33 to 128 tokens, 16-bit weights: 33 x 4096 x 4096 15.3 / 16.0, 96 x 5120 x 15360 26.3 / 28.9, 40 x 20480 x 512 25.8 / 26.4; with
+//     more features one compute unit has too much of a row: 100 x 24576 x 1024 31.0 / 30.3, 128 x 49152 x 2048 53.3 / 49.4
+//   the same without 16-bit weights, where the rebuilt rows of W wait for the records: 64 x 4096 x 4096 16.5 / 16.9, but 60 x
+//     8192 x 28672 49.9 / 48.7, 128 x 12288 x 4096 30.3 / 29.0
+//   zeropoint, 33 to 128 tokens: 64 x 4096 x 4096 16.2 / 19.8, 40 x 49152 x 512 52.0 / 54.7, 48 x 12288 x 4096 26.3 / 26.0 the least
+//   above: 256 x 4096 x 4096 19.8 / 24.8, 200 x 49152 x 512 53.7 / 53.7, 2047 x 5120 x 1024 34.8 / 40.3, 4000 x 1000 x 1000 21.8 /
+//     32.1, zeropoint 4096 x 1024 x 1024 26.5 / 37.5
+//   the columns known: 20 x 4096 26.9 / 31.7 (three calls), 4096 x 5120 47.3 / 53.3; not where a second row of many features falls
+//     to some compute units (300 x 49152 64.9 / 63.7; 30 x 49152 50.7 / 53.1, 700 x 49152 99.8 / 100.2)
+// Above 2 048 records (16 384 tokens) every workgroup of settle_rows_kernel would read too many of them.
+bool row_codes_takes(int s, int h, int cap, RowCall call, size_t room)
+{
+    if (h < 8 || h > 65536 || cap > JOB_MAX_CAP) return false;
+    if (call == RowCall::known) return !(h > 32768 && s > 256 && s < 512);
+    if (s <= 128 && call != RowCall::zeropoint && h > (call == RowCall::rebuilt ? 4096 : 20480)) return false;
+    const int nrec = (row_tiles(s) * 32) >> row_shape(s, h).lr;
+    return nrec <= 2048 && (size_t)nrec * record_words(cap) * 2 <= room;
+}
+
+template <bool ZP, bool KNOWN>
+static hipError_t launch_row_codes(const RowArgs& g, hipStream_t st)
+{
+    const RowShape q = row_shape(g.s, g.h);
+    const int nb = (row_tiles(g.s) * 32) >> q.lr;
+    const size_t shm = (size_t)((g.h + 31) / 32) * 4;
+    const bool ragged = g.h % 128 != 0 || ((uintptr_t)g.X & 15) != 0;
+    switch (q.nt + q.lr * 16 + q.n) {
+#define ROWS(NT, LR, N)                                                                     \
+    case NT + LR * 16 + N:                                                                  \
+        if (ragged)                                                                         \
+            row_codes_kernel<N, LR, NT, ZP, KNOWN, true><<<nb, NT, shm, st>>>(g);           \
+        else                                                                                \
+            row_codes_kernel<N, LR, NT, ZP, KNOWN, false><<<nb, NT, shm, st>>>(g);          \
+        break
+        ROWS(256, 3, 1); ROWS(256, 3, 2); ROWS(256, 3, 3); ROWS(256, 3, 4);
+        ROWS(256, 2, 1); ROWS(256, 2, 2);
+        ROWS(256, 1, 1); ROWS(256, 1, 2); ROWS(256, 1, 3); ROWS(256, 1, 4); ROWS(256, 1, 5); ROWS(256, 1, 6);
+        ROWS(256, 0, 1); ROWS(256, 0, 2); ROWS(256, 0, 3); ROWS(256, 0, 4);
+        ROWS(512, 3, 3); ROWS(512, 3, 4); ROWS(512, 3, 5);
+        ROWS(512, 2, 3); ROWS(512, 2, 4); ROWS(512, 2, 5);
+        ROWS(512, 1, 4); ROWS(512, 1, 5);
+        ROWS(512, 0, 3); ROWS(512, 0, 4); ROWS(512, 0, 5); ROWS(512, 0, 6); ROWS(512, 0, 7); ROWS(512, 0, 8);
+        ROWS(1024, 1, 3); ROWS(1024, 1, 4); ROWS(1024, 1, 5); ROWS(1024, 1, 6); ROWS(1024, 1, 7); ROWS(1024, 1, 8);
+#undef ROWS
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_prepass_rows(const void* X, int s, int h, unsigned thr, void* records, int32_t* idx, int cap,
+                               int32_t* count, int32_t* status, int8_t* Xq, unsigned short* cx, int4* zc,
+                               unsigned short* Xo, const ColumnJob* cj, hipStream_t st)
+{
+    const RowArgs g = {(const unsigned short*)X, s, h, k_tiles(h), cap, opad_of(cap), thr, nullptr, nullptr,
+                       (unsigned short*)records, Xq, cx, zc, nullptr};
+    const hipError_t e = zc ? launch_row_codes<true, false>(g, st) : launch_row_codes<false, false>(g, st);
+    if (e != hipSuccess) return e;
+    const int nrec = (row_tiles(s) * 32) >> row_shape(s, h).lr;
+    const ColumnJob job = cj ? *cj : ColumnJob{nullptr, nullptr, nullptr, 0, 0};
+    const int parts = zc ? 1 : (g.opad + JOB_SLOTS - 1) / JOB_SLOTS;
+    const int grid = (s + SR - 1) / SR + job.pitch / 256 * parts;
+    const size_t shm = (size_t)((h + 31) / 32) * 4;
+    if (zc)
+        settle_rows_kernel<true><<<grid, 256, shm, st>>>(g.X, s, h, thr, g.rec, nrec, idx, cap, g.opad, count, status, Xq, g.KT, cx, zc, Xo, job);
+    else
+        settle_rows_kernel<false><<<grid, 256, shm, st>>>(g.X, s, h, thr, g.rec, nrec, idx, cap, g.opad, count, status, Xq, g.KT, cx, zc, Xo, job);
+    return hipGetLastError();
+}
+
+hipError_t launch_quantize_rows_known(const void* X, int s, int h, const int32_t* idx, const int32_t* count, int cap,
+                                      int8_t* Xq, unsigned short* cx, int4* zc, unsigned short* Xo, hipStream_t st)
+{
+    const RowArgs g = {(const unsigned short*)X, s, h, k_tiles(h), cap, opad_of(cap), 0, idx, count, nullptr, Xq, cx, zc, Xo};
+    return zc ? launch_row_codes<true, true>(g, st) : launch_row_codes<false, true>(g, st);
+}
+
+int scan_records(int s, int h, int cap, size_t room)
+{
+    if (h < 8 || h > 65536 || cap > JOB_MAX_CAP) return 0;
+    const long long per = 2048 * SCAN_U, want = ((long long)s * h + per - 1) / per;
+    const size_t fit = room / (record_words(cap) * 2);
+    long long n = want < 1024 ? want : 1024;
+    return (int)(n < (long long)fit ? n : (long long)fit);
+}
+
+hipError_t launch_outlier_scan(const void* X, int s, int h, unsigned thr, void* records, int nrec, int32_t* idx, int cap,
+                               int32_t* count, int32_t* status, hipStream_t st)
+{
+    const int nw = (h + 31) / 32;
+    outlier_scan_kernel<<<nrec, 256, nw * 4, st>>>((const unsigned short*)X, (long long)s * h, h, nw, thr, cap, (unsigned short*)records);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    merge_records_kernel<<<1, 256, nw * 4, st>>>((const unsigned short*)records, nrec, nw, idx, cap, count, status);
+    return hipGetLastError();
+}
+
+}  // namespace llmint8

@@ -1,0 +1,136 @@
+"""The pre-pass that reads X once (rows held in registers, the outlier set settled afterwards) and the stand-alone calls
+that share its kernels, against the oracle, bit for bit.
+
+Sizes: one on each side of every rule that picks rows per workgroup, threads and groups per thread, feature counts that are
+multiples of 128, of 8 and of nothing.  Data: outlier columns that one row alone reaches (the other rows' entries there
+went into their constants and codes and have to go), with the largest entry of some rows in such a column (the row is made
+anew), and more columns than the buffer takes."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import bits
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(33, 8), (40, 264), (64, 4104), (100, 16384), (45, 20479), (200, 40000),        # one row, and more where rows are short
+         (512, 136), (520, 1000), (600, 12288), (513, 16400), (514, 20481), (515, 50176),  # two rows
+         (2048, 264), (2049, 2048), (2050, 2056), (2048, 5120), (2051, 8200), (2048, 10248)]  # eight rows, or what fits
+
+
+def hidden_states(s, h, n, one_sided, seed):
+    rng = np.random.default_rng(seed)
+    X = rng.standard_normal((s, h), dtype=np.float32)
+    if one_sided:
+        X = np.maximum(X, -0.25)
+    cols = np.sort(rng.choice(h, size=min(n, h // 2), replace=False))
+    for q, j in enumerate(cols):
+        X[rng.integers(0, s), j] = 9.0 + q         # one row alone
+        X[rng.integers(0, s, 3), j] = 5.75         # the largest ordinary entry of its row, in an outlier column
+        X[rng.integers(0, s, 3), j] = -0.25 if one_sided else -5.75
+    if s > 3:
+        X[1] = 0.0
+        X[2, :] = 0.5
+    return X.astype(np.float16)
+
+
+def device(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).cuda().view(torch.float16)
+
+
+def buffers(s, h, cap, zp):
+    import torch
+
+    import paper_2208_07339_amd as L
+    outl = L.Outliers(*(torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (cap, 1, 1)), cap)
+    Xq = torch.full((L.xq_bytes(s, h),), 99, dtype=torch.int8, device="cuda")
+    Xo = torch.full((s, L.opad(cap)), 7.0, dtype=torch.float16, device="cuda")
+    if zp:
+        return outl, L.ZpRows(Xq, torch.full((s, 4), 77, dtype=torch.int32, device="cuda"), Xo, s, h)
+    return outl, L.QuantizedRows(Xq, torch.full((s,), 7.0, dtype=torch.float16, device="cuda"), Xo, s, h)
+
+
+def check(X, outl, rows, alpha, cap, zp):
+    import torch
+
+    import paper_2208_07339_amd as L
+    torch.cuda.synchronize()
+    s, h = X.shape
+    full = oracle.find_outliers(X, alpha)
+    idx = full[:cap]
+    assert int(outl.status.item()) == (1 if len(full) > cap else 0)
+    n = int(outl.count.item())
+    assert outl.idx[:n].cpu().numpy().tolist() == idx.tolist()
+    Xo = rows.Xo.cpu().numpy()
+    assert np.array_equal(bits(Xo[:, :n]), bits(X[:, idx])) and not bits(Xo[:, n:]).any()
+    if zp:
+        x = oracle.zp_quantize_rows(X, idx)
+        zc = rows.zc.cpu().numpy()
+        assert np.array_equal(zc[:, 0] & 0xffff, bits(x["lo"]).ravel()) and np.array_equal((zc[:, 0] >> 16) & 0xffff, bits(x["hi"]).ravel())
+        assert np.array_equal(zc[:, 1], x["zp"]) and np.array_equal(zc[:, 2], x["rowsum"]) and not zc[:, 3].any()
+        want = x["Xq"]
+    else:
+        want, cx = oracle.quantize_rows(X, idx)
+        assert np.array_equal(bits(rows.cx.cpu().numpy()), bits(cx))
+    assert np.array_equal(L.export_rows(L.QuantizedRows(rows.Xq, None, None, s, h)).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("zp", [False, True])
+@pytest.mark.parametrize("cap", [32, 6])
+@pytest.mark.parametrize("s,h", SIZES)
+def test_rows_against_the_oracle(s, h, cap, zp):
+    import paper_2208_07339_amd as L
+    n, alpha, o = 9 if cap == 6 else 17, 6.0, 40
+    X = hidden_states(s, h, n, zp, seed=s * 31 + h)
+    Xd, Wd = device(X), device(np.random.default_rng(5).standard_normal((h, o)).astype(np.float16))
+    ws = L.Workspace.allocate(s, h, o, cap)
+    qw = L.zp_quantize_weight(Wd, ws) if zp else L.quantize_weight(Wd, ws)
+    outl, rows = buffers(s, h, cap, zp)
+    for _ in range(2):  # twice: what the first call left in the workspace must not matter
+        out = (L.zp_linear if zp else L.linear)(Xd, qw, alpha, outl, rows, ws)
+    check(X, outl, rows, alpha, cap, zp)
+    # the stand-alone calls: the same bits, and the same product from them
+    outl2, rows2 = buffers(s, h, cap, zp)
+    L.find_outliers(Xd, alpha, cap, ws, outl2)
+    (L.zp_quantize_rows if zp else L.quantize_rows)(Xd, outl2, rows2)
+    check(X, outl2, rows2, alpha, cap, zp)
+    out2 = (L.zp_matmul if zp else L.matmul)(rows2, outl2, qw, ws)
+    assert np.array_equal(bits(out.cpu().numpy()), bits(out2.cpu().numpy()))
+
+
+@pytest.mark.parametrize("zp", [False, True])
+@pytest.mark.parametrize("alpha,cap", [(0.0, 256), (0.0, 8), (1e9, 8), (3.0, 256)])
+def test_thresholds_that_every_or_no_entry_reaches(alpha, cap, zp):
+    """Every column an outlier (and the columns past the buffer's end ordinary again), none, and about as many as fit."""
+    import paper_2208_07339_amd as L
+    s, h, o = 70, 250, 40
+    X = hidden_states(s, h, 3, zp, seed=11)
+    Xd, Wd = device(X), device(np.random.default_rng(6).standard_normal((h, o)).astype(np.float16))
+    ws = L.Workspace.allocate(s, h, 4096, cap)
+    qw = L.zp_quantize_weight(Wd, ws) if zp else L.quantize_weight(Wd, ws)
+    outl, rows = buffers(s, h, cap, zp)
+    (L.zp_linear if zp else L.linear)(Xd, qw, alpha, outl, rows, ws)
+    check(X, outl, rows, alpha, cap, zp)
+    outl, rows = buffers(s, h, cap, zp)
+    L.find_outliers(Xd, alpha, cap, ws, outl)
+    (L.zp_quantize_rows if zp else L.quantize_rows)(Xd, outl, rows)
+    check(X, outl, rows, alpha, cap, zp)
+
+
+@pytest.mark.parametrize("offset", [1, 3, 8])
+def test_hidden_states_that_start_anywhere(offset):
+    """X at any element of an allocation, an h that would otherwise take whole chunks."""
+    import torch
+
+    import paper_2208_07339_amd as L
+    s, h, o, cap = 90, 1024, 40, 32
+    X = hidden_states(s, h, 5, False, seed=offset)
+    room = torch.empty(s * h + 16, dtype=torch.float16, device="cuda")
+    Xd = room[offset:offset + s * h].view(s, h)
+    Xd.copy_(device(X))
+    ws = L.Workspace.allocate(s, h, o, cap)
+    qw = L.quantize_weight(device(np.random.default_rng(7).standard_normal((h, o)).astype(np.float16)), ws)
+    outl, rows = buffers(s, h, cap, False)
+    L.linear(Xd, qw, 6.0, outl, rows, ws)
+    check(X, outl, rows, 6.0, cap, False)
