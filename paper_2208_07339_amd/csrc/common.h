@@ -35,6 +35,27 @@ __device__ inline float f16_bits_to_float(unsigned short b)
     return (float)__builtin_bit_cast(_Float16, b);  // exact widening
 }
 
+// ---- two 16-bit values to a word ----------------------------------------------------------------------------
+__device__ __forceinline__ unsigned pk_max_u16(unsigned a, unsigned b)
+{
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(us2, a), __builtin_bit_cast(us2, b)));
+}
+// two fp16 values each, finite: larger and smaller as numbers (the operators of the language insert an instruction per
+// operand that only signalling NaNs need)
+__device__ __forceinline__ unsigned pk_max_f16(unsigned a, unsigned b)
+{
+    unsigned r;
+    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ unsigned pk_min_f16(unsigned a, unsigned b)
+{
+    unsigned r;
+    asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // ---- 16-byte accesses to rows of fp16 matrices ------------------------------------------------------------
 // Eight elements at any element-aligned address: the hardware takes 16-byte accesses at 2-byte alignment, so
 // matrices whose rows do not start on 16 bytes go the same way as those whose rows do.
@@ -128,6 +149,18 @@ __device__ __forceinline__ float code_factor(float c)
 __device__ __forceinline__ unsigned code_bits(unsigned short x, float factor)
 {
     const float q = __builtin_fmaf(f16_bits_to_float(x), factor, 0.0f);  // conversion and product in one instruction
+    const float t = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, q) & ~7u);
+    return __builtin_bit_cast(unsigned, t + 12582912.0f);
+}
+
+// The same for half of a word of two features, picked by the instruction that converts and multiplies.
+__device__ __forceinline__ unsigned code_of_half(unsigned w, float f, bool high)
+{
+    float q;
+    if (high)
+        asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(q) : "v"(w), "v"(f));
+    else
+        asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(q) : "v"(w), "v"(f));
     const float t = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, q) & ~7u);
     return __builtin_bit_cast(unsigned, t + 12582912.0f);
 }

@@ -35,24 +35,6 @@ __device__ __forceinline__ w8 words(us8 a, us8 b)
     const u4 x = __builtin_bit_cast(u4, a), y = __builtin_bit_cast(u4, b);
     return {{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]}};
 }
-__device__ __forceinline__ unsigned pk_max_u16(unsigned a, unsigned b)
-{
-    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(us2, a), __builtin_bit_cast(us2, b)));
-}
-// two fp16 values each, finite: larger and smaller as numbers (the operators of the language insert an instruction per
-// operand that only signalling NaNs need)
-__device__ __forceinline__ unsigned pk_max_f16(unsigned a, unsigned b)
-{
-    unsigned r;
-    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ unsigned pk_min_f16(unsigned a, unsigned b)
-{
-    unsigned r;
-    asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
 __device__ __forceinline__ w8 mags(const w8& v)
 {
     w8 a;
@@ -114,25 +96,14 @@ __device__ __forceinline__ void clear16(w8& v, unsigned off)
     for (int q = 0; q < 8; q++) v.w[q] &= ~spread(off, q);
 }
 
-// 16 codes of a row, from its 16 features: absmax.  code_bits() (common.h) with the half of a word picked by the instruction
-// that converts and multiplies.
-__device__ __forceinline__ unsigned code_of(unsigned w, float f, bool high)
-{
-    float q;
-    if (high)
-        asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(q) : "v"(w), "v"(f));
-    else
-        asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(q) : "v"(w), "v"(f));
-    const float t = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, q) & ~7u);
-    return __builtin_bit_cast(unsigned, t + 12582912.0f);
-}
+// 16 codes of a row, from its 16 features: absmax
 __device__ __forceinline__ u4 codes16(const w8& v, float f)
 {
     u4 r;
 #pragma unroll
     for (int e = 0; e < 4; e++)
-        r[e] = pack_low_bytes(code_of(v.w[2 * e], f, false), code_of(v.w[2 * e], f, true), code_of(v.w[2 * e + 1], f, false),
-                              code_of(v.w[2 * e + 1], f, true));
+        r[e] = pack_low_bytes(code_of_half(v.w[2 * e], f, false), code_of_half(v.w[2 * e], f, true), code_of_half(v.w[2 * e + 1], f, false),
+                              code_of_half(v.w[2 * e + 1], f, true));
     return r;
 }
 
