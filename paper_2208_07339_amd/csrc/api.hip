@@ -282,19 +282,19 @@ static int linear_impl(const void* X_f16, int s, int h, float alpha, int granula
                                               (const unsigned short*)W_f16, o, idx, cap, count, status, Xq,
                                               (unsigned short*)cx_f16, (unsigned short*)Xo_f16, (unsigned short*)Out_f16,
                                               st));
-    if (s <= 32) {
-        // without 16-bit weights the second kernel also rebuilds the outlier rows of W from the codes
-        const ColumnJob job = {Wq, cw_f16, base + scan_ws(s, h, o, cap), o, (o + 255) & ~255};
-        e = launch_prepass_small(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status,
-                                 (unsigned short*)cx_f16, (unsigned short*)Xo_f16, Xq, shared_cx, st, nullptr,
-                                 W_f16 ? nullptr : &job);
-    } else if (!shared_cx && !(std::isinf(alpha) && alpha > 0.0f) &&
-               row_codes_takes(s, h, cap, W_f16 ? RowCall::absmax : RowCall::rebuilt, scan_ws(s, h, o, cap) - scratch_ws(h, cap))) {
+    if (!shared_cx && !(std::isinf(alpha) && alpha > 0.0f) &&
+        row_codes_takes(s, h, cap, W_f16 ? RowCall::absmax : RowCall::rebuilt, scan_ws(s, h, o, cap) - scratch_ws(h, cap))) {
         // X read once: codes by rows held in registers, then the outlier set settled
         const ColumnJob job = {Wq, cw_f16, base + scan_ws(s, h, o, cap), o, (o + 255) & ~255};
         e = launch_prepass_rows(X_f16, s, h, threshold_bits(alpha), base + scratch_ws(h, cap), idx, cap, count, status, Xq,
                                 (unsigned short*)cx_f16, nullptr, (unsigned short*)Xo_f16, W_f16 ? nullptr : &job, st);
         have_rows = true;
+    } else if (s <= 32) {
+        // without 16-bit weights the second kernel also rebuilds the outlier rows of W from the codes
+        const ColumnJob job = {Wq, cw_f16, base + scan_ws(s, h, o, cap), o, (o + 255) & ~255};
+        e = launch_prepass_small(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status,
+                                 (unsigned short*)cx_f16, (unsigned short*)Xo_f16, Xq, shared_cx, st, nullptr,
+                                 W_f16 ? nullptr : &job);
     } else if (!shared_cx && !(std::isinf(alpha) && alpha > 0.0f) && prepass_mid_takes(s, h, cap, false, slab_ws(s, h) + rowpart_ws(s, h))) {
         OutlierLists Lm = L;  // the partial row maxima in the place of the slab maxima
         Lm.rowpart = (unsigned short*)(base + scratch_ws(h, cap));
@@ -481,7 +481,12 @@ int llmint8_zp_linear(const void* X_f16, int s, int h, float alpha, const int8_t
     if (h > LLMINT8_MAX_H) return LLMINT8_SHAPE;
     if (ws_bytes < llmint8_workspace_bytes(s, h, o, cap)) return LLMINT8_WORKSPACE;
     int r;
-    if (s <= 32) {
+    if (row_codes_takes(s, h, cap, RowCall::zeropoint, scan_ws(s, h, o, cap) - scratch_ws(h, cap))) {
+        char* base = (char*)ws_base(ws);
+        const ColumnJob job = {Wq, zc_w, base + scan_ws(s, h, o, cap) + rows_ws(o, cap), o, zp_col_pitch(o)};
+        r = hip_status(launch_prepass_rows(X_f16, s, h, threshold_bits(alpha), base + scratch_ws(h, cap), idx, cap, count, status, Xq,
+                                           nullptr, (int4*)zc_x, (unsigned short*)Xo_f16, &job, (hipStream_t)stream));
+    } else if (s <= 32) {
         // short X: outlier scan, records, codes and gathered columns in two kernels (the same results as the
         // two calls below); the second one also makes the per-column factors the matmul kernel needs
         const OutlierLists L = carve_outlier_lists((char*)ws_base(ws), h, cap);
@@ -489,11 +494,6 @@ int llmint8_zp_linear(const void* X_f16, int s, int h, float alpha, const int8_t
                                zp_col_pitch(o)};
         r = hip_status(launch_prepass_small(X_f16, s, h, threshold_bits(alpha), L, idx, cap, count, status, nullptr,
                                             (unsigned short*)Xo_f16, Xq, 0, (hipStream_t)stream, (int4*)zc_x, &job));
-    } else if (row_codes_takes(s, h, cap, RowCall::zeropoint, scan_ws(s, h, o, cap) - scratch_ws(h, cap))) {
-        char* base = (char*)ws_base(ws);
-        const ColumnJob job = {Wq, zc_w, base + scan_ws(s, h, o, cap) + rows_ws(o, cap), o, zp_col_pitch(o)};
-        r = hip_status(launch_prepass_rows(X_f16, s, h, threshold_bits(alpha), base + scratch_ws(h, cap), idx, cap, count, status, Xq,
-                                           nullptr, (int4*)zc_x, (unsigned short*)Xo_f16, &job, (hipStream_t)stream));
     } else if (prepass_mid_takes(s, h, cap, true, slab_ws(s, h) + rowpart_ws(s, h))) {
         char* base = (char*)ws_base(ws);
         OutlierLists L = carve_outlier_lists(base, h, cap);

@@ -1,4 +1,4 @@
-// Hidden states of 33 tokens and more: constants and codes with X read once.
+// Hidden states: constants and codes with X read once.
 //
 // row_codes_kernel     a workgroup holds a few whole rows in registers.  Inside the one-call entry points the outlier
 //                      columns are not known yet: the kernel takes its rows' constants over the entries below the
@@ -210,6 +210,12 @@ __global__ void __launch_bounds__(NT, N <= 3 ? 8 : N <= 4 ? 7 : N <= 5 ? 6 : N <
     const bool valid = i < s;  // (a row past the last one: the last one again, its constant and codes zero in the end)
     const unsigned short* row = g.X + (size_t)(valid ? i : s - 1) * h;
     const int g0 = w * (64 >> LR) + (lane >> LR);  // this lane's first group
+    int8_t* dst = g.Xq + ((size_t)((rg * R) >> 5) * g.KT) * TILE_BYTES + (((rg * R) & 31) + r) * 16;
+    if (rg * R >= s) {  // no such rows (the end of the last row tile): codes 0, no columns
+        for (int grp = g0; grp < G; grp += STEP) *(u4*)(dst + (size_t)grp * 512) = (u4)(0u);
+        if (!KNOWN && tid == 0) g.rec[(size_t)rg * record_words(g.cap)] = 0;
+        return;
+    }
     // first feature of this lane's group n; past the last group: the last one again
     auto first = [&](int n) { return (n < N - 1 ? g0 + n * STEP : min(g0 + n * STEP, G - 1)) * 16; };
     w8 v[N];
@@ -327,7 +333,6 @@ __global__ void __launch_bounds__(NT, N <= 3 ? 8 : N <= 4 ? 7 : N <= 5 ? 6 : N <
         }
     }
     // ---- codes
-    int8_t* dst = g.Xq + ((size_t)((rg * R) >> 5) * g.KT) * TILE_BYTES + (((rg * R) & 31) + r) * 16;
     int sum = 0;
     int4 rec = make_int4(0, 0, 0, 0);
     double D = 0.0;
@@ -381,27 +386,28 @@ __device__ __forceinline__ void gather_records(const unsigned short* __restrict_
     // Most records name the same columns.  Sixteen of them go into the bitmap first, two columns to a thread; of the others only
     // those that know more add anything.  (Every record's columns added to the bitmap by its thread, 64 at a time to one
     // word of LDS: 34 us for 2 048 records of 20 columns.)
-    us8 a[U], b[U];
-    auto request = [&](int r0) {
+    us8 a[U], b[U], c[U], d[U];
+    auto request = [&](int r0, us8* x, us8* y, int at) {
 #pragma unroll
         for (int u = 0; u < U; u++) {
             const int r = r0 + 256 * u < nrec ? r0 + 256 * u : nrec - 1;
-            a[u] = *(const us8*)(rec + (size_t)r * pitch);
-            b[u] = *(const us8*)(rec + (size_t)r * pitch + 8);
+            x[u] = *(const us8*)(rec + (size_t)r * pitch + min(at, pitch - 8));
+            y[u] = *(const us8*)(rec + (size_t)r * pitch + min(at + 8, pitch - 8));
         }
     };
     const int e0 = tid & 15;
     const unsigned short* seed = rec + (size_t)((long long)(tid >> 4) * nrec >> 4) * pitch;
     const int sn = min((int)seed[0], cap + 1);
     const unsigned sj = seed[e0], sk = seed[min(16 + e0, pitch - 1)];
-    request(tid);
+    request(tid, a, b, 0);
+    if (U == 1) request(tid, c, d, 16);  // (few records: columns 16 to 31 along with the others, no round trip of their own)
     for (int q = tid; q < nw; q += 256) bitmap[q] = 0;
     __syncthreads();
     if (e0 > 0 && e0 <= sn) add_bit(bitmap, sj);
     if (16 + e0 <= sn) add_bit(bitmap, sk);
     __syncthreads();
     for (int r0 = tid; r0 < nrec; r0 += 256 * U) {
-        if (r0 != tid) request(r0);
+        if (r0 != tid) request(r0, a, b, 0);
         int n[U], most = 0;
         unsigned known[U];
 #pragma unroll
@@ -425,14 +431,9 @@ __device__ __forceinline__ void gather_records(const unsigned short* __restrict_
         look(a, 0, 1);
         if (__any(most > 7)) look(b, 7, 0);
         if (__any(most > 15)) {
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                const int r = r0 + 256 * u < nrec ? r0 + 256 * u : nrec - 1;
-                a[u] = *(const us8*)(rec + (size_t)r * pitch + min(16, pitch - 8));
-                b[u] = *(const us8*)(rec + (size_t)r * pitch + min(24, pitch - 8));
-            }
-            look(a, 15, 0);
-            if (__any(most > 23)) look(b, 23, 0);
+            if (U > 1) request(r0, c, d, 16);
+            look(c, 15, 0);
+            if (__any(most > 23)) look(d, 23, 0);
         }
 #pragma unroll
         for (int u = 0; u < U; u++)
@@ -734,7 +735,7 @@ __global__ void __launch_bounds__(256) merge_records_kernel(const unsigned short
 struct RowShape { int lr, n, nt; };
 // Rows per workgroup (log2), groups per thread and threads.  Eight rows where that gives the chip at least one workgroup per
 // compute unit, two or one below, so that more of them are in flight; as many more as fill 256 threads where rows are short; and
-// fewer where the registers do not hold them (n <= 8).
+// fewer where the registers do not hold them (n <= 8).  One row: more threads sooner, its latency is what counts.
 static RowShape row_shape(int s, int h)
 {
     const int G = k_tiles(h) * 2;
@@ -742,16 +743,19 @@ static RowShape row_shape(int s, int h)
     while (lr < 3 && (G << lr) < 256) lr++;
     while (lr > 1 && (G << lr) > 512 * 5) lr--;
     const int items = G << lr;
-    const int nt = items <= (lr == 1 ? 1536 : 1024) ? 256 : items <= 512 * (lr ? 5 : 8) ? 512 : 1024;
+    const int nt = items <= (lr == 1 ? 1536 : lr ? 1024 : 512) ? 256 : items <= 512 * (lr ? 5 : 8) ? 512 : 1024;
     return {lr, (items + nt - 1) / nt, nt};
 }
 
 // Which calls come here, us per call, here / with the kernels of prepass.hip and zeropoint.hip (which keep the rest):
-//   33 to 128 tokens, 16-bit weights: 33 x 4096 x 4096 15.3 / 16.0, 96 x 5120 x 15360 26.3 / 28.9, 40 x 20480 x 512 25.8 / 26.4; with
-//     more features one compute unit has too much of a row: 100 x 24576 x 1024 31.0 / 30.3, 128 x 49152 x 2048 53.3 / 49.4
-//   the same without 16-bit weights, where the rebuilt rows of W wait for the records: 64 x 4096 x 4096 16.5 / 16.9, but 60 x
-//     8192 x 28672 49.9 / 48.7, 128 x 12288 x 4096 30.3 / 29.0
-//   zeropoint, 33 to 128 tokens: 64 x 4096 x 4096 16.2 / 19.8, 40 x 49152 x 512 52.0 / 54.7, 48 x 12288 x 4096 26.3 / 26.0 the least
+//   up to 128 tokens, 16-bit weights: 16 x 4096 x 2048 15.0 / 17.7, 32 x 4100 x 4100 16.1 / 19.3, 16 x 12288 x 49152 99.1 / 101.1, 33 x 4096
+//     x 4096 15.3 / 16.0, 96 x 5120 x 15360 26.3 / 28.9, 2 x 20480 x 2048 22.8 / 23.7, 40 x 20480 x 512 25.8 / 26.4; with more features
+//     one compute unit has too much of a row: 2 x 37120 x 2048 32.2 / 31.3, 100 x 24576 x 1024 31.0 / 30.3, 128 x 49152 x 2048 53.3 / 49.4
+//   the same without 16-bit weights, where the rebuilt rows of W wait for the records: 16 x 4096 x 2048 17.1 / 18.0, 64 x 4096 x
+//     4096 16.5 / 16.9, but 32 x 12288 x 2048 22.3 / 21.8, 60 x 8192 x 28672 49.9 / 48.7
+//   zeropoint, up to 128 tokens: 2 x 1024 x 2048 14.2 / 17.1, 32 x 4096 x 2048 15.5 / 21.8, 64 x 4096 x 4096 16.2 / 19.8, 2 x 12288 x 2048
+//     20.1 / 22.2, 16 x 37120 x 2048 36.5 / 38.7, 40 x 49152 x 512 52.0 / 54.7, 48 x 12288 x 4096 with 20 columns 26.3 / 26.0 the least;
+//     but 2 x 37120 x 2048 34.9 / 33.2, 12 x 20480 x 2048 with 20 columns 28.9 / 28.2, 3 x 14591 x 1240 with 16 24.3 / 23.5
 //   above: 256 x 4096 x 4096 19.8 / 24.8, 200 x 49152 x 512 53.7 / 53.7, 2047 x 5120 x 1024 34.8 / 40.3, 4000 x 1000 x 1000 21.8 /
 //     32.1, zeropoint 4096 x 1024 x 1024 26.5 / 37.5
 //   the columns known: 20 x 4096 26.9 / 31.7 (three calls), 4096 x 5120 47.3 / 53.3; not where a second row of many features falls
@@ -761,7 +765,7 @@ bool row_codes_takes(int s, int h, int cap, RowCall call, size_t room)
 {
     if (h < 8 || h > 65536 || cap > JOB_MAX_CAP) return false;
     if (call == RowCall::known) return !(h > 32768 && s > 256 && s < 512);
-    if (s <= 128 && call != RowCall::zeropoint && h > (call == RowCall::rebuilt ? 4096 : 20480)) return false;
+    if (call == RowCall::zeropoint ? s < 16 && h > 12288 : s <= 128 && h > (call == RowCall::rebuilt ? 4096 : 20480)) return false;
     const int nrec = (row_tiles(s) * 32) >> row_shape(s, h).lr;
     return nrec <= 2048 && (size_t)nrec * record_words(cap) * 2 <= room;
 }
@@ -784,11 +788,11 @@ static hipError_t launch_row_codes(const RowArgs& g, hipStream_t st)
         ROWS(256, 3, 1); ROWS(256, 3, 2); ROWS(256, 3, 3); ROWS(256, 3, 4);
         ROWS(256, 2, 1); ROWS(256, 2, 2);
         ROWS(256, 1, 1); ROWS(256, 1, 2); ROWS(256, 1, 3); ROWS(256, 1, 4); ROWS(256, 1, 5); ROWS(256, 1, 6);
-        ROWS(256, 0, 1); ROWS(256, 0, 2); ROWS(256, 0, 3); ROWS(256, 0, 4);
+        ROWS(256, 0, 1); ROWS(256, 0, 2);
         ROWS(512, 3, 3); ROWS(512, 3, 4); ROWS(512, 3, 5);
         ROWS(512, 2, 3); ROWS(512, 2, 4); ROWS(512, 2, 5);
         ROWS(512, 1, 4); ROWS(512, 1, 5);
-        ROWS(512, 0, 3); ROWS(512, 0, 4); ROWS(512, 0, 5); ROWS(512, 0, 6); ROWS(512, 0, 7); ROWS(512, 0, 8);
+        ROWS(512, 0, 2); ROWS(512, 0, 3); ROWS(512, 0, 4); ROWS(512, 0, 5); ROWS(512, 0, 6); ROWS(512, 0, 7); ROWS(512, 0, 8);
         ROWS(1024, 1, 3); ROWS(1024, 1, 4); ROWS(1024, 1, 5); ROWS(1024, 1, 6); ROWS(1024, 1, 7); ROWS(1024, 1, 8);
 #undef ROWS
         default: return hipErrorInvalidValue;

@@ -350,9 +350,11 @@ static bool tiled_order(int s, int h, int o) { return !ksplit_takes(s, h, o) && 
 //   more workgroups, where it takes the weight-streaming kernel: as long as K is too short for a full batch of loads there:
 //     12 x 768 x 49152 26.2 / 31.1, 16 x 896 x 36864 24.6 / 31.3, 32 x 384 x 36864 28.9 / 31.0, but 16 x 1024 x 49152 30.2 / 25.9,
 //     32 x 512 x 40960 30.5 / 28.4, and with its two full rounds of 2 x 4 tiles 32 x 384 x 32768 26.5 / 23.1
-//   9 to 16 chunks: 1 x 32768 x 4096 32.6 / 44.8, 16 x 2048 x 4096 14.3 / 16.6, 8 x 4096 x 12288 18.9 / 21.7 (384 column
+//   9 to 16 chunks: 1 x 32768 x 4096 32.6 / 44.8, 8 x 4096 x 12288 18.9 / 21.7 (384 column
 //     tiles), but 1 x 32768 x 16384 94.9 / 92.9 (512) and 32 x 1024 x 32768 35.5 / 27.5 (1 024): taken up to
 //     one and a half workgroups per compute unit
+//   13 and more of them, against separate kernels that read X once: 1 x 20480 x 4096 23.8 / 31.0, 8 x 4096 x 4096 14.5 / 14.7, but
+//     16 x 2048 x 4096 14.5 / 13.7, 32 x 1024 x 1024 15.8 / 13.6, 20 x 1024 x 8192 14.5 / 13.0: not from 16 tokens on
 bool linear_small_takes(int s, int h, int o, int cap)
 {
     int lg, cus = 0;
@@ -362,7 +364,7 @@ bool linear_small_takes(int s, int h, int o, int cap)
     if (cap > SSLOTS && tiled_order(s, h, o)) return false;
     if (prefill_device_setup(&cus) != hipSuccess) cus = 256;
     const int JT = row_tiles(o);
-    if (n > 8) return 2 * JT <= 3 * cus;
+    if (n > 8) return 2 * JT <= 3 * cus && (s < 16 || n <= 12);
     if (JT <= 2 * cus || s <= 8) return true;
     if (tiled_order(s, h, o)) return 2 * JT <= 5 * cus ? s <= 16 || n <= 4 : s <= 16 && n <= 4;
     const int kq = k_tiles(h) / 4;  // k-tiles per wave there

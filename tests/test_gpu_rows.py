@@ -13,7 +13,8 @@ from gpu_util import bits
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [(33, 8), (40, 264), (64, 4104), (100, 16384), (45, 20479), (200, 40000),        # one row, and more where rows are short
+SIZES = [(2, 16392), (9, 12288), (16, 40001), (32, 4100),                                     # up to 32 tokens
+         (33, 8), (40, 264), (64, 4104), (100, 16384), (45, 20479), (200, 40000),        # one row, and more where rows are short
          (512, 136), (520, 1000), (600, 12288), (513, 16400), (514, 20481), (515, 50176),  # two rows
          (2048, 264), (2049, 2048), (2050, 2056), (2048, 5120), (2051, 8200), (2048, 10248)]  # eight rows, or what fits
 
