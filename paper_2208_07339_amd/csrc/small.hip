@@ -1,5 +1,7 @@
 // A whole call in one kernel, for a few tokens of few features (s * h up to 32 768): outlier scan, row constants,
 // codes (Section 3.2, 2.1, 3.1) and the product (Eq. 7 + Eq. 8).
+#include <type_traits>
+
 #include "common.h"
 
 namespace llmint8 {
@@ -50,12 +52,18 @@ struct SmallArgs {
 
 constexpr int SSLOTS = 32;  // outlier slots whose operands are fetched before the weight stream goes on
 
-template <int XC>
-__global__ void __launch_bounds__(256, XC <= 4 ? 4 : 3) linear_small_kernel(const SmallArgs a)
+// T = 16 (up to 16 tokens): a workgroup has half a tile, 16 columns, and 16 x 16 x 64 MFMAs; the waves take the pairs of k-tiles
+// in turn.  Twice as many workgroups reach more compute units, or share them more evenly (half_tiles() has the figures).
+// Four loads to a batch leave registers for five workgroups per compute unit up to 4 chunks (with eight, four of them and 640
+// column tiles in two rounds: 1 x 5120 x 20480 21 us instead of 17); at 8 chunks long sums want eight (2 x 8192 x 11000 16.2 / 17.6).
+template <int XC, int T>
+__global__ void __launch_bounds__(256, XC <= 4 ? (T == 16 ? 5 : 4) : 3) linear_small_kernel(const SmallArgs a)
 {
-    constexpr int U = 8;                       // k-tiles per batch
+    constexpr int U = T == 16 && XC != 8 ? 4 : 8;  // loads per batch: k-tiles, or halves of pairs of them
+    constexpr int NG = 256 / T, NQ = T * T / 64;  // threads per column, accumulators per lane
+    typedef std::conditional_t<T == 16, v4i, v16i> acc_t;
     extern __shared__ __attribute__((aligned(16))) int8_t xq[];  // codes [KT][2][sp][16], then 16 zero bytes
-    __shared__ int red[4][16][64];
+    __shared__ int red[4][NQ][64];
     __shared__ unsigned bitmap[XC * 64];       // outlier columns, 32 per word
     __shared__ int s_idx[JOB_MAX_CAP];
     __shared__ unsigned s_row[32];             // row constants, fp16 bits
@@ -75,15 +83,18 @@ __global__ void __launch_bounds__(256, XC <= 4 ? 4 : 3) linear_small_kernel(cons
         const int c = g + (m << lg);
         v[m] = load8(row + (8 * c + 8 <= h ? 8 * c : 0));  // h >= 8; what does not exist is replaced below
     }
-    const int jj = tid & 31, ig = tid >> 5;
-    const int jt = blockIdx.x, j = jt * 32 + jj;
+    const int jj = tid & (T - 1), ig = tid / T;
+    const int jt = T == 16 ? blockIdx.x >> 1 : blockIdx.x, jr = (T == 16 ? (blockIdx.x & 1) * 16 : 0) + jj, j = jt * 32 + jr;
     const unsigned short cwb = a.cw[j < o ? j : 0];
-    const int kq = KT / 4;  // KT is a multiple of 4
-    const v4i* wp = (const v4i*)(a.Wq + ((size_t)jt * KT + (size_t)w * kq) * TILE_BYTES) + lane;
+    const int kq = T == 16 ? (KT / 2 - w + 3) >> 2 : KT / 4;  // this wave's loads (KT is a multiple of 4)
+    const v4i* wp = T == 16 ? (const v4i*)(a.Wq + ((size_t)jt * KT + 2 * w) * TILE_BYTES) + (blockIdx.x & 1) * 16 + (lane >> 4) * 32 + (lane & 15)
+                            : (const v4i*)(a.Wq + ((size_t)jt * KT + (size_t)w * kq) * TILE_BYTES) + lane;
+    if (T == 16 && kq == 0) wp -= 2 * w * 64;  // (no pair for this wave: the first one, not used)
     v4i wv[2][U];
     auto load = [&](int B, int kt) {
 #pragma unroll
-        for (int u = 0; u < U; u++) wv[B][u] = __builtin_nontemporal_load(wp + (size_t)(kt + u < kq ? kt + u : kq - 1) * 64);
+        for (int u = 0; u < U; u++)
+            wv[B][u] = __builtin_nontemporal_load(wp + (size_t)max(0, kt + u < kq ? kt + u : kq - 1) * (T == 16 ? 512 : 64));
     };
     FENCE();
     load(0, 0);
@@ -159,18 +170,18 @@ __global__ void __launch_bounds__(256, XC <= 4 ? 4 : 3) linear_small_kernel(cons
                 if (total > cnt) bitmap[4 * tid + q] = b[q];
             }
         }
-        if (jt == 0 && tid == 0) {
+        if (blockIdx.x == 0 && tid == 0) {
             *a.count = cnt;
             if (a.status) *a.status = total > a.cap ? 1 : 0;
         }
     }
     __syncthreads();
 
-    // ---- this workgroup's outlier operands: slots ig, ig + 8, .. of column jj, and of the tokens
-    unsigned short wo[SSLOTS / 8], xo[SSLOTS / 8];
+    // ---- this workgroup's outlier operands: slots ig, ig + NG, .. of column jj, and of the tokens
+    unsigned short wo[SSLOTS / NG], xo[SSLOTS / NG];
 #pragma unroll
-    for (int q = 0; q < SSLOTS / 8; q++) {
-        const int t = ig + 8 * q;
+    for (int q = 0; q < SSLOTS / NG; q++) {
+        const int t = ig + NG * q;
         wo[q] = xo[q] = 0;
         if (t < cnt) {
             const int k = s_idx[t];
@@ -178,7 +189,7 @@ __global__ void __launch_bounds__(256, XC <= 4 ? 4 : 3) linear_small_kernel(cons
             if (a.Wf)
                 wo[q] = a.Wf[(size_t)k * o + (j < o ? j : 0)];
             else
-                wo[q] = (unsigned char)a.Wq[((size_t)jt * KT + (k >> 5)) * TILE_BYTES + tile_byte(jj, k & 31)];
+                wo[q] = (unsigned char)a.Wq[((size_t)jt * KT + (k >> 5)) * TILE_BYTES + tile_byte(jr, k & 31)];
         }
     }
 
@@ -222,28 +233,31 @@ __global__ void __launch_bounds__(256, XC <= 4 ? 4 : 3) linear_small_kernel(cons
         }
     }
     __syncthreads();
-    const int lr = lane & 31;
-    const int8_t* xb = lr < sp ? xq + ((lane >> 5) * sp + lr) * 16 : xq + sp * KT * 32;
-    const int xstep = lr < sp ? 32 * sp : 0;
+    const int lr = lane & (T - 1);
+    const int8_t* xb = lr < sp ? xq + ((lane / T) * sp + lr) * 16 : xq + sp * KT * 32;
+    const int xstep = lr < sp ? (T == 16 ? 256 : 32) * sp : 0;  // from one load of this wave to the next
 
     // ---- the stream goes on
     if (XC > 8) load(1, U);
-    v16i acc;
+    acc_t acc;
 #pragma unroll
-    for (int q = 0; q < 16; q++) acc[q] = 0;
-    const int8_t* xw = xb + w * kq * xstep;
+    for (int q = 0; q < NQ; q++) acc[q] = 0;
+    const int8_t* xw = T == 16 ? (lr < sp ? xb + w * 64 * sp : xb) : xb + w * kq * xstep;
+    auto mfma = [&](v4i p, v4i x) {
+        if constexpr (T == 16) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(p, x, acc, 0, 0, 0);
+        else acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(p, x, acc, 0, 0, 0);
+    };
     auto mm = [&](int B, int kt) {
         v4i x[U];
 #pragma unroll
         for (int u = 0; u < U; u++) x[u] = *(const v4i*)(xw + (kt + u) * xstep);
 #pragma unroll
-        for (int u = 0; u < U; u++) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wv[B][u], x[u], acc, 0, 0, 0);
+        for (int u = 0; u < U; u++) mfma(wv[B][u], x[u]);
     };
     auto mm_rest = [&](int B, int kt) {
 #pragma unroll
         for (int u = 0; u < U; u++)
-            if (kt + u < kq)
-                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wv[B][u], *(const v4i*)(xw + (kt + u) * xstep), acc, 0, 0, 0);
+            if (kt + u < kq) mfma(wv[B][u], *(const v4i*)(xw + (kt + u) * xstep));
     };
     int kt = 0;
     for (; kt + 2 * U <= kq; kt += 2 * U) {
@@ -260,8 +274,10 @@ __global__ void __launch_bounds__(256, XC <= 4 ? 4 : 3) linear_small_kernel(cons
     mm_rest(1, kt + U);
 
     // ---- this workgroup's share of the outputs of the pre-pass
-    for (int t = jt * 4 + w; t < KT; t += gridDim.x * 4) *((v4i*)(a.Xq + (size_t)t * TILE_BYTES) + lane) = *(const v4i*)(xb + t * xstep);
-    if (jt == 0) {
+    for (int t = blockIdx.x * 4 + w; t < KT; t += gridDim.x * 4)
+        *((v4i*)(a.Xq + (size_t)t * TILE_BYTES) + lane) =
+            *(const v4i*)((lane & 31) < sp ? xq + ((2 * t + (lane >> 5)) * sp + (lane & 31)) * 16 : xq + sp * KT * 32);
+    if (blockIdx.x == 0) {
         for (int q = tid; q < cnt; q += 256) a.idx[q] = s_idx[q];
         for (int q = tid; q < s * a.opad; q += 256) {
             const int i = q / a.opad, t = q - i * a.opad;
@@ -271,13 +287,13 @@ __global__ void __launch_bounds__(256, XC <= 4 ? 4 : 3) linear_small_kernel(cons
     }
 
     // ---- the four partial sums meet in LDS; token i, column jj of the tile: register 4 (jj / 8) + jj % 4 of lane
-    // i + 32 ((jj / 4) % 2)
+    // i + 32 ((jj / 4) % 2), or jj % 4 of lane i + 16 (jj / 4)
 #pragma unroll
-    for (int q = 0; q < 16; q++) red[w][q][lane] = acc[q];
+    for (int q = 0; q < NQ; q++) red[w][q][lane] = acc[q];
 #pragma unroll
-    for (int q = 0; q < SSLOTS / 8; q++) {
-        s_xo[ig + 8 * q][jj] = xo[q];
-        s_wo[ig + 8 * q][jj] = a.Wf ? wo[q] : dequant_bits((int)(int8_t)wo[q], cwb);
+    for (int q = 0; q < SSLOTS / NG; q++) {
+        s_xo[ig + NG * q][jj] = xo[q];
+        s_wo[ig + NG * q][jj] = a.Wf ? wo[q] : dequant_bits((int)(int8_t)wo[q], cwb);
     }
     __syncthreads();
     __shared__ float s_t[16][64];  // the outlier product, laid out as the sums
@@ -303,10 +319,11 @@ __global__ void __launch_bounds__(256, XC <= 4 ? 4 : 3) linear_small_kernel(cons
     }
     if (j >= o) return;
     const int rr = 4 * (jj >> 3) + (jj & 3), l0 = 32 * ((jj >> 2) & 1);
+    const int rq = T == 16 ? jj & 3 : rr, lq = T == 16 ? 16 * (jj >> 2) : l0;
     const float cwj = f16_bits_to_float(cwb);
-    for (int i = ig; i < s; i += 8) {
+    for (int i = ig; i < s; i += NG) {
         const int l = l0 + i;
-        const int c = red[0][rr][l] + red[1][rr][l] + red[2][rr][l] + red[3][rr][l];
+        const int c = red[0][rq][lq + i] + red[1][rq][lq + i] + red[2][rq][lq + i] + red[3][rq][lq + i];
         if (a.tiled_order) {
             const float sx = f16_bits_to_float((unsigned short)s_row[i]) * (1.0f / 16129.0f);
             a.Out[(size_t)i * o + j] = (_Float16)__builtin_fmaf((float)c * sx, cwj, s_t[rr][l]);
@@ -320,7 +337,7 @@ __global__ void __launch_bounds__(256, XC <= 4 ? 4 : 3) linear_small_kernel(cons
             const int k = s_idx[t];
             const unsigned short wk =
                 a.Wf ? a.Wf[(size_t)k * o + j]
-                     : dequant_bits((int)a.Wq[((size_t)jt * KT + (k >> 5)) * TILE_BYTES + tile_byte(jj, k & 31)], cwb);
+                     : dequant_bits((int)a.Wq[((size_t)jt * KT + (k >> 5)) * TILE_BYTES + tile_byte(jr, k & 31)], cwb);
             d = __builtin_fmaf(f16_bits_to_float(a.X[(size_t)i * h + k]), f16_bits_to_float(wk), d);
         }
         a.Out[(size_t)i * o + j] = (_Float16)d;
@@ -372,6 +389,20 @@ bool linear_small_takes(int s, int h, int o, int cap)
     return JT > 4 * cus ? kq < 4 : n <= 4;
 }
 
+// Whether a workgroup takes half a tile.  Us per call, half / whole tiles:
+//   up to 4 chunks: while all workgroups are resident, five to a compute unit: 1 x 4096 x 4096 7.6 / 9.2, 1 x 5120 x 20480 on int8 rows
+//     17.1 / 18.2, 8 x 512 x 16384 9.0 / 9.3, 1 x 8192 x 20480 26.4 / 29.2; but 1 x 5120 x 25600 23.4 / 22.3, 3 x 768 x 40960 16.9 / 15.6
+//   8: three: 1 x 12288 x 4096 12.3 / 16.7, 2 x 8192 x 11000 16.2 / 20.1, 1 x 16384 x 12288 31.0 / 38.7, 8 x 2048 x 8192 11.3 / 11.3; but
+//     4 x 4096 x 16384 19.0 / 15.2, 8 x 2048 x 20480 20.8 / 16.1
+//   16: one: 1 x 32768 x 4096 27.5 / 32.0, 8 x 4096 x 2048 13.0 / 14.6; but 1 x 20480 x 5120 25.7 / 24.3
+static bool half_tiles(int s, int o, int n)
+{
+    int cus = 0;
+    if (prefill_device_setup(&cus) != hipSuccess) cus = 256;
+    const int JT = row_tiles(o);
+    return s <= 16 && 2 * JT <= (n <= 4 ? 5 : n <= 8 ? 3 : 1) * cus;
+}
+
 hipError_t launch_linear_small(const void* X, int s, int h, unsigned thr, const int8_t* Wq, const unsigned short* cw,
                                const unsigned short* Wf, int o, int32_t* idx, int cap, int32_t* count, int32_t* status,
                                int8_t* Xq, unsigned short* cx, unsigned short* Xo, unsigned short* Out, hipStream_t st)
@@ -382,16 +413,25 @@ hipError_t launch_linear_small(const void* X, int s, int h, unsigned thr, const 
     const int KT = k_tiles(h);
     const SmallArgs a = {(const unsigned short*)X, s, h, o, KT, lg, thr, Wq, cw, Wf, idx, cap, opad_of(cap), count, status,
                          Xq, cx, Xo, (_Float16*)Out, tiled_order(s, h, o) ? 1 : 0};
-    const int grid = row_tiles(o);
     const size_t shm = (size_t)(256 >> lg) * KT * 32 + 16;
+    const bool half = half_tiles(s, o, n);
+    const int grid = row_tiles(o) * (half ? 2 : 1);
+#define SMALL(XC)                                               \
+    do {                                                        \
+        if (half)                                               \
+            linear_small_kernel<XC, 16><<<grid, 256, shm, st>>>(a); \
+        else                                                    \
+            linear_small_kernel<XC, 32><<<grid, 256, shm, st>>>(a); \
+    } while (0)
     if (n <= 1)
-        linear_small_kernel<1><<<grid, 256, shm, st>>>(a);
+        SMALL(1);
     else if (n <= 4)
-        linear_small_kernel<4><<<grid, 256, shm, st>>>(a);
+        SMALL(4);
     else if (n <= 8)
-        linear_small_kernel<8><<<grid, 256, shm, st>>>(a);
+        SMALL(8);
     else
-        linear_small_kernel<16><<<grid, 256, shm, st>>>(a);
+        SMALL(16);
+#undef SMALL
     return hipGetLastError();
 }
 
