@@ -1,4 +1,6 @@
 // Eq. 7 + Eq. 8 for products that are too small to fill the chip with the tiles of gemm.hip.
+#include <type_traits>
+
 #include "common.h"
 
 namespace llmint8 {
@@ -44,13 +46,17 @@ struct KsplitArgs {
 // points in K that differ from workgroup to workgroup (all the same time); W streamed past the caches (96 x 5120 x
 // 15360 26.5 -> 23.3 us from memory, but 19.4 -> 22.0 from the last-level cache).
 //
+// T = 16 (one column tile, up to 16 tokens): half a column tile and 16 x 16 x 64 MFMAs, the waves take pairs of k-tiles.
+//
 // ZP: zeropoint constants, as in gemm.hip.
 // ---------------------------------------------------------------------------
-template <int NJ, int NI, int R, bool ZP>
+template <int NJ, int NI, int R, int T, bool ZP>
 __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
 {
-    constexpr int NW = 8, NC = 32 * NJ, NTK = 32 * NI;
-    __shared__ v4i red[4][NJ * 4][64];                  // [wave][4 columns of a tile][token + 32 half, swizzled]
+    static_assert(T == 32 || (NJ == 1 && NI == 1), "half tiles come alone");
+    constexpr int NW = 8, NC = T * NJ, NTK = T * NI, NM = T == 16 ? 1 : NJ * 4, STEP = NW * (T == 16 ? 128 : 64);
+    typedef std::conditional_t<T == 16, v4i, v16i> acc_t;
+    __shared__ v4i red[4][NM][64];                      // [wave][4 columns of a tile][token + 32 half, swizzled]
     __shared__ unsigned short s_wo[KSLOTS][NC];
     __shared__ __attribute__((aligned(16))) unsigned short s_xo[NTK][KSLOTS];
     __shared__ float s_sx[ZP ? 1 : NTK];
@@ -91,7 +97,7 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
         if constexpr (ZP) zx = a.zp.zcx[i < s ? i : s - 1]; else cx_raw = a.cx[i < s ? i : s - 1];
     }
     // this thread's outputs: token il of a tile, columns jl .. jl + 3
-    const int il = tid / (8 * NJ), ch = tid % (8 * NJ), jl = 4 * ch, j = J0 + jl;
+    const int il = tid / (NC / 4), ch = tid % (NC / 4), jl = 4 * ch, j = J0 + jl;
     if constexpr (ZP) {
         if (tid < NC) {
 #pragma unroll
@@ -101,43 +107,46 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
     FENCE();
 
     // ---- this wave's part of K
-    const int n = (KT - w + NW - 1) / NW;  // k-tiles w, w + 8, ..; none in a short K
-    const int k0 = n > 0 ? w : 0;
+    const int n = ((T == 16 ? KT / 2 : KT) - w + NW - 1) / NW;  // k-tiles (or pairs) w, w + 8, ..; none in a short K
+    const int k0 = n > 0 ? (T == 16 ? 2 * w : w) : 0;
+    const int half = T == 16 ? (lane >> 4) * 32 + (lane & 15) : lane;  // this lane's piece
     const v4i *wp[NJ], *xp[NI];
 #pragma unroll
     for (int c = 0; c < NJ; c++) {
-        const int jt = cb * NJ + c < a.JT ? cb * NJ + c : a.JT - 1;
-        wp[c] = (const v4i*)(a.Wq + ((size_t)jt * KT + k0) * TILE_BYTES) + lane;
+        const int jt = T == 16 ? cb >> 1 : cb * NJ + c < a.JT ? cb * NJ + c : a.JT - 1;
+        wp[c] = (const v4i*)(a.Wq + ((size_t)jt * KT + k0) * TILE_BYTES) + half + (T == 16 ? (cb & 1) * 16 : 0);
     }
 #pragma unroll
     for (int t = 0; t < NI; t++) {
         const int rt = tb * NI + t < a.RT ? tb * NI + t : a.RT - 1;
         // lane -> token lane % 32 of the tile; for tokens that do not exist the first one again, so that their zeros are not
         // fetched (unused: nothing is stored for them)
-        xp[t] = (const v4i*)(a.Xq + ((size_t)rt * KT + k0) * TILE_BYTES) + (NI > 1 || 32 * rt + (lane & 31) < s ? lane : lane & 32);
+        xp[t] = (const v4i*)(a.Xq + ((size_t)rt * KT + k0) * TILE_BYTES) + (NI > 1 || 32 * rt + (lane & (T - 1)) < s ? half : half & ~(T - 1));
     }
-    v16i acc[NJ][NI];
+    acc_t acc[NJ][NI];
 #pragma unroll
     for (int c = 0; c < NJ; c++)
 #pragma unroll
         for (int t = 0; t < NI; t++)
 #pragma unroll
-            for (int q = 0; q < 16; q++) acc[c][t][q] = 0;
+            for (int q = 0; q < T * T / 64; q++) acc[c][t][q] = 0;
     v4i wv[R][NJ], xv[R][NI];
     auto load = [&](int r, int kt) {
         int k = kt < n ? kt : n - 1;
         k = k > 0 ? k : 0;
 #pragma unroll
-        for (int c = 0; c < NJ; c++) wv[r][c] = wp[c][(size_t)k * (NW * 64)];
+        for (int c = 0; c < NJ; c++) wv[r][c] = wp[c][(size_t)k * STEP];
 #pragma unroll
-        for (int t = 0; t < NI; t++) xv[r][t] = xp[t][(size_t)k * (NW * 64)];
+        for (int t = 0; t < NI; t++) xv[r][t] = xp[t][(size_t)k * STEP];
     };
     auto mm = [&](int r) {
 #pragma unroll
         for (int c = 0; c < NJ; c++)
 #pragma unroll
-            for (int t = 0; t < NI; t++)
-                acc[c][t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wv[r][c], xv[r][t], acc[c][t], 0, 0, 0);
+            for (int t = 0; t < NI; t++) {
+                if constexpr (T == 16) acc[c][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv[r][c], xv[r][t], acc[c][t], 0, 0, 0);
+                else acc[c][t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wv[r][c], xv[r][t], acc[c][t], 0, 0, 0);
+            }
     };
 #pragma unroll
     for (int r = 0; r < R; r++) {
@@ -218,14 +227,14 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
             }
             __syncthreads();  // the chunk is in LDS
             const int ns = cnt - q0 < KSLOTS ? cnt - q0 : KSLOTS;
-            if (il < 32)
+            if (il < T)
                 for (int q = 0; q < ns; q++) {
                     float wf[4];
 #pragma unroll
                     for (int e = 0; e < 4; e++) wf[e] = f16_bits_to_float(s_wo[q][jl + e]);
 #pragma unroll
                     for (int t = 0; t < NI; t++) {
-                        const float x = f16_bits_to_float(s_xo[32 * t + il][q]);
+                        const float x = f16_bits_to_float(s_xo[T * t + il][q]);
 #pragma unroll
                         for (int e = 0; e < 4; e++) od[t][e] = __builtin_fmaf(x, wf[e], od[t][e]);
                     }
@@ -248,7 +257,7 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
         // waves 4 .. 7 hand their sums to waves 0 .. 3
         if (w >= 4) {
 #pragma unroll
-            for (int m = 0; m < 4 * NJ; m++) {
+            for (int m = 0; m < NM; m++) {
                 const v4i v = {acc[m >> 2][t][4 * (m & 3)], acc[m >> 2][t][4 * (m & 3) + 1], acc[m >> 2][t][4 * (m & 3) + 2],
                                acc[m >> 2][t][4 * (m & 3) + 3]};
                 red[w - 4][m][lane ^ ((m & 7) << 2)] = v;
@@ -257,7 +266,7 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
         __syncthreads();
         if (w < 4) {
 #pragma unroll
-            for (int m = 0; m < 4 * NJ; m++) {
+            for (int m = 0; m < NM; m++) {
                 v4i v = red[w][m][lane ^ ((m & 7) << 2)];
 #pragma unroll
                 for (int e = 0; e < 4; e++) v[e] += acc[m >> 2][t][4 * (m & 3) + e];
@@ -265,9 +274,9 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
             }
         }
         __syncthreads();
-        const int i = I0 + 32 * t + il;
-        if (il < 32 && i < s && j < o) {
-            const int m = ch >> 1, l = (il + 32 * (ch & 1)) ^ ((m & 7) << 2);
+        const int i = I0 + T * t + il;
+        if (il < T && i < s && j < o) {
+            const int m = T == 16 ? 0 : ch >> 1, l = T == 16 ? il + 16 * ch : (il + 32 * (ch & 1)) ^ ((m & 7) << 2);
             const v4i c = red[0][m][l] + red[1][m][l] + red[2][m][l] + red[3][m][l];
             if (a.Cdbg) {
 #pragma unroll
@@ -278,7 +287,7 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
             // to 32 tokens, last, as in the weight-streaming kernel (the one-call path there gives the same bits)
             float p[4], d[4] = {0, 0, 0, 0};
             if constexpr (ZP) {
-                const int4 rec = s_zx[32 * t + il];
+                const int4 rec = s_zx[T * t + il];
                 const double sa = zp_range((unsigned)rec.x) * (1.0 / 254.0), za = (double)rec.y, rs = (double)rec.z;
 #pragma unroll
                 for (int e = 0; e < 4; e++)
@@ -286,7 +295,7 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
                                                       __builtin_fma(rs, s_zc[1][jl + e], za * s_zc[2][jl + e])));
             } else {
 #pragma unroll
-                for (int e = 0; e < 4; e++) p[e] = (float)c[e] * s_sx[32 * t + il];
+                for (int e = 0; e < 4; e++) p[e] = (float)c[e] * s_sx[T * t + il];
             }
             if (s <= 32) {
 #pragma unroll
@@ -298,7 +307,7 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
             }
             const int ns = many ? 0 : cnt < KSLOTS ? cnt : KSLOTS;
             for (int q = 0; q < ns; q++) {
-                const float x = f16_bits_to_float(s_xo[32 * t + il][q]);
+                const float x = f16_bits_to_float(s_xo[T * t + il][q]);
 #pragma unroll
                 for (int e = 0; e < 4; e++) d[e] = __builtin_fmaf(x, f16_bits_to_float(s_wo[q][jl + e]), d[e]);
             }
@@ -328,16 +337,16 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
 }
 
 // R, RZ: k-tiles in flight per wave, absmax and zeropoint
-template <int NJ, int NI, int R, int RZ>
+template <int NJ, int NI, int R, int RZ, int T = 32>
 static hipError_t launch(KsplitArgs& a, bool zp, hipStream_t st)
 {
-    a.nP = (a.JT + NJ - 1) / NJ;
+    a.nP = T == 16 ? 2 * a.JT : (a.JT + NJ - 1) / NJ;
     a.nQ = (a.RT + NI - 1) / NI;
     const int grid = a.nP * a.nQ;
     if (zp)
-        gemm_ksplit_kernel<NJ, NI, RZ, true><<<grid, 512, 0, st>>>(a);
+        gemm_ksplit_kernel<NJ, NI, RZ, T, true><<<grid, 512, 0, st>>>(a);
     else
-        gemm_ksplit_kernel<NJ, NI, R, false><<<grid, 512, 0, st>>>(a);
+        gemm_ksplit_kernel<NJ, NI, R, T, false><<<grid, 512, 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -365,18 +374,20 @@ static const int ks_nj[KS_SHAPES] = {1, 2, 2, 2}, ks_ni[KS_SHAPES] = {1, 1, 2, 3
 // It counts a W of up to 40 MB as cached; on a W from memory the choice is the faster one all the same: 33 x 4096 x 4096 20.9
 // us there, 8.9 here, 128 x 12288 x 8192 56.5 / 35.4, 1000 x 8192 x 768 37.0 / 21.3, 96 x 5120 x 9000 27.2 / 23.4, 96 x 12288 x
 // 12288 56.6 / 46.2.
-// Up to 32 tokens, the weight-streaming kernel keeps every W that gives a quarter of the compute units a column tile
-// (8 x 8192 x 8192 14.2 against 21.4 us).  Below that, 8 waves per column tile pull more than 4 where the tokens are
-// many or K is long; the matmul alone there / here on a W from memory: 32 x 2048 x 2048 7.3 / 7.0 us, 24 x 8192 x 512 12.0 /
-// 11.8, 8 x 8192 x 512 10.2 / 10.5 (from the caches 7.6 to 9.2 / 7.6), 16 x 12288 x 1024 15.2 / 14.7, 3 x 34608 x 512 34.9 /
-// 28.5, but 8 x 4096 x 1024 6.9 / 7.8, 1 x 2048 x 2048 4.8 / 6.2, 16 x 2048 x 512 5.8 / 6.3.
+// Up to 16 tokens half a column tile to a workgroup: twice the compute units that whole tiles reach, per call half tiles here / the
+// weight-streaming kernel or whole tiles here: 3 x 37120 x 640 22.8 / 30.7 us, 16 x 12288 x 2048 16.1 / 18.6, 16 x 4096 x 4096 13.2 /
+// 16.0, 12 x 20480 x 4096 25.0 / 32.8, 6 x 7793 x 5000 18.7 / 20.3, 4 x 20480 x 5120 30.1 / 32.0; at 8 x 8192 x 6000 21.5 / 21.2.  From a pair of k-tiles for each wave on.
+// 17 to 32 tokens: the weight-streaming kernel keeps every W that gives a quarter of the compute units a column tile; below that
+// 8 waves per column tile pull more than 4; the matmul alone there / here on a W from memory: 32 x 2048 x 2048 7.3 / 7.0 us,
+// 24 x 8192 x 512 12.0 / 11.8.
 int ksplit_shape(int s, int h, int o)
 {
     if (g_decode_cfg.load(std::memory_order_relaxed) >= 0 || g_force_cfg.load(std::memory_order_relaxed) >= 0)
         return -1;  // test hooks: the other kernels
     int cus = 0;
     if (prefill_device_setup(&cus) != hipSuccess) cus = 256;
-    if (s <= 32) return 4 * row_tiles(o) <= cus && (s > 16 || h >= 8192) ? 0 : -1;
+    if (s <= 16) return 8 * row_tiles(o) <= 5 * cus && k_tiles(h) >= 16 ? 0 : -1;
+    if (s <= 32) return 4 * row_tiles(o) <= cus ? 0 : -1;
     int cols, toks;
     prefill_tile_size(s, h, o, &cols, &toks);
     if ((long)((o + cols - 1) / cols) * ((s + toks - 1) / toks) >= cus) return -1;
@@ -404,7 +415,7 @@ hipError_t launch_gemm_ksplit(const int8_t* Xq, const unsigned short* cx, const 
                     rows_are_slots ? opad_of(cap) : h, idx, Xo, count, cap, opad_of(cap), (_Float16*)Out, Cdbg, s, h, o,
                     zp ? *zp : ZpArgs{nullptr, nullptr, 0}};
     switch (ksplit_shape(s, h, o)) {
-        case 0: return launch<1, 1, 8, 8>(a, zp, st);
+        case 0: return s <= 16 ? launch<1, 1, 8, 8, 16>(a, zp, st) : launch<1, 1, 8, 8>(a, zp, st);
         case 1: return launch<2, 1, 6, 5>(a, zp, st);  // two workgroups per compute unit
         case 2: return launch<2, 2, 6, 6>(a, zp, st);
         case 3: return launch<2, 3, 4, 4>(a, zp, st);
