@@ -91,6 +91,8 @@ __global__ void __launch_bounds__(1024) colconst_kernel(const unsigned short* __
     }
 }
 
+constexpr int codes_waves(bool ahead) { return ahead ? 8 : 4; }
+
 // ---------------------------------------------------------------------------
 // Codes in the tiled layout (tile rows = output columns, tile K = features), and for the zeropoint variant
 // each workgroup's part of the column sums of the codes.
@@ -105,13 +107,17 @@ __global__ void __launch_bounds__(1024) colconst_kernel(const unsigned short* __
 // or 16-byte load per row at a time, 178 and 219 us.  W is streamed past the caches (102 us for both passes
 // together if not, 89 so); the codes are not (103 us).
 // ---------------------------------------------------------------------------
-template <bool ZP>
-__global__ void __launch_bounds__(256, ZP ? 2 : 4) weight_codes_kernel(const unsigned short* __restrict__ W, int h, int o,
+// AHEAD (zeropoint): eight waves (the sums of a column's codes are kept per workgroup in the scratch that the ranges had, which
+// limits how many workgroups there can be), and a wave requests the features of its next step before it codes these: two waves
+// per SIMD are all that the registers allow, and neither covers the other's loads otherwise.  5 120 x 20 480 67 -> 57 us.
+template <bool ZP, bool AHEAD>
+__global__ void __launch_bounds__(64 * codes_waves(AHEAD), ZP ? 2 : 4) weight_codes_kernel(const unsigned short* __restrict__ W, int h, int o,
                                                            const unsigned short* __restrict__ cw, const int4* __restrict__ zc,
                                                            int8_t* __restrict__ Wq, int KT, int JT, int steps,
                                                            int* __restrict__ psum)
 {
-    __shared__ u4 stage[4][512];
+    constexpr int NW = codes_waves(AHEAD);
+    __shared__ u4 stage[NW][512];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int jb = blockIdx.x * 512, j0 = jb + lane * 8;
     const bool ragged = jb + 512 > o;  // some lanes of this block hold columns that do not exist
@@ -139,20 +145,28 @@ __global__ void __launch_bounds__(256, ZP ? 2 : 4) weight_codes_kernel(const uns
 
     u4* mine = stage[w];
     const int k_end = KT * 32;
-    int k = (blockIdx.y * steps * 4 + w) * 16;
-    for (int it = 0; it < steps && k < k_end; it++, k += 64) {  // uniform in a wave; no barrier in the loop
-        us8 v[16];
-        // rows past h: the last row again, zeroed below
+    int k = (blockIdx.y * steps * NW + w) * 16;
+    us8 v[16], ahead[AHEAD ? 16 : 1];
+    // rows past h: the last row again, zeroed below
+    auto load = [&](us8* to, int k) {
         if (!ragged || (k + 15 < h - 1 && h >= 16 && o >= 8)) {
             const unsigned short* p = W + jl;
 #pragma unroll
-            for (int i = 0; i < 16; i++) v[i] = load8_once(p + (size_t)(k + i < h ? k + i : h - 1) * o);
+            for (int i = 0; i < 16; i++) to[i] = load8_once(p + (size_t)(k + i < h ? k + i : h - 1) * o);
         } else {
 #pragma unroll
             for (int i = 0; i < 16; i++)
 #pragma unroll
                 for (int e = 0; e < 8; e++)
-                    v[i][e] = W[(size_t)(k + i < h ? k + i : h - 1) * o + (jl + e < o ? jl + e : o - 1)];
+                    to[i][e] = W[(size_t)(k + i < h ? k + i : h - 1) * o + (jl + e < o ? jl + e : o - 1)];
+        }
+    };
+    if (AHEAD && k < k_end) load(v, k);
+    for (int it = 0; it < steps && k < k_end; it++, k += 16 * NW) {  // uniform in a wave; no barrier in the loop
+        if constexpr (AHEAD) {
+            if (it + 1 < steps && k + 16 * NW < k_end) load(ahead, k + 16 * NW);
+        } else {
+            load(v, k);
         }
         if (k + 16 > h) {
 #pragma unroll
@@ -197,18 +211,23 @@ __global__ void __launch_bounds__(256, ZP ? 2 : 4) weight_codes_kernel(const uns
             if (blockIdx.x * 16 + jt < JT) *(u4*)(out + (size_t)jt * KT * TILE_BYTES) = piece;
         }
         asm volatile("" ::: "memory");  // the next step's pieces stay behind these reads
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int i = 0; i < 16; i++) v[i] = ahead[i];
+        }
     }
     if constexpr (ZP) {
-        // the four waves' sums meet in LDS; a workgroup stores its own, zp_colsum_kernel adds them up
+        // the waves' sums meet in LDS; a workgroup stores its own, zp_colsum_kernel adds them up
         __syncthreads();
         int* s_sum = (int*)stage;
 #pragma unroll
         for (int e = 0; e < 8; e++) s_sum[w * 512 + e * 64 + lane] = sum[e];
         __syncthreads();
-        for (int q = threadIdx.x; q < 512; q += 256) {
-            const int at = (q & 7) * 64 + (q >> 3);
-            if (jb + q < o)
-                psum[(size_t)blockIdx.y * o + jb + q] = s_sum[at] + s_sum[512 + at] + s_sum[1024 + at] + s_sum[1536 + at];
+        for (int q = threadIdx.x; q < 512; q += 64 * NW) {
+            int t = 0;
+#pragma unroll
+            for (int x = 0; x < NW; x++) t += s_sum[x * 512 + (q & 7) * 64 + (q >> 3)];
+            if (jb + q < o) psum[(size_t)blockIdx.y * o + jb + q] = t;
         }
     }
 }
@@ -520,7 +539,7 @@ hipError_t launch_quantize_weight(const void* W, int h, int o, unsigned short* p
     if (e != hipSuccess) return e;
     // one step per workgroup: 88.7 us for the whole conversion of a 5 120 x 20 480 W, 91.8 with two, 96.1 with four
     const int KT = k_tiles(h), JT = row_tiles(o);
-    weight_codes_kernel<false><<<dim3((JT + 15) / 16, KT / 2), 256, 0, st>>>((const unsigned short*)W, h, o, cw, nullptr, Wq,
+    weight_codes_kernel<false, false><<<dim3((JT + 15) / 16, KT / 2), 256, 0, st>>>((const unsigned short*)W, h, o, cw, nullptr, Wq,
                                                                             KT, JT, 1, nullptr);
     return hipGetLastError();
 }
@@ -556,9 +575,31 @@ hipError_t launch_zp_quantize_weight(const void* W, int h, int o, int8_t* Wq, in
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     // a workgroup's sums take the place of the ranges of a slab in the scratch (4 bytes per column): no more of them than slabs
-    const int KT = k_tiles(h), JT = row_tiles(o), most = zp_colrange_slabs(h, o);
-    const int steps = (KT / 2 + most - 1) / most, ny = (KT / 2 + steps - 1) / steps;
-    weight_codes_kernel<true><<<dim3((JT + 15) / 16, ny), 256, 0, st>>>((const unsigned short*)W, h, o, nullptr, zc, Wq, KT, JT,
+    const int KT = k_tiles(h), JT = row_tiles(o), most = zp_colrange_slabs(h, o), nx = (JT + 15) / 16;
+    // With the next step requested ahead, steps of 16 features per wave so that rounds of the compute units (one workgroup
+    // each) times steps are as few as can be.  Us, so / four waves and no request ahead: 5 120 x 20 480 96.5 / 105.2, 10 000 x
+    // 10 240 98.0 / 105.3, 8 486 x 2 944 36.8 / 46.1, 9 216 x 9 216 84.3 / 85.6, 21 632 x 2 392 66.7 / 75.4, 49 152 x 2 048 91.9 / 93.9; but
+    // 12 288 x 8 192 101.9 / 95.1, x 4 096 54.0 / 52.7, x 1 000 34.4 / 32.4, 16 264 x 3 584 63.3 / 62.0 (12 288 x 8 200 104.8 / 109.1),
+    // and where less than half of the compute units would have a workgroup.
+    constexpr int nw = codes_waves(true);
+    int steps = 0, ny = 0;
+    long least = 0;
+    for (int n = 1; n <= 64 || !steps; n++) {
+        const int y = (2 * KT + n * nw - 1) / (n * nw);
+        if (y > most) continue;
+        const long cost = (long)((nx * y + cus - 1) / cus) * (n + 1);
+        if (!steps || cost < least) { least = cost; steps = n; ny = y; }
+    }
+    const bool ahead = (h <= 10240 || h > 20480) && 2 * nx * ny >= cus;
+    if (!ahead) {
+        steps = (KT / 2 + most - 1) / most;
+        ny = (KT / 2 + steps - 1) / steps;
+    }
+    if (ahead)
+        weight_codes_kernel<true, true><<<dim3(nx, ny), 64 * nw, 0, st>>>((const unsigned short*)W, h, o, nullptr, zc, Wq, KT, JT,
+                                                                          steps, (int*)part);
+    else
+        weight_codes_kernel<true, false><<<dim3(nx, ny), 256, 0, st>>>((const unsigned short*)W, h, o, nullptr, zc, Wq, KT, JT,
                                                                        steps, (int*)part);
     e = hipGetLastError();
     if (e != hipSuccess) return e;

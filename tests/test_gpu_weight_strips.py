@@ -102,3 +102,10 @@ print("ratio", (t[1] - t[0]) / (t[2] - t[1]))
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr
     assert float(r.stdout.split()[1]) < 0.22
+
+
+# two reads with the next step requested ahead (zeropoint): workgroups of one step and of several with a short last one, rows past
+# the last feature within a step, a last block of 512 columns that is nearly empty, and the sizes on both sides of its rule
+@pytest.mark.parametrize("h,o", [(6500, 3001), (10240, 1541), (10241, 1541), (20481, 1027), (9001, 2056), (3000, 9001)])
+def test_two_reads_with_the_next_step_requested_ahead(h, o):
+    convert_and_compare(h, o, True, offset=1)
