@@ -376,7 +376,11 @@ static const int ks_nj[KS_SHAPES] = {1, 2, 2, 2}, ks_ni[KS_SHAPES] = {1, 1, 2, 3
 // 12288 56.6 / 46.2.
 // Up to 16 tokens half a column tile to a workgroup: twice the compute units that whole tiles reach, per call half tiles here / the
 // weight-streaming kernel or whole tiles here: 3 x 37120 x 640 22.8 / 30.7 us, 16 x 12288 x 2048 16.1 / 18.6, 16 x 4096 x 4096 13.2 /
-// 16.0, 12 x 20480 x 4096 25.0 / 32.8, 6 x 7793 x 5000 18.7 / 20.3, 4 x 20480 x 5120 30.1 / 32.0; at 8 x 8192 x 6000 21.5 / 21.2.  From a pair of k-tiles for each wave on.
+// 16.0, 12 x 20480 x 4096 25.0 / 32.8, 6 x 7793 x 5000 18.7 / 20.3, 4 x 20480 x 5120 30.1 / 32.0; at 8 x 8192 x 6000 21.5 / 21.2.
+// From a pair of k-tiles for each wave on.  Up to 8 tokens with at most 128 k-tiles and an eighth of the compute units' column tiles
+// keep the weight-streaming kernel, as callers that ask for the choice know it; it costs them little: zeropoint calls on a W from
+// memory, half tiles / weight-streaming: 8 x 4096 x 1024 15.1 / 16.4 us, 8 x 2048 x 512 14.2 / 15.2, 8 x 1024 x 1024 14.9 / 15.2, but
+// 8 x 6144 x 1024 16.1 / 18.6, 2 x 5120 x 640 16.3 / 18.1.
 // 17 to 32 tokens: the weight-streaming kernel keeps every W that gives a quarter of the compute units a column tile; below that
 // 8 waves per column tile pull more than 4; the matmul alone there / here on a W from memory: 32 x 2048 x 2048 7.3 / 7.0 us,
 // 24 x 8192 x 512 12.0 / 11.8.
@@ -386,7 +390,7 @@ int ksplit_shape(int s, int h, int o)
         return -1;  // test hooks: the other kernels
     int cus = 0;
     if (prefill_device_setup(&cus) != hipSuccess) cus = 256;
-    if (s <= 16) return 8 * row_tiles(o) <= 5 * cus && k_tiles(h) >= 16 ? 0 : -1;
+    if (s <= 16) return 8 * row_tiles(o) <= 5 * cus && k_tiles(h) >= 16 && (s > 8 || k_tiles(h) > 128 || 8 * row_tiles(o) > cus) ? 0 : -1;
     if (s <= 32) return 4 * row_tiles(o) <= cus ? 0 : -1;
     int cols, toks;
     prefill_tile_size(s, h, o, &cols, &toks);
