@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(256, XC <= 4 ? (T == 16 ? 5 : 4) : 3) linear_s
     auto load = [&](int B, int kt) {
 #pragma unroll
         for (int u = 0; u < U; u++)
-            wv[B][u] = __builtin_nontemporal_load(wp + (size_t)max(0, kt + u < kq ? kt + u : kq - 1) * (T == 16 ? 512 : 64));
+            wv[B][u] = __builtin_nontemporal_load(wp + (size_t)(kt + u < kq ? kt + u : T == 16 ? max(0, kq - 1) : kq - 1) * (T == 16 ? 512 : 64));
     };
     FENCE();
     load(0, 0);
@@ -274,9 +274,11 @@ __global__ void __launch_bounds__(256, XC <= 4 ? (T == 16 ? 5 : 4) : 3) linear_s
     mm_rest(1, kt + U);
 
     // ---- this workgroup's share of the outputs of the pre-pass
+    // (whole tiles: the lane's own address again; as with the clamp of load(), the general form cost them 0.7 of 17.4 us at
+    // 4 x 4096 x 22000)
     for (int t = blockIdx.x * 4 + w; t < KT; t += gridDim.x * 4)
         *((v4i*)(a.Xq + (size_t)t * TILE_BYTES) + lane) =
-            *(const v4i*)((lane & 31) < sp ? xq + ((2 * t + (lane >> 5)) * sp + (lane & 31)) * 16 : xq + sp * KT * 32);
+            *(const v4i*)(T == 32 ? xb + t * xstep : (lane & 31) < sp ? xq + ((2 * t + (lane >> 5)) * sp + (lane & 31)) * 16 : xq + sp * KT * 32);
     if (blockIdx.x == 0) {
         for (int q = tid; q < cnt; q += 256) a.idx[q] = s_idx[q];
         for (int q = tid; q < s * a.opad; q += 256) {
