@@ -287,6 +287,8 @@ __global__ void __launch_bounds__(NT, N <= 3 ? 8 : N <= 4 ? 7 : N <= 5 ? 6 : N <
         unsigned off = !RAGGED || c < h ? (bitmap[c >> 5] >> (c & 31)) & 0xffffu : 0u;
         if constexpr (ZP) {
             if (RAGGED) off |= past_row(c, h);
+            // (the last group once more: its own thread alone counts towards how many have an extreme)
+            if (!KNOWN && n == N - 1 && g0 + n * STEP >= G) off = 0xffffu;
             if (__any(off != 0)) {
                 range16_without(v[n], off, hi, lo);
                 skip[n / 2] |= off << (16 * (n & 1));

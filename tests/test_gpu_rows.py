@@ -135,3 +135,34 @@ def test_hidden_states_that_start_anywhere(offset):
     outl, rows = buffers(s, h, cap, False)
     L.linear(Xd, qw, 6.0, outl, rows, ws)
     check(X, outl, rows, 6.0, cap, False)
+
+
+# One size per work split (rows of a workgroup, groups and threads) in which threads whose last group lies past the row hold the
+# row's last group once more, with 96 to 128 features in the last 128.
+REPEATED_END = [(40, 113), (40, 640), (33, 1272), (48, 4220), (96, 5120), (64, 12288), (40, 20480), (100, 28672), (33, 33020),
+                (34, 43008), (33, 56064), (40, 64512), (600, 2300), (514, 4220), (600, 5120), (513, 6656), (520, 9216), (530, 11264),
+                (514, 14336), (520, 18432), (514, 21118), (516, 28672), (513, 33020), (514, 43008), (516, 56064), (515, 64512),
+                (2048, 640), (2050, 1272), (2049, 1790), (2051, 2300), (2048, 3200), (2050, 4220), (2049, 5374), (2048, 6656),
+                (2050, 9216), (2048, 7168)]
+
+
+@pytest.mark.parametrize("zp", [False, True])
+@pytest.mark.parametrize("s,h", REPEATED_END)
+def test_a_row_whose_extreme_goes_with_a_column_at_either_end(s, h, zp):
+    """Outlier columns among the last and the first 16 features that row 0 alone reaches, in which rows of other workgroups
+    have their only smallest or largest entry below the threshold: these rows are made anew."""
+    import paper_2208_07339_amd as L
+    o, cap, alpha = 40, 32, 6.0
+    X = np.clip(np.random.default_rng(s + h).standard_normal((s, h), dtype=np.float32), -0.25 if zp else -4.0, 4.0)
+    for t, j in enumerate((h - 1, h - 3, h - 16, 0, 2, 15)):
+        X[0, j] = 9.0
+        X[s - 1 - 2 * t, j] = 5.5      # the largest of its row, by magnitude too
+        X[s - 2 - 2 * t, j] = -5.5     # the smallest
+        X[s - 13 - t, j], X[s - 13 - t, 7] = 5.5, -5.25
+    X = X.astype(np.float16)
+    Xd, Wd = device(X), device(np.random.default_rng(8).standard_normal((h, o)).astype(np.float16))
+    ws = L.Workspace.allocate(s, h, o, cap)
+    qw = L.zp_quantize_weight(Wd, ws) if zp else L.quantize_weight(Wd, ws)
+    outl, rows = buffers(s, h, cap, zp)
+    (L.zp_linear if zp else L.linear)(Xd, qw, alpha, outl, rows, ws)
+    check(X, outl, rows, alpha, cap, zp)
