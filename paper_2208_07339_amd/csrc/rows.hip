@@ -547,7 +547,8 @@ __global__ void __launch_bounds__(256) settle_rows_kernel(const unsigned short* 
     // workgroup reached the threshold there.  Where it is an extreme of the row (its code is then 127 in magnitude) and
     // the row may have no other like it, the row is made anew; else its code goes.
     int8_t* q = Xq + (size_t)(mine ? i >> 5 : 0) * KT * TILE_BYTES;
-    bool need = total > cap;
+    // (Zeropoint: a constant row has no codes to say so, and with no ordinary column left its record is zero.)
+    bool need = total > cap || (ZP && cnt == h);
     int gone = 0, nlo = 0, nhi = 0;  // zeropoint: sum of the codes that go, entries that are the smallest, the largest
     for (int t = tid & 31; t < opad; t += 32) {
         const int j = t < cnt ? s_idx[t] : 0;

@@ -166,3 +166,22 @@ def test_a_row_whose_extreme_goes_with_a_column_at_either_end(s, h, zp):
     outl, rows = buffers(s, h, cap, zp)
     (L.zp_linear if zp else L.linear)(Xd, qw, alpha, outl, rows, ws)
     check(X, outl, rows, alpha, cap, zp)
+
+
+@pytest.mark.parametrize("zp", [False, True])
+@pytest.mark.parametrize("s,h", [(40, 8), (41, 27), (600, 30)])
+def test_constant_rows_where_every_column_is_an_outlier(s, h, zp):
+    """One row reaches the threshold everywhere; rows of other workgroups, constant ones among them, have no ordinary
+    column left: their constants are zero."""
+    import paper_2208_07339_amd as L
+    o, cap, alpha = 4096, 32, 6.0  # (a W wide enough for the scratch to hold the records)
+    X = np.random.default_rng(h).uniform(-0.25 if zp else -4.0, 4.0, (s, h))
+    X[0] = 9.0
+    X[20], X[25], X[30] = 0.5, -0.25, 0.0
+    X = X.astype(np.float16)
+    Xd, Wd = device(X), device(np.random.default_rng(8).standard_normal((h, o)).astype(np.float16))
+    ws = L.Workspace.allocate(s, h, o, cap)
+    qw = L.zp_quantize_weight(Wd, ws) if zp else L.quantize_weight(Wd, ws)
+    outl, rows = buffers(s, h, cap, zp)
+    (L.zp_linear if zp else L.linear)(Xd, qw, alpha, outl, rows, ws)
+    check(X, outl, rows, alpha, cap, zp)
