@@ -152,8 +152,6 @@ int llmint8_find_outliers(const void* X_f16, int s, int h, float alpha, int32_t*
     char* base = (char*)ws_base(ws);
     const OutlierLists L = carve_outlier_lists(base, h, cap);
     unsigned short* part = (unsigned short*)(base + scratch_ws(h, cap));
-    const int nrec = scan_records(s, h, cap, slab_ws(s, h) + rowpart_ws(s, h));
-    if (nrec) return hip_status(launch_outlier_scan(X_f16, s, h, threshold_bits(alpha), part, nrec, idx, cap, count, status, st));
     const int nslab = colmax_slabs(s, h);
     hipError_t e = launch_colmax_partial(X_f16, s, h, part, nslab, false, st);
     if (e == hipSuccess) e = launch_outlier_lists(part, nslab, h, threshold_bits(alpha), L, cap, st);

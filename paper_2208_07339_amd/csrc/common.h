@@ -497,10 +497,6 @@ hipError_t launch_prepass_rows(const void* X, int s, int h, unsigned thr, void* 
                                unsigned short* Xo, const ColumnJob* cj, hipStream_t st);
 hipError_t launch_quantize_rows_known(const void* X, int s, int h, const int32_t* idx, const int32_t* count, int cap,
                                       int8_t* Xq, unsigned short* cx, int4* zc, unsigned short* Xo, hipStream_t st);
-// the stand-alone scan through records (how many fit in room; 0: it does not take these sizes)
-int scan_records(int s, int h, int cap, size_t room);
-hipError_t launch_outlier_scan(const void* X, int s, int h, unsigned thr, void* records, int nrec, int32_t* idx, int cap,
-                               int32_t* count, int32_t* status, hipStream_t st);
 // constants and codes of W (weights.hip); part: scratch for colmax_slabs(h, o) * o magnitudes; shared: one constant
 // for all columns
 hipError_t launch_quantize_weight(const void* W, int h, int o, unsigned short* part, int shared, unsigned short* cw,

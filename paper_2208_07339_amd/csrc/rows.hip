@@ -10,7 +10,6 @@
 //                      entries below the threshold in outlier columns, and makes the rows anew whose constant came
 //                      from one of those (or all rows, where more columns qualify than the buffer takes: the columns
 //                      past its end are ordinary ones).
-// outlier_scan_kernel  the lists alone, merge_records_kernel the set from them: the stand-alone scan.
 #include "common.h"
 
 namespace llmint8 {
@@ -672,67 +671,6 @@ __global__ void __launch_bounds__(256) settle_rows_kernel(const unsigned short* 
 }
 
 // ---------------------------------------------------------------------------
-// The stand-alone scan.  X as one run of fp16 values: a workgroup takes 2 048 * U of them per round, 8 per thread and load.
-// ---------------------------------------------------------------------------
-constexpr int SCAN_U = 8;
-__global__ void __launch_bounds__(256) outlier_scan_kernel(const unsigned short* __restrict__ X, long long n, int h, int nw,
-                                                           unsigned thr, int cap, unsigned short* __restrict__ rec)
-{
-    extern __shared__ unsigned bitmap[];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    constexpr int U = SCAN_U;
-    for (int q = tid; q < nw; q += 256) bitmap[q] = 0;
-    __syncthreads();
-    const int step = 2048 % h;  // columns from one load of a thread to its next one
-    for (long long b0 = (long long)blockIdx.x * 2048 * U; b0 < n; b0 += (long long)gridDim.x * 2048 * U) {
-        us8 v[U];
-#pragma unroll
-        for (int u = 0; u < U; u++) {  // (past the end: the last eight values again; what they reach counts for their own columns)
-            const long long e = b0 + tid * 8 + 2048 * u;
-            v[u] = load8(X + (e + 8 <= n ? e : n - 8));
-        }
-        int c = (int)((b0 + tid * 8) % h);
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            const u4 x = __builtin_bit_cast(u4, v[u]) & 0x7fff7fffu;
-            const unsigned m2 = pk_max_u16(pk_max_u16(x[0], x[1]), pk_max_u16(x[2], x[3]));
-            if ((m2 >> 16) >= thr || (m2 & 0xffffu) >= thr) {
-                const long long e = b0 + tid * 8 + 2048 * u;
-                int c1 = e + 8 <= n ? c : h - 8;
-                unsigned f = 0;
-#pragma unroll
-                for (int k = 0; k < 8; k++)
-                    if ((unsigned)(v[u][k] & 0x7fff) >= thr) f |= 1u << k;
-                for (; f; f &= f - 1) {
-                    int j = c1 + __ffs(f) - 1;
-                    j = j < h ? j : j - h;
-                    add_bit(bitmap, (unsigned)j);
-                }
-            }
-            c += step;
-            c = c < h ? c : c - h;
-        }
-    }
-    __syncthreads();
-    if (w == 0) write_record(bitmap, nw, lane, cap, rec + (size_t)blockIdx.x * record_words(cap));
-}
-
-__global__ void __launch_bounds__(256) merge_records_kernel(const unsigned short* __restrict__ rec, int nrec, int nw,
-                                                            int32_t* __restrict__ idx, int cap, int32_t* __restrict__ count,
-                                                            int32_t* __restrict__ status)
-{
-    extern __shared__ unsigned bitmap[];
-    __shared__ int s_idx[JOB_MAX_CAP];
-    const int total = join_records(rec, nrec, cap, nw, bitmap, s_idx);
-    const int cnt = total < cap ? total : cap;
-    for (int t = threadIdx.x; t < cnt; t += 256) idx[t] = s_idx[t];
-    if (threadIdx.x == 0) {
-        *count = cnt;
-        if (status) *status = total > cap ? 1 : 0;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
 struct RowShape { int lr, n, nt; };
@@ -828,26 +766,6 @@ hipError_t launch_quantize_rows_known(const void* X, int s, int h, const int32_t
 {
     const RowArgs g = {(const unsigned short*)X, s, h, k_tiles(h), cap, opad_of(cap), 0, idx, count, nullptr, Xq, cx, zc, Xo};
     return zc ? launch_row_codes<true, true>(g, st) : launch_row_codes<false, true>(g, st);
-}
-
-int scan_records(int s, int h, int cap, size_t room)
-{
-    if (h < 8 || h > 65536 || cap > JOB_MAX_CAP) return 0;
-    const long long per = 2048 * SCAN_U, want = ((long long)s * h + per - 1) / per;
-    const size_t fit = room / (record_words(cap) * 2);
-    long long n = want < 1024 ? want : 1024;
-    return (int)(n < (long long)fit ? n : (long long)fit);
-}
-
-hipError_t launch_outlier_scan(const void* X, int s, int h, unsigned thr, void* records, int nrec, int32_t* idx, int cap,
-                               int32_t* count, int32_t* status, hipStream_t st)
-{
-    const int nw = (h + 31) / 32;
-    outlier_scan_kernel<<<nrec, 256, nw * 4, st>>>((const unsigned short*)X, (long long)s * h, h, nw, thr, cap, (unsigned short*)records);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    merge_records_kernel<<<1, 256, nw * 4, st>>>((const unsigned short*)records, nrec, nw, idx, cap, count, status);
-    return hipGetLastError();
 }
 
 }  // namespace llmint8

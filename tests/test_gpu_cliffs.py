@@ -63,6 +63,25 @@ def ratio(a, b, calls=20, reps=7):
     return best[0] / best[1]
 
 
+def scan(s, h, ncol, cap, alpha=6.0):
+    """-> a call of find_outliers."""
+    import torch
+
+    import paper_2208_07339_amd as L
+    X = torch.from_numpy(wl.make_custom(s, h, 1, ncol, seed=5)["X"].view(np.int16)).cuda().view(torch.float16)
+    ws = L.Workspace.allocate(s, h, 1, cap)
+    outl = L.Outliers(*(torch.zeros(n, dtype=torch.int32, device="cuda") for n in (cap, 1, 1)), cap)
+    return lambda: L.find_outliers(X, alpha, cap, ws, outl)
+
+
+@pytest.mark.parametrize("s,h,ncol,cap,alpha", [(4096, 5120, 200, 256, 6.0), (64, 5120, 200, 256, 6.0), (4096, 5120, 40, 32, 6.0),
+                                                (4096, 5120, 0, 32, 0.0)])
+def test_many_columns_in_the_scan(s, h, ncol, cap, alpha):
+    """200 columns found, or more than the buffer takes (alpha = 0: all of them), against none: 1.0 to 1.3.  With a list of
+    columns from each of up to 1 024 workgroups, 2.8 to 8."""
+    assert ratio(scan(s, h, ncol, cap, alpha), scan(s, h, 0, 32)) < 1.8
+
+
 @pytest.mark.parametrize("zeropoint", [False, True])
 def test_an_outlier_buffer_above_256_columns_at_128_tokens(zeropoint):
     """128 against 129 tokens with 2 000 outlier columns: 1.00, the same pre-pass.  With the two-kernel one, in which
