@@ -10,12 +10,13 @@
 //                      entries below the threshold in outlier columns, and makes the rows anew whose constant came
 //                      from one of those (or all rows, where more columns qualify than the buffer takes: the columns
 //                      past its end are ordinary ones).
+#include <type_traits>
+
 #include "common.h"
 
 namespace llmint8 {
 
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 
 // A record: the outlier columns that one workgroup found.  Word 0 counts them, words 1 .. hold the first cap + 1 of them in
 // ascending order: the set is cut after cap columns, none of its first cap columns is missing from the first cap of the
@@ -166,113 +167,27 @@ __device__ __forceinline__ void add_bit(unsigned* bitmap, unsigned j)
     if (!((*(volatile unsigned*)&bitmap[j >> 5] >> (j & 31)) & 1u)) atomicOr(&bitmap[j >> 5], 1u << (j & 31));  // (mostly there already)
 }
 
-}  // namespace
+// first feature of a lane's group n; past the last group: the last one again
+template <int N, int STEP>
+__device__ __forceinline__ int first_feature(int g0, int n, int G)
+{
+    return (n < N - 1 ? g0 + n * STEP : min(g0 + n * STEP, G - 1)) * 16;
+}
 
-// ---------------------------------------------------------------------------
-// R = 2^LR rows per workgroup of NT threads, N groups of 16 features per thread.  Lane l of a wave holds row l % R: a
-// wave's 16-byte stores are R * 16 bytes side by side in the tiled layout, its loads 64 / R * 32 bytes of each row.
-//
-// Bound by memory where X is large and by its own arithmetic close behind (about 100 instructions for 16 features, a third of
-// a large call's time), by one workgroup's chain of loads, two barriers and stores where it is not.  Us, against the floor of
-// 2.8 us of launch and drain and 6.9 TB/s, and then both kernels against the four that were there before (colmax_rowmax,
-// outlier_lists, row_const, quantize_rows): 4096 x 5120 13.5 (floor 11.9), with settle_rows 19.8 / 33; 2048 x 4096 7.8
-// (6.4), 12.2 / 20; 1013 x 4099 7.7 (4.6), 12.8 / 19; 2048 x 49152 71 (46), 82 / 103; zeropoint 2048 x 5120 11.4 (7.4), 16.5 / 27.
-// The columns that a workgroup's own rows make outliers are left out at once, between the two barriers: where outlier columns
-// are outliers in most tokens, eight rows know nearly all of them and settle_rows_kernel has next to nothing to take back.
-// ---------------------------------------------------------------------------
-struct RowArgs {
-    const unsigned short* X;
-    int s, h, KT, cap, opad;
-    unsigned thr;          // !KNOWN
-    const int32_t *idx, *count;  // KNOWN
-    unsigned short* rec;   // !KNOWN: a record per workgroup
-    int8_t* Xq;
-    unsigned short* cx;    // absmax
-    int4* zc;              // zeropoint
-    unsigned short* Xo;    // KNOWN
-};
-
-// RAGGED: h is not a multiple of 128 or X not 16-byte aligned.
-template <int N, int LR, int NT, bool ZP, bool KNOWN, bool RAGGED>
-__global__ void __launch_bounds__(NT, N <= 3 ? 8 : N <= 4 ? 7 : N <= 5 ? 6 : N <= 7 ? 5 : N <= 8 ? 4 : 3) row_codes_kernel(const RowArgs g)
+// The constants and codes of R rows that a workgroup holds in registers: row r in the lanes l of every wave with l % R = r,
+// N groups of 16 features per lane in v (group g0 + n STEP of the row; past its last group, that one again), without the
+// columns whose bits are set in bitmap.  FIRST: the columns are those that the workgroup's own rows mark, top[] holds the groups' largest
+// magnitudes, and zeropoint records carry how many threads hold the row's extremes, for settle_rows_kernel.  valid: the lane's row
+// exists (constant and codes zero if not); store: its codes are written, to dst; cx, zc: its constant's place.
+template <int N, int LR, int NT, bool ZP, bool FIRST, bool RAGGED>
+__device__ __forceinline__ void constants_and_codes(w8 (&v)[N], const unsigned (&top)[N], const unsigned* bitmap, int h, int G, int g0,
+                                                    bool valid, bool store, int8_t* dst, unsigned short* cx, int4* zc)
 {
     constexpr int R = 1 << LR, STEP = NT >> LR, NW = NT / 64;
-    extern __shared__ unsigned bitmap[];  // ceil(h / 32) words
     __shared__ unsigned red[ZP ? 2 : 1][NW][R];
-    __shared__ int s_sum[ZP ? NW : 1][R], s_like[ZP && !KNOWN ? NW : 1][R];
+    __shared__ int s_sum[ZP ? NW : 1][R], s_like[ZP && FIRST ? NW : 1][R];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & (R - 1);
-    const int s = g.s, h = g.h, G = g.KT * 2;
-    // Row groups that share 128-byte lines of the codes go to one XCD, one after the other.
-    const int nb = gridDim.x, xcd = blockIdx.x & 7;
-    const int rg = xcd * (nb >> 3) + min(xcd, nb & 7) + (blockIdx.x >> 3);
-    const int i = rg * R + r;
-    const bool valid = i < s;  // (a row past the last one: the last one again, its constant and codes zero in the end)
-    const unsigned short* row = g.X + (size_t)(valid ? i : s - 1) * h;
-    const int g0 = w * (64 >> LR) + (lane >> LR);  // this lane's first group
-    int8_t* dst = g.Xq + ((size_t)((rg * R) >> 5) * g.KT) * TILE_BYTES + (((rg * R) & 31) + r) * 16;
-    if (rg * R >= s) {  // no such rows (the end of the last row tile): codes 0, no columns
-        for (int grp = g0; grp < G; grp += STEP) *(u4*)(dst + (size_t)grp * 512) = (u4)(0u);
-        if (!KNOWN && tid == 0) g.rec[(size_t)rg * record_words(g.cap)] = 0;
-        return;
-    }
-    // first feature of this lane's group n; past the last group: the last one again
-    auto first = [&](int n) { return (n < N - 1 ? g0 + n * STEP : min(g0 + n * STEP, G - 1)) * 16; };
-    w8 v[N];
-    us8 x[N][2];
-#pragma unroll
-    for (int n = 0; n < N; n++) {
-        const int c = first(n);
-        x[n][0] = RAGGED ? chunk_load(row, c, h) : *(const us8*)(row + c);
-        x[n][1] = RAGGED ? chunk_load(row, c + 8, h) : *(const us8*)(row + c + 8);
-    }
-    const int nw = (h + 31) >> 5;
-    for (int q = tid; q < nw; q += NT) bitmap[q] = 0;
-    int cnt = 0;
-    if constexpr (KNOWN) {
-        cnt = *g.count;
-        cnt = cnt < 0 ? 0 : (cnt > g.cap ? g.cap : cnt);
-    }
-    __syncthreads();
-    if constexpr (KNOWN) {
-        for (int t = tid; t < cnt; t += NT) {
-            const unsigned j = (unsigned)g.idx[t];
-            if (j < (unsigned)h) atomicOr(&bitmap[j >> 5], 1u << (j & 31));
-        }
-        for (int q = tid; q < R * g.opad; q += NT) {
-            const int rr = q / g.opad, t = q - rr * g.opad, ii = rg * R + rr;
-            unsigned short x = 0;
-            if (t < cnt && ii < s) {
-                const unsigned j = (unsigned)g.idx[t];
-                if (j < (unsigned)h) x = g.X[(size_t)ii * h + j];
-            }
-            if (ii < s) g.Xo[(size_t)ii * g.opad + t] = x;
-        }
-    }
-    // ---- the columns that reach the threshold
-    unsigned top[N];  // largest magnitude of each group
-    const unsigned thr2 = (g.thr ? g.thr - 1 : 0) * 0x10001u, all = g.thr ? 0u : 0xffffu;
-#pragma unroll
-    for (int n = 0; n < N; n++) {
-        const int c = first(n);
-        if (RAGGED && c + 16 > h) {
-            x[n][0] = chunk_fix(x[n][0], c, h);
-            x[n][1] = chunk_fix(x[n][1], c + 8, h);
-        }
-        v[n] = words(x[n][0], x[n][1]);
-        if (KNOWN) continue;
-        const w8 a = mags(v[n]);
-        top[n] = top16(a);
-        if (top[n] >= g.thr) {
-            unsigned f = reach16(a, thr2) | all;
-            if (RAGGED) f &= ~past_row(c, h);
-            if (!RAGGED || f) atomicOr(&bitmap[c >> 5], f << (c & 31));
-        }
-        // (opaque: what was worked out from them is not kept for later)
-#pragma unroll
-        for (int q = 0; q < 8; q++) asm volatile("" : "+v"(v[n].w[q]));
-    }
-    __syncthreads();
-    // ---- constants of the rows, without those columns
+    // ---- constants
     unsigned skip[ZP ? (N + 1) / 2 : 1];  // zeropoint: features without a code, 16 bits per group
     unsigned mx = 0, kmin = 0xffffu, kmax = 0;
     unsigned hi = 0xfbfffbffu, lo = 0x7bff7bffu;
@@ -282,12 +197,12 @@ __global__ void __launch_bounds__(NT, N <= 3 ? 8 : N <= 4 ? 7 : N <= 5 ? 6 : N <
     }
 #pragma unroll
     for (int n = 0; n < N; n++) {
-        const int c = first(n);
+        const int c = first_feature<N, STEP>(g0, n, G);
         unsigned off = !RAGGED || c < h ? (bitmap[c >> 5] >> (c & 31)) & 0xffffu : 0u;
         if constexpr (ZP) {
             if (RAGGED) off |= past_row(c, h);
             // (the last group once more: its own thread alone counts towards how many have an extreme)
-            if (!KNOWN && n == N - 1 && g0 + n * STEP >= G) off = 0xffffu;
+            if (FIRST && n == N - 1 && g0 + n * STEP >= G) off = 0xffffu;
             if (__any(off != 0)) {
                 range16_without(v[n], off, hi, lo);
                 skip[n / 2] |= off << (16 * (n & 1));
@@ -295,10 +210,10 @@ __global__ void __launch_bounds__(NT, N <= 3 ? 8 : N <= 4 ? 7 : N <= 5 ? 6 : N <
                 range16(v[n], hi, lo);
             }
         } else {
-            unsigned m = KNOWN ? 0u : top[n];
+            unsigned m = FIRST ? top[n] : 0u;
             const bool some = __any(off != 0);
             if (some) clear16(v[n], off);
-            if (KNOWN || some) m = top16(mags(v[n]));
+            if (!FIRST || some) m = top16(mags(v[n]));
             mx = m > mx ? m : mx;
         }
     }
@@ -345,7 +260,7 @@ __global__ void __launch_bounds__(NT, N <= 3 ? 8 : N <= 4 ? 7 : N <= 5 ? 6 : N <
 #pragma unroll
     for (int n = 0; n < N; n++) {
         const int grp = g0 + n * STEP;
-        if (n < N - 1 || grp < G) {
+        if (store && (n < N - 1 || grp < G)) {
             if constexpr (ZP)
                 *(u4*)(dst + (size_t)grp * 512) = zp_codes16(v[n], D, rec.y, (skip[n / 2] >> (16 * (n & 1))) & 0xffffu, sum);
             else
@@ -356,7 +271,7 @@ __global__ void __launch_bounds__(NT, N <= 3 ? 8 : N <= 4 ? 7 : N <= 5 ? 6 : N <
 #pragma unroll
         for (int d = 32; d >= R; d >>= 1) sum += __shfl_xor(sum, d);
         if (lane < R) s_sum[w][r] = sum;
-        if constexpr (!KNOWN) {  // how many threads have the smallest and the largest, for settle_rows_kernel
+        if constexpr (FIRST) {  // how many threads have the smallest and the largest, for settle_rows_kernel
             const unsigned long long mine = (R == 8 ? 0x0101010101010101ull : R == 4 ? 0x1111111111111111ull : R == 2 ? 0x5555555555555555ull : ~0ull) << r;
             const int n0 = __popcll(__ballot((mykeys & 0xffffu) == kmin) & mine), n1 = __popcll(__ballot(mykeys >> 16 == kmax) & mine);
             if (lane < R) s_like[w][r] = n0 | n1 << 16;
@@ -367,20 +282,128 @@ __global__ void __launch_bounds__(NT, N <= 3 ? 8 : N <= 4 ? 7 : N <= 5 ? 6 : N <
 #pragma unroll
             for (int q = 0; q < NW; q++) sum += s_sum[q][r];
             rec.z = sum;
-            if constexpr (!KNOWN) {
+            if constexpr (FIRST) {
 #pragma unroll
                 for (int q = 0; q < NW; q++) rec.w += s_like[q][r];
             }
-            g.zc[i] = rec;
+            *zc = rec;
         }
     } else {
-        if (tid < R && valid) g.cx[i] = (unsigned short)mx;
+        if (tid < R && valid) *cx = (unsigned short)mx;
     }
+}
+
+}  // namespace
+
+// ---------------------------------------------------------------------------
+// R = 2^LR rows per workgroup of NT threads, N groups of 16 features per thread.  Lane l of a wave holds row l % R: a
+// wave's 16-byte stores are R * 16 bytes side by side in the tiled layout, its loads 64 / R * 32 bytes of each row.
+//
+// Bound by memory where X is large and by its own arithmetic close behind (about 100 instructions for 16 features, a third of
+// a large call's time), by one workgroup's chain of loads, two barriers and stores where it is not.  Us, against the floor of
+// 2.8 us of launch and drain and 6.9 TB/s, and then both kernels against the four that were there before (colmax_rowmax,
+// outlier_lists, row_const, quantize_rows): 4096 x 5120 13.5 (floor 11.9), with settle_rows 19.8 / 33; 2048 x 4096 7.8
+// (6.4), 12.2 / 20; 1013 x 4099 7.7 (4.6), 12.8 / 19; 2048 x 49152 71 (46), 82 / 103; zeropoint 2048 x 5120 11.4 (7.4), 16.5 / 27.
+// The columns that a workgroup's own rows make outliers are left out at once, between the two barriers: where outlier columns
+// are outliers in most tokens, eight rows know nearly all of them and settle_rows_kernel has next to nothing to take back.
+// ---------------------------------------------------------------------------
+struct RowArgs {
+    const unsigned short* X;
+    int s, h, KT, cap, opad;
+    unsigned thr;          // !KNOWN
+    const int32_t *idx, *count;  // KNOWN
+    unsigned short* rec;   // !KNOWN: a record per workgroup
+    int8_t* Xq;
+    unsigned short* cx;    // absmax
+    int4* zc;              // zeropoint
+    unsigned short* Xo;    // KNOWN
+};
+
+// waves per SIMD that the registers are to leave room for
+constexpr int row_waves(int n) { return n <= 3 ? 8 : n <= 4 ? 7 : n <= 5 ? 6 : n <= 7 ? 5 : 4; }
+
+// RAGGED: h is not a multiple of 128 or X not 16-byte aligned.
+template <int N, int LR, int NT, bool ZP, bool KNOWN, bool RAGGED>
+__global__ void __launch_bounds__(NT, row_waves(N)) row_codes_kernel(const RowArgs g)
+{
+    constexpr int R = 1 << LR, STEP = NT >> LR, NW = NT / 64;
+    extern __shared__ unsigned bitmap[];  // ceil(h / 32) words
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & (R - 1);
+    const int s = g.s, h = g.h, G = g.KT * 2;
+    // Row groups that share 128-byte lines of the codes go to one XCD, one after the other.
+    const int nb = gridDim.x, xcd = blockIdx.x & 7;
+    const int rg = xcd * (nb >> 3) + min(xcd, nb & 7) + (blockIdx.x >> 3);
+    const int i = rg * R + r;
+    const bool valid = i < s;  // (a row past the last one: the last one again, its constant and codes zero in the end)
+    const unsigned short* row = g.X + (size_t)(valid ? i : s - 1) * h;
+    const int g0 = w * (64 >> LR) + (lane >> LR);  // this lane's first group
+    int8_t* dst = g.Xq + ((size_t)((rg * R) >> 5) * g.KT) * TILE_BYTES + (((rg * R) & 31) + r) * 16;
+    if (rg * R >= s) {  // no such rows (the end of the last row tile): codes 0, no columns
+        for (int grp = g0; grp < G; grp += STEP) *(u4*)(dst + (size_t)grp * 512) = (u4)(0u);
+        if (!KNOWN && tid == 0) g.rec[(size_t)rg * record_words(g.cap)] = 0;
+        return;
+    }
+    w8 v[N];
+    us8 x[N][2];
+#pragma unroll
+    for (int n = 0; n < N; n++) {
+        const int c = first_feature<N, STEP>(g0, n, G);
+        x[n][0] = RAGGED ? chunk_load(row, c, h) : *(const us8*)(row + c);
+        x[n][1] = RAGGED ? chunk_load(row, c + 8, h) : *(const us8*)(row + c + 8);
+    }
+    const int nw = (h + 31) >> 5;
+    for (int q = tid; q < nw; q += NT) bitmap[q] = 0;
+    int cnt = 0;
+    if constexpr (KNOWN) {
+        cnt = *g.count;
+        cnt = cnt < 0 ? 0 : (cnt > g.cap ? g.cap : cnt);
+    }
+    __syncthreads();
+    if constexpr (KNOWN) {
+        for (int t = tid; t < cnt; t += NT) {
+            const unsigned j = (unsigned)g.idx[t];
+            if (j < (unsigned)h) atomicOr(&bitmap[j >> 5], 1u << (j & 31));
+        }
+        for (int q = tid; q < R * g.opad; q += NT) {
+            const int rr = q / g.opad, t = q - rr * g.opad, ii = rg * R + rr;
+            unsigned short x = 0;
+            if (t < cnt && ii < s) {
+                const unsigned j = (unsigned)g.idx[t];
+                if (j < (unsigned)h) x = g.X[(size_t)ii * h + j];
+            }
+            if (ii < s) g.Xo[(size_t)ii * g.opad + t] = x;
+        }
+    }
+    // ---- the columns that reach the threshold
+    unsigned top[N];  // largest magnitude of each group
+    const unsigned thr2 = (g.thr ? g.thr - 1 : 0) * 0x10001u, all = g.thr ? 0u : 0xffffu;
+#pragma unroll
+    for (int n = 0; n < N; n++) {
+        const int c = first_feature<N, STEP>(g0, n, G);
+        if (RAGGED && c + 16 > h) {
+            x[n][0] = chunk_fix(x[n][0], c, h);
+            x[n][1] = chunk_fix(x[n][1], c + 8, h);
+        }
+        v[n] = words(x[n][0], x[n][1]);
+        if (KNOWN) continue;
+        const w8 a = mags(v[n]);
+        top[n] = top16(a);
+        if (top[n] >= g.thr) {
+            unsigned f = reach16(a, thr2) | all;
+            if (RAGGED) f &= ~past_row(c, h);
+            if (!RAGGED || f) atomicOr(&bitmap[c >> 5], f << (c & 31));
+        }
+        // (opaque: what was worked out from them is not kept for later)
+#pragma unroll
+        for (int q = 0; q < 8; q++) asm volatile("" : "+v"(v[n].w[q]));
+    }
+    __syncthreads();
+    constants_and_codes<N, LR, NT, ZP, !KNOWN, RAGGED>(v, top, bitmap, h, G, g0, valid, true, dst, g.cx + i, g.zc + i);
     if (!KNOWN && w == NW - 1) write_record(bitmap, nw, lane, g.cap, g.rec + (size_t)rg * record_words(g.cap));
 }
 
 // The records' columns into the bitmap (cleared here), U records in flight per thread
-template <int U>
+template <int NT, int U>
 __device__ __forceinline__ void gather_records(const unsigned short* __restrict__ rec, int nrec, int cap, int nw, unsigned* bitmap)
 {
     const int tid = threadIdx.x, pitch = record_words(cap);
@@ -391,29 +414,31 @@ __device__ __forceinline__ void gather_records(const unsigned short* __restrict_
     auto request = [&](int r0, us8* x, us8* y, int at) {
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            const int r = r0 + 256 * u < nrec ? r0 + 256 * u : nrec - 1;
+            const int r = r0 + NT * u < nrec ? r0 + NT * u : nrec - 1;
             x[u] = *(const us8*)(rec + (size_t)r * pitch + min(at, pitch - 8));
             y[u] = *(const us8*)(rec + (size_t)r * pitch + min(at + 8, pitch - 8));
         }
     };
     const int e0 = tid & 15;
-    const unsigned short* seed = rec + (size_t)((long long)(tid >> 4) * nrec >> 4) * pitch;
+    const unsigned short* seed = rec + (size_t)((long long)((tid >> 4) & 15) * nrec >> 4) * pitch;
     const int sn = min((int)seed[0], cap + 1);
     const unsigned sj = seed[e0], sk = seed[min(16 + e0, pitch - 1)];
     request(tid, a, b, 0);
     if (U == 1) request(tid, c, d, 16);  // (few records: columns 16 to 31 along with the others, no round trip of their own)
-    for (int q = tid; q < nw; q += 256) bitmap[q] = 0;
+    for (int q = tid; q < nw; q += NT) bitmap[q] = 0;
     __syncthreads();
-    if (e0 > 0 && e0 <= sn) add_bit(bitmap, sj);
-    if (16 + e0 <= sn) add_bit(bitmap, sk);
+    if (tid < 256) {
+        if (e0 > 0 && e0 <= sn) add_bit(bitmap, sj);
+        if (16 + e0 <= sn) add_bit(bitmap, sk);
+    }
     __syncthreads();
-    for (int r0 = tid; r0 < nrec; r0 += 256 * U) {
+    for (int r0 = tid; r0 < nrec; r0 += NT * U) {
         if (r0 != tid) request(r0, a, b, 0);
         int n[U], most = 0;
         unsigned known[U];
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            n[u] = r0 + 256 * u < nrec ? min((int)a[u][0], cap + 1) : 0;
+            n[u] = r0 + NT * u < nrec ? min((int)a[u][0], cap + 1) : 0;
             known[u] = ~0u;
             most = n[u] > most ? n[u] : most;
         }
@@ -439,7 +464,7 @@ __device__ __forceinline__ void gather_records(const unsigned short* __restrict_
 #pragma unroll
         for (int u = 0; u < U; u++)
             if (n[u] > 31 || !(known[u] & 1u)) {
-                const unsigned short* p = rec + (size_t)(r0 + 256 * u) * pitch;
+                const unsigned short* p = rec + (size_t)(r0 + NT * u) * pitch;
                 for (int e = 0; e < n[u]; e += 8) {
                     unsigned short c[8];
 #pragma unroll
@@ -452,20 +477,21 @@ __device__ __forceinline__ void gather_records(const unsigned short* __restrict_
 }
 
 // ---------------------------------------------------------------------------
-// The outlier set from the records, by all 256 threads of a workgroup: s_idx[0 .. min(total, cap)) ascending.  bitmap:
+// The outlier set from the records, by all NT threads of a workgroup: s_idx[0 .. min(total, cap)) ascending.  bitmap:
 // ceil(h / 32) words of LDS, left with the bits of all qualifying columns.  Returns their number.
 // ---------------------------------------------------------------------------
+template <int NT>
 __device__ __forceinline__ int join_records(const unsigned short* __restrict__ rec, int nrec, int cap, int nw, unsigned* bitmap,
                                             int* s_idx)
 {
-    __shared__ int s_wsum[4];
+    __shared__ int s_wsum[NT / 64];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    if (nrec <= 256)
-        gather_records<1>(rec, nrec, cap, nw, bitmap);
+    if (nrec <= NT)
+        gather_records<NT, 1>(rec, nrec, cap, nw, bitmap);
     else
-        gather_records<4>(rec, nrec, cap, nw, bitmap);
+        gather_records<NT, 1024 / NT>(rec, nrec, cap, nw, bitmap);
     __syncthreads();
-    const int q = (nw + 255) >> 8, b0 = tid * q, b1 = min(nw, b0 + q);
+    const int q = (nw + NT - 1) / NT, b0 = tid * q, b1 = min(nw, b0 + q);
     int mine = 0;
     for (int x = b0; x < b1; x++) mine += __popc(bitmap[x]);
     int incl = mine;
@@ -478,7 +504,7 @@ __device__ __forceinline__ int join_records(const unsigned short* __restrict__ r
     __syncthreads();
     int woff = 0, total = 0;
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
+    for (int k = 0; k < NT / 64; k++) {
         if (k < w) woff += s_wsum[k];
         total += s_wsum[k];
     }
@@ -491,182 +517,163 @@ __device__ __forceinline__ int join_records(const unsigned short* __restrict__ r
 }
 
 // ---------------------------------------------------------------------------
-// A workgroup settles SR = 8 rows (32 lanes each); the workgroups past the rows take a column job.  A chain of round trips:
-// records, columns of X and codes, stores; 4 us for 256 records, 6.3 for 512, 10.5 for 1 024 of 20 columns (2.8 of them launch
-// and drain).
+// A workgroup settles 2^lsr rows (one or more of those that row_codes_kernel, of the same shape, gave a workgroup), NT >> lsr
+// threads to a row; the workgroups past the rows take a column job.  A chain of round trips: records, columns of X and codes,
+// stores; 4 us for 256 records, 6.3 for 512, 10.5 for 1 024 of 20 columns (2.8 of them launch and drain).
+// Rows to be made anew are held in registers as there, R at a time and all of a workgroup's lanes on them.  Where that is every
+// row, calls with 64 output columns, us (one row after the other / the kernels of prepass.hip, zeropoint.hip): 96 x 5120 16.1
+// (27.8 / 16.5), 1024 x 8192 33.0 (44.5 / 35.1), 4096 x 5120 37.9 (52.2 / 48.0), 4096 x 12288 86.0 (105.4 / 84.0), 2048 x 49152 205
+// (296 / 170), zeropoint 512 x 4096 19.9 (32.0 / 22.6), 2048 x 5120 35.1 (47.8 / 34.5), 1024 x 28672 81.5 (110.5 / 71.6).
 // ---------------------------------------------------------------------------
-constexpr int SR = 8;
+constexpr int MAX_SR = 8;
+struct SettleArgs {
+    const unsigned short* X;
+    int s, h, KT, cap, opad, nrec;
+    int lsr, nb;  // rows of a workgroup (log2), workgroups of rows
+    const unsigned short* rec;
+    int32_t *idx, *count, *status;
+    int8_t* Xq;
+    unsigned short* cx;
+    int4* zc;
+    unsigned short* Xo;
+    ColumnJob cj;
+};
 
-template <bool ZP>
-__global__ void __launch_bounds__(256) settle_rows_kernel(const unsigned short* __restrict__ X, int s, int h, unsigned thr,
-                                                          const unsigned short* __restrict__ rec, int nrec,
-                                                          int32_t* __restrict__ idx, int cap, int opad,
-                                                          int32_t* __restrict__ count, int32_t* __restrict__ status,
-                                                          int8_t* __restrict__ Xq, int KT, unsigned short* __restrict__ cx,
-                                                          int4* __restrict__ zc, unsigned short* __restrict__ Xo,
-                                                          ColumnJob cj)
+template <int N, int LR, int NT, bool ZP>
+__global__ void __launch_bounds__(NT, 4) settle_rows_kernel(const SettleArgs a)
 {
+    constexpr int R = 1 << LR, STEP = NT >> LR, K = 4;
     extern __shared__ unsigned bitmap[];
     __shared__ int s_idx[JOB_MAX_CAP];
     __shared__ unsigned s_need;
-    __shared__ unsigned s_red[2][4];
-    __shared__ int s_sum[4];
+    __shared__ int s_gone[ZP ? 3 : 1][MAX_SR];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int nw = (h + 31) >> 5, nrows = (s + SR - 1) / SR;
-    const int i = (int)blockIdx.x * SR + (tid >> 5);
+    const int s = a.s, h = a.h, KT = a.KT, opad = a.opad, nw = (h + 31) >> 5;
+    const int tpr = NT >> a.lsr, tr = tid / tpr, t1 = tid & (tpr - 1);  // this thread's row of the workgroup, its first outlier column
+    const bool job = (int)blockIdx.x >= a.nb;
+    // (the rows on the XCD whose L2 may still have their codes)
+    const int xcd = blockIdx.x & 7, b = job ? 0 : xcd * (a.nb >> 3) + min(xcd, a.nb & 7) + (blockIdx.x >> 3);
+    const int i0 = b << a.lsr, i = i0 + tr;
+    if (i0 >= s) return;  // the end of the last row tile
     const bool mine = i < s;
     unsigned m1 = 0;
     int4 z = make_int4(0, 0, 0, 0);
     if constexpr (ZP)
-        z = zc[mine ? i : 0];
+        z = a.zc[mine ? i : 0];
     else
-        m1 = cx[mine ? i : 0];
+        m1 = a.cx[mine ? i : 0];
     if (tid == 0) s_need = 0;
-    const int total = join_records(rec, nrec, cap, nw, bitmap, s_idx);
-    const int cnt = total < cap ? total : cap;
-    if ((int)blockIdx.x >= nrows) {
-        const int jb = (int)blockIdx.x - nrows, parts = cj.pitch >> 8;
-        const int j = (jb % parts) * 256 + tid;
+    if (ZP && tid < 3 * MAX_SR) s_gone[tid / MAX_SR][tid % MAX_SR] = 0;
+    const int total = join_records<NT>(a.rec, a.nrec, a.cap, nw, bitmap, s_idx);
+    const int cnt = total < a.cap ? total : a.cap;
+    if (job) {
+        if (tid >= 256) return;
+        const int jb = (int)blockIdx.x - a.nb, parts = a.cj.pitch >> 8, j = (jb % parts) * 256 + tid;
         if constexpr (ZP)
-            zp_col_factors(cj.Wq, (const int4*)cj.wconst, h, cj.o, KT, s_idx, cnt, cj.pitch, (double*)cj.out, j);
-        else if (j < cj.o)
-            rebuild_rows(cj.Wq, (const unsigned short*)cj.wconst, h, cj.o, KT, s_idx, cnt, jb / parts * JOB_SLOTS,
-                         min(jb / parts * JOB_SLOTS + JOB_SLOTS, opad), (unsigned short*)cj.out, j);
+            zp_col_factors(a.cj.Wq, (const int4*)a.cj.wconst, h, a.cj.o, KT, s_idx, cnt, a.cj.pitch, (double*)a.cj.out, j);
+        else if (j < a.cj.o)
+            rebuild_rows(a.cj.Wq, (const unsigned short*)a.cj.wconst, h, a.cj.o, KT, s_idx, cnt, jb / parts * JOB_SLOTS,
+                         min(jb / parts * JOB_SLOTS + JOB_SLOTS, opad), (unsigned short*)a.cj.out, j);
         return;
     }
-    if (blockIdx.x == 0) {
-        for (int t = tid; t < cnt; t += 256) idx[t] = s_idx[t];
+    if (b == 0) {
+        for (int t = tid; t < cnt; t += NT) a.idx[t] = s_idx[t];
         if (tid == 0) {
-            *count = cnt;
-            if (status) *status = total > cap ? 1 : 0;
+            *a.count = cnt;
+            if (a.status) *a.status = total > a.cap ? 1 : 0;
         }
     }
-    const unsigned short* row = X + (size_t)(mine ? i : 0) * h;
     // An entry below the threshold in an outlier column went into its row's constants and has a code if no row of its
     // workgroup reached the threshold there.  Where it is an extreme of the row (its code is then 127 in magnitude) and
     // the row may have no other like it, the row is made anew; else its code goes.
-    int8_t* q = Xq + (size_t)(mine ? i >> 5 : 0) * KT * TILE_BYTES;
     // (Zeropoint: a constant row has no codes to say so, and with no ordinary column left its record is zero.)
-    bool need = total > cap || (ZP && cnt == h);
-    int gone = 0, nlo = 0, nhi = 0;  // zeropoint: sum of the codes that go, entries that are the smallest, the largest
-    for (int t = tid & 31; t < opad; t += 32) {
-        const int j = t < cnt ? s_idx[t] : 0;
-        int8_t* at = q + (size_t)(j >> 5) * TILE_BYTES + tile_byte(i & 31, j & 31);
-        const unsigned short x = t < cnt ? row[j] : (unsigned short)0;
-        const int code = *at;
-        if (mine) Xo[(size_t)i * opad + t] = x;
-        if (mine && t < cnt && code != 0) {
-            if constexpr (ZP) {
-                nlo += code == -127;
-                nhi += code == 127;
-                gone += code;
-            } else {
-                need |= (unsigned)(x & 0x7fff) == m1;
+    const bool all = total > a.cap || (ZP && cnt == h);
+    const unsigned short* row = a.X + (size_t)(mine ? i : 0) * h;
+    int8_t* q = a.Xq + (size_t)(mine ? i >> 5 : 0) * KT * TILE_BYTES;
+    for (int base = 0; base < opad; base += K * tpr) {
+        unsigned short x[K];
+        int code[K];
+        int8_t* at[K];
+#pragma unroll
+        for (int u = 0; u < K; u++) {
+            const int t = base + u * tpr + t1;
+            if (base + u * tpr >= cnt) continue;  // uniform
+            const int j = t < cnt ? s_idx[t] : 0;
+            at[u] = q + (size_t)(j >> 5) * TILE_BYTES + tile_byte(i & 31, j & 31);
+            x[u] = row[j];
+            code[u] = *at[u];
+        }
+#pragma unroll
+        for (int u = 0; u < K; u++) {
+            const int t = base + u * tpr + t1;
+            if (base + u * tpr >= opad) continue;
+            const bool in = t < cnt;
+            if (mine && t < opad) a.Xo[(size_t)i * opad + t] = in ? x[u] : (unsigned short)0;
+            if (mine && in && code[u] != 0) {
+                if constexpr (ZP) {  // the sum of the codes that go, entries that are the smallest, the largest
+                    atomicAdd(&s_gone[0][tr], code[u]);
+                    if (code[u] == -127) atomicAdd(&s_gone[1][tr], 1);
+                    if (code[u] == 127) atomicAdd(&s_gone[2][tr], 1);
+                } else {
+                    if ((unsigned)(x[u] & 0x7fff) == m1) atomicOr(&s_need, 1u << tr);
+                }
+                *at[u] = 0;
             }
-            *at = 0;
         }
     }
+    __syncthreads();
     if constexpr (ZP) {
-#pragma unroll
-        for (int d = 16; d >= 1; d >>= 1) {
-            gone += __shfl_xor(gone, d);
-            nlo += __shfl_xor(nlo, d);
-            nhi += __shfl_xor(nhi, d);
-        }
-        need |= nlo > 0 && nlo >= (z.w & 0xffff);
-        need |= nhi > 0 && nhi >= (int)((unsigned)z.w >> 16);
-    }
-    need = ((__ballot(need) >> (lane & 32)) & 0xffffffffull) != 0 && mine;  // (the half of the wave that shares the row)
-    if ((tid & 31) == 0 && mine) {
-        if (need) {
-            atomicOr(&s_need, 1u << (tid >> 5));
-        } else if (ZP) {
-            z.z -= gone;
-            z.w = 0;
-            zc[i] = z;
-        }
-    }
-    __syncthreads();
-    unsigned again = s_need;
-    if (!again) return;
-    // ---- rows to be made anew: the bitmap of the outlier columns that the buffer takes, then each row by the whole workgroup
-    for (int q = tid; q < nw; q += 256) bitmap[q] = 0;
-    __syncthreads();
-    for (int t = tid; t < cnt; t += 256) atomicOr(&bitmap[s_idx[t] >> 5], 1u << (s_idx[t] & 31));
-    __syncthreads();
-    for (; again; again &= again - 1) {
-        const int i2 = (int)blockIdx.x * SR + __ffs(again) - 1, G = KT * 2;
-        const unsigned short* row2 = X + (size_t)i2 * h;
-        unsigned kmin = 0xffffu, kmax = 0, hi = 0xfbfffbffu, lo = 0x7bff7bffu;
-        // two groups of 16 features in flight per thread, in both passes
-        auto pass = [&](auto f) {
-            for (int g0 = tid; g0 < G; g0 += 512) {
-                us8 a[2][2];
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    a[u][0] = chunk_load(row2, (g0 + 256 * u) * 16, h);
-                    a[u][1] = chunk_load(row2, (g0 + 256 * u) * 16 + 8, h);
-                }
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    const int grp = g0 + 256 * u, c = grp * 16;
-                    if (grp >= G) continue;
-                    unsigned off = past_row(c, h);
-                    if (off) {
-                        a[u][0] = chunk_fix(a[u][0], c, h);
-                        a[u][1] = chunk_fix(a[u][1], c + 8, h);
-                    }
-                    if (c < h) off |= (bitmap[c >> 5] >> (c & 31)) & 0xffffu;
-                    w8 v = words(a[u][0], a[u][1]);
-                    if (!ZP) clear16(v, off);
-                    f(grp, v, off);
-                }
+        if (t1 == 0 && mine) {
+            const int nlo = s_gone[1][tr], nhi = s_gone[2][tr];
+            if ((nlo > 0 && nlo >= (z.w & 0xffff)) || (nhi > 0 && nhi >= (int)((unsigned)z.w >> 16))) {
+                atomicOr(&s_need, 1u << tr);
+            } else if (!all) {
+                z.z -= s_gone[0][tr];
+                z.w = 0;
+                a.zc[i] = z;
             }
-        };
-        pass([&](int, const w8& v, unsigned off) {
-            if constexpr (ZP) {
-                range16_without(v, off, hi, lo);
-            } else {
-                const unsigned x = top16(mags(v));
-                kmax = x > kmax ? x : kmax;
-            }
-        });
-        if constexpr (ZP) keys_of(hi, lo, kmin, kmax);
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            const unsigned a = (unsigned)__shfl_xor((int)kmin, d), b = (unsigned)__shfl_xor((int)kmax, d);
-            kmin = a < kmin ? a : kmin;
-            kmax = b > kmax ? b : kmax;
-        }
-        __syncthreads();  // s_red and s_sum of the row before have been read
-        if (lane == 0) {
-            s_red[0][w] = kmin;
-            s_red[1][w] = kmax;
         }
         __syncthreads();
+    }
+    const unsigned again = all ? (1u << (1 << a.lsr)) - 1 : s_need;
+    if (!again) return;
+    // ---- rows to be made anew
+    if (total > a.cap) {  // the columns that the buffer takes, in place of all
+        for (int x = tid; x < nw; x += NT) bitmap[x] = 0;
+        __syncthreads();
+        for (int t = tid; t < cnt; t += NT) atomicOr(&bitmap[s_idx[t] >> 5], 1u << (s_idx[t] & 31));
+    }
+    const int r = lane & (R - 1), G = KT * 2;
+    for (int r0 = 0; r0 < 1 << a.lsr; r0 += R) {
+        if (!((again >> r0) & ((1u << R) - 1))) continue;
+        __syncthreads();  // the bitmap is there; the rows before have left LDS
+        const int ir = i0 + r0 + r;
+        int g0 = w * (64 >> LR) + (lane >> LR);
+        asm volatile("" : "+v"(g0));  // (opaque: what follows from it is worked out here, not kept from one turn to the next)
+        const bool act = ((again >> (r0 + r)) & 1u) && ir < s;
+        us8 x[N][2];
+        if (act) {
+            const unsigned short* row2 = a.X + (size_t)ir * h;
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            kmin = s_red[0][q] < kmin ? s_red[0][q] : kmin;
-            kmax = s_red[1][q] > kmax ? s_red[1][q] : kmax;
+            for (int n = 0; n < N; n++) {
+                const int c = first_feature<N, STEP>(g0, n, G);
+                x[n][0] = chunk_load(row2, c, h);
+                x[n][1] = chunk_load(row2, c + 8, h);
+            }
         }
-        int8_t* q2 = Xq + (size_t)(i2 >> 5) * KT * TILE_BYTES + (i2 & 31) * 16;
-        if constexpr (ZP) {
-            int4 r = make_int4(0, 0, 0, 0);
-            if (kmin <= kmax) r = make_const(kmin, kmax);
-            const double fd = zp_factor(zp_range((unsigned)r.x));
-            int sum = 0;
-            pass([&](int grp, const w8& v, unsigned off) { *(u4*)(q2 + (size_t)grp * 512) = zp_codes16(v, fd, r.y, off, sum); });
+        w8 v[N];
+        unsigned none[N];
 #pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
-            if (lane == 0) s_sum[w] = sum;
-            __syncthreads();
-            r.z = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
-            if (tid == 0) zc[i2] = r;
-        } else {
-            const float ff = code_factor(f16_bits_to_float((unsigned short)kmax));
-            pass([&](int grp, const w8& v, unsigned) { *(u4*)(q2 + (size_t)grp * 512) = codes16(v, ff); });
-            if (tid == 0) cx[i2] = (unsigned short)kmax;
+        for (int n = 0; n < N; n++) {
+            const int c = first_feature<N, STEP>(g0, n, G);
+            if (c + 16 > h) {
+                x[n][0] = chunk_fix(x[n][0], c, h);
+                x[n][1] = chunk_fix(x[n][1], c + 8, h);
+            }
+            v[n] = words(x[n][0], x[n][1]);
         }
+        constants_and_codes<N, LR, NT, ZP, false, true>(v, none, bitmap, h, G, g0, act, act,
+                                                        a.Xq + (size_t)(ir >> 5) * KT * TILE_BYTES + (ir & 31) * 16, a.cx + ir, a.zc + ir);
     }
 }
 
@@ -711,20 +718,14 @@ bool row_codes_takes(int s, int h, int cap, RowCall call, size_t room)
     return nrec <= 2048 && (size_t)nrec * record_words(cap) * 2 <= room;
 }
 
-template <bool ZP, bool KNOWN>
-static hipError_t launch_row_codes(const RowArgs& g, hipStream_t st)
+// f(threads, log2 of the rows of a workgroup, groups per thread) of q, as constants
+template <class F>
+static hipError_t with_shape(const RowShape& q, F f)
 {
-    const RowShape q = row_shape(g.s, g.h);
-    const int nb = (row_tiles(g.s) * 32) >> q.lr;
-    const size_t shm = (size_t)((g.h + 31) / 32) * 4;
-    const bool ragged = g.h % 128 != 0 || ((uintptr_t)g.X & 15) != 0;
     switch (q.nt + q.lr * 16 + q.n) {
-#define ROWS(NT, LR, N)                                                                     \
-    case NT + LR * 16 + N:                                                                  \
-        if (ragged)                                                                         \
-            row_codes_kernel<N, LR, NT, ZP, KNOWN, true><<<nb, NT, shm, st>>>(g);           \
-        else                                                                                \
-            row_codes_kernel<N, LR, NT, ZP, KNOWN, false><<<nb, NT, shm, st>>>(g);          \
+#define ROWS(NT, LR, N)                                                                                                             \
+    case NT + LR * 16 + N:                                                                                                          \
+        f(std::integral_constant<int, NT>(), std::integral_constant<int, LR>(), std::integral_constant<int, N>());                  \
         break
         ROWS(256, 3, 1); ROWS(256, 3, 2); ROWS(256, 3, 3); ROWS(256, 3, 4);
         ROWS(256, 2, 1); ROWS(256, 2, 2);
@@ -741,6 +742,29 @@ static hipError_t launch_row_codes(const RowArgs& g, hipStream_t st)
     return hipGetLastError();
 }
 
+template <bool ZP, bool KNOWN>
+static hipError_t launch_row_codes(const RowArgs& g, hipStream_t st)
+{
+    const RowShape q = row_shape(g.s, g.h);
+    const int nb = (row_tiles(g.s) * 32) >> q.lr;
+    const size_t shm = (size_t)((g.h + 31) / 32) * 4;
+    const bool ragged = g.h % 128 != 0 || ((uintptr_t)g.X & 15) != 0;
+    return with_shape(q, [&](auto nt, auto lr, auto n) {
+        if (ragged)
+            row_codes_kernel<n(), lr(), nt(), ZP, KNOWN, true><<<nb, nt(), shm, st>>>(g);
+        else
+            row_codes_kernel<n(), lr(), nt(), ZP, KNOWN, false><<<nb, nt(), shm, st>>>(g);
+    });
+}
+
+template <bool ZP>
+static hipError_t launch_settle(const SettleArgs& a, int jobs, hipStream_t st)
+{
+    return with_shape(row_shape(a.s, a.h), [&](auto nt, auto lr, auto n) {
+        settle_rows_kernel<n(), lr(), nt(), ZP><<<a.nb + jobs, nt(), (size_t)((a.h + 31) / 32) * 4, st>>>(a);
+    });
+}
+
 hipError_t launch_prepass_rows(const void* X, int s, int h, unsigned thr, void* records, int32_t* idx, int cap,
                                int32_t* count, int32_t* status, int8_t* Xq, unsigned short* cx, int4* zc,
                                unsigned short* Xo, const ColumnJob* cj, hipStream_t st)
@@ -749,16 +773,13 @@ hipError_t launch_prepass_rows(const void* X, int s, int h, unsigned thr, void* 
                        (unsigned short*)records, Xq, cx, zc, nullptr};
     const hipError_t e = zc ? launch_row_codes<true, false>(g, st) : launch_row_codes<false, false>(g, st);
     if (e != hipSuccess) return e;
-    const int nrec = (row_tiles(s) * 32) >> row_shape(s, h).lr;
+    const int lr = row_shape(s, h).lr, nrec = (row_tiles(s) * 32) >> lr;
+    int lsr = lr;  // more rows to a workgroup while that leaves one for every compute unit: each joins the records for itself
+    while ((1 << lsr) < MAX_SR && s >= 256 << (lsr + 1)) lsr++;
     const ColumnJob job = cj ? *cj : ColumnJob{nullptr, nullptr, nullptr, 0, 0};
     const int parts = zc ? 1 : (g.opad + JOB_SLOTS - 1) / JOB_SLOTS;
-    const int grid = (s + SR - 1) / SR + job.pitch / 256 * parts;
-    const size_t shm = (size_t)((h + 31) / 32) * 4;
-    if (zc)
-        settle_rows_kernel<true><<<grid, 256, shm, st>>>(g.X, s, h, thr, g.rec, nrec, idx, cap, g.opad, count, status, Xq, g.KT, cx, zc, Xo, job);
-    else
-        settle_rows_kernel<false><<<grid, 256, shm, st>>>(g.X, s, h, thr, g.rec, nrec, idx, cap, g.opad, count, status, Xq, g.KT, cx, zc, Xo, job);
-    return hipGetLastError();
+    const SettleArgs a = {g.X, s, h, g.KT, cap, g.opad, nrec, lsr, (row_tiles(s) * 32) >> lsr, g.rec, idx, count, status, Xq, cx, zc, Xo, job};
+    return zc ? launch_settle<true>(a, job.pitch / 256 * parts, st) : launch_settle<false>(a, job.pitch / 256 * parts, st);
 }
 
 hipError_t launch_quantize_rows_known(const void* X, int s, int h, const int32_t* idx, const int32_t* count, int cap,
