@@ -162,9 +162,14 @@ __device__ __forceinline__ void keys_of(unsigned hi, unsigned lo, unsigned& kmin
     kmax = k3 > k2 ? k3 : k2;
 }
 
+// what runs seldom is to lie outside the way of what runs always
+__device__ __forceinline__ bool rare(bool x) { return __builtin_expect(x, 0); }
+
 __device__ __forceinline__ void add_bit(unsigned* bitmap, unsigned j)
 {
-    if (!((*(volatile unsigned*)&bitmap[j >> 5] >> (j & 31)) & 1u)) atomicOr(&bitmap[j >> 5], 1u << (j & 31));  // (mostly there already)
+    // (mostly there already; an atomic load, because a volatile one comes out as a flat access that waits for all of memory)
+    const unsigned there = __hip_atomic_load(&bitmap[j >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (!((there >> (j & 31)) & 1u)) atomicOr(&bitmap[j >> 5], 1u << (j & 31));
 }
 
 // first feature of a lane's group n; past the last group: the last one again
@@ -313,6 +318,7 @@ struct RowArgs {
     unsigned thr;          // !KNOWN
     const int32_t *idx, *count;  // KNOWN
     unsigned short* rec;   // !KNOWN: a record per workgroup
+    unsigned* joined;      // !KNOWN: words of a bitmap of h to clear, or NULL
     int8_t* Xq;
     unsigned short* cx;    // absmax
     int4* zc;              // zeropoint
@@ -353,6 +359,8 @@ __global__ void __launch_bounds__(NT, row_waves(N)) row_codes_kernel(const RowAr
     }
     const int nw = (h + 31) >> 5;
     for (int q = tid; q < nw; q += NT) bitmap[q] = 0;
+    if (!KNOWN && g.joined && rg == 0)
+        for (int q = tid; q < nw; q += NT) g.joined[q] = 0;
     int cnt = 0;
     if constexpr (KNOWN) {
         cnt = *g.count;
@@ -402,95 +410,162 @@ __global__ void __launch_bounds__(NT, row_waves(N)) row_codes_kernel(const RowAr
     if (!KNOWN && w == NW - 1) write_record(bitmap, nw, lane, g.cap, g.rec + (size_t)rg * record_words(g.cap));
 }
 
-// The records' columns into the bitmap (cleared here), U records in flight per thread
+// The columns of nrec <= U NT records into the bitmap (cleared here), U records in flight per thread; complete after the barrier
+// at the end.
 template <int NT, int U>
 __device__ __forceinline__ void gather_records(const unsigned short* __restrict__ rec, int nrec, int cap, int nw, unsigned* bitmap)
 {
+    __shared__ unsigned s_long[U * NT];  // records of more than 31 columns: their numbers, their columns << 16
+    __shared__ int s_longs, s_most;
     const int tid = threadIdx.x, pitch = record_words(cap);
-    // Most records name the same columns.  Sixteen of them go into the bitmap first, two columns to a thread; of the others only
-    // those that know more add anything.  (Every record's columns added to the bitmap by its thread, 64 at a time to one
-    // word of LDS: 34 us for 2 048 records of 20 columns.)
+    // Most records name the same columns.  Sixteen of them go into the bitmap first, two columns of the first 31 and up to
+    // sixteen of the others to a thread; of the rest only those that know more add anything.  (Every record's columns added to
+    // the bitmap by its thread, 64 at a time to one word of LDS: 34 us for 2 048 records of 20 columns.)
     us8 a[U], b[U], c[U], d[U];
-    auto request = [&](int r0, us8* x, us8* y, int at) {
+    auto request = [&](us8* x, int at) {
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            const int r = r0 + NT * u < nrec ? r0 + NT * u : nrec - 1;
+            const int r = tid + NT * u < nrec ? tid + NT * u : nrec - 1;
             x[u] = *(const us8*)(rec + (size_t)r * pitch + min(at, pitch - 8));
-            y[u] = *(const us8*)(rec + (size_t)r * pitch + min(at + 8, pitch - 8));
         }
     };
     const int e0 = tid & 15;
     const unsigned short* seed = rec + (size_t)((long long)((tid >> 4) & 15) * nrec >> 4) * pitch;
     const int sn = min((int)seed[0], cap + 1);
     const unsigned sj = seed[e0], sk = seed[min(16 + e0, pitch - 1)];
-    request(tid, a, b, 0);
-    if (U == 1) request(tid, c, d, 16);  // (few records: columns 16 to 31 along with the others, no round trip of their own)
+    us8 t0 = (us8)(0), t1 = (us8)(0);
+    if (cap > 32) {
+        t0 = *(const us8*)(seed + min(32 + 8 * e0, pitch - 8));
+        t1 = *(const us8*)(seed + min(160 + 8 * e0, pitch - 8));
+    }
+    request(a, 0);
+    request(b, 8);
+    if (U == 1) {  // (few records: columns 16 to 31 along with the others, no round trip of their own)
+        request(c, 16);
+        request(d, 24);
+    }
     for (int q = tid; q < nw; q += NT) bitmap[q] = 0;
+    if (tid == 0) s_longs = s_most = 0;
     __syncthreads();
     if (tid < 256) {
         if (e0 > 0 && e0 <= sn) add_bit(bitmap, sj);
         if (16 + e0 <= sn) add_bit(bitmap, sk);
+        if (rare(cap > 32 && __any(sn > 31))) {
+#pragma unroll
+            for (int k = 0; k < 8; k++)
+                if (31 + 8 * e0 + k < sn) atomicOr(&bitmap[t0[k] >> 5], 1u << (t0[k] & 31));
+        }
+        if (rare(cap > 32 && __any(sn > 159))) {
+#pragma unroll
+            for (int k = 0; k < 8; k++)
+                if (159 + 8 * e0 + k < sn) atomicOr(&bitmap[t1[k] >> 5], 1u << (t1[k] & 31));
+        }
     }
     __syncthreads();
-    for (int r0 = tid; r0 < nrec; r0 += NT * U) {
-        if (r0 != tid) request(r0, a, b, 0);
-        int n[U], most = 0;
-        unsigned known[U];
+    // the n columns from word k of a piece on, looked up together; those that are not there are added
+    auto look = [&](const us8& piece, int n, int k0) {
+        unsigned lack = 0;
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            n[u] = r0 + NT * u < nrec ? min((int)a[u][0], cap + 1) : 0;
-            known[u] = ~0u;
-            most = n[u] > most ? n[u] : most;
+        for (int k = k0; k < 8; k++) {
+            const bool in = k - k0 < n;
+            const unsigned j = in ? piece[k] : 0u;
+            const unsigned there = bitmap[j >> 5] >> (j & 31);
+            lack |= (in ? ~there & 1u : 0u) << k;
         }
-        // eight columns (e, ... of each record, from word k of a piece) looked up together
-        auto look = [&](const us8* piece, int e, int k0) {
+        if (rare(__any(lack != 0))) {
 #pragma unroll
-            for (int u = 0; u < U; u++)
-#pragma unroll
-                for (int k = k0; k < 8; k++) {
-                    const bool in = e + k - k0 < n[u];
-                    const unsigned j = in ? piece[u][k] : 0u;
-                    const unsigned word = bitmap[j >> 5] >> (j & 31);
-                    known[u] &= in ? word : ~0u;
-                }
-        };
-        look(a, 0, 1);
-        if (__any(most > 7)) look(b, 7, 0);
-        if (__any(most > 15)) {
-            if (U > 1) request(r0, c, d, 16);
-            look(c, 15, 0);
-            if (__any(most > 23)) look(d, 23, 0);
+            for (int k = k0; k < 8; k++)
+                if ((lack >> k) & 1u) atomicOr(&bitmap[piece[k] >> 5], 1u << (piece[k] & 31));
         }
+    };
+    int n[U], most = 0;
 #pragma unroll
-        for (int u = 0; u < U; u++)
-            if (n[u] > 31 || !(known[u] & 1u)) {
-                const unsigned short* p = rec + (size_t)(r0 + NT * u) * pitch;
-                for (int e = 0; e < n[u]; e += 8) {
-                    unsigned short c[8];
-#pragma unroll
-                    for (int k = 0; k < 8; k++) c[k] = p[1 + (e + k < n[u] ? e + k : e)];
-#pragma unroll
-                    for (int k = 0; k < 8; k++) add_bit(bitmap, c[k]);
-                }
-            }
+    for (int u = 0; u < U; u++) {
+        n[u] = tid + NT * u < nrec ? min((int)a[u][0], cap + 1) : 0;
+        most = n[u] > most ? n[u] : most;
+        if (rare(n[u] > 31)) {
+            s_long[atomicAdd(&s_longs, 1)] = (unsigned)(tid + NT * u) | (unsigned)n[u] << 16;
+            atomicMax(&s_most, n[u]);
+        }
     }
+    auto look_all = [&](const us8* piece, int e, int k0) {
+#pragma unroll
+        for (int u = 0; u < U; u++) look(piece[u], n[u] - e, k0);
+    };
+    look_all(a, 0, 1);
+    if (__any(most > 7)) look_all(b, 7, 0);
+    if (__any(most > 15)) {
+        if (U > 1) {
+            request(c, 16);
+            request(d, 24);
+        }
+        look_all(c, 15, 0);
+        if (__any(most > 23)) look_all(d, 23, 0);
+    }
+    __syncthreads();
+    // The columns from the 32nd on, in chunks of eight, of which every thread has four in flight.  (A thread for each record, one chunk
+    // after the other: calls of 200 columns and 64 output columns 42.7 us instead of 27.8 at 96 x 5120, 90 / 42.6 at 1024 x 8192, 137 / 47.5
+    // at 4096 x 5120; a wave for each record, eight at a time: 29.6, 43.2, 48.2, and 46 against 42.7 at 2048 x 4096.)
+    const int longs = s_longs, C = (s_most - 31 + 7) >> 3;
+    if (!rare(longs > 0)) return;  // uniform
+    constexpr int Q = 4;
+    const int items = longs * C;  // (record, chunk)
+    const unsigned inv = ((1u << 20) + C - 1) / C;  // item / C: exact below 512 * 32
+    for (int i0 = tid; i0 < items; i0 += Q * NT) {
+        us8 x[Q];
+        int left[Q];  // columns of the chunk
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            const int i = i0 + q * NT < items ? i0 + q * NT : items - 1;
+            const int l = (int)(((unsigned)i * inv) >> 20), c = i - l * C;
+            const unsigned r = s_long[l];
+            left[q] = i0 + q * NT < items ? (int)(r >> 16) - 31 - 8 * c : 0;
+            x[q] = *(const us8*)(rec + (size_t)(r & 0xffffu) * pitch + 32 + (left[q] > 0 ? 8 * c : 0));
+        }
+#pragma unroll
+        for (int q = 0; q < Q; q++)
+            if (__any(left[q] > 0)) look(x[q], left[q], 0);
+    }
+    __syncthreads();
 }
 
+// More records than a workgroup joins in little time: 32 of them to a workgroup here, what these find added to one bitmap, which
+// row_codes_kernel has cleared.
+constexpr int JOIN_SLICE = 32;
+__global__ void __launch_bounds__(256) join_records_kernel(const unsigned short* __restrict__ rec, int nrec, int cap, int nw,
+                                                           unsigned* __restrict__ joined)
+{
+    extern __shared__ unsigned bitmap[];
+    const int first = blockIdx.x * JOIN_SLICE;
+    gather_records<256, 1>(rec + (size_t)first * record_words(cap), min(JOIN_SLICE, nrec - first), cap, nw, bitmap);
+    for (int q = threadIdx.x; q < nw; q += 256)
+        if (bitmap[q]) atomicOr(&joined[q], bitmap[q]);
+}
+
+// Which calls take that kernel: those of many records, and of fewer where they may be long.  Us per call with 512 output columns, so /
+// joined by every workgroup for itself: 256 records (512 x 4096), 7 columns 18.2 / 16.8, 40 columns 21.7 / 21.8, 200 columns 29.9 / 35.5;
+// 512 records of a buffer of 32 (1024 x 8192), 7 columns 29.6 / 28.3, 31 columns 31.3 / 31.0; of a buffer of 256, 7 columns 29.7 / 28.7, 40
+// columns 34.7 / 38.8, 200 columns 45.7 / 60.7.
+static bool join_first(int nrec, int cap) { return nrec > (cap > 32 ? 256 : 512); }
+
 // ---------------------------------------------------------------------------
-// The outlier set from the records, by all NT threads of a workgroup: s_idx[0 .. min(total, cap)) ascending.  bitmap:
-// ceil(h / 32) words of LDS, left with the bits of all qualifying columns.  Returns their number.
+// The outlier set, by all NT threads of a workgroup: s_idx[0 .. min(total, cap)) ascending, from up to 512 records or the joined
+// bitmap.  bitmap: ceil(h / 32) words of LDS, left with the bits of all qualifying columns.  Returns their number.
 // ---------------------------------------------------------------------------
 template <int NT>
-__device__ __forceinline__ int join_records(const unsigned short* __restrict__ rec, int nrec, int cap, int nw, unsigned* bitmap,
-                                            int* s_idx)
+__device__ __forceinline__ int outlier_set(const unsigned short* __restrict__ rec, int nrec, const unsigned* __restrict__ joined, int cap,
+                                           int nw, unsigned* bitmap, int* s_idx)
 {
     __shared__ int s_wsum[NT / 64];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    if (nrec <= NT)
+    if (rare(joined != nullptr)) {
+        for (int q = tid; q < nw; q += NT) bitmap[q] = joined[q];
+        __syncthreads();
+    } else if (NT >= 512 || nrec <= NT) {
         gather_records<NT, 1>(rec, nrec, cap, nw, bitmap);
-    else
-        gather_records<NT, 1024 / NT>(rec, nrec, cap, nw, bitmap);
-    __syncthreads();
+    } else {
+        gather_records<NT, NT >= 512 ? 1 : 2>(rec, nrec, cap, nw, bitmap);
+    }
     const int q = (nw + NT - 1) / NT, b0 = tid * q, b1 = min(nw, b0 + q);
     int mine = 0;
     for (int x = b0; x < b1; x++) mine += __popc(bitmap[x]);
@@ -519,11 +594,11 @@ __device__ __forceinline__ int join_records(const unsigned short* __restrict__ r
 // ---------------------------------------------------------------------------
 // A workgroup settles 2^lsr rows (one or more of those that row_codes_kernel, of the same shape, gave a workgroup), NT >> lsr
 // threads to a row; the workgroups past the rows take a column job.  A chain of round trips: records, columns of X and codes,
-// stores; 4 us for 256 records, 6.3 for 512, 10.5 for 1 024 of 20 columns (2.8 of them launch and drain).
+// stores; 4.4 us for 256 records of 7 columns, 5.2 of 20, 15 of 200 (2.8 of them launch and drain).
 // Rows to be made anew are held in registers as there, R at a time and all of a workgroup's lanes on them.  Where that is every
-// row, calls with 64 output columns, us (one row after the other / the kernels of prepass.hip, zeropoint.hip): 96 x 5120 16.1
-// (27.8 / 16.5), 1024 x 8192 33.0 (44.5 / 35.1), 4096 x 5120 37.9 (52.2 / 48.0), 4096 x 12288 86.0 (105.4 / 84.0), 2048 x 49152 205
-// (296 / 170), zeropoint 512 x 4096 19.9 (32.0 / 22.6), 2048 x 5120 35.1 (47.8 / 34.5), 1024 x 28672 81.5 (110.5 / 71.6).
+// row, calls with 64 output columns, us (one row after the other / the kernels of prepass.hip, zeropoint.hip): 96 x 5120 15.8
+// (27.8 / 16.5), 1024 x 8192 31.1 (44.5 / 35.1), 4096 x 5120 37.7 (52.2 / 48.0), 4096 x 12288 81.3 (105.4 / 84.0), 2048 x 49152 206
+// (296 / 170), zeropoint 512 x 4096 19.2 (32.0 / 22.6), 2048 x 5120 33.7 (47.8 / 34.5), 1024 x 28672 80.8 (110.5 / 71.6).
 // ---------------------------------------------------------------------------
 constexpr int MAX_SR = 8;
 struct SettleArgs {
@@ -531,6 +606,7 @@ struct SettleArgs {
     int s, h, KT, cap, opad, nrec;
     int lsr, nb;  // rows of a workgroup (log2), workgroups of rows
     const unsigned short* rec;
+    const unsigned* joined;  // or NULL
     int32_t *idx, *count, *status;
     int8_t* Xq;
     unsigned short* cx;
@@ -542,14 +618,17 @@ struct SettleArgs {
 template <int N, int LR, int NT, bool ZP>
 __global__ void __launch_bounds__(NT, 4) settle_rows_kernel(const SettleArgs a)
 {
-    constexpr int R = 1 << LR, STEP = NT >> LR, K = 4;
+    constexpr int R = 1 << LR, STEP = NT >> LR;
     extern __shared__ unsigned bitmap[];
     __shared__ int s_idx[JOB_MAX_CAP];
     __shared__ unsigned s_need;
     __shared__ int s_gone[ZP ? 3 : 1][MAX_SR];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int s = a.s, h = a.h, KT = a.KT, opad = a.opad, nw = (h + 31) >> 5;
-    const int tpr = NT >> a.lsr, tr = tid / tpr, t1 = tid & (tpr - 1);  // this thread's row of the workgroup, its first outlier column
+    // (all arguments requested at once: behind the first branch they would be another round trip)
+    asm volatile("" ::"s"(a.X), "s"(a.rec), "s"(a.joined), "s"(a.nrec), "s"(a.cap), "s"(a.opad), "s"(a.KT), "s"(a.idx), "s"(a.count), "s"(a.Xq),
+                 "s"(ZP ? (const void*)a.zc : (const void*)a.cx), "s"(a.Xo));
+    const int tpr = NT >> a.lsr, tr = tid >> (__builtin_ctz(NT) - a.lsr), t1 = tid & (tpr - 1);  // this thread's row of the workgroup, its first outlier column
     const bool job = (int)blockIdx.x >= a.nb;
     // (the rows on the XCD whose L2 may still have their codes)
     const int xcd = blockIdx.x & 7, b = job ? 0 : xcd * (a.nb >> 3) + min(xcd, a.nb & 7) + (blockIdx.x >> 3);
@@ -564,9 +643,9 @@ __global__ void __launch_bounds__(NT, 4) settle_rows_kernel(const SettleArgs a)
         m1 = a.cx[mine ? i : 0];
     if (tid == 0) s_need = 0;
     if (ZP && tid < 3 * MAX_SR) s_gone[tid / MAX_SR][tid % MAX_SR] = 0;
-    const int total = join_records<NT>(a.rec, a.nrec, a.cap, nw, bitmap, s_idx);
+    const int total = outlier_set<NT>(a.rec, a.nrec, a.joined, a.cap, nw, bitmap, s_idx);
     const int cnt = total < a.cap ? total : a.cap;
-    if (job) {
+    if (rare(job)) {
         if (tid >= 256) return;
         const int jb = (int)blockIdx.x - a.nb, parts = a.cj.pitch >> 8, j = (jb % parts) * 256 + tid;
         if constexpr (ZP)
@@ -590,37 +669,44 @@ __global__ void __launch_bounds__(NT, 4) settle_rows_kernel(const SettleArgs a)
     const bool all = total > a.cap || (ZP && cnt == h);
     const unsigned short* row = a.X + (size_t)(mine ? i : 0) * h;
     int8_t* q = a.Xq + (size_t)(mine ? i >> 5 : 0) * KT * TILE_BYTES;
-    for (int base = 0; base < opad; base += K * tpr) {
-        unsigned short x[K];
-        int code[K];
-        int8_t* at[K];
+    auto take_back = [&](auto in_flight) {
+        constexpr int K = in_flight;
+        for (int base = 0; base < opad; base += K * tpr) {
+            unsigned short x[K];
+            int code[K];
+            int8_t* at[K];
 #pragma unroll
-        for (int u = 0; u < K; u++) {
-            const int t = base + u * tpr + t1;
-            if (base + u * tpr >= cnt) continue;  // uniform
-            const int j = t < cnt ? s_idx[t] : 0;
-            at[u] = q + (size_t)(j >> 5) * TILE_BYTES + tile_byte(i & 31, j & 31);
-            x[u] = row[j];
-            code[u] = *at[u];
-        }
+            for (int u = 0; u < K; u++) {
+                const int t = base + u * tpr + t1;
+                if (base + u * tpr >= cnt) continue;  // uniform
+                const int j = t < cnt ? s_idx[t] : 0;
+                at[u] = q + (size_t)(j >> 5) * TILE_BYTES + tile_byte(i & 31, j & 31);
+                x[u] = row[j];
+                code[u] = *at[u];
+            }
 #pragma unroll
-        for (int u = 0; u < K; u++) {
-            const int t = base + u * tpr + t1;
-            if (base + u * tpr >= opad) continue;
-            const bool in = t < cnt;
-            if (mine && t < opad) a.Xo[(size_t)i * opad + t] = in ? x[u] : (unsigned short)0;
-            if (mine && in && code[u] != 0) {
-                if constexpr (ZP) {  // the sum of the codes that go, entries that are the smallest, the largest
-                    atomicAdd(&s_gone[0][tr], code[u]);
-                    if (code[u] == -127) atomicAdd(&s_gone[1][tr], 1);
-                    if (code[u] == 127) atomicAdd(&s_gone[2][tr], 1);
-                } else {
-                    if ((unsigned)(x[u] & 0x7fff) == m1) atomicOr(&s_need, 1u << tr);
+            for (int u = 0; u < K; u++) {
+                const int t = base + u * tpr + t1;
+                if (base + u * tpr >= opad) continue;
+                const bool in = t < cnt;
+                if (mine && t < opad) a.Xo[(size_t)i * opad + t] = in ? x[u] : (unsigned short)0;
+                if (rare(mine && in && code[u] != 0)) {
+                    if constexpr (ZP) {  // the sum of the codes that go, entries that are the smallest, the largest
+                        atomicAdd(&s_gone[0][tr], code[u]);
+                        if (code[u] == -127) atomicAdd(&s_gone[1][tr], 1);
+                        if (code[u] == 127) atomicAdd(&s_gone[2][tr], 1);
+                    } else {
+                        if ((unsigned)(x[u] & 0x7fff) == m1) atomicOr(&s_need, 1u << tr);
+                    }
+                    *at[u] = 0;
                 }
-                *at[u] = 0;
             }
         }
-    }
+    };
+    if (opad <= tpr)
+        take_back(std::integral_constant<int, 1>());
+    else
+        take_back(std::integral_constant<int, 4>());
     __syncthreads();
     if constexpr (ZP) {
         if (t1 == 0 && mine) {
@@ -636,7 +722,7 @@ __global__ void __launch_bounds__(NT, 4) settle_rows_kernel(const SettleArgs a)
         __syncthreads();
     }
     const unsigned again = all ? (1u << (1 << a.lsr)) - 1 : s_need;
-    if (!again) return;
+    if (!rare(again != 0)) return;
     // ---- rows to be made anew
     if (total > a.cap) {  // the columns that the buffer takes, in place of all
         for (int x = tid; x < nw; x += NT) bitmap[x] = 0;
@@ -695,6 +781,9 @@ static RowShape row_shape(int s, int h)
     return {lr, (items + nt - 1) / nt, nt};
 }
 
+// the joined bitmap's place in front of the records
+static size_t joined_bytes(int h, int nrec, int cap) { return join_first(nrec, cap) ? (size_t)((h + 255) / 256) * 32 : 0; }
+
 // Which calls come here, us per call, here / with the kernels of prepass.hip and zeropoint.hip (which keep the rest):
 //   up to 128 tokens, 16-bit weights: 16 x 4096 x 2048 15.0 / 17.7, 32 x 4100 x 4100 16.1 / 19.3, 16 x 12288 x 49152 99.1 / 101.1, 33 x 4096
 //     x 4096 15.3 / 16.0, 96 x 5120 x 15360 26.3 / 28.9, 2 x 20480 x 2048 22.8 / 23.7, 40 x 20480 x 512 25.8 / 26.4; with more features
@@ -715,7 +804,7 @@ bool row_codes_takes(int s, int h, int cap, RowCall call, size_t room)
     if (call == RowCall::known) return !(h > 32768 && s > 256 && s < 512);
     if (call == RowCall::zeropoint ? s < 16 && h > 12288 : s <= 128 && h > (call == RowCall::rebuilt ? 4096 : 20480)) return false;
     const int nrec = (row_tiles(s) * 32) >> row_shape(s, h).lr;
-    return nrec <= 2048 && (size_t)nrec * record_words(cap) * 2 <= room;
+    return nrec <= 2048 && (size_t)nrec * record_words(cap) * 2 + joined_bytes(h, nrec, cap) <= room;
 }
 
 // f(threads, log2 of the rows of a workgroup, groups per thread) of q, as constants
@@ -769,23 +858,29 @@ hipError_t launch_prepass_rows(const void* X, int s, int h, unsigned thr, void* 
                                int32_t* count, int32_t* status, int8_t* Xq, unsigned short* cx, int4* zc,
                                unsigned short* Xo, const ColumnJob* cj, hipStream_t st)
 {
+    const int lr = row_shape(s, h).lr, nrec = (row_tiles(s) * 32) >> lr, nw = (h + 31) / 32;
+    unsigned* joined = join_first(nrec, cap) ? (unsigned*)records : nullptr;
     const RowArgs g = {(const unsigned short*)X, s, h, k_tiles(h), cap, opad_of(cap), thr, nullptr, nullptr,
-                       (unsigned short*)records, Xq, cx, zc, nullptr};
-    const hipError_t e = zc ? launch_row_codes<true, false>(g, st) : launch_row_codes<false, false>(g, st);
+                       (unsigned short*)((char*)records + joined_bytes(h, nrec, cap)), joined, Xq, cx, zc, nullptr};
+    hipError_t e = zc ? launch_row_codes<true, false>(g, st) : launch_row_codes<false, false>(g, st);
     if (e != hipSuccess) return e;
-    const int lr = row_shape(s, h).lr, nrec = (row_tiles(s) * 32) >> lr;
+    if (joined) {
+        join_records_kernel<<<(nrec + JOIN_SLICE - 1) / JOIN_SLICE, 256, nw * 4, st>>>(g.rec, nrec, cap, nw, joined);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     int lsr = lr;  // more rows to a workgroup while that leaves one for every compute unit: each joins the records for itself
     while ((1 << lsr) < MAX_SR && s >= 256 << (lsr + 1)) lsr++;
     const ColumnJob job = cj ? *cj : ColumnJob{nullptr, nullptr, nullptr, 0, 0};
     const int parts = zc ? 1 : (g.opad + JOB_SLOTS - 1) / JOB_SLOTS;
-    const SettleArgs a = {g.X, s, h, g.KT, cap, g.opad, nrec, lsr, (row_tiles(s) * 32) >> lsr, g.rec, idx, count, status, Xq, cx, zc, Xo, job};
+    const SettleArgs a = {g.X, s, h, g.KT, cap, g.opad, nrec, lsr, (row_tiles(s) * 32) >> lsr, g.rec, joined, idx, count, status, Xq, cx, zc, Xo, job};
     return zc ? launch_settle<true>(a, job.pitch / 256 * parts, st) : launch_settle<false>(a, job.pitch / 256 * parts, st);
 }
 
 hipError_t launch_quantize_rows_known(const void* X, int s, int h, const int32_t* idx, const int32_t* count, int cap,
                                       int8_t* Xq, unsigned short* cx, int4* zc, unsigned short* Xo, hipStream_t st)
 {
-    const RowArgs g = {(const unsigned short*)X, s, h, k_tiles(h), cap, opad_of(cap), 0, idx, count, nullptr, Xq, cx, zc, Xo};
+    const RowArgs g = {(const unsigned short*)X, s, h, k_tiles(h), cap, opad_of(cap), 0, idx, count, nullptr, nullptr, Xq, cx, zc, Xo};
     return zc ? launch_row_codes<true, true>(g, st) : launch_row_codes<false, true>(g, st);
 }
 

@@ -102,6 +102,15 @@ def test_more_outlier_columns_than_the_buffer_takes_at_33_to_128_tokens(s, alpha
     assert ratio(a, b) < 3.0
 
 
+@pytest.mark.parametrize("s,h,zeropoint", [(96, 5120, False), (96, 5120, True), (256, 4096, False), (1024, 8192, False), (2048, 4096, False),
+                                           (2048, 5120, True), (4096, 12288, False)])
+def test_many_outlier_columns_in_the_pre_pass_that_reads_x_once(s, h, zeropoint):
+    """200 outlier columns in a buffer of 256 against one of 257, which the kernels that read X twice take: 0.6 to 1.0.  With
+    records of more than 31 columns joined by a thread for each, 1.4 to 4."""
+    a, b = (prepare(s, h, 64, 200, cap, zeropoint) for cap in (256, 257))
+    assert ratio(a, b) < 1.15
+
+
 def rows_decided_by_outlier_columns(s, h):
     """Six columns that one token each takes above the threshold and that hold the largest entries of all others."""
     X = np.clip(wl.make_custom(s, h, 1, 0, seed=5)["X"].astype(np.float32), -0.25, 4.4)

@@ -185,3 +185,39 @@ def test_constant_rows_where_every_column_is_an_outlier(s, h, zp):
     outl, rows = buffers(s, h, cap, zp)
     (L.zp_linear if zp else L.linear)(Xd, qw, alpha, outl, rows, ws)
     check(X, outl, rows, alpha, cap, zp)
+
+
+def scratch_for_records(s, h, o, cap):
+    """Bytes that the workspace of a call has for the records."""
+    import paper_2208_07339_amd as L
+
+    def up(n):
+        return (n + 255) // 256 * 256
+    scan = L.workspace_bytes(s, h, o, cap) - 256 - up(L.opad(cap) * o * 2) - 24 * (up(o) + 256)
+    return scan - up(4096 + (h + 255) // 256 * min(cap, 256) * 4 + (h + 511) // 512 * 128)
+
+
+@pytest.mark.parametrize("zp", [False, True])
+@pytest.mark.parametrize("cap,n", [(256, 45), (256, 200), (256, 300), (60, 50), (32, 33), (32, 32)])
+@pytest.mark.parametrize("s,h,records", [(40, 5120, 64), (256, 4096, 256), (258, 4100, 288), (600, 8200, 304), (1024, 8192, 512), (1030, 4096, 528),
+                                         (2050, 1000, 260), (2048, 12288, 1024)])
+def test_many_columns_in_the_records(s, h, records, cap, n, zp):
+    """Records of up to more columns than a thread looks at, as many as the buffer takes and more; joined by each workgroup
+    for itself or by a kernel of their own (more than 256 records, or 512 of a buffer of up to 32)."""
+    import paper_2208_07339_amd as L
+    o, alpha = 4096, 6.0
+    assert scratch_for_records(s, h, o, cap) >= records * (cap + 17) // 16 * 32 + (h + 255) // 256 * 32
+    rng = np.random.default_rng(s + h + n)
+    X = np.clip(rng.standard_normal((s, h), dtype=np.float32), -0.25 if zp else -4.0, 4.0)
+    for t, j in enumerate(rng.choice(h, size=n, replace=False)):  # from one row alone to nearly all
+        X[:, j] = np.where(rng.random(s) < t / n, 9.0, X[:, j])
+        X[rng.integers(0, s), j] = 9.0
+        X[rng.integers(0, s), j] = 5.5
+    X = X.astype(np.float16)
+    Xd, Wd = device(X), device(rng.standard_normal((h, o), dtype=np.float32).astype(np.float16))
+    ws = L.Workspace.allocate(s, h, o, cap)
+    qw = L.zp_quantize_weight(Wd, ws) if zp else L.quantize_weight(Wd, ws)
+    outl, rows = buffers(s, h, cap, zp)
+    for _ in range(2):  # twice: what the first call left in the workspace must not matter
+        (L.zp_linear if zp else L.linear)(Xd, qw, alpha, outl, rows, ws)
+    check(X, outl, rows, alpha, cap, zp)
