@@ -190,17 +190,18 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
             for (int q = 0; q < 3; q++) s_zc[q][tid] = zc[q];
         }
     }
-    // More outlier columns than fit: their product comes first, a chunk of slots in LDS after the other, the next one's
-    // operands on their way meanwhile.  (Up to 32 tokens, where it comes last, past the first chunk from memory below.)
-    // Calls with 200 columns, 128 x 12288 x 8192: 56 us; with every column's operands from memory for each output 180, with
-    // the tiles of gemm.hip 93.
-    const bool many = s > 32 && cnt > KSLOTS;
+    // More outlier columns than fit: a chunk of slots in LDS after the other, the next one's operands on their way meanwhile;
+    // their product comes first, or last up to 32 tokens.  Calls with 200 columns, 128 x 12288 x 8192: 56 us; with every column's
+    // operands from memory for each output 180, with the tiles of gemm.hip 93.  Products of few tokens with 200, so / from memory
+    // for each output / with the weight-streaming kernel: 8 x 8192 x 4096 12.7 / 66.9 / 40.2, 16 x 4096 x 4096 9.9 / 44.9 / 66.1, 32 x
+    // 4096 x 2048 11.8 / 47.2, zeropoint 8 x 12288 x 4096 33.7 / 92 / 65.4.
+    const bool many = cnt > KSLOTS;
     float od[NI][4];
 #pragma unroll
     for (int t = 0; t < NI; t++)
 #pragma unroll
         for (int e = 0; e < 4; e++) od[t][e] = 0.0f;
-    if (__builtin_expect(many, 0)) {  // uniform
+    auto chunks = [&]() {  // by all threads; od goes on from what it holds
         auto rows_of = [&](int q0) {  // the rows of this thread's slots of a chunk
 #pragma unroll
             for (int q = 0; q < NS; q++) {
@@ -245,7 +246,8 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
             for (int q = 0; q < NS; q++) s_wo[t0 + q * TPC][jc] = wo[q];
             if (tid < 4 * NTK) *(us8*)&s_xo[tid >> 2][xs] = xo;
         }
-    }
+    };
+    if (T == 32 && __builtin_expect(many && s > 32, 0)) chunks();  // uniform
     float cwj[4] = {0, 0, 0, 0};
     if constexpr (!ZP) {
 #pragma unroll
@@ -275,7 +277,9 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
         }
         __syncthreads();
         const int i = I0 + T * t + il;
-        if (il < T && i < s && j < o) {
+        const bool mine = il < T && i < s && j < o;
+        float p[4] = {0, 0, 0, 0}, d[4] = {0, 0, 0, 0};
+        if (mine) {
             const int m = T == 16 ? 0 : ch >> 1, l = T == 16 ? il + 16 * ch : (il + 32 * (ch & 1)) ^ ((m & 7) << 2);
             const v4i c = red[0][m][l] + red[1][m][l] + red[2][m][l] + red[3][m][l];
             if (a.Cdbg) {
@@ -285,7 +289,6 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
             }
             // Eq. 7 (zeropoint: Eq. 5), to which Eq. 8 adds the outlier product: that sum first, as in gemm.hip, or, up
             // to 32 tokens, last, as in the weight-streaming kernel (the one-call path there gives the same bits)
-            float p[4], d[4] = {0, 0, 0, 0};
             if constexpr (ZP) {
                 const int4 rec = s_zx[T * t + il];
                 const double sa = zp_range((unsigned)rec.x) * (1.0 / 254.0), za = (double)rec.y, rs = (double)rec.z;
@@ -301,23 +304,24 @@ __global__ void __launch_bounds__(512, 2) gemm_ksplit_kernel(const KsplitArgs a)
 #pragma unroll
                 for (int e = 0; e < 4; e++) d[e] = ZP ? p[e] : p[e] * cwj[e];
             }
+        }
+        if constexpr (NJ == 1 && NI == 1) {  // (the only shape of up to 32 tokens)
+            if (__builtin_expect(many && s <= 32, 0)) {  // uniform
+#pragma unroll
+                for (int e = 0; e < 4; e++) od[t][e] = d[e];
+                chunks();
+            }
+        }
+        if (mine) {
             if (many) {
 #pragma unroll
                 for (int e = 0; e < 4; e++) d[e] = od[t][e];
             }
-            const int ns = many ? 0 : cnt < KSLOTS ? cnt : KSLOTS;
+            const int ns = many ? 0 : cnt;
             for (int q = 0; q < ns; q++) {
                 const float x = f16_bits_to_float(s_xo[T * t + il][q]);
 #pragma unroll
                 for (int e = 0; e < 4; e++) d[e] = __builtin_fmaf(x, f16_bits_to_float(s_wo[q][jl + e]), d[e]);
-            }
-            for (int q = many ? cnt : KSLOTS; q < cnt; q++) {  // up to 32 tokens, more outlier columns than fit: rare
-                const unsigned k = a.rows_are_slots ? (unsigned)q : (unsigned)a.idx[q];
-                if (k >= (unsigned)a.wrows) continue;
-                const float x = f16_bits_to_float(a.Xo[(size_t)i * a.opad + q]);
-#pragma unroll
-                for (int e = 0; e < 4; e++)
-                    d[e] = __builtin_fmaf(x, f16_bits_to_float(a.Wf[(size_t)k * o + (j + e < o ? j + e : 0)]), d[e]);
             }
             if (s > 32) {
 #pragma unroll

@@ -147,6 +147,25 @@ def test_many_outlier_columns_where_k_is_split_over_the_waves(s, h, o):
     assert r < 1.3
 
 
+@pytest.mark.parametrize("s,h,o,zeropoint", [(8, 8192, 4096, False), (8, 12288, 4096, True), (16, 4096, 4096, False), (32, 4096, 2048, True)])
+def test_many_outlier_columns_of_few_tokens_where_k_is_split_over_the_waves(s, h, o, zeropoint):
+    """200 outlier columns, in the kernel that the library chooses against the weight-streaming one: 0.3 to 0.6.  With the columns past
+    the 32nd from memory for every output, 0.9 to 1.5."""
+    import paper_2208_07339_amd as L
+    call = prepare(s, h, o, 200, 256, zeropoint)
+
+    def streaming():
+        L.debug_decode_shape(1)
+        call()
+        L.debug_decode_shape(-1)
+
+    try:
+        r = ratio(call, streaming)
+    finally:
+        L.debug_decode_shape(-1)
+    assert r < 0.9
+
+
 def test_many_rows_of_w_rebuilt_at_64_tokens():
     """200 outlier columns on weights kept as codes only against fp16 rows: 1.05.  With all rows of a column rebuilt by
     one thread, 2.7."""

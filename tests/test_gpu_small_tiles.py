@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import assert_out_close, bits
+from gpu_util import assert_out_close, bits, through
 from paper_2208_07339_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -46,3 +46,31 @@ def test_half_tiles_against_the_separate_calls(s, h, o, n, rows16):
                               bits(b.cpu().numpy().ravel()) if b.dtype == torch.float16 else b.cpu().numpy())
     if rows16:
         assert_out_close(out.cpu().numpy(), oracle.linear(X, W, 6.0)["Out"])
+
+
+@pytest.mark.parametrize("zeropoint", [False, True])
+@pytest.mark.parametrize("cap,n", [(64, 33), (64, 64), (256, 97), (250, 250)])
+@pytest.mark.parametrize("s,h,o", [(1, 5000, 513), (9, 2000, 2049), (16, 4096, 1000), (17, 2048, 1030), (32, 700, 2016)])
+def test_columns_past_the_32nd_with_k_split_over_the_waves(s, h, o, cap, n, zeropoint):
+    """Up to 32 tokens, against the weight-streaming kernel, which adds up in the same order: the same bits."""
+    import torch
+
+    import paper_2208_07339_amd as L
+    d = wl.make_custom(s, h, o, n, seed=s + h + n)
+    Xd, Wd = (torch.from_numpy(a.view(np.int16)).cuda().view(torch.float16) for a in (d["X"], d["W"]))
+    ws = L.Workspace.allocate(s, h, o, cap)
+    outl = L.find_outliers(Xd, 6.0, cap, ws)
+    assert int(outl.count.item()) > 32
+    qw, rows = (L.zp_quantize_weight(Wd, ws), L.zp_quantize_rows(Xd, outl)) if zeropoint else (L.quantize_weight(Wd, ws), L.quantize_rows(Xd, outl))
+    product = L.zp_matmul if zeropoint else L.matmul
+    assert L.debug_kernel_for(s, h, o, zeropoint) >= 2
+    out = product(rows, outl, qw, ws)
+    with through("streaming"):
+        want = product(rows, outl, qw, ws)
+    assert np.array_equal(bits(out.cpu().numpy()), bits(want.cpu().numpy()))
+    if not zeropoint:
+        qw.W = None
+        out = L.matmul(rows, outl, qw, ws)
+        with through("streaming"):
+            want = L.matmul(rows, outl, qw, ws)
+        assert np.array_equal(bits(out.cpu().numpy()), bits(want.cpu().numpy()))
