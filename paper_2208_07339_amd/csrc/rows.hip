@@ -788,8 +788,10 @@ static size_t joined_bytes(int h, int nrec, int cap) { return join_first(nrec, c
 //   up to 128 tokens, 16-bit weights: 16 x 4096 x 2048 15.0 / 17.7, 32 x 4100 x 4100 16.1 / 19.3, 16 x 12288 x 49152 99.1 / 101.1, 33 x 4096
 //     x 4096 15.3 / 16.0, 96 x 5120 x 15360 26.3 / 28.9, 2 x 20480 x 2048 22.8 / 23.7, 40 x 20480 x 512 25.8 / 26.4; with more features
 //     one compute unit has too much of a row: 2 x 37120 x 2048 32.2 / 31.3, 100 x 24576 x 1024 31.0 / 30.3, 128 x 49152 x 2048 53.3 / 49.4
-//   the same without 16-bit weights, where the rebuilt rows of W wait for the records: 16 x 4096 x 2048 17.1 / 18.0, 64 x 4096 x
-//     4096 16.5 / 16.9, but 32 x 12288 x 2048 22.3 / 21.8, 60 x 8192 x 28672 49.9 / 48.7
+//   the same without 16-bit weights, where the rebuilt rows of W wait for the records: 16 x 4096 x 4096 14.7 / 17.3, 32 x 4096 x 4096
+//     18.6 / 19.1, 96 x 2048 x 4096 15.6 / 16.2, 128 x 4096 x 4096 17.7 / 17.6, but 32 x 12288 x 2048 22.3 / 21.8, 60 x 8192 x 28672 49.9 / 48.7,
+//     and from 33 to 64 tokens 33 x 1024 x 4096 13.7 / 13.3, 48 x 4096 x 4096 16.2 / 15.5, 64 x 4096 x 16384 25.7 / 25.0, with 200 columns
+//     64 x 4096 x 4096 35.0 / 30.1
 //   zeropoint, up to 128 tokens: 2 x 1024 x 2048 14.2 / 17.1, 32 x 4096 x 2048 15.5 / 21.8, 64 x 4096 x 4096 16.2 / 19.8, 2 x 12288 x 2048
 //     20.1 / 22.2, 16 x 37120 x 2048 36.5 / 38.7, 40 x 49152 x 512 52.0 / 54.7, 48 x 12288 x 4096 with 20 columns 26.3 / 26.0 the least;
 //     but 2 x 37120 x 2048 34.9 / 33.2, 12 x 20480 x 2048 with 20 columns 28.9 / 28.2, 3 x 14591 x 1240 with 16 24.3 / 23.5
@@ -803,6 +805,7 @@ bool row_codes_takes(int s, int h, int cap, RowCall call, size_t room)
     if (h < 8 || h > 65536 || cap > JOB_MAX_CAP) return false;
     if (call == RowCall::known) return !(h > 32768 && s > 256 && s < 512);
     if (call == RowCall::zeropoint ? s < 16 && h > 12288 : s <= 128 && h > (call == RowCall::rebuilt ? 4096 : 20480)) return false;
+    if (call == RowCall::rebuilt && s > 32 && s <= 64) return false;
     const int nrec = (row_tiles(s) * 32) >> row_shape(s, h).lr;
     return nrec <= 2048 && (size_t)nrec * record_words(cap) * 2 + joined_bytes(h, nrec, cap) <= room;
 }
