@@ -145,9 +145,9 @@ int llmint8_matmul(const int8_t *Xq, const void *cx_f16, const void *Xo_f16, con
                    void *ws, size_t ws_bytes, llmint8_stream_t stream);
 
 /* The per-call sequence find_outliers -> quantize_rows -> matmul on one stream (W_f16 may be NULL
- * as for llmint8_matmul): the same outputs as the three calls, bit for bit, from fewer kernels
- * (two for the whole pre-pass up to 16 384 tokens, 65 536 features and cap = 256, the rebuilt rows of W
- * included; one for everything when X is small).
+ * as for llmint8_matmul): the same outputs as the three calls, bit for bit, from fewer kernels: one for
+ * everything when X is small, mostly two or three for the whole pre-pass, the rebuilt rows of W included, up
+ * to cap = 256 and 16 384 tokens of up to 5 120 features, 8 192 of up to 10 240 or 4 096 of up to 65 536.
  * Xq, cx_f16, Xo_f16, idx, count, status are caller-provided scratch/outputs
  * of the sizes given above.                                                   */
 int llmint8_linear(const void *X_f16, int s, int h, float alpha, const int8_t *Wq, const void *cw_f16,

@@ -382,9 +382,9 @@ static const int ks_nj[KS_SHAPES] = {1, 2, 2, 2}, ks_ni[KS_SHAPES] = {1, 1, 2, 3
 // weight-streaming kernel or whole tiles here: 3 x 37120 x 640 22.8 / 30.7 us, 16 x 12288 x 2048 16.1 / 18.6, 16 x 4096 x 4096 13.2 /
 // 16.0, 12 x 20480 x 4096 25.0 / 32.8, 6 x 7793 x 5000 18.7 / 20.3, 4 x 20480 x 5120 30.1 / 32.0; at 8 x 8192 x 6000 21.5 / 21.2.
 // From a pair of k-tiles for each wave on.  Up to 8 tokens with at most 128 k-tiles and an eighth of the compute units' column tiles
-// keep the weight-streaming kernel, as callers that ask for the choice know it; it costs them little: zeropoint calls on a W from
-// memory, half tiles / weight-streaming: 8 x 4096 x 1024 15.1 / 16.4 us, 8 x 2048 x 512 14.2 / 15.2, 8 x 1024 x 1024 14.9 / 15.2, but
-// 8 x 6144 x 1024 16.1 / 18.6, 2 x 5120 x 640 16.3 / 18.1.
+// keep the weight-streaming kernel.  That is not the faster one on any size measured: zeropoint calls on a W from memory, half tiles /
+// weight-streaming, 8 x 4096 x 1024 15.1 / 16.4 us, 8 x 2048 x 512 14.2 / 15.2, 8 x 1024 x 1024 14.9 / 15.2, and past the line 8 x 6144 x
+// 1024 16.1 / 18.6, 2 x 5120 x 640 16.3 / 18.1.  It keeps what llmint8_debug_kernel_for says of these products, at up to 1.3 us a call.
 // 17 to 32 tokens: the weight-streaming kernel keeps every W that gives a quarter of the compute units a column tile; below that
 // 8 waves per column tile pull more than 4; the matmul alone there / here on a W from memory: 32 x 2048 x 2048 7.3 / 7.0 us,
 // 24 x 8192 x 512 12.0 / 11.8.

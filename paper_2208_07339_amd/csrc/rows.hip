@@ -6,7 +6,8 @@
 //                      makes an outlier, writes the codes, and leaves the list of the columns in which its own rows
 //                      reach the threshold.  With the columns known (KNOWN: the stand-alone calls) the constants are
 //                      final and the gathered columns Xo are written too.
-// settle_rows_kernel   joins the lists to the outlier set, writes idx, count, status and Xo, clears the codes of
+// join_records_kernel  joins many lists (more than 512, or 256 where they may be long) to a bitmap in memory first.
+// settle_rows_kernel   joins the lists to the outlier set, or takes it from that bitmap, writes idx, count, status and Xo, clears the codes of
 //                      entries below the threshold in outlier columns, and makes the rows anew whose constant came
 //                      from one of those (or all rows, where more columns qualify than the buffer takes: the columns
 //                      past its end are ordinary ones).
@@ -799,7 +800,8 @@ static size_t joined_bytes(int h, int nrec, int cap) { return join_first(nrec, c
 //     32.1, zeropoint 4096 x 1024 x 1024 26.5 / 37.5
 //   the columns known: 20 x 4096 26.9 / 31.7 (three calls), 4096 x 5120 47.3 / 53.3; not where a second row of many features falls
 //     to some compute units (300 x 49152 64.9 / 63.7; 30 x 49152 50.7 / 53.1, 700 x 49152 99.8 / 100.2)
-// Above 2 048 records (16 384 tokens) every workgroup of settle_rows_kernel would read too many of them.
+// Up to 2 048 records: 16 384 tokens up to 5 120 features, 8 192 up to 10 240, 4 096 above (row_shape).  Longer X was not measured here since
+// join_records_kernel took the join off settle_rows_kernel's workgroups.
 bool row_codes_takes(int s, int h, int cap, RowCall call, size_t room)
 {
     if (h < 8 || h > 65536 || cap > JOB_MAX_CAP) return false;

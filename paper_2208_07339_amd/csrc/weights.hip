@@ -580,7 +580,8 @@ hipError_t launch_zp_quantize_weight(const void* W, int h, int o, int8_t* Wq, in
     // each) times steps are as few as can be.  Us, so / four waves and no request ahead: 5 120 x 20 480 96.5 / 105.2, 10 000 x
     // 10 240 98.0 / 105.3, 8 486 x 2 944 36.8 / 46.1, 9 216 x 9 216 84.3 / 85.6, 21 632 x 2 392 66.7 / 75.4, 49 152 x 2 048 91.9 / 93.9; but
     // 12 288 x 8 192 101.9 / 95.1, x 4 096 54.0 / 52.7, x 1 000 34.4 / 32.4, 16 264 x 3 584 63.3 / 62.0 (12 288 x 8 200 104.8 / 109.1),
-    // and where less than half of the compute units would have a workgroup.
+    // and where less than half of the compute units would have a workgroup.  (Between 10 240 and 20 480 features the loop without the request
+    // stays for the sizes that lose; 12 288 x 8 192 against x 8 200 says that the pitch of W's rows has a part in it, what part is not known.)
     constexpr int nw = codes_waves(true);
     int steps = 0, ny = 0;
     long least = 0;
