@@ -782,6 +782,17 @@ static RowShape row_shape(int s, int h)
     return {lr, (items + nt - 1) / nt, nt};
 }
 
+// The same for settle_rows_kernel.  In place of eight or four rows in 512 threads half as many in 256, the registers per lane the same: a
+// thread more than a row's 32 outlier columns only waits.  Calls with 7 columns, us, so / in 512 threads: 2048 x 4096 x 4096 45.1 /
+// 45.6, 4096 x 5120 x 64 27.1 / 27.4.  Not for longer buffers (2048 x 4096 x 64, 200 columns 44.5 / 41.9), nor in place of 1 024 threads, which hold
+// rows of many features (2048 x 49152 x 64 with every row made anew 237 / 207, with 7 columns no difference).
+static RowShape settle_shape(int s, int h, int cap)
+{
+    RowShape q = row_shape(s, h);
+    if (cap <= 32 && q.nt == 512 && q.lr > 1) { q.nt = 256; q.lr--; }
+    return q;
+}
+
 // the joined bitmap's place in front of the records
 static size_t joined_bytes(int h, int nrec, int cap) { return join_first(nrec, cap) ? (size_t)((h + 255) / 256) * 32 : 0; }
 
@@ -822,7 +833,7 @@ static hipError_t with_shape(const RowShape& q, F f)
         f(std::integral_constant<int, NT>(), std::integral_constant<int, LR>(), std::integral_constant<int, N>());                  \
         break
         ROWS(256, 3, 1); ROWS(256, 3, 2); ROWS(256, 3, 3); ROWS(256, 3, 4);
-        ROWS(256, 2, 1); ROWS(256, 2, 2);
+        ROWS(256, 2, 1); ROWS(256, 2, 2); ROWS(256, 2, 3); ROWS(256, 2, 4); ROWS(256, 2, 5);
         ROWS(256, 1, 1); ROWS(256, 1, 2); ROWS(256, 1, 3); ROWS(256, 1, 4); ROWS(256, 1, 5); ROWS(256, 1, 6);
         ROWS(256, 0, 1); ROWS(256, 0, 2);
         ROWS(512, 3, 3); ROWS(512, 3, 4); ROWS(512, 3, 5);
@@ -854,7 +865,7 @@ static hipError_t launch_row_codes(const RowArgs& g, hipStream_t st)
 template <bool ZP>
 static hipError_t launch_settle(const SettleArgs& a, int jobs, hipStream_t st)
 {
-    return with_shape(row_shape(a.s, a.h), [&](auto nt, auto lr, auto n) {
+    return with_shape(settle_shape(a.s, a.h, a.cap), [&](auto nt, auto lr, auto n) {
         settle_rows_kernel<n(), lr(), nt(), ZP><<<a.nb + jobs, nt(), (size_t)((a.h + 31) / 32) * 4, st>>>(a);
     });
 }
