@@ -308,8 +308,9 @@ __device__ __forceinline__ void constants_and_codes(w8 (&v)[N], const unsigned (
 // Bound by memory where X is large and by its own arithmetic close behind (about 100 instructions for 16 features, a third of
 // a large call's time), by one workgroup's chain of loads, two barriers and stores where it is not.  Us, against the floor of
 // 2.8 us of launch and drain and 6.9 TB/s, and then both kernels against the four that were there before (colmax_rowmax,
-// outlier_lists, row_const, quantize_rows): 4096 x 5120 13.5 (floor 11.9), with settle_rows 19.8 / 33; 2048 x 4096 7.8
-// (6.4), 12.2 / 20; 1013 x 4099 7.7 (4.6), 12.8 / 19; 2048 x 49152 71 (46), 82 / 103; zeropoint 2048 x 5120 11.4 (7.4), 16.5 / 27.
+// outlier_lists, row_const, quantize_rows): 4096 x 5120 13.5 (floor 11.9), with settle_rows 18.9 / 33; 2048 x 4096 8.3
+// (6.4), 12.5 / 20; 1013 x 4099 7.7 (4.6), 12.8 / 19; 2048 x 49152 70 (46), 80 / 103 (with join_records); zeropoint 2048 x 5120 11.8 (7.4),
+// 17.1 / 27.
 // The columns that a workgroup's own rows make outliers are left out at once, between the two barriers: where outlier columns
 // are outliers in most tokens, eight rows know nearly all of them and settle_rows_kernel has next to nothing to take back.
 // ---------------------------------------------------------------------------
