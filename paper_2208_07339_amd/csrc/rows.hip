@@ -594,7 +594,7 @@ __device__ __forceinline__ int outlier_set(const unsigned short* __restrict__ re
 }
 
 // ---------------------------------------------------------------------------
-// A workgroup settles 2^lsr rows (one or more of those that row_codes_kernel, of the same shape, gave a workgroup), NT >> lsr
+// A workgroup settles 2^lsr rows (one or more times those that row_codes_kernel gave a workgroup), NT >> lsr
 // threads to a row; the workgroups past the rows take a column job.  A chain of round trips: records, columns of X and codes,
 // stores; 4.4 us for 256 records of 7 columns, 5.2 of 20, 15 of 200 (2.8 of them launch and drain).
 // Rows to be made anew are held in registers as there, R at a time and all of a workgroup's lanes on them.  Where that is every
